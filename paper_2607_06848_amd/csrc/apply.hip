@@ -7,11 +7,14 @@
 // block H^E_ee = H^phiphi - C B^T - E C^T and the projector rows
 // P~^phi = P^phi - P^C C^T are formed in FP64 (setup.hip).  The apply of
 // Y = alpha H^E X (+ the terms of the Chebyshev recurrence) then runs as
+//   cells      Yc  = H_c s X^C_c        (tensor products, every cell at once)
 //   project    W   = D (P^C s X^C + P~^phi X^E)
-//   init       Y^C = alpha P^C^T W + beta Z1 + gamma Z2 + alpha G Cl
-//   cell       Y^C += alpha sum_c P_c^T [H_c | E_c^T] [s X^C_c ; X^E_c]
+//   init       Y^C = alpha (sum_c P_c^T Yc + P^C^T W) + beta Z1 + gamma Z2 + alpha G Cl
+//   couple     Y^C += alpha sum_c P_c^T E_c^T X^E_c
 //              Yp_c = E_c s X^C_c       (MFMA cell GEMM, eight colour passes,
 //                                        no two cells of a pass share a node)
+// Gauss rules with nq != p + 1 points take [H_c | E_c^T] [s X^C_c ; X^E_c] as
+// one dense product in the colour passes instead of the cells step.
 //   reduce     Y^E = alpha (sum_c Yp_c + H^E_ee X^E + P~^phi^T W) + ...
 // where s = 1, or 1/m when the caller folds the CFE part of (M~^E)^-1 in.
 #include <algorithm>
@@ -189,6 +192,7 @@ struct CellOps {
   int64_t ldp;
   const int32_t *cell_eptr, *cell_epair, *pair_atom;
   const int64_t *cell_noff;
+  bool hcell;                      // with the cell Hamiltonians, or the coupling alone
 };
 
 // waves per SIMD the wide tiles are compiled for: the FP64 accumulators of
@@ -247,8 +251,9 @@ void k_cell3(CellOps<T> a) {
   const int RBE = nep / 16;
   // enrichment-row parts beyond the cell's rows (uniform over the work-group)
   if (erole && (!ENR || (part - a.nparts_c) * 4 * RBW >= RBE)) return;
-  const int NCHc = (a.KS + 3) / 4;
-  const int KCF = NCHc * 16;                 // CFE rows of the gathered block, padded
+  if (!erole && !a.hcell && RBE == 0) return;
+  const int NCHc = erole || a.hcell ? (a.KS + 3) / 4 : 0;
+  const int KCF = (a.KS + 3) / 4 * 16;       // CFE rows of the gathered block, padded
   const int32_t *g = a.c2g + (int64_t)cell * nloc;
   for (int l = t; l < KCF; l += 256) {
     const int32_t node = g[min(l, nloc - 1)];
@@ -294,10 +299,11 @@ void k_cell3(CellOps<T> a) {
     const bool ce = ENR && ch >= NCHc;
     const double *base = ce ? a.XE : a.X;
     const uint32_t ld = (uint32_t)(ce ? a.lde : a.ldx);
+    const int32_t *gr = gs + (ce ? KCF + (ch - NCHc) * KC : ch * KC);
 #pragma unroll
     for (int j = 0; j < EPT2; ++j) {
       const int idx = t + 256 * j, r = idx / NP, cp = idx % NP;
-      const uint32_t row = (uint32_t)gs[ch * KC + r];
+      const uint32_t row = (uint32_t)gr[r];
       if constexpr (PAIRS) {
         xr[j] = *reinterpret_cast<const double2 *>(base + row * ld +
                                                    2u * (uint32_t)min(cp, NPV - 1));
@@ -648,13 +654,21 @@ __device__ inline double epi_terms(const EpiArgs &e, int64_t o, int col) {
   return v;
 }
 
-// Y^C[node] = alpha sum_e P^C_e W[atom_e] + epilogue terms on every interior
-// node (boundary rows 0): the projector expansion, and the start value of the
-// colour passes' read-modify-write.  Flat over (node, column pair): a thread
-// takes two adjacent columns of one node, so every array is read and written
-// in coalesced 16-byte pieces, and the threads of a wave share one or two
-// nodes, whose projector entries they loop over together.  Even ld (the host
-// checks it) keeps the pairs aligned.
+// Products of the cells with their nodes, Yc[cell][local node][column]
+struct CellSum {
+  const double *Yc;                  // nullptr: none
+  int p, P, nloc, ncx, ncy;
+  int64_t n1x, n1y;
+};
+
+// Y^C[node] = alpha (sum_e P^C_e W[atom_e] + the products of the node's up to
+// eight cells, in a fixed order) + epilogue terms on every interior node
+// (boundary rows 0).  A work-group stays on one line of nodes (fixed y, z),
+// flat over (node, column pair) along it: a thread takes two adjacent columns
+// of one node, so every array is read and written in coalesced 16-byte pieces,
+// the threads of a wave share one or two nodes, whose projector entries they
+// loop over together, and the y and z places of the node in its cells are
+// uniform.  Even ld (the host checks it) keeps the pairs aligned.
 constexpr int EXP_P = 2;   // column pairs per thread of k_expand_init
 
 __global__ __launch_bounds__(256) void k_expand_init(int64_t n_nodes, int ncols,
@@ -663,21 +677,16 @@ __global__ __launch_bounds__(256) void k_expand_init(int64_t n_nodes, int ncols,
                                                      const double *__restrict__ Pc_nm,
                                                      const double *__restrict__ W,
                                                      const double *__restrict__ minv,
-                                                     EpiArgs e, double *Y, int64_t ldy,
-                                                     bool vec) {
+                                                     EpiArgs e, CellSum cs, int nbx, double *Y,
+                                                     int64_t ldy, bool vec) {
   const int npr = (ncols + 1) / 2;             // column pairs of a node
   const int nth = (npr + EXP_P - 1) / EXP_P;   // threads of a node
-  const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (idx >= n_nodes * nth) return;
-  int64_t node;
-  int j;
-  if (n_nodes * nth < (1ll << 31)) {          // 32-bit division where it fits
-    node = (uint32_t)idx / (uint32_t)nth;
-    j = (int)((uint32_t)idx - (uint32_t)node * (uint32_t)nth);
-  } else {
-    node = idx / nth;
-    j = (int)(idx % nth);
-  }
+  const uint32_t line = blockIdx.x / nbx;
+  const uint32_t idx = (blockIdx.x - line * nbx) * 256u + threadIdx.x;
+  const uint32_t gi = idx / (uint32_t)nth;
+  if (gi >= (uint32_t)cs.n1x) return;
+  const int j = (int)(idx - gi * (uint32_t)nth);
+  const int64_t node = (int64_t)line * cs.n1x + gi;
   // this thread's pairs: j, j + nth, ... (adjacent threads, adjacent pairs)
   int c0[EXP_P];
   bool has[EXP_P], two[EXP_P];
@@ -716,6 +725,33 @@ __global__ __launch_bounds__(256) void k_expand_init(int64_t n_nodes, int ncols,
   double2 a[EXP_P];
 #pragma unroll
   for (int q = 0; q < EXP_P; ++q) a[q] = make_double2(0.0, 0.0);
+  if (cs.Yc && inner) {
+    // an interior node lies in one cell per axis, or in two when its index
+    // is a multiple of p
+    const uint32_t gj = line % (uint32_t)cs.n1y, gk = line / (uint32_t)cs.n1y;
+    const int cx = (int)(gi / (uint32_t)cs.p), cy = (int)(gj / (uint32_t)cs.p),
+              cz = (int)(gk / (uint32_t)cs.p);
+    const int lx = (int)gi - cx * cs.p, ly = (int)gj - cy * cs.p, lz = (int)gk - cz * cs.p;
+    for (int z = lz == 0 ? -1 : 0; z <= 0; ++z)
+      for (int y = ly == 0 ? -1 : 0; y <= 0; ++y)
+        for (int x = lx == 0 ? -1 : 0; x <= 0; ++x) {
+          const int cell = cx + x + cs.ncx * (cy + y + cs.ncy * (cz + z));
+          const int l = (x ? cs.p : lx) + cs.P * ((y ? cs.p : ly) + cs.P * (z ? cs.p : lz));
+          const int64_t row = (int64_t)cell * cs.nloc + l;
+#pragma unroll
+          for (int q = 0; q < EXP_P; ++q) {
+            const double *yc = cs.Yc + row * ncols + c0[q];
+            if (two[q] && ncols % 2 == 0) {
+              const double2 v = ld_nt2(yc);
+              a[q].x += v.x;
+              a[q].y += v.y;
+            } else {
+              if (has[q]) a[q].x += yc[0];
+              if (two[q]) a[q].y += yc[1];
+            }
+          }
+        }
+  }
   if (kbnm_ptr) {
     const int32_t e0 = kbnm_ptr[node], e1 = kbnm_ptr[node + 1];
     for (int32_t en = e0; en < e1; ++en) {
@@ -824,9 +860,11 @@ template <typename T, int RBW, int CBM>
 static void launch_cell3(efe_ctx *c, const T *Ht, const T *Et, const T *Ee, const double *X,
                          int64_t ldx, const double *scale, const double *XE, int64_t lde,
                          double *Y, int64_t ldy, double alpha, double *Yp, int64_t ldp,
-                         int ncols) {
+                         int ncols, bool hcell) {
   const bool enr = c->n_enr > 0 && c->ncpairs > 0;
+  if (!enr && !hcell) return;
   CellOps<T> a;
+  a.hcell = hcell;
   a.nparts_c = (int)cdiv(c->RB, 4 * RBW);
   a.nparts_e = enr ? (int)cdiv(c->max_rbe, 4 * RBW) : 0;
   a.c2g = c->d_c2g;
@@ -932,6 +970,12 @@ efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, const
   EpiArgs ec{ep.alpha, ep.beta, ep.gamma, ep.Z1, ep.Z2, ep.G, ep.Cl};
   const int t_cls = ncols <= 16 ? EFE_T_APPLY_NARROW : EFE_T_APPLY;
   const int t_apply = efe_timer_begin(c, t_cls);
+  // 0. cell Hamiltonians by tensor products, into a workspace that the start
+  //    values of Y^C gather from (one launch, fixed order); without room for
+  //    it, added to Y^C colour by colour below
+  const bool tp = c->tp && prec != EFE_BF16;
+  double *Yc = tp ? efe_ws_try(c, 15, (size_t)c->n_cells * c->nloc * ncols * 8) : nullptr;
+  if (Yc && (s = efe_tp_apply(c, XC, ldx, scale != nullptr, ncols, Yc, nullptr, 0, 0.0))) return s;
   // 1. projector coefficients W = D (P^C s X^C + P~^phi X^E), then Y^C =
   //    alpha P^C^T W + epilogue terms on every node
   {
@@ -953,26 +997,31 @@ efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, const
     }
     auto al = [](const double *p) { return p == nullptr || (uintptr_t)p % 16 == 0; };
     const bool vec = ldy % 2 == 0 && al(Y) && al(ep.Z1) && al(ep.Z2) && al(ep.G);
-    k_expand_init<<<cdiv(nn * (((ncols + 1) / 2 + EXP_P - 1) / EXP_P), 256), 256, 0, c->stream>>>(
+    const CellSum cs{Yc, c->p, c->P, c->nloc, c->ncell[0], c->ncell[1], c->n1[0], c->n1[1]};
+    const int64_t nbx = cdiv(c->n1[0] * (((ncols + 1) / 2 + EXP_P - 1) / EXP_P), 256);
+    k_expand_init<<<nbx * c->n1[1] * c->n1[2], 256, 0, c->stream>>>(
         nn, ncols, c->nproj ? c->d_kbnm_ptr : nullptr, c->d_kbnm_atom, c->d_Pc_nm, W, c->d_minv,
-        ec, Y, ldy, vec);
+        ec, cs, (int)nbx, Y, ldy, vec);
     efe_timer_end(c, EFE_T_PRE, t);
   }
+  if (tp && !Yc &&
+      (s = efe_tp_apply(c, XC, ldx, scale != nullptr, ncols, nullptr, Y, ldy, ep.alpha)))
+    return s;
   // 2. cell GEMM, colour by colour: 160-column register tiles; a single
   //    16-column tile (six row blocks per wave) for narrow blocks such as the
   //    Lanczos vector
   if (prec == EFE_FP64 && ncols <= 16)
     launch_cell3<double, 6, 1>(c, c->d_Htile64, c->d_Et64, c->d_Ee64, XC, ldx, scale, XE, lde, Y,
-                               ldy, ep.alpha, Yp, ncols, ncols);
+                               ldy, ep.alpha, Yp, ncols, ncols, !tp);
   else if (prec == EFE_FP64)
     launch_cell3<double, 1, 10>(c, c->d_Htile64, c->d_Et64, c->d_Ee64, XC, ldx, scale, XE, lde, Y,
-                                ldy, ep.alpha, Yp, ncols, ncols);
+                                ldy, ep.alpha, Yp, ncols, ncols, !tp);
   else if (prec == EFE_FP32 && ncols <= 16)
     launch_cell3<float, 6, 1>(c, c->d_Htile32, c->d_Et32, c->d_Ee32, XC, ldx, scale, XE, lde, Y,
-                              ldy, ep.alpha, Yp, ncols, ncols);
+                              ldy, ep.alpha, Yp, ncols, ncols, !tp);
   else if (prec == EFE_FP32)
     launch_cell3<float, 2, 10>(c, c->d_Htile32, c->d_Et32, c->d_Ee32, XC, ldx, scale, XE, lde, Y,
-                               ldy, ep.alpha, Yp, ncols, ncols);
+                               ldy, ep.alpha, Yp, ncols, ncols, !tp);
   else {
     const int NT = 32;
     const int ntiles = (int)cdiv(ncols, NT);

@@ -56,6 +56,22 @@ efe_status efe_ws(efe_ctx *ctx, int slot, size_t bytes, void **p) {
   return EFE_OK;
 }
 
+double *efe_ws_try(efe_ctx *ctx, int slot, size_t bytes) {
+  void *p = nullptr;
+  if (ctx->arena) {
+    // only out of what the call's other slots leave
+    if (ctx->arena_len[slot] == 0) {
+      if (bytes + 256 > ctx->arena_spare) return nullptr;
+      ctx->arena_spare -= bytes + 256;
+    }
+    return efe_ws(ctx, slot, bytes, &p) == EFE_OK ? (double *)p : nullptr;
+  }
+  if (efe_ws(ctx, slot, bytes, &p) == EFE_OK) return (double *)p;
+  (void)hipGetLastError();
+  ctx->err.clear();
+  return nullptr;
+}
+
 template <class T>
 static efe_status upload(efe_ctx *ctx, T **dst, const std::vector<T> &src) {
   efe_status s = efe_alloc(ctx, (void **)dst, src.size() * sizeof(T));
@@ -600,7 +616,7 @@ extern "C" void efe_destroy(efe_ctx *c) {
                   c->d_Bkin_pair, c->d_B_pair,       c->d_Et64,       c->d_Ee64,
                   c->d_Et32,      c->d_Ee32,         c->d_Hee,
                   c->d_Ptil,      c->d_cpair_ptr,    c->d_cpair_atom, c->d_cpair_spair,
-                  c->d_cpair_lmap};
+                  c->d_cpair_lmap, c->d_s1,          c->d_tpm};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   for (auto &b : c->ws)

@@ -24,6 +24,17 @@ struct DevBuf {
   size_t bytes = 0;
 };
 
+// tensor-product cell operator (cell_tp.hip)
+struct TpArgs {
+  const double *X, *vq, *s1, *mask1;   // s1: per-axis row factors of X
+  const int32_t *cells;                // nullptr: every cell
+  double *Yc, *Y;
+  int64_t ldx, ldy, ncells, n1x, n1y;
+  int ncols, ncx, ncy;
+  double alpha;
+  const double *m;                     // 1-D matrices of the axes
+};
+
 struct efe_ctx {
   hipStream_t stream = nullptr;
   int device = 0;
@@ -128,6 +139,11 @@ struct efe_ctx {
   int32_t *d_kbtrip = nullptr;                         // (cell, I_kb, J_enr)
   double *d_Pphi = nullptr, *d_D = nullptr;            // [nproj][n_enr], [nproj]
 
+  // tensor-product cell operator (nq = p + 1): matrices, and the separable
+  // row factors [2][n1x + n1y + n1z] (interior mask, 1/m)
+  bool tp = false;
+  double *d_tpm = nullptr, *d_s1 = nullptr;
+
   // potential-dependent operators
   bool have_potential = false;
   double *d_vq = nullptr;
@@ -145,6 +161,7 @@ struct efe_ctx {
   // (slot -> offset, bytes; reset for every call)
   char *arena = nullptr;
   size_t arena_cap = 0, arena_used = 0;
+  size_t arena_spare = 0;   // bytes of the region no required slot needs (efe_ws_try)
   static constexpr int kArenaSlots = 64;
   size_t arena_off[kArenaSlots] = {0}, arena_len[kArenaSlots] = {0};
 
@@ -242,6 +259,15 @@ efe_status efe_syev_jacobi(efe_ctx *ctx, int64_t n, const double *H, int64_t ldh
                            double *Q, double *work, int *iwork, int *sweeps);
 size_t efe_syev_work(int64_t n);
 size_t efe_syev_iwork(int64_t n);
+
+// tensor-product cell operator (cell_tp.hip): the products of every cell into
+// Yc [cell][local node][column], or (Yc = nullptr) added to Y times alpha
+efe_status efe_tp_setup(efe_ctx *ctx, const std::vector<double> &xq, const std::vector<double> &wq,
+                        const std::vector<double> &N1, const std::vector<double> &wg);
+efe_status efe_tp_apply(efe_ctx *ctx, const double *X, int64_t ldx, bool minv, int ncols,
+                        double *Yc, double *Y, int64_t ldy, double alpha);
+// workspace slot that may be missing: nullptr (no error) when it does not fit
+double *efe_ws_try(efe_ctx *ctx, int slot, size_t bytes);
 
 // operator applications (apply.hip)
 // Affine epilogue of an H apply (the Chebyshev recurrence fused into the

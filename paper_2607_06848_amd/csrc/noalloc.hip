@@ -70,6 +70,7 @@ extern "C" efe_status efe_cheb_filter_noalloc(efe_ctx *c, double *V, const doubl
   c->arena = (char *)base;
   c->arena_cap = EFE_NOALLOC_SCRATCH_BYTES;
   c->arena_used = 0;
+  c->arena_spare = c->arena_cap - need;
   for (int i = 0; i < efe_ctx::kArenaSlots; ++i) c->arena_len[i] = 0;
   s = efe_filter_run(c, V, lambda, ncols, ld, prm);
   c->arena = nullptr;
