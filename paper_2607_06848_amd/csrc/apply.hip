@@ -2,21 +2,22 @@
 // Discrete_Eig_Gen_H), the exact overlap M^E and its approximate inverse
 // (Eq. MEInvApprox) to a block of node-major vectors.
 //
-// T = [[I, -C^T], [0, I]] is applied when the operator is built: per cell the
-// coupling of the orthogonalized basis E_c = B_c - C_c H_c, the enrichment
-// block H^E_ee = H^phiphi - C B^T - E C^T and the projector rows
-// P~^phi = P^phi - P^C C^T are formed in FP64 (setup.hip).  The apply of
-// Y = alpha H^E X (+ the terms of the Chebyshev recurrence) then runs as
-//   cells      Yc  = H_c s X^C_c        (tensor products, every cell at once)
-//   project    W   = D (P^C s X^C + P~^phi X^E)
-//   init       Y^C = alpha (sum_c P_c^T Yc + P^C^T W) + beta Z1 + gamma Z2 + alpha G Cl
-//   couple     Y^C += alpha sum_c P_c^T E_c^T X^E_c
-//              Yp_c = E_c s X^C_c       (MFMA cell GEMM, eight colour passes,
-//                                        no two cells of a pass share a node)
-// Gauss rules with nq != p + 1 points take [H_c | E_c^T] [s X^C_c ; X^E_c] as
-// one dense product in the colour passes instead of the cells step.
-//   reduce     Y^E = alpha (sum_c Yp_c + H^E_ee X^E + P~^phi^T W) + ...
-// where s = 1, or 1/m when the caller folds the CFE part of (M~^E)^-1 in.
+// T = [[I, -C^T], [0, I]] is applied when the operator is built: the coupling
+// E = B - C H^cc of the orthogonalized basis to the nodes, the enrichment block
+// H^phiphi - C B^T - E C^T and the projector rows P~^phi = P^phi - P^C C^T are
+// formed in FP64 (setup.hip, couple.hip).  The apply of Y = alpha H^E X (+ the
+// terms of the Chebyshev recurrence) then runs as
+//   cells    Yc  = H_c s X^C_c                   (tensor products, every cell at once)
+//   gather   Yp  = [E ; P^C] s X^C box by box    (MFMA)
+//   sum      E s X^C, P^C s X^C and X^E atom by atom
+//   dense    Y^E = alpha (E s X^C + H^E_ee X^E + P~^phi^T W) + ...,
+//            W   = D (P^C s X^C + P~^phi X^E)    (MFMA)
+//   nodes    Y^C = alpha (sum_c P_c^T Yc + E^T X^E + P^C^T W) + beta Z1 + gamma Z2
+//                  + alpha G Cl                  (MFMA, one pass over the rows)
+// in five launches, with s = 1, or X = M~^-1 Z: s = 1/m and X^E = (M~^ee)^-1
+// Z^E formed by the sum step.  Gauss rules with nq != p + 1 points, and BF16,
+// add dense cell products H_c s X^C_c to Y^C in eight colour passes instead of
+// the cells step (no two cells of a pass share a node).
 #include <algorithm>
 
 #include "efe_device.h"
@@ -44,21 +45,6 @@ __device__ inline double2 ld_nt2(const double *p) {
 __device__ inline void st_nt2(double2 v, double *p) {
   const v2d t = {v.x, v.y};
   __builtin_nontemporal_store(t, reinterpret_cast<v2d *>(p));
-}
-
-// value of v in lane l (l wave-uniform), for every lane: two readlanes
-__device__ inline double lane_bcast(double v, int l) {
-  const long long u = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(unsigned)(u & 0xffffffffll), l);
-  const int hi = __builtin_amdgcn_readlane((int)(u >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
-// block index of the calling work-group under an XcdSplit, or -1
-__device__ inline int64_t xcd_block(const XcdSplit &x) {
-  const int xcd = blockIdx.x % 8;
-  const int64_t i = x.off[xcd] + blockIdx.x / 8;
-  return i < x.off[xcd + 1] ? i : -1;
 }
 
 // ------------------------------------------------------------------ pre
@@ -176,23 +162,16 @@ struct CellMfma<float> {
 
 template <typename T>
 struct CellOps {
-  int ncells, nparts_c, nparts_e;
+  int ncells, nparts;
   const int32_t *cells, *c2g;
-  int nloc, RB, KS, nf, ncols;
-  const T *Ht, *Et, *Ee;           // cell Hamiltonians, E_c^T and E_c tiles
+  int nloc, RB, KS, ncols;
+  const T *Ht;                     // cell Hamiltonian tiles
   const double *X;                 // CFE rows (even ld, 16-byte aligned)
   int64_t ldx;
   const double *scale, *minv;      // row scale of X (NULL: 1), 1/m (0 on the boundary)
-  const double *XE;                // enrichment rows
-  int64_t lde;
   double *Y;                       // CFE rows, read-modify-write
   int64_t ldy;
   double alpha;
-  double *Yp;                      // enrichment partial rows, one row block per (cell, atom)
-  int64_t ldp;
-  const int32_t *cell_eptr, *cell_epair, *pair_atom;
-  const int64_t *cell_noff;
-  bool hcell;                      // with the cell Hamiltonians, or the coupling alone
 };
 
 // waves per SIMD the wide tiles are compiled for: the FP64 accumulators of
@@ -203,75 +182,43 @@ constexpr int cell_waves() {
   return CBM == 1 ? 1 : (sizeof(T) == 8 || RBW > 1 ? 3 : 4);
 }
 
-// Cell GEMM of one colour pass of H^E = T^T Hhat T written per cell in the
-// orthogonalized basis: with X_c = [s X^C_c ; X^E_c] (the cell's nodes, scaled
-// by s, then the rows of its enrichment atoms),
-//   Y^C_c += alpha [H_c | E_c^T] X_c          (parts 0 .. nparts_c - 1)
-//   Yp_c   = E_c (s X^C_c)                      (parts nparts_c ..: the cell's
-//                                               enrichment rows, summed over
-//                                               cells afterwards)
+// Dense cell GEMM of one colour pass, Y^C_c += alpha H_c (s X^C_c), for Gauss
+// rules that the tensor-product form (cell_tp.hip) does not take (nq != p + 1).
 // One work-group = one cell of the colour and a part of its row blocks, all
 // (up to 160) columns.  Each wave keeps RBW row blocks x CBM column blocks of
 // accumulators, so every matrix fragment loaded from memory feeds CBM MFMAs.
 // The gathered rows stream through LDS in 16-row chunks, double buffered; the
 // matrix fragments of the next chunk are loaded into registers while the
 // current chunk is multiplied.  T = double (v_mfma_f64_16x16x4) or float
-// (v_mfma_f32_16x16x4, FP32 accumulation).  ENR = false: plain CFE.
-template <typename T, int RBW, int CBM, bool ENR>
+// (v_mfma_f32_16x16x4, FP32 accumulation).
+template <typename T, int RBW, int CBM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(cell_waves<T, RBW, CBM>())))
 void k_cell3(CellOps<T> a) {
   typedef CellMfma<T> M;
   typedef typename M::acc_t acc_t;
   constexpr int NC = CBM * 16, KC = 16;
   __shared__ T Xs[2][KC][M::ncp(NC)];
-  // rows of the gathered block: the cell's nodes (CFE chunks, with their row
-  // scales), then the rows of its enrichment atoms (padding rows read row 0:
-  // the E_c^T tiles are zero in their columns)
-  __shared__ int32_t gs[16 * ((EFE_MAXLOC + 15) / 16) + (ENR ? EFE_MAX_CELL_ENR : 0)];
+  __shared__ int32_t gs[16 * ((EFE_MAXLOC + 15) / 16)];
   __shared__ double gsc[16 * ((EFE_MAXLOC + 15) / 16)];
   const int b = blockIdx.x;
-  const int nparts = a.nparts_c + a.nparts_e;
   const int xcd = b % 8, slot = b / 8;
-  const int ci = (slot / nparts) * 8 + xcd;
-  const int part = slot % nparts;
+  const int ci = (slot / a.nparts) * 8 + xcd;
+  const int part = slot % a.nparts;
   if (ci >= a.ncells) return;
   const int cell = a.cells[ci];
   const int nloc = a.nloc, ncols = a.ncols;
   const int t = threadIdx.x, wave = t / 64, lane = t % 64, li = lane % 16, lk = lane / 16;
-  const bool erole = part >= a.nparts_c;
-  int ne = 0, nep = 0;
-  int32_t p0 = 0;
-  int64_t noff = 0;
-  if (ENR) {
-    p0 = a.cell_eptr[cell];
-    ne = (a.cell_eptr[cell + 1] - p0) * a.nf;
-    nep = (ne + 15) / 16 * 16;
-    noff = a.cell_noff[cell];
-  }
-  const int RBE = nep / 16;
-  // enrichment-row parts beyond the cell's rows (uniform over the work-group)
-  if (erole && (!ENR || (part - a.nparts_c) * 4 * RBW >= RBE)) return;
-  if (!erole && !a.hcell && RBE == 0) return;
-  const int NCHc = erole || a.hcell ? (a.KS + 3) / 4 : 0;
-  const int KCF = (a.KS + 3) / 4 * 16;       // CFE rows of the gathered block, padded
+  const int NCH = (a.KS + 3) / 4;
   const int32_t *g = a.c2g + (int64_t)cell * nloc;
-  for (int l = t; l < KCF; l += 256) {
+  for (int l = t; l < 16 * NCH; l += 256) {
     const int32_t node = g[min(l, nloc - 1)];
     gs[l] = node;
     gsc[l] = (l >= nloc || a.minv[node] == 0.0) ? 0.0 : (a.scale ? a.scale[node] : 1.0);
   }
-  if (ENR && !erole)
-    for (int r = t; r < nep; r += 256)
-      gs[KCF + r] = r < ne ? a.pair_atom[a.cell_epair[p0 + r / a.nf]] * a.nf + r % a.nf : 0;
   __syncthreads();
-  const int nrb = erole ? RBE : a.RB;
-  const int rbase = ((erole ? part - a.nparts_c : part) * 4 + wave) * RBW;
+  const int rbase = (part * 4 + wave) * RBW;
   const int CB = (ncols + 15) / 16;
-  const int NCH = NCHc + ((ENR && !erole) ? RBE : 0);
-  const int kse_n = nep / 4;
-  const T *hp = erole ? a.Ee + 4 * (int64_t)a.KS * noff + lane
-                      : a.Ht + ((int64_t)cell * a.RB) * a.KS * 64 + lane;
-  const T *tp = ENR ? a.Et + 16 * (int64_t)a.RB * noff + lane : hp;
+  const T *hp = a.Ht + ((int64_t)cell * a.RB) * a.KS * 64 + lane;
 
   T a0[4][RBW], a1[4][RBW];
   acc_t acc[RBW][CBM];
@@ -293,31 +240,25 @@ void k_cell3(CellOps<T> a) {
   static_assert(KC * NP % 256 == 0, "the gather must cover the chunk exactly");
   const int NPV = (ncols + 1) / 2;
   double2 xr[EPT2];
-  // chunk ch reads rows ch*16 .. of the gathered block: CFE rows from X,
-  // enrichment rows from XE (a uniform choice per chunk)
   auto stage_load = [&](int ch) {
-    const bool ce = ENR && ch >= NCHc;
-    const double *base = ce ? a.XE : a.X;
-    const uint32_t ld = (uint32_t)(ce ? a.lde : a.ldx);
-    const int32_t *gr = gs + (ce ? KCF + (ch - NCHc) * KC : ch * KC);
+    const uint32_t ld = (uint32_t)a.ldx;
 #pragma unroll
     for (int j = 0; j < EPT2; ++j) {
       const int idx = t + 256 * j, r = idx / NP, cp = idx % NP;
-      const uint32_t row = (uint32_t)gr[r];
+      const uint32_t row = (uint32_t)gs[ch * KC + r];
       if constexpr (PAIRS) {
-        xr[j] = *reinterpret_cast<const double2 *>(base + row * ld +
+        xr[j] = *reinterpret_cast<const double2 *>(a.X + row * ld +
                                                    2u * (uint32_t)min(cp, NPV - 1));
       } else {
-        xr[j].x = base[(int64_t)row * ld + min(cp, ncols - 1)];
+        xr[j].x = a.X[(int64_t)row * ld + min(cp, ncols - 1)];
       }
     }
   };
   auto stage_store = [&](int buf, int ch) {
-    const bool ce = ENR && ch >= NCHc;
 #pragma unroll
     for (int j = 0; j < EPT2; ++j) {
       const int idx = t + 256 * j, r = idx / NP, cp = idx % NP;
-      const double s = ce ? 1.0 : gsc[ch * KC + r];
+      const double s = gsc[ch * KC + r];
       if constexpr (PAIRS) {
         Xs[buf][r][2 * cp] = 2 * cp < ncols ? (T)(s * xr[j].x) : (T)0;
         Xs[buf][r][2 * cp + 1] = 2 * cp + 1 < ncols ? (T)(s * xr[j].y) : (T)0;
@@ -326,19 +267,13 @@ void k_cell3(CellOps<T> a) {
       }
     }
   };
-  // A fragments of chunk ch: cell Hamiltonian (or E_c) tiles, then E_c^T tiles
   auto a_load = [&](int ch, T (&dst)[4][RBW]) {
-    const bool ce = ENR && ch >= NCHc;
-    const T *ap = ce ? tp : hp;
-    const int64_t rs = ce ? kse_n : a.KS;
-    const int k0 = ce ? (ch - NCHc) * 4 : ch * 4;
-    const int kmax = ce ? kse_n - 1 : a.KS - 1;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int r = 0; r < RBW; ++r) {
-        const int64_t rb = min(rbase + r, nrb - 1);
-        dst[s][r] = ld_nt(&ap[(rb * rs + min(k0 + s, kmax)) * 64]);
+        const int64_t rb = min(rbase + r, a.RB - 1);
+        dst[s][r] = ld_nt(&hp[(rb * a.KS + min(4 * ch + s, a.KS - 1)) * 64]);
       }
   };
   auto compute = [&](int buf, const T (&src)[4][RBW]) {
@@ -371,26 +306,6 @@ void k_cell3(CellOps<T> a) {
   for (int ch = 0; ch < NCH; ch += 2) {
     step(ch, a0, a1, 0);
     if (ch + 1 < NCH) step(ch + 1, a1, a0, 1);
-  }
-  if (erole) {
-    // the cell's enrichment rows: partial sums of E_c (s X^C_c)
-#pragma unroll
-    for (int r = 0; r < RBW; ++r) {
-      const int rb = rbase + r;
-      if (rb >= RBE) continue;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int e = rb * 16 + M::row(v, lk);
-        if (e >= ne) continue;
-        double *yp = a.Yp + ((int64_t)a.nf * p0 + e) * a.ldp;
-#pragma unroll
-        for (int cb = 0; cb < CBM; ++cb) {
-          const int col = cb * 16 + li;
-          if (cb < CB && col < ncols) st_nt((double)acc[r][cb][v], &yp[col]);
-        }
-      }
-    }
-    return;
   }
   // scatter: per row block, all reads of Y first, then all writes, so the
   // reads overlap instead of each waiting for the one before; the wide tiles
@@ -509,142 +424,6 @@ struct EpiArgs {
   double alpha, beta, gamma;
   const double *Z1, *Z2, *G, *Cl;
 };
-// ------------------------------------------------------------------ projectors
-// W[I] += D_I sum_s P^C_s s_node X[node_s] over one work item (atom, support-list
-// range); the items of a node region run back to back, so the rows of X they
-// read are shared through the caches.  Waves take one support node at a time
-// (wave-uniform); a lane owns two column pairs (256 columns per work-group
-// column block), read as 16-byte pairs with 32-bit offsets (X has an even
-// leading dimension, 16-byte aligned, n_nodes x ld < 2^31: the apply ensures
-// it), and four entries' rows are in flight at a time.
-constexpr int KBP = 2;   // column pairs per lane
-
-__global__ __launch_bounds__(256) void k_kb_project(int ncols, const int32_t *__restrict__ items,
-                                                    XcdSplit xs,
-                                                    const int32_t *__restrict__ kbnode,
-                                                    const double *__restrict__ Pc,
-                                                    const double *__restrict__ X, int64_t ldx,
-                                                    const double *__restrict__ scale,
-                                                    const double *__restrict__ D,
-                                                    double *__restrict__ W) {
-  __shared__ double2 red[3][64 * KBP];
-  const int64_t item = xcd_block(xs);
-  if (item < 0) return;
-  const int32_t *it = items + 3 * item;
-  const int I = it[0];
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-  const int lane = threadIdx.x % 64;
-  const int c0 = blockIdx.y * 128 * KBP;
-  const int npv = (min(ncols - c0, 128 * KBP) + 1) / 2;   // column pairs of this block
-  int pofs[KBP];
-#pragma unroll
-  for (int q = 0; q < KBP; ++q) pofs[q] = c0 + 2 * min(lane + 64 * q, npv - 1);
-  double2 acc[KBP];
-#pragma unroll
-  for (int q = 0; q < KBP; ++q) acc[q] = make_double2(0.0, 0.0);
-  // entries it[1] + wave + 4 i: node numbers and coefficients (times the row
-  // scale) come in 64 at a time by vector loads and reach the wave by
-  // readlane; clamped pairs keep the row loads unconditional (their sums are
-  // not stored)
-  const int32_t s0 = it[1], s1 = it[2];
-  const uint32_t ld = (uint32_t)ldx;
-  for (int32_t sb = s0 + wave; sb < s1; sb += 256) {
-    const int cnt = min(64, (s1 - sb + 3) / 4);
-    const int32_t sl = min(sb + 4 * lane, s1 - 1);
-    const int32_t nodes = kbnode[sl];
-    const double pv = Pc[sl] * (scale ? scale[nodes] : 1.0);
-    for (int i = 0; i < cnt; i += 4) {
-      double2 xv[4][KBP];
-      double pj[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int ii = min(i + j, cnt - 1);
-        const uint32_t node = (uint32_t)__builtin_amdgcn_readlane(nodes, ii);
-        const double pb = lane_bcast(pv, ii);
-        pj[j] = i + j < cnt ? pb : 0.0;
-#pragma unroll
-        for (int q = 0; q < KBP; ++q)
-          xv[j][q] = *reinterpret_cast<const double2 *>(X + (node * ld + (uint32_t)pofs[q]));
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int q = 0; q < KBP; ++q) {
-          acc[q].x += pj[j] * xv[j][q].x;
-          acc[q].y += pj[j] * xv[j][q].y;
-        }
-    }
-  }
-  if (wave > 0)
-#pragma unroll
-    for (int q = 0; q < KBP; ++q) red[wave - 1][64 * q + lane] = acc[q];
-  __syncthreads();
-  if (wave == 0)
-#pragma unroll
-    for (int q = 0; q < KBP; ++q) {
-      const int pp = lane + 64 * q;
-      if (pp >= npv) continue;
-      const int col = c0 + 2 * pp;
-      const double2 r0 = red[0][64 * q + lane], r1 = red[1][64 * q + lane],
-                    r2 = red[2][64 * q + lane];
-      atomicAdd(&W[(int64_t)I * ncols + col], D[I] * (acc[q].x + r0.x + r1.x + r2.x));
-      if (col + 1 < ncols)
-        atomicAdd(&W[(int64_t)I * ncols + col + 1], D[I] * (acc[q].y + r0.y + r1.y + r2.y));
-    }
-}
-
-// sum of x over the work-group (256 threads), in a fixed order
-__device__ inline double block_sum256(double x, double *red) {
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-  if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = x;
-  __syncthreads();
-  const double t = (red[0] + red[1]) + (red[2] + red[3]);
-  __syncthreads();
-  return t;
-}
-
-// the same for one column: threads over the item's entries
-__global__ __launch_bounds__(256) void k_kb_project1(const int32_t *__restrict__ items,
-                                                     const int32_t *__restrict__ kbnode,
-                                                     const double *__restrict__ Pc,
-                                                     const double *__restrict__ X, int64_t ldx,
-                                                     const double *__restrict__ scale,
-                                                     const double *__restrict__ D,
-                                                     double *__restrict__ W) {
-  __shared__ double red[4];
-  const int32_t *it = items + 3 * (int64_t)blockIdx.x;
-  const int I = it[0];
-  double acc = 0.0;
-  for (int32_t s = it[1] + threadIdx.x; s < it[2]; s += 256) {
-    const int64_t node = kbnode[s];
-    acc += Pc[s] * (scale ? scale[node] : 1.0) * X[node * ldx];
-  }
-  const double t = block_sum256(acc, red);
-  if (threadIdx.x == 0) atomicAdd(&W[I], D[I] * t);
-}
-
-// W[I] = D_I sum_f P~^phi_If XE_f (the enrichment part of the projector
-// coefficients): one work-group per (projector, 64 columns); the four waves
-// take every fourth f and their sums meet in LDS in a fixed order
-__global__ __launch_bounds__(256) void k_kb_w_pphi(int ncols, int64_t n_enr,
-                                                   const double *__restrict__ Pphi,
-                                                   const double *__restrict__ XE, int64_t lde,
-                                                   const double *__restrict__ D,
-                                                   double *__restrict__ W) {
-  __shared__ double red[4][64];
-  const int I = blockIdx.x;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int col = blockIdx.y * 64 + lane;
-  const int cc = min(col, ncols - 1);
-  const double *p = Pphi + (int64_t)I * n_enr;
-  double acc = 0.0;
-  for (int64_t f = wave; f < n_enr; f += 4) acc += p[f] * XE[f * lde + cc];
-  red[wave][lane] = acc;
-  __syncthreads();
-  if (wave == 0 && col < ncols)
-    W[(int64_t)I * ncols + col] = D[I] * (((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane]);
-}
-
 // Affine epilogue terms of one element: beta Z1 + gamma Z2 + alpha G Cl
 __device__ inline double epi_terms(const EpiArgs &e, int64_t o, int col) {
   double v = 0.0;
@@ -654,178 +433,570 @@ __device__ inline double epi_terms(const EpiArgs &e, int64_t o, int col) {
   return v;
 }
 
-// Products of the cells with their nodes, Yc[cell][local node][column]
-struct CellSum {
-  const double *Yc;                  // nullptr: none
-  int p, P, nloc, ncx, ncy;
-  int64_t n1x, n1y;
-};
+// ------------------------------------------------------------------ coupling
+// Column of column block cb and lane li in the wide tiles: a lane's blocks 2q
+// and 2q + 1 are adjacent columns, so its operands come from LDS as one pair
+// and its results go to memory as 16-byte pairs.  A single block (CBM = 1, up
+// to 16 vectors) keeps the plain order.
+template <int CBM>
+__device__ __forceinline__ int tile_col(int cb, int li) {
+  return CBM == 1 ? li : 32 * (cb / 2) + 2 * li + (cb & 1);
+}
 
-// Y^C[node] = alpha (sum_e P^C_e W[atom_e] + the products of the node's up to
-// eight cells, in a fixed order) + epilogue terms on every interior node
-// (boundary rows 0).  A work-group stays on one line of nodes (fixed y, z),
-// flat over (node, column pair) along it: a thread takes two adjacent columns
-// of one node, so every array is read and written in coalesced 16-byte pieces,
-// the threads of a wave share one or two nodes, whose projector entries they
-// loop over together, and the y and z places of the node in its cells are
-// uniform.  Even ld (the host checks it) keeps the pairs aligned.
-constexpr int EXP_P = 2;   // column pairs per thread of k_expand_init
-
-__global__ __launch_bounds__(256) void k_expand_init(int64_t n_nodes, int ncols,
-                                                     const int32_t *__restrict__ kbnm_ptr,
-                                                     const int32_t *__restrict__ kbnm_atom,
-                                                     const double *__restrict__ Pc_nm,
-                                                     const double *__restrict__ W,
-                                                     const double *__restrict__ minv,
-                                                     EpiArgs e, CellSum cs, int nbx, double *Y,
-                                                     int64_t ldy, bool vec) {
-  const int npr = (ncols + 1) / 2;             // column pairs of a node
-  const int nth = (npr + EXP_P - 1) / EXP_P;   // threads of a node
-  const uint32_t line = blockIdx.x / nbx;
-  const uint32_t idx = (blockIdx.x - line * nbx) * 256u + threadIdx.x;
-  const uint32_t gi = idx / (uint32_t)nth;
-  if (gi >= (uint32_t)cs.n1x) return;
-  const int j = (int)(idx - gi * (uint32_t)nth);
-  const int64_t node = (int64_t)line * cs.n1x + gi;
-  // this thread's pairs: j, j + nth, ... (adjacent threads, adjacent pairs)
-  int c0[EXP_P];
-  bool has[EXP_P], two[EXP_P];
+// 16 rows x 16 CBM columns of an operand block on their way to LDS: thread t
+// carries pairs t, t + 256, ... (CBM = 1: one element).  Rows come from
+// `base` at row numbers in LDS; `vec`: even ld and 16-byte aligned rows.
+template <typename T, int CBM>
+struct RowStage {
+  static constexpr int NC = 16 * CBM, NP = NC / 2, E = CBM == 1 ? 1 : 16 * NP / 256;
+  static_assert(CBM == 1 || 16 * NP % 256 == 0, "the rows must be covered exactly");
+  double2 x[E];
+  __device__ __forceinline__ void load(const double *base, int64_t ld, const int32_t *rows,
+                                       int ncols, bool vec) {
 #pragma unroll
-  for (int q = 0; q < EXP_P; ++q) {
-    c0[q] = 2 * (j + q * nth);
-    has[q] = c0[q] < ncols;
-    two[q] = c0[q] + 1 < ncols;
-  }
-  const int64_t rowo = node * ldy;
-  // pairs by 16-byte accesses when the layout allows it (vec: even ld,
-  // aligned arrays), else element by element
-  auto ld2 = [&](const double *p, int q) -> double2 {
-    const int64_t o = rowo + c0[q];
-    if (vec && two[q]) return ld_nt2(p + o);
-    double2 r;
-    r.x = has[q] ? p[o] : 0.0;
-    r.y = two[q] ? p[o + 1] : 0.0;
-    return r;
-  };
-  // the streamed rows first, so that they are in flight while the
-  // projector entries (two dependent loads each) come in
-  double2 z1[EXP_P], z2[EXP_P], g[EXP_P], cl[EXP_P];
-#pragma unroll
-  for (int q = 0; q < EXP_P; ++q) {
-    z1[q] = z2[q] = g[q] = cl[q] = make_double2(0.0, 0.0);
-    if (e.Z1) z1[q] = ld2(e.Z1, q);
-    if (e.Z2) z2[q] = ld2(e.Z2, q);
-    if (e.G) {
-      g[q] = ld2(e.G, q);
-      cl[q].x = has[q] ? e.Cl[c0[q]] : 0.0;
-      cl[q].y = two[q] ? e.Cl[c0[q] + 1] : 0.0;
-    }
-  }
-  const bool inner = minv[node] != 0.0;
-  double2 a[EXP_P];
-#pragma unroll
-  for (int q = 0; q < EXP_P; ++q) a[q] = make_double2(0.0, 0.0);
-  if (cs.Yc && inner) {
-    // an interior node lies in one cell per axis, or in two when its index
-    // is a multiple of p
-    const uint32_t gj = line % (uint32_t)cs.n1y, gk = line / (uint32_t)cs.n1y;
-    const int cx = (int)(gi / (uint32_t)cs.p), cy = (int)(gj / (uint32_t)cs.p),
-              cz = (int)(gk / (uint32_t)cs.p);
-    const int lx = (int)gi - cx * cs.p, ly = (int)gj - cy * cs.p, lz = (int)gk - cz * cs.p;
-    for (int z = lz == 0 ? -1 : 0; z <= 0; ++z)
-      for (int y = ly == 0 ? -1 : 0; y <= 0; ++y)
-        for (int x = lx == 0 ? -1 : 0; x <= 0; ++x) {
-          const int cell = cx + x + cs.ncx * (cy + y + cs.ncy * (cz + z));
-          const int l = (x ? cs.p : lx) + cs.P * ((y ? cs.p : ly) + cs.P * (z ? cs.p : lz));
-          const int64_t row = (int64_t)cell * cs.nloc + l;
-#pragma unroll
-          for (int q = 0; q < EXP_P; ++q) {
-            const double *yc = cs.Yc + row * ncols + c0[q];
-            if (two[q] && ncols % 2 == 0) {
-              const double2 v = ld_nt2(yc);
-              a[q].x += v.x;
-              a[q].y += v.y;
-            } else {
-              if (has[q]) a[q].x += yc[0];
-              if (two[q]) a[q].y += yc[1];
-            }
-          }
+    for (int j = 0; j < E; ++j) {
+      const int idx = threadIdx.x + 256 * j;
+      if constexpr (CBM == 1) {
+        x[j].x = base[rows[idx / 16] * ld + min(idx % 16, ncols - 1)];
+      } else {
+        const double *r = base + rows[idx / NP] * ld;
+        const int c = 2 * (idx % NP);
+        if (vec) {
+          x[j] = *reinterpret_cast<const double2 *>(r + min(c, (ncols - 1) & ~1));
+        } else {
+          x[j].x = r[min(c, ncols - 1)];
+          x[j].y = r[min(c + 1, ncols - 1)];
         }
-  }
-  if (kbnm_ptr) {
-    const int32_t e0 = kbnm_ptr[node], e1 = kbnm_ptr[node + 1];
-    for (int32_t en = e0; en < e1; ++en) {
-      const double p = Pc_nm[en];
-      const double *w = W + (int64_t)kbnm_atom[en] * ncols;
-#pragma unroll
-      for (int q = 0; q < EXP_P; ++q) {
-        if (has[q]) a[q].x += p * w[c0[q]];
-        if (two[q]) a[q].y += p * w[c0[q] + 1];
       }
     }
   }
+  // scale (may be NULL: 1) per row; a zero drops the row
+  __device__ __forceinline__ void store(T *Xs, const double *scale) const {
 #pragma unroll
-  for (int q = 0; q < EXP_P; ++q) {
-    if (!has[q]) continue;
-    double2 v;
-    v.x = e.alpha * (a[q].x + g[q].x * cl[q].x);
-    v.y = e.alpha * (a[q].y + g[q].y * cl[q].y);
-    if (e.Z1) {
-      v.x += e.beta * z1[q].x;
-      v.y += e.beta * z1[q].y;
+    for (int j = 0; j < E; ++j) {
+      const int idx = threadIdx.x + 256 * j;
+      const int r = CBM == 1 ? idx / 16 : idx / NP;
+      const double s = scale ? scale[r] : 1.0;
+      const T vx = s != 0.0 ? (T)(s * x[j].x) : (T)0;
+      if constexpr (CBM == 1) {
+        Xs[idx] = vx;
+      } else {
+        const T vy = s != 0.0 ? (T)(s * x[j].y) : (T)0;
+        Xs[r * NC + 2 * (idx % NP)] = vx;
+        Xs[r * NC + 2 * (idx % NP) + 1] = vy;
+      }
     }
-    if (e.Z2) {
-      v.x += e.gamma * z2[q].x;
-      v.y += e.gamma * z2[q].y;
-    }
-    if (!inner) v.x = v.y = 0.0;
-    const int64_t o = rowo + c0[q];
-    if (vec && two[q]) {
-      st_nt2(v, Y + o);
-    } else {
-      Y[o] = v.x;
-      if (two[q]) Y[o + 1] = v.y;
+  }
+};
+
+// acc += (16 x 4 operand fragment a of k step s) (rows 4 s .. of the chunk)
+template <typename T, int CBM, typename Acc>
+__device__ __forceinline__ void tile_step(const T *Xs, int s, T a, int li, int lk, Acc (&acc)[CBM]) {
+  typedef T T2 __attribute__((ext_vector_type(2)));
+  const T *row = Xs + (4 * s + lk) * 16 * CBM;
+  if constexpr (CBM == 1) {
+    acc[0] = CellMfma<T>::op(a, row[li], acc[0]);
+  } else {
+    T2 b[CBM / 2];
+#pragma unroll
+    for (int q = 0; q < CBM / 2; ++q) b[q] = *reinterpret_cast<const T2 *>(row + 32 * q + 2 * li);
+#pragma unroll
+    for (int q = 0; q < CBM / 2; ++q) {
+      acc[2 * q] = CellMfma<T>::op(a, b[q].x, acc[2 * q]);
+      acc[2 * q + 1] = CellMfma<T>::op(a, b[q].y, acc[2 * q + 1]);
     }
   }
 }
 
-// Y^E[I] = alpha (sum over the cells of atom I of their partial rows + TE[I])
-// + epilogue terms, the partial rows added in cell order (fixed).  One
-// work-group per (atom, 64 columns); the four waves take every fourth function.
-__global__ __launch_bounds__(576) void k_enr_reduce(int nf, int ncols,
-                                                    const int32_t *__restrict__ cpair_ptr,
-                                                    const int32_t *__restrict__ cpair_cpos,
-                                                    const double *__restrict__ Yp, int64_t ldp,
-                                                    const double *__restrict__ TE,
-                                                    EpiArgs e, double *YE, int64_t ldy) {
-  const int I = blockIdx.x;
-  const int k = threadIdx.x / 64, lane = threadIdx.x % 64;   // one wave per function
-  const int col = blockIdx.y * 64 + lane;
-  const int colc = min(col, ncols - 1);      // every lane runs: the readlanes below
-  const int32_t q0 = cpair_ptr[I], q1 = cpair_ptr[I + 1];
-  // four partial sums over the atom's pairs (pair q into sum q mod 4), added
-  // in a fixed order; pair positions come 64 at a time by one vector load
-  double a[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int32_t qb = q0; qb < q1; qb += 64) {
-    const int cnt = min(64, q1 - qb);
-    const int32_t cpv = cpair_cpos[min(qb + lane, q1 - 1)];
-    for (int i = 0; i < cnt; i += 4) {
-      double v[4];
+// blocks of one set of functions (couple.hip) as the kernels take them
+template <typename T>
+struct BoxSet {
+  const int32_t *ptr, *rboff, *atom;
+  const int64_t *ksoff;
+  const T *tile;
+  const uint32_t *live;
+  int nf;
+};
+
+// Yp = [E ; P^C] (s X^C) box by box: one partial row per (box, function).  A
+// work-group takes four 16-row blocks of a box (couple.hip orders them E first,
+// then P^C), one a wave, and all columns; the box's 512 nodes stream through
+// LDS in 16-row chunks, double buffered, while the next chunk's rows and matrix
+// fragments are on their way in registers.  Bound by the FP64 matrix cores at
+// 160 vectors (64 atoms: 22 GF of non-zero products in 0.86 ms; two waves a
+// SIMD without spills beat three with 21 spilled registers and every chunk
+// multiplied, 1.23 ms) and by reading the blocks at one.
+template <typename T>
+struct GatherArgs {
+  const int32_t *items;
+  const double *X, *minv;
+  int64_t ldx, ldp, prow;          // prow: first partial row of the projectors
+  double *Yp;
+  BoxSet<T> E;
+  BoxSet<double> K;
+  NodeGrid g;
+  int ncols;
+  bool scaled, vec;
+};
+
+template <typename T, int CBM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CBM > 8 ? 2 : 3)))
+void k_box_gather(GatherArgs<T> a) {
+  typedef CellMfma<T> M;
+  typedef typename M::acc_t acc_t;
+  constexpr int NB = EFE_BOX * EFE_BOX * EFE_BOX, KS = NB / 4, NCH = NB / 16;
+  __shared__ __align__(16) T Xs[2][16 * 16 * CBM];
+  __shared__ int32_t gs[NB];
+  __shared__ double gsc[NB];
+  int64_t blk = blockIdx.x;        // the parts of a box run on one XCD
+  if (gridDim.x % 8 == 0) blk = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const int box = a.items[2 * blk];
+  const int t = threadIdx.x, wave = t / 64, lane = t % 64, li = lane % 16, lk = lane / 16;
+  const int r0 = a.items[2 * blk + 1];
+  const int ne = a.E.rboff[box + 1] - a.E.rboff[box], nk = a.K.rboff[box + 1] - a.K.rboff[box];
+  // with T = float only E blocks are listed; with T = double both layouts are
+  // the same.  A wave past the last block repeats the first one's loads.
+  // Which wave (SIMD) is left over turns with the work-group.
+  const int rw = r0 + (wave + (int)blockIdx.x / 8) % 4;
+  const bool work = rw < ne + (sizeof(T) == 8 ? nk : 0);
+  const int r = work ? rw : r0;
+  const bool isE = r < ne;
+  int o[3], ijk[3];
+  box_origin(a.g, EFE_BOX, box, o);
+  for (int i = t; i < NB; i += 256) {
+    const bool in = box_node(a.g, EFE_BOX, o, i, ijk);
+    const int32_t node = in ? ijk[0] + a.g.n1[0] * (ijk[1] + a.g.n1[1] * ijk[2]) : 0;
+    gs[i] = node;
+    gsc[i] = in ? (a.scaled ? a.minv[node] : 1.0) : 0.0;
+  }
+  __syncthreads();
+  const T *tp = (isE ? a.E.tile + (int64_t)(a.E.rboff[box] + r) * KS * 64
+                     : (const T *)a.K.tile + (int64_t)(a.K.rboff[box] + r - ne) * KS * 64) +
+                lane;
+  // chunks whose entries are not all zero (a box reaches beyond the atoms' cells)
+  static_assert(NCH == 32, "one bit per chunk");
+  const uint32_t live = work ? __builtin_amdgcn_readfirstlane(
+                                   isE ? a.E.live[a.E.rboff[box] + r] : a.K.live[a.K.rboff[box] + r - ne])
+                             : 0u;
+  acc_t acc[CBM];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t cp = __builtin_amdgcn_readlane(cpv, min(i + j, cnt - 1));
-        v[j] = ld_nt(&Yp[((int64_t)nf * cp + k) * ldp + colc]);
-      }
+  for (int cb = 0; cb < CBM; ++cb) acc[cb] = (acc_t){0, 0, 0, 0};
+  RowStage<T, CBM> st;
+  T a0[4], a1[4];
+  auto a_load = [&](int ch, T (&d)[4]) {
+    if (live >> ch & 1)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (i + j < cnt) a[j] += v[j];
+      for (int s = 0; s < 4; ++s) d[s] = ld_nt(tp + (4 * ch + s) * 64);
+  };
+  auto step = [&](int ch, const T (&cur)[4], T (&nxt)[4], int buf) {
+    if (ch + 1 < NCH) {
+      st.load(a.X, a.ldx, gs + 16 * (ch + 1), a.ncols, a.vec);
+      a_load(ch + 1, nxt);
+    }
+    if (live >> ch & 1)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) tile_step<T, CBM>(Xs[buf], s, cur[s], li, lk, acc);
+    if (ch + 1 < NCH) st.store(Xs[buf ^ 1], gsc + 16 * (ch + 1));
+    __syncthreads();
+  };
+  st.load(a.X, a.ldx, gs, a.ncols, a.vec);
+  a_load(0, a0);
+  st.store(Xs[0], gsc);
+  __syncthreads();
+  // FP32 sums run over one brick (64 nodes) and are added up in FP64: the terms
+  // of E s X^C cancel, so rounding the running sum over all 512 nodes cost more
+  // than rounding the operands (filter error 7.0e-5 against 4.2e-5)
+  v4d sum[sizeof(T) == 4 ? CBM : 1];
+  if constexpr (sizeof(T) == 4)
+#pragma unroll
+    for (int cb = 0; cb < CBM; ++cb) sum[cb] = (v4d){0.0, 0.0, 0.0, 0.0};
+  for (int ch = 0; ch < NCH; ch += 4) {
+    step(ch, a0, a1, 0);
+    step(ch + 1, a1, a0, 1);
+    step(ch + 2, a0, a1, 0);
+    step(ch + 3, a1, a0, 1);
+    if constexpr (sizeof(T) == 4) {
+      if (live >> ch & 15)
+#pragma unroll
+        for (int cb = 0; cb < CBM; ++cb) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sum[cb][v] += (double)acc[cb][v];
+          acc[cb] = (acc_t){0, 0, 0, 0};
+        }
     }
   }
-  if (col >= ncols) return;
-  const int64_t f = (int64_t)I * nf + k;
-  const double acc = (a[0] + a[1]) + (a[2] + a[3]) + TE[f * ncols + col];
-  const int64_t o = f * ldy + col;
-  YE[o] = e.alpha * acc + epi_terms(e, o, col);
+  if (!work) return;
+  const int nf = isE ? a.E.nf : 1, rb = isE ? r : r - ne;
+  const int32_t *ptr = isE ? a.E.ptr : a.K.ptr;
+  const int nrow = (ptr[box + 1] - ptr[box]) * nf;
+  const int64_t row0 = (isE ? 0 : a.prow) + (int64_t)ptr[box] * nf;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int f = 16 * rb + M::row(v, lk);
+    if (f >= nrow) continue;
+    double *yp = a.Yp + (row0 + f) * a.ldp;
+#pragma unroll
+    for (int cb = 0; cb < CBM; ++cb) {
+      const int col = tile_col<CBM>(cb, li);
+      if (col >= a.ncols) continue;
+      if constexpr (sizeof(T) == 4)
+        st_nt(sum[cb][v], yp + col);
+      else
+        st_nt(acc[cb][v], yp + col);
+    }
+  }
+}
+
+// Coefficients of one apply, interleaved atom by atom: rows (I, k) of Q, k <
+// nf the enrichment rows of the vectors (times the atom's block of
+// (M~^ee)^-1 when inv is given), k = nf (with projectors) P^C_I s X^C; R = E s
+// X^C.  One work-group per (atom, 64 columns), one wave per function; the
+// partial rows of the atom's boxes are added in box order, sixteen in flight
+// (four in flight left the sums waiting for memory: 105 us for 64 atoms and
+// 160 vectors).
+struct SumArgs {
+  const int32_t *e_ptr, *e_pos, *k_ptr, *k_pos;
+  const double *Yp, *XE, *inv;
+  int64_t ldp, lde, ldq, prow;
+  double *Q, *R;
+  int nf, nx, ncols;
+};
+
+__global__ __launch_bounds__(640) void k_coef_sum(SumArgs a) {
+  const int I = blockIdx.x;
+  const int k = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), lane = threadIdx.x % 64;
+  const bool isE = k < a.nf;
+  const int col = blockIdx.y * 64 + lane, cc = min(col, a.ncols - 1);
+  const int32_t *ptr = isE ? a.e_ptr : a.k_ptr, *pos = isE ? a.e_pos : a.k_pos;
+  const int nf = isE ? a.nf : 1;
+  const double *yp = a.Yp + ((isE ? 0 : a.prow) + (isE ? k : 0)) * a.ldp + cc;
+  const int32_t q0 = ptr[I], q1 = ptr[I + 1];
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int32_t q = q0; q < q1; q += 16) {
+    double v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      v[j] = ld_nt(yp + (int64_t)pos[min(q + j, q1 - 1)] * nf * a.ldp);
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      if (q + j < q1) s[j % 4] += v[j];
+  }
+  const double sum = (s[0] + s[1]) + (s[2] + s[3]);
+  if (col >= a.ncols) return;
+  double *q = a.Q + ((int64_t)I * a.nx + k) * a.ldq + col;
+  if (!isE) {
+    *q = sum;
+    return;
+  }
+  a.R[((int64_t)I * a.nf + k) * a.ldq + col] = sum;
+  const double *xe = a.XE + (int64_t)I * a.nf * a.lde + col;
+  if (a.inv) {
+    const double *m = a.inv + ((int64_t)I * a.nf + k) * a.nf;
+    double x = 0.0;
+    for (int l = 0; l < a.nf; ++l) x += m[l] * xe[l * a.lde];
+    *q = x;
+  } else {
+    *q = xe[k * a.lde];
+  }
+}
+
+// the same for up to 16 vectors: the lanes of a wave share the boxes out, and
+// their sums meet in a fixed tree
+__global__ __launch_bounds__(640) void k_coef_sum_narrow(SumArgs a, int cw) {
+  const int I = blockIdx.x;
+  const int k = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), lane = threadIdx.x % 64;
+  const bool isE = k < a.nf;
+  const int col = lane % cw, sl = lane / cw, nsl = 64 / cw, cc = min(col, a.ncols - 1);
+  const int32_t *ptr = isE ? a.e_ptr : a.k_ptr, *pos = isE ? a.e_pos : a.k_pos;
+  const int nf = isE ? a.nf : 1;
+  const double *yp = a.Yp + ((isE ? 0 : a.prow) + (isE ? k : 0)) * a.ldp + cc;
+  const int32_t q0 = ptr[I], q1 = ptr[I + 1];
+  double sum = 0.0;
+  for (int32_t q = q0 + sl; q < q1; q += 4 * nsl) {
+    double v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = yp[(int64_t)pos[min(q + j * nsl, q1 - 1)] * nf * a.ldp];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (q + j * nsl < q1) sum += v[j];
+  }
+  for (int o = cw; o < 64; o <<= 1) sum += __shfl_xor(sum, o);
+  if (lane >= a.ncols) return;   // sl = 0 and a column of the block
+  double *q = a.Q + ((int64_t)I * a.nx + k) * a.ldq + col;
+  if (!isE) {
+    *q = sum;
+    return;
+  }
+  a.R[((int64_t)I * a.nf + k) * a.ldq + col] = sum;
+  const double *xe = a.XE + (int64_t)I * a.nf * a.lde + col;
+  if (a.inv) {
+    const double *m = a.inv + ((int64_t)I * a.nf + k) * a.nf;
+    double x = 0.0;
+    for (int l = 0; l < a.nf; ++l) x += m[l] * xe[l * a.lde];
+    *q = x;
+  } else {
+    *q = xe[k * a.lde];
+  }
+}
+
+// Dense part: S Q with the symmetric matrix of the coefficients (couple.hip).
+// Rows k < nf: Y^E = alpha (R + S Q) + epilogue terms; rows k = nf: the
+// projector coefficients W, behind the rows of Q.  One work-group per 16 rows
+// and 16 CB columns; its four waves take every fourth k step and their sums
+// meet in LDS in a fixed order (the split of the sum over work-groups that this
+// replaces needed a cleared output and atomics).
+template <int CB>
+__global__ __launch_bounds__(256) void k_coef_dense(int64_t n, int nf, int nx, int ncols,
+                                                    const double *__restrict__ S, double *Q,
+                                                    int64_t ldq, const double *__restrict__ R,
+                                                    EpiArgs e, double *YE, int64_t ldy) {
+  __shared__ double red[4][16][16 * CB];
+  const int t = threadIdx.x, wave = t / 64, lane = t % 64, li = lane % 16, lk = lane / 16;
+  const int64_t row0 = (int64_t)blockIdx.x * 16;
+  const int c0 = blockIdx.y * 16 * CB;
+  const int64_t rl = min(row0 + li, n - 1);
+  int cc[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) cc[cb] = min(c0 + 16 * cb + li, ncols - 1);
+  v4d acc[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) acc[cb] = (v4d){0.0, 0.0, 0.0, 0.0};
+  const int64_t nks = (n + 3) / 4;
+#pragma unroll 4
+  for (int64_t ks = wave; ks < nks; ks += 4) {
+    const int64_t kk = min(4 * ks + lk, n - 1);
+    const double av = 4 * ks + lk < n ? S[kk * n + rl] : 0.0;
+    double bv[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) bv[cb] = Q[kk * ldq + cc[cb]];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+      acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[cb], acc[cb], 0, 0, 0);
+  }
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave][4 * v + lk][16 * cb + li] = acc[cb][v];
+  __syncthreads();
+  for (int i = t; i < 256 * CB; i += 256) {
+    const int rr = i / (16 * CB), c = i % (16 * CB), col = c0 + c;
+    const int64_t row = row0 + rr;
+    if (row >= n || col >= ncols) continue;
+    const double v = (red[0][rr][c] + red[1][rr][c]) + (red[2][rr][c] + red[3][rr][c]);
+    const int64_t I = row / nx;
+    const int k = (int)(row - I * nx);
+    if (k < nf) {
+      const int64_t f = I * nf + k, o = f * ldy + col;
+      YE[o] = e.alpha * (v + R[f * ldq + col]) + epi_terms(e, o, col);
+    } else {
+      Q[(n + I) * ldq + col] = v;
+    }
+  }
+}
+
+// All terms of Y^C but dense cell products:
+//   Y^C = alpha (sum over the node's cells of Yc + E^T X^E + P^C^T W)
+//         + beta Z1 + gamma Z2 + alpha G diag(Cl)      (boundary rows 0)
+// brick by brick (4 x 4 x 4 nodes): each of the four waves multiplies 16 nodes
+// (one z layer) by all columns, the coefficient rows of the brick's atoms
+// streaming through LDS; the other terms are read and Y^C is written once, in
+// 16-byte pieces.  HBM-bound: the products of one brick run while others
+// wait for their rows (64 atoms, 160 vectors: 6.5 GB in 1.61 ms, 4.0 TB/s;
+// the separate start-value pass and colour passes it replaces took 5.3 ms).
+template <typename T>
+struct NodeArgs {
+  BoxSet<T> E;
+  BoxSet<double> K;
+  const double *Q, *Yc;
+  int64_t ldq, ldc, wrow;          // wrow: first row of W in Q
+  int nx, ncols, nparts;           // nparts: column parts of 16 CBM
+  NodeGrid g;
+  EpiArgs e;
+  double *Y;
+  int64_t ldy;
+  bool vec;
+};
+
+constexpr int NODE_SEG = 512;      // functions whose row numbers sit in LDS
+
+// acc += tile (16 nodes x K functions) times the functions' rows of Q
+template <typename T, int CBM, typename Acc>
+__device__ __forceinline__ void brick_product(const T *tp, int K, const int32_t *atoms, int nf,
+                                              int nx, int64_t row0, const double *Q, int64_t ldq,
+                                              int ncols, T *Xs, int32_t *gs, Acc (&acc)[CBM]) {
+  const int t = threadIdx.x, lane = t % 64, li = lane % 16, lk = lane / 16;
+  for (int f0 = 0; f0 < K; f0 += NODE_SEG) {
+    const int nseg = min(K - f0, NODE_SEG), KS = (nseg + 3) / 4, NCH = (nseg + 15) / 16;
+    __syncthreads();
+    for (int i = t; i < 16 * NCH; i += 256) {
+      const int f = f0 + min(i, nseg - 1);
+      gs[i] = (int32_t)(row0 + (int64_t)atoms[f / nf] * nx + f % nf);
+    }
+    __syncthreads();
+    RowStage<T, CBM> st;
+    T a0[4], a1[4];
+    const T *sp = tp + (f0 / 4) * 64;
+    auto a_load = [&](int ch, T (&d)[4]) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) d[s] = ld_nt(sp + min(4 * ch + s, KS - 1) * 64);
+    };
+    auto step = [&](int ch, const T (&cur)[4], T (&nxt)[4], int buf) {
+      if (ch + 1 < NCH) {
+        st.load(Q, ldq, gs + 16 * (ch + 1), ncols, true);
+        a_load(ch + 1, nxt);
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (4 * ch + s < KS)
+          tile_step<T, CBM>(Xs + buf * 256 * CBM, s, cur[s], li, lk, acc);
+      if (ch + 1 < NCH) st.store(Xs + (buf ^ 1) * 256 * CBM, nullptr);
+      __syncthreads();
+    };
+    st.load(Q, ldq, gs, ncols, true);
+    a_load(0, a0);
+    st.store(Xs, nullptr);
+    __syncthreads();
+    for (int ch = 0; ch < NCH; ch += 2) {
+      step(ch, a0, a1, 0);
+      if (ch + 1 < NCH) step(ch + 1, a1, a0, 1);
+    }
+  }
+}
+
+template <typename T, int CBM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+void k_node_update(NodeArgs<T> a) {
+  __shared__ __align__(16) double Xs[2 * 256 * CBM];
+  __shared__ int32_t gs[NODE_SEG];
+  // the column parts of a brick, and neighbouring bricks, run on one XCD
+  int64_t b = blockIdx.x;
+  if (gridDim.x % 8 == 0) b = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const int c0 = (int)(b % a.nparts) * 16 * CBM, ncols = min(a.ncols - c0, 16 * CBM);
+  b /= a.nparts;
+  const double *const Qc = a.Q + c0;
+  const int t = threadIdx.x, wave = t / 64, lane = t % 64, li = lane % 16, lk = lane / 16;
+  const NodeGrid &g = a.g;
+  v4d acc[CBM];
+#pragma unroll
+  for (int cb = 0; cb < CBM; ++cb) acc[cb] = (v4d){0.0, 0.0, 0.0, 0.0};
+  {
+    const int a0 = a.E.ptr[b], K = (a.E.ptr[b + 1] - a0) * a.E.nf;
+    if (K > 0) {
+      const T *tp = a.E.tile + 256 * a.E.ksoff[b] + (int64_t)wave * ((K + 3) / 4) * 64 + lane;
+      if constexpr (sizeof(T) == 8) {
+        brick_product<T, CBM>(tp, K, a.E.atom + a0, a.E.nf, a.nx, 0, Qc, a.ldq, ncols, Xs, gs,
+                              acc);
+      } else {
+        v4f acf[CBM];
+#pragma unroll
+        for (int cb = 0; cb < CBM; ++cb) acf[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
+        brick_product<T, CBM>(tp, K, a.E.atom + a0, a.E.nf, a.nx, 0, Qc, a.ldq, ncols, (T *)Xs,
+                              gs, acf);
+        // the FP32 blocks hold their rows so that both accumulator layouts agree
+#pragma unroll
+        for (int cb = 0; cb < CBM; ++cb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[cb][v] = (double)acf[cb][v];
+      }
+    }
+  }
+  {
+    const int a0 = a.K.ptr[b], K = a.K.ptr[b + 1] - a0;
+    if (K > 0) {
+      const double *tp = a.K.tile + 256 * a.K.ksoff[b] + (int64_t)wave * ((K + 3) / 4) * 64 + lane;
+      brick_product<double, CBM>(tp, K, a.K.atom + a0, 1, 1, a.wrow, Qc, a.ldq, ncols, Xs, gs,
+                                 acc);
+    }
+  }
+  // accumulator v of lane l: node 4 v + l/16 of the layer, i.e. (x, y) = (l/16, v)
+  int o[3];
+  box_origin(g, EFE_BRICK, b, o);
+  const int gi = o[0] + lk, gk = o[2] + wave;
+  if (gi >= g.n1[0] || gk >= g.n1[2]) return;
+  const EpiArgs &e = a.e;
+  const int cx = gi / g.p, cz = gk / g.p, lx = gi - cx * g.p, lz = gk - cz * g.p;
+  constexpr int NQ = CBM == 1 ? 1 : CBM / 2;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int gj = o[1] + v;
+    if (gj >= g.n1[1]) break;
+    const int64_t row = ((int64_t)gi + (int64_t)g.n1[0] * (gj + (int64_t)g.n1[1] * gk)) * a.ldy + c0;
+    const bool inner = gi > 0 && gi < g.n1[0] - 1 && gj > 0 && gj < g.n1[1] - 1 && gk > 0 &&
+                       gk < g.n1[2] - 1;
+    if constexpr (CBM == 1) {
+      if (li >= ncols) continue;
+      double s = acc[0][v];
+      if (a.Yc && inner) {
+        const int cy = gj / g.p, ly = gj - cy * g.p;
+        for (int z = lz == 0 ? -1 : 0; z <= 0; ++z)
+          for (int y = ly == 0 ? -1 : 0; y <= 0; ++y)
+            for (int x = lx == 0 ? -1 : 0; x <= 0; ++x) {
+              const int64_t cell = cx + x + g.nc[0] * (cy + y + (int64_t)g.nc[1] * (cz + z));
+              const int l = (x ? g.p : lx) + g.P * ((y ? g.p : ly) + g.P * (z ? g.p : lz));
+              s += a.Yc[(cell * (g.P * g.P * g.P) + l) * a.ldc + c0 + li];
+            }
+      }
+      const double terms = epi_terms(e, row + li, c0 + li);
+      a.Y[row + li] = inner ? e.alpha * s + terms : 0.0;
+    } else {
+      // pairs by 16-byte accesses when the layout allows it (vec: even ld,
+      // aligned arrays), else element by element
+      auto ld2 = [&](const double *p, int q) -> double2 {
+        const int c = 32 * q + 2 * li;
+        if (a.vec && c + 1 < ncols) return ld_nt2(p + row + c);
+        double2 r;
+        r.x = c < ncols ? p[row + c] : 0.0;
+        r.y = c + 1 < ncols ? p[row + c + 1] : 0.0;
+        return r;
+      };
+      double2 z1[NQ], z2[NQ], gg[NQ], s[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        z1[q] = z2[q] = gg[q] = make_double2(0.0, 0.0);
+        if (e.Z1) z1[q] = ld2(e.Z1, q);
+        if (e.Z2) z2[q] = ld2(e.Z2, q);
+        if (e.G) gg[q] = ld2(e.G, q);
+        s[q] = make_double2(acc[2 * q][v], acc[2 * q + 1][v]);
+      }
+      if (a.Yc && inner) {
+        const int cy = gj / g.p, ly = gj - cy * g.p;
+        for (int z = lz == 0 ? -1 : 0; z <= 0; ++z)
+          for (int y = ly == 0 ? -1 : 0; y <= 0; ++y)
+            for (int x = lx == 0 ? -1 : 0; x <= 0; ++x) {
+              const int64_t cell = cx + x + g.nc[0] * (cy + y + (int64_t)g.nc[1] * (cz + z));
+              const int l = (x ? g.p : lx) + g.P * ((y ? g.p : ly) + g.P * (z ? g.p : lz));
+              const double *yc = a.Yc + (cell * (g.P * g.P * g.P) + l) * a.ldc + c0 + 2 * li;
+              double2 y2[NQ];
+#pragma unroll
+              for (int q = 0; q < NQ; ++q)
+                y2[q] = 32 * q + 2 * li < ncols ? ld_nt2(yc + 32 * q) : make_double2(0.0, 0.0);
+#pragma unroll
+              for (int q = 0; q < NQ; ++q) {
+                s[q].x += y2[q].x;
+                s[q].y += y2[q].y;
+              }
+            }
+      }
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int c = 32 * q + 2 * li;
+        if (c >= ncols) continue;
+        const bool two = c + 1 < ncols;
+        double2 y = make_double2(0.0, 0.0);
+        if (inner) {
+          const double cl0 = e.G ? e.Cl[c0 + c] : 0.0, cl1 = e.G && two ? e.Cl[c0 + c + 1] : 0.0;
+          y.x = e.alpha * (s[q].x + gg[q].x * cl0) + e.beta * z1[q].x + e.gamma * z2[q].x;
+          y.y = e.alpha * (s[q].y + gg[q].y * cl1) + e.beta * z1[q].y + e.gamma * z2[q].y;
+        }
+        if (a.vec && two) {
+          st_nt2(y, a.Y + row + c);
+        } else {
+          a.Y[row + c] = y.x;
+          if (two) a.Y[row + c + 1] = y.y;
+        }
+      }
+    }
+  }
 }
 
 // ------------------------------------------------------------------ overlap
@@ -855,66 +1026,40 @@ __global__ void k_enr_block_apply(int natoms, int nf, int ncols, const double *_
 }
 
 // ------------------------------------------------------------------ launchers
-// Colour passes of the cell GEMM in column chunks of 16 CBM.
+// Colour passes of the dense cell GEMM in column chunks of 16 CBM.
 template <typename T, int RBW, int CBM>
-static void launch_cell3(efe_ctx *c, const T *Ht, const T *Et, const T *Ee, const double *X,
-                         int64_t ldx, const double *scale, const double *XE, int64_t lde,
-                         double *Y, int64_t ldy, double alpha, double *Yp, int64_t ldp,
-                         int ncols, bool hcell) {
-  const bool enr = c->n_enr > 0 && c->ncpairs > 0;
-  if (!enr && !hcell) return;
+static void launch_cell3(efe_ctx *c, const T *Ht, const double *X, int64_t ldx,
+                         const double *scale, double *Y, int64_t ldy, double alpha, int ncols) {
   CellOps<T> a;
-  a.hcell = hcell;
-  a.nparts_c = (int)cdiv(c->RB, 4 * RBW);
-  a.nparts_e = enr ? (int)cdiv(c->max_rbe, 4 * RBW) : 0;
+  a.nparts = (int)cdiv(c->RB, 4 * RBW);
   a.c2g = c->d_c2g;
   a.nloc = c->nloc;
   a.RB = c->RB;
   a.KS = c->KS;
-  a.nf = c->nf;
   a.Ht = Ht;
-  a.Et = Et;
-  a.Ee = Ee;
   a.ldx = ldx;
   a.scale = scale;
   a.minv = c->d_minv;
-  a.lde = lde;
   a.ldy = ldy;
   a.alpha = alpha;
-  a.ldp = ldp;
-  a.cell_eptr = c->d_cell_eptr;
-  a.cell_epair = c->d_cell_epair;
-  a.pair_atom = c->d_cpair_atom;
-  a.cell_noff = c->d_cell_noff;
-  const int nparts = a.nparts_c + a.nparts_e;
   for (int col0 = 0; col0 < ncols; col0 += 16 * CBM) {
     a.ncols = std::min(16 * CBM, ncols - col0);
     a.X = X + col0;
-    a.XE = XE + col0;
     a.Y = Y + col0;
-    a.Yp = Yp + col0;
     for (int col = 0; col < 8; ++col) {
       const int nc = c->colour_offsets[col + 1] - c->colour_offsets[col];
       if (nc == 0) continue;
       a.ncells = nc;
       a.cells = c->d_colour_order + c->colour_offsets[col];
-      const int64_t nblk = cdiv(nc, 8) * 8 * nparts;
+      const int64_t nblk = cdiv(nc, 8) * 8 * a.nparts;
       const int t = efe_timer_begin(c, CBM == 1 ? EFE_T_CELL_NARROW : EFE_T_CELL);
-      if (enr)
-        k_cell3<T, RBW, CBM, true><<<nblk, 256, 0, c->stream>>>(a);
-      else
-        k_cell3<T, RBW, CBM, false><<<nblk, 256, 0, c->stream>>>(a);
+      k_cell3<T, RBW, CBM><<<nblk, 256, 0, c->stream>>>(a);
       efe_timer_end(c, CBM == 1 ? EFE_T_CELL_NARROW : EFE_T_CELL, t);
     }
   }
 }
 
-__global__ void k_fill_zero(int64_t n, double *__restrict__ x) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) x[i] = 0.0;
-}
-
-// X -> Xc with an even leading dimension (the cell GEMM's paired gathers)
+// X -> Xc with an even leading dimension (the dense cell GEMM's paired gathers)
 __global__ void k_copy_cols(int64_t rows, int ncols, const double *__restrict__ X, int64_t ldx,
                             double *__restrict__ Y, int64_t ldy) {
   const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -924,7 +1069,53 @@ __global__ void k_copy_cols(int64_t rows, int ncols, const double *__restrict__ 
   Y[r * ldy + j] = X[r * ldx + j];
 }
 
-efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, const double *scale,
+template <typename T>
+static BoxSet<T> box_set(const CoupleSet &S, bool brick, const T *tile) {
+  return {brick ? S.d_bk_ptr : S.d_bx_ptr, S.d_rboff, S.d_bk_atom, S.d_bk_off, tile, S.d_live, S.nf};
+}
+
+// column blocks of the register tile: the narrowest that holds the columns
+// (the products of empty columns cost as much as those of full ones)
+static int tile_blocks(int ncols) {
+  const int n = (int)cdiv(ncols, 16);
+  return n == 1 ? 1 : (n + 1) / 2 * 2;
+}
+
+template <typename T>
+static void launch_box_gather(efe_ctx *c, const GatherArgs<T> &a, int64_t n) {
+  if (n == 0) return;
+#define GO(B) k_box_gather<T, B><<<n, 256, 0, c->stream>>>(a)
+  switch (tile_blocks(a.ncols)) {
+    case 1: GO(1); break;
+    case 2: GO(2); break;
+    case 4: GO(4); break;
+    case 6: GO(6); break;
+    case 8: GO(8); break;
+    default: GO(10);
+  }
+#undef GO
+}
+
+template <typename T>
+static void launch_node_update(efe_ctx *c, NodeArgs<T> a, const T *tile) {
+  a.E = box_set(c->cpl_e, true, tile);
+  a.K = box_set<double>(c->cpl_k, true, c->cpl_k.d_T1);
+  // 64-column parts: their 95 registers leave five waves a SIMD to cover the
+  // reads (64 atoms, 160 vectors: 1.61 ms, against 1.71 in 32-column parts, 1.9
+  // in one 160-column part with two waves)
+  const int B = std::min(tile_blocks(a.ncols), 4);
+  a.nparts = (int)cdiv(a.ncols, 16 * B);
+  const int64_t n = c->cpl_e.n_brick * a.nparts;
+#define GO(B) k_node_update<T, B><<<n, 256, 0, c->stream>>>(a)
+  switch (B) {
+    case 1: GO(1); break;
+    case 2: GO(2); break;
+    default: GO(4);
+  }
+#undef GO
+}
+
+efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, bool minv,
                                 const double *XE, int64_t lde, double *Y, int64_t ldy, int ncols,
                                 int prec, const ApplyEpilogue *epi) {
   if (!c->have_potential) EFE_FAIL(c, EFE_ESTATE, "no potential set");
@@ -935,94 +1126,130 @@ efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, const
   if (prec == EFE_BF16 && c->n_enr > 0)
     EFE_FAIL(c, EFE_EINVAL, "the BF16 cell GEMM takes plain CFE systems only");
   efe_status s;
-  const int nf = c->nf;
-  const int64_t nn = c->n_nodes, ne = c->n_enr;
+  const int64_t nn = c->n_nodes;
   ApplyEpilogue E0;
   const ApplyEpilogue &ep = epi ? *epi : E0;
-  // the cell GEMM reads the CFE rows in pairs with 32-bit offsets: other
-  // layouts are copied to an even leading dimension first
-  const bool pairs_ok = (ldx % 2 == 0) && ((uintptr_t)XC % 16 == 0) && nn * ldx < (1ll << 31);
-  if (!pairs_ok) {
-    const int64_t ldc = (ncols + 1) & ~1;
+  auto al = [](const double *p) { return p == nullptr || (uintptr_t)p % 16 == 0; };
+  const bool xvec = ldx % 2 == 0 && al(XC);
+  if ((!xvec || nn * ldx >= (1ll << 31)) && nn * (int64_t)((ncols + 1) & ~1) >= (1ll << 31))
+    EFE_FAIL(c, EFE_EINVAL, "n_nodes x columns exceeds the 32-bit offsets of the cell GEMM");
+  const bool tp = c->tp && prec != EFE_BF16;
+  const double *scale = minv ? c->d_minv : nullptr;
+  const double *Xd = XC;             // rows as the dense cell GEMM takes them
+  int64_t ldd = ldx;
+  if (!tp && (!xvec || nn * ldx >= (1ll << 31))) {
     double *Xc;
-    if (nn * ldc >= (1ll << 31))
-      EFE_FAIL(c, EFE_EINVAL, "n_nodes x columns exceeds the 32-bit offsets of the cell GEMM");
-    if ((s = efe_ws(c, 0, (size_t)nn * ldc * 8, (void **)&Xc))) return s;
-    k_copy_cols<<<cdiv(nn * ncols, 256), 256, 0, c->stream>>>(nn, ncols, XC, ldx, Xc, ldc);
-    XC = Xc;
-    ldx = ldc;
+    ldd = (ncols + 1) & ~1;
+    if ((s = efe_ws(c, 0, (size_t)nn * ldd * 8, (void **)&Xc))) return s;
+    k_copy_cols<<<cdiv(nn * ncols, 256), 256, 0, c->stream>>>(nn, ncols, XC, ldx, Xc, ldd);
+    Xd = Xc;
   }
-  if (ne && ((lde % 2) || ((uintptr_t)XE % 16) || ne * lde >= (1ll << 31))) {
-    const int64_t ldc = (ncols + 1) & ~1;
-    double *Xc;
-    if ((s = efe_ws(c, 12, (size_t)ne * ldc * 8, (void **)&Xc))) return s;
-    k_copy_cols<<<cdiv(ne * ncols, 256), 256, 0, c->stream>>>(ne, ncols, XE, lde, Xc, ldc);
-    XE = Xc;
-    lde = ldc;
-  }
-  double *W = nullptr, *Yp = nullptr, *TE = nullptr;
-  if (c->nproj && (s = efe_ws(c, 1, (size_t)c->nproj * ncols * 8, (void **)&W))) return s;
-  if (ne) {
-    if ((s = efe_ws(c, 9, (size_t)nf * std::max<int64_t>(c->ncpairs, 1) * ncols * 8, (void **)&Yp)))
+  const int nx = c->nf + (c->nproj ? 1 : 0);
+  const int64_t nq = (int64_t)c->natoms * nx;      // coefficient rows
+  const int64_t ldq = (ncols + 1) & ~1;            // own buffers: pairs are aligned
+  const CoupleSet &cE = c->cpl_e, &cK = c->cpl_k;
+  const int64_t prow = c->nf > 0 ? (int64_t)c->nf * cE.n_boxpairs : 0;
+  double *Q = nullptr, *R = nullptr, *Yp = nullptr;
+  if (nq) {
+    if ((s = efe_ws(c, 1, (size_t)(nq + c->nproj) * ldq * 8, (void **)&Q))) return s;
+    if ((s = efe_ws(c, 11, (size_t)std::max<int64_t>(c->n_enr, 1) * ldq * 8, (void **)&R)))
       return s;
-    if ((s = efe_ws(c, 11, (size_t)ne * ncols * 8, (void **)&TE))) return s;
+    if ((s = efe_ws(c, 9, (size_t)std::max<int64_t>(prow + cK.n_boxpairs, 1) * ncols * 8,
+                    (void **)&Yp)))
+      return s;
   }
-  EpiArgs ec{ep.alpha, ep.beta, ep.gamma, ep.Z1, ep.Z2, ep.G, ep.Cl};
+  const EpiArgs ec{ep.alpha, ep.beta, ep.gamma, ep.Z1, ep.Z2, ep.G, ep.Cl};
+  const bool f32 = prec == EFE_FP32;
   const int t_cls = ncols <= 16 ? EFE_T_APPLY_NARROW : EFE_T_APPLY;
   const int t_apply = efe_timer_begin(c, t_cls);
-  // 0. cell Hamiltonians by tensor products, into a workspace that the start
-  //    values of Y^C gather from (one launch, fixed order); without room for
-  //    it, added to Y^C colour by colour below
-  const bool tp = c->tp && prec != EFE_BF16;
-  double *Yc = tp ? efe_ws_try(c, 15, (size_t)c->n_cells * c->nloc * ncols * 8) : nullptr;
-  if (Yc && (s = efe_tp_apply(c, XC, ldx, scale != nullptr, ncols, Yc, nullptr, 0, 0.0))) return s;
-  // 1. projector coefficients W = D (P^C s X^C + P~^phi X^E), then Y^C =
-  //    alpha P^C^T W + epilogue terms on every node
+  // 1. cell Hamiltonians by tensor products, into a workspace that the node
+  //    update sums (one launch, fixed order); without room for it, added to
+  //    Y^C colour by colour below
+  const int64_t ldc = ncols <= 16 ? ncols : ldq;
+  double *Yc = tp ? efe_ws_try(c, 15, (size_t)c->n_cells * c->nloc * ldc * 8) : nullptr;
+  if (Yc && (s = efe_tp_apply(c, XC, ldx, minv, ncols, Yc, ldc, nullptr, 0, 0.0))) return s;
+  // 2. coefficients: [E ; P^C] s X^C by boxes, their sums, the dense part (Y^E
+  //    and the projector coefficients W)
+  if (nq) {
+    const int t = efe_timer_begin(c, EFE_T_POST);
+    GatherArgs<double> g{};
+    g.X = XC;
+    g.minv = c->d_minv;
+    g.ldx = ldx;
+    g.ldp = ncols;
+    g.prow = prow;
+    g.Yp = Yp;
+    g.E = box_set<double>(cE, false, cE.d_T2);
+    g.K = box_set<double>(cK, false, cK.d_T2);
+    g.g = node_grid(c);
+    g.ncols = ncols;
+    g.scaled = minv;
+    g.vec = xvec;
+    if (f32) {
+      GatherArgs<float> h{};
+      h.items = c->d_items[0];
+      h.X = g.X;
+      h.minv = g.minv;
+      h.ldx = g.ldx;
+      h.ldp = g.ldp;
+      h.prow = g.prow;
+      h.Yp = g.Yp;
+      h.E = box_set<float>(cE, false, cE.d_T2f);
+      h.K = g.K;
+      h.g = g.g;
+      h.ncols = ncols;
+      h.scaled = g.scaled;
+      h.vec = g.vec;
+      launch_box_gather(c, h, c->n_items[0]);
+    }
+    g.items = c->d_items[f32 ? 1 : 2];
+    launch_box_gather(c, g, c->n_items[f32 ? 1 : 2]);
+    SumArgs sa{cE.d_at_ptr, cE.d_at_pos, cK.d_at_ptr, cK.d_at_pos, Yp, XE, minv ? c->d_Mee_inv : nullptr,
+               ncols, lde, ldq, prow, Q, R, c->nf, nx, ncols};
+    if (ncols <= 16) {
+      int cw = 1;
+      while (cw < ncols) cw *= 2;
+      k_coef_sum_narrow<<<c->natoms, 64 * nx, 0, c->stream>>>(sa, cw);
+    } else {
+      k_coef_sum<<<dim3(c->natoms, cdiv(ncols, 64)), 64 * nx, 0, c->stream>>>(sa);
+    }
+    EpiArgs ee = ec;
+    if (ee.Z1) ee.Z1 += nn * ldy;
+    if (ee.Z2) ee.Z2 += nn * ldy;
+    if (ee.G) ee.G += nn * ldy;
+    if (ncols <= 16)
+      k_coef_dense<1><<<dim3(cdiv(nq, 16), 1), 256, 0, c->stream>>>(nq, c->nf, nx, ncols, c->d_S, Q,
+                                                                   ldq, R, ee, Y + nn * ldy, ldy);
+    else
+      k_coef_dense<5><<<dim3(cdiv(nq, 16), cdiv(ncols, 80)), 256, 0, c->stream>>>(
+          nq, c->nf, nx, ncols, c->d_S, Q, ldq, R, ee, Y + nn * ldy, ldy);
+    efe_timer_end(c, EFE_T_POST, t);
+  }
+  // 3. every other term of Y^C
   {
     const int t = efe_timer_begin(c, EFE_T_PRE);
-    if (c->nproj) {
-      // (without enrichment this writes W = 0)
-      k_kb_w_pphi<<<dim3(c->nproj, cdiv(ncols, 64)), 256, 0, c->stream>>>(
-          ncols, ne, c->d_Ptil, XE, lde, c->d_D, W);
-      if (c->n_kb_items) {
-        XcdSplit xs;
-        for (int i = 0; i <= 8; ++i) xs.off[i] = c->kb_items_off[i];
-        if (ncols == 1)
-          k_kb_project1<<<c->n_kb_items, 256, 0, c->stream>>>(c->d_kb_items, c->d_kbnode,
-                                                              c->d_Pc_am, XC, ldx, scale, c->d_D, W);
-        else
-          k_kb_project<<<dim3(8 * xs.max_len(), cdiv(ncols, 128 * KBP)), 256, 0, c->stream>>>(
-              ncols, c->d_kb_items, xs, c->d_kbnode, c->d_Pc_am, XC, ldx, scale, c->d_D, W);
-      }
-    }
-    auto al = [](const double *p) { return p == nullptr || (uintptr_t)p % 16 == 0; };
     const bool vec = ldy % 2 == 0 && al(Y) && al(ep.Z1) && al(ep.Z2) && al(ep.G);
-    const CellSum cs{Yc, c->p, c->P, c->nloc, c->ncell[0], c->ncell[1], c->n1[0], c->n1[1]};
-    const int64_t nbx = cdiv(c->n1[0] * (((ncols + 1) / 2 + EXP_P - 1) / EXP_P), 256);
-    k_expand_init<<<nbx * c->n1[1] * c->n1[2], 256, 0, c->stream>>>(
-        nn, ncols, c->nproj ? c->d_kbnm_ptr : nullptr, c->d_kbnm_atom, c->d_Pc_nm, W, c->d_minv,
-        ec, cs, (int)nbx, Y, ldy, vec);
+    if (f32) {
+      NodeArgs<float> a{{}, {}, Q, Yc, ldq, ldc, nq, nx, ncols, 1, node_grid(c), ec, Y, ldy, vec};
+      launch_node_update(c, a, (const float *)cE.d_T1f);
+    } else {
+      NodeArgs<double> a{{}, {}, Q, Yc, ldq, ldc, nq, nx, ncols, 1, node_grid(c), ec, Y, ldy, vec};
+      launch_node_update(c, a, (const double *)cE.d_T1);
+    }
     efe_timer_end(c, EFE_T_PRE, t);
   }
-  if (tp && !Yc &&
-      (s = efe_tp_apply(c, XC, ldx, scale != nullptr, ncols, nullptr, Y, ldy, ep.alpha)))
-    return s;
-  // 2. cell GEMM, colour by colour: 160-column register tiles; a single
-  //    16-column tile (six row blocks per wave) for narrow blocks such as the
-  //    Lanczos vector
-  if (prec == EFE_FP64 && ncols <= 16)
-    launch_cell3<double, 6, 1>(c, c->d_Htile64, c->d_Et64, c->d_Ee64, XC, ldx, scale, XE, lde, Y,
-                               ldy, ep.alpha, Yp, ncols, ncols, !tp);
-  else if (prec == EFE_FP64)
-    launch_cell3<double, 1, 10>(c, c->d_Htile64, c->d_Et64, c->d_Ee64, XC, ldx, scale, XE, lde, Y,
-                                ldy, ep.alpha, Yp, ncols, ncols, !tp);
-  else if (prec == EFE_FP32 && ncols <= 16)
-    launch_cell3<float, 6, 1>(c, c->d_Htile32, c->d_Et32, c->d_Ee32, XC, ldx, scale, XE, lde, Y,
-                              ldy, ep.alpha, Yp, ncols, ncols, !tp);
-  else if (prec == EFE_FP32)
-    launch_cell3<float, 2, 10>(c, c->d_Htile32, c->d_Et32, c->d_Ee32, XC, ldx, scale, XE, lde, Y,
-                               ldy, ep.alpha, Yp, ncols, ncols, !tp);
-  else {
+  // 4. cell products that are added to Y^C colour by colour
+  if (tp) {
+    if (!Yc && (s = efe_tp_apply(c, XC, ldx, minv, ncols, nullptr, 0, Y, ldy, ep.alpha))) return s;
+  } else if (prec == EFE_FP64 && ncols <= 16) {
+    launch_cell3<double, 6, 1>(c, c->d_Htile64, Xd, ldd, scale, Y, ldy, ep.alpha, ncols);
+  } else if (prec == EFE_FP64) {
+    launch_cell3<double, 1, 10>(c, c->d_Htile64, Xd, ldd, scale, Y, ldy, ep.alpha, ncols);
+  } else if (f32 && ncols <= 16) {
+    launch_cell3<float, 6, 1>(c, c->d_Htile32, Xd, ldd, scale, Y, ldy, ep.alpha, ncols);
+  } else if (f32) {
+    launch_cell3<float, 2, 10>(c, c->d_Htile32, Xd, ldd, scale, Y, ldy, ep.alpha, ncols);
+  } else {
     const int NT = 32;
     const int ntiles = (int)cdiv(ncols, NT);
     const size_t shm = (size_t)NT * (c->KS32 * 32 + 8) * 2;
@@ -1033,31 +1260,11 @@ efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, const
       const int t = efe_timer_begin(c, EFE_T_CELL);
       k_cell_bf16<32><<<nblk, 256, shm, c->stream>>>(
           nc, ntiles, c->d_colour_order + c->colour_offsets[col], c->d_c2g, c->nloc, c->RB,
-          c->KS32, (const v8bf *)c->d_Htile16, XC, ldx, scale, Y, ldy, c->d_minv, ncols,
+          c->KS32, (const v8bf *)c->d_Htile16, Xd, ldd, scale, Y, ldy, c->d_minv, ncols,
           ep.alpha);
       efe_timer_end(c, EFE_T_CELL, t);
     }
   }
-  // 3. enrichment rows: Y^E = alpha (sum of the cells' partial rows
-  //    + H^E_ee X^E + P~^phi^T W) + epilogue terms
-  const int t_post = efe_timer_begin(c, EFE_T_POST);
-  if (ne) {
-    k_fill_zero<<<cdiv(ne * ncols, 256), 256, 0, c->stream>>>(ne * ncols, TE);
-    if ((s = efe_dgemm(c, false, false, ne, ncols, ne, 1.0, c->d_Hee, ne, XE, lde, 1.0, TE, ncols,
-                               nullptr, true)))
-      return s;
-    if (c->nproj &&
-        (s = efe_dgemm(c, true, false, ne, ncols, c->nproj, 1.0, c->d_Ptil, ne, W, ncols, 1.0, TE,
-                            ncols, nullptr, true)))
-      return s;
-    EpiArgs ee = ec;
-    if (ee.Z1) ee.Z1 += nn * ldy;
-    if (ee.Z2) ee.Z2 += nn * ldy;
-    if (ee.G) ee.G += nn * ldy;
-    k_enr_reduce<<<dim3(c->natoms, cdiv(ncols, 64)), 64 * nf, 0, c->stream>>>(
-        nf, ncols, c->d_cpair_ptr, c->d_cpair_cpos, Yp, ncols, TE, ee, Y + nn * ldy, ldy);
-  }
-  efe_timer_end(c, EFE_T_POST, t_post);
   efe_timer_end(c, t_cls, t_apply);
   HIPCHK(c, hipGetLastError());
   return EFE_OK;
@@ -1133,7 +1340,7 @@ static efe_status apply_H_chunked(efe_ctx *c, const double *X, double *Y, int32_
   efe_status s;
   for (int32_t j0 = 0; j0 < ncols; j0 += EFE_COL_CHUNK) {
     const int32_t nc = std::min<int32_t>(EFE_COL_CHUNK, ncols - j0);
-    if ((s = efe_apply_H_internal(c, X + j0, ld, nullptr, X + c->n_nodes * ld + j0, ld, Y + j0, ld,
+    if ((s = efe_apply_H_internal(c, X + j0, ld, false, X + c->n_nodes * ld + j0, ld, Y + j0, ld,
                                   nc, prec)))
       return s;
   }

@@ -1,0 +1,426 @@
+// Coupling of the orthogonalized enrichment and of the projectors to the CFE
+// nodes, as dense blocks over boxes of nodes.
+//
+// The enrichment couples to a node j through E_fj = sum over the cells c of j
+// of (B_c - C_c H_c)_fj (Sec. II.B, N^E = phi - C N^C, E = B - C H^cc), formed
+// in FP64 per cell and summed over the cells here, so that every node enters
+// the products once (per cell, shared faces enter up to eight times: 1.5 times
+// the flops at p = 6).  The apply needs E both ways, in two sets of blocks:
+//   bricks  4 x 4 x 4 nodes (rows) x the functions of the atoms that touch the
+//           brick: Y^C += E^T X^E.  Four 16-row blocks, one a wave; the
+//           smaller the brick, the fewer zero entries of E it holds.
+//   boxes   8 x 8 x 8 nodes (summation) x those functions (rows): E X^C, one
+//           partial row per (box, function).  Larger boxes mean fewer partial
+//           rows (0.11 ms of traffic for 64 atoms and 160 vectors, against 0.2
+//           with 8 x 8 x 4), at 7% more products.
+// The projectors P^C have the same two sets, one function per atom, always in
+// FP64 (E follows the cell products' precision).
+#include <algorithm>
+
+#include "efe_device.h"
+
+namespace {
+constexpr int BK = EFE_BRICK, BX = EFE_BOX;   // edges of a brick and of a box, in nodes
+
+// Sum over the (up to eight) cells of an interior node that form a pair with
+// atom I of val(pair, local node), x fastest; first: stop at the first pair
+// whose value exists (assembled quantities).
+struct PairMap {
+  const int32_t *box, *map;   // per atom: x0 y0 z0 nx ny nz and the place of its table
+  const int64_t *off;
+};
+
+__device__ inline int pair_of(const PairMap &m, int I, int cx, int cy, int cz) {
+  const int32_t *b = m.box + 6 * I;
+  const int x = cx - b[0], y = cy - b[1], z = cz - b[2];
+  if (x < 0 || y < 0 || z < 0 || x >= b[3] || y >= b[4] || z >= b[5]) return -1;
+  return m.map[m.off[I] + x + b[3] * (y + (int64_t)b[4] * z)];
+}
+
+template <class F>
+__device__ inline void over_cells(const NodeGrid &g, const int ijk[3], F &&f) {
+  const int cx = ijk[0] / g.p, cy = ijk[1] / g.p, cz = ijk[2] / g.p;
+  const int lx = ijk[0] - cx * g.p, ly = ijk[1] - cy * g.p, lz = ijk[2] - cz * g.p;
+  for (int z = lz == 0 ? -1 : 0; z <= 0; ++z)
+    for (int y = ly == 0 ? -1 : 0; y <= 0; ++y)
+      for (int x = lx == 0 ? -1 : 0; x <= 0; ++x)
+        f(cx + x, cy + y, cz + z,
+          (x ? g.p : lx) + g.P * ((y ? g.p : ly) + g.P * (z ? g.p : lz)));
+}
+
+// What the blocks hold: E (epair: E_c per coupling pair), E + B (bam too) or
+// P^C (epair nullptr: bam is the assembled P^C, nf = 1).
+struct Entries {
+  NodeGrid g;
+  PairMap m;
+  int nf, nloc;
+  const double *epair;    // [pair][local node][k]
+  const double *bam;      // [support node][k]
+  const int32_t *lmap;    // [pair][local node] -> support node
+};
+
+__device__ inline double entry(const Entries &s, int I, int k, const int ijk[3]) {
+  double v = 0.0, b = 0.0;
+  bool have = s.bam == nullptr;
+  over_cells(s.g, ijk, [&](int cx, int cy, int cz, int l) {
+    const int pr = pair_of(s.m, I, cx, cy, cz);
+    if (pr < 0) return;
+    const int64_t o = (int64_t)pr * s.nloc + l;
+    if (s.epair) v += s.epair[o * s.nf + k];
+    if (!have) {
+      const int32_t sn = s.lmap[o];
+      if (sn >= 0) {
+        b = s.bam[(int64_t)sn * s.nf + k];
+        have = true;
+      }
+    }
+  });
+  return v + b;
+}
+
+// Bricks: tile[rb][ks][lane] = entry(function 4 ks + lane/16, node 16 rb + row
+// of the lane), the A operand of v_mfma_*_16x16x4.  The FP32 copy has rows
+// 4 a + b and 4 b + a exchanged, so that the accumulators of both precisions
+// hold the same nodes.  One wave per 16-row block.
+__global__ __launch_bounds__(256) void k_tiles_brick(Entries s, const int32_t *__restrict__ ptr,
+                                                     const int32_t *__restrict__ atom,
+                                                     const int64_t *__restrict__ off,
+                                                     double *__restrict__ T64,
+                                                     float *__restrict__ T32) {
+  const int64_t b = blockIdx.x;
+  const int a0 = ptr[b], na = ptr[b + 1] - a0;
+  if (na == 0) return;
+  const int K = na * s.nf, KS = (K + 3) / 4;
+  const int rb = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
+  int o[3], ijk[3];
+  box_origin(s.g, BK, b, o);
+  const bool in = box_node(s.g, BK, o, 16 * rb + li, ijk);
+  const int64_t base = 256 * off[b] + (int64_t)rb * KS * 64;
+  const int lp = 16 * lk + 4 * (li % 4) + li / 4;
+  for (int ks = 0; ks < KS; ++ks) {
+    const int f = 4 * ks + lk;
+    const double v = in && f < K ? entry(s, atom[a0 + f / s.nf], f % s.nf, ijk) : 0.0;
+    T64[base + (int64_t)ks * 64 + lane] = v;
+    if (T32) T32[base + (int64_t)ks * 64 + lp] = (float)v;
+  }
+}
+
+// Boxes: tile[rb][ks][lane] = entry(function 16 rb + lane%16, node 4 ks +
+// lane/16); live: bit c set where the nodes 16 c .. hold a non-zero entry
+__global__ __launch_bounds__(256) void k_tiles_box(Entries s, const int32_t *__restrict__ ptr,
+                                                   const int32_t *__restrict__ atom,
+                                                   const int32_t *__restrict__ rboff,
+                                                   const int32_t *__restrict__ rbbox,
+                                                   double *__restrict__ T64,
+                                                   float *__restrict__ T32,
+                                                   uint32_t *__restrict__ live) {
+  __shared__ uint32_t mask;
+  if (threadIdx.x == 0) mask = 0;
+  __syncthreads();
+  const int64_t row = blockIdx.x;
+  const int b = rbbox[row], rb = (int)row - rboff[b];
+  const int a0 = ptr[b], K = (ptr[b + 1] - a0) * s.nf;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
+  const int f = 16 * rb + li;
+  const int I = f < K ? atom[a0 + f / s.nf] : 0, k = f % s.nf;
+  int o[3], ijk[3];
+  box_origin(s.g, BX, b, o);
+  constexpr int KS = BX * BX * BX / 4;
+  for (int ks = wave; ks < KS; ks += 4) {
+    const bool in = box_node(s.g, BX, o, 4 * ks + lk, ijk);
+    const double v = in && f < K ? entry(s, I, k, ijk) : 0.0;
+    const int64_t at = (row * KS + ks) * 64 + lane;
+    T64[at] = v;
+    if (T32) T32[at] = (float)v;
+    if (__ballot(v != 0.0) && lane == 0) atomicOr(&mask, 1u << (ks / 4));
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) live[row] = mask;
+}
+
+// Enrichment block of the orthogonalized Hamiltonian without the projectors,
+// H^E_ee = H^phiphi - C B^T - E C^T: the symmetric part of H^phiphi - (B + E)
+// C^T (H^phiphi - C B^T - E C^T is symmetric), as products of the box blocks
+// of B + E with C.  One work-group takes a box and 16 functions of C (its
+// nodes x 16 in LDS as the B operand), each wave every fourth row block; the
+// 16 x 16 results are added into Hee atomically.
+typedef double v4d_c __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(256) void k_hee_box(Entries s, const int32_t *__restrict__ ptr,
+                                                 const int32_t *__restrict__ atom,
+                                                 const int32_t *__restrict__ rboff,
+                                                 const int32_t *__restrict__ rbbox,
+                                                 const double *__restrict__ T,
+                                                 const double *__restrict__ C_am, int64_t n_enr,
+                                                 double *__restrict__ Hee) {
+  constexpr int NB = BX * BX * BX, KS = NB / 4;
+  __shared__ double Cs[NB][16];
+  const int64_t row = blockIdx.x;
+  const int b = rbbox[row], cb = (int)row - rboff[b], nrb = rboff[b + 1] - rboff[b];
+  const int a0 = ptr[b], K = (ptr[b + 1] - a0) * s.nf;
+  int o[3];
+  box_origin(s.g, BX, b, o);
+  Entries c = s;
+  c.epair = nullptr;
+  c.bam = C_am;
+  for (int i = threadIdx.x; i < NB * 16; i += 256) {
+    const int f = 16 * cb + i % 16;
+    int ijk[3];
+    const bool in = box_node(s.g, BX, o, i / 16, ijk);
+    Cs[i / 16][i % 16] = in && f < K ? entry(c, atom[a0 + f / s.nf], f % s.nf, ijk) : 0.0;
+  }
+  __syncthreads();
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
+  const int f2 = 16 * cb + li;
+  const int64_t g2 = f2 < K ? (int64_t)atom[a0 + f2 / s.nf] * s.nf + f2 % s.nf : 0;
+  for (int rb = wave; rb < nrb; rb += 4) {
+    const double *tp = T + ((int64_t)(rboff[b] + rb) * KS) * 64 + lane;
+    v4d_c acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+    for (int ks = 0; ks < KS; ++ks)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tp[(int64_t)ks * 64], Cs[4 * ks + lk][li], acc, 0,
+                                                 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int f1 = 16 * rb + 4 * v + lk;
+      if (f1 < K && f2 < K)
+        atomicAdd(&Hee[((int64_t)atom[a0 + f1 / s.nf] * s.nf + f1 % s.nf) * n_enr + g2], -acc[v]);
+    }
+  }
+}
+
+// Matrix of the dense part of an apply (apply.hip) over the coefficients
+// (I, k), k < nf the enrichment functions and (with projectors) k = nf the
+// projector of atom I: [[H^E_ee + P~^T D P~, P~^T D], [D P~, D]]; Hee holds the
+// projector term already.
+__global__ void k_coef_matrix(int natoms, int nf, int nx, const double *__restrict__ Hee,
+                              const double *__restrict__ Pt, const double *__restrict__ D,
+                              double *__restrict__ S) {
+  const int64_t n = (int64_t)natoms * nx, ne = (int64_t)natoms * nf;
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= n * n) return;
+  const int64_t r = i / n, c = i % n;
+  const int64_t I = r / nx, J = c / nx;
+  const int k = (int)(r % nx), l = (int)(c % nx);
+  double v;
+  if (k < nf && l < nf) v = Hee[(I * nf + k) * ne + J * nf + l];
+  else if (k < nf) v = Pt[J * ne + I * nf + k] * D[J];
+  else if (l < nf) v = Pt[I * ne + J * nf + l] * D[I];
+  else v = I == J ? D[I] : 0.0;
+  S[i] = v;
+}
+
+// ------------------------------------------------------------------ host
+template <class T>
+efe_status upload(efe_ctx *c, T **dst, const std::vector<T> &src) {
+  efe_status s = efe_alloc(c, (void **)dst, std::max<size_t>(src.size(), 1) * sizeof(T));
+  if (s) return s;
+  if (!src.empty())
+    HIPCHK(c, hipMemcpyAsync(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice,
+                             c->stream));
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  return EFE_OK;
+}
+
+// atoms touching every box of edge e (ascending), from each atom's cells
+void box_atoms(const efe_ctx *c, const std::vector<int32_t> &ptr, const std::vector<int32_t> &cells,
+               int e, std::vector<int32_t> &bptr, std::vector<int32_t> &batom) {
+  const NodeGrid g = node_grid(c);
+  const int nb[3] = {(g.n1[0] + e - 1) / e, (g.n1[1] + e - 1) / e, (g.n1[2] + e - 1) / e};
+  const int64_t n = (int64_t)nb[0] * nb[1] * nb[2];
+  std::vector<int32_t> mark(n, -1), list, lptr(c->natoms + 1, 0);
+  bptr.assign(n + 1, 0);
+  for (int I = 0; I < c->natoms; ++I) {
+    for (int32_t q = ptr[I]; q < ptr[I + 1]; ++q) {
+      const int32_t cl = cells[q];
+      const int cc[3] = {cl % g.nc[0], (cl / g.nc[0]) % g.nc[1], cl / (g.nc[0] * g.nc[1])};
+      int lo[3], hi[3];   // boxes of the cell's interior nodes
+      for (int d = 0; d < 3; ++d) {
+        lo[d] = std::max(cc[d] * g.p, 1) / e;
+        hi[d] = std::min(cc[d] * g.p + g.p, g.n1[d] - 2) / e;
+      }
+      for (int z = lo[2]; z <= hi[2]; ++z)
+        for (int y = lo[1]; y <= hi[1]; ++y)
+          for (int x = lo[0]; x <= hi[0]; ++x) {
+            const int64_t b = x + nb[0] * (y + (int64_t)nb[1] * z);
+            if (mark[b] == I) continue;
+            mark[b] = I;
+            list.push_back((int32_t)b);
+            bptr[b + 1]++;
+          }
+    }
+    lptr[I + 1] = (int32_t)list.size();
+  }
+  for (int64_t b = 0; b < n; ++b) bptr[b + 1] += bptr[b];
+  batom.resize(list.size());
+  std::vector<int32_t> fill(bptr.begin(), bptr.end() - 1);
+  for (int I = 0; I < c->natoms; ++I)
+    for (int32_t q = lptr[I]; q < lptr[I + 1]; ++q) batom[fill[list[q]]++] = I;
+}
+
+efe_status build_set(efe_ctx *c, const std::vector<int32_t> &ptr, const std::vector<int32_t> &cells,
+                     int nf, CoupleSet &S) {
+  efe_status s;
+  S.nf = nf;
+  // (atom, cell) -> pair over the bounding box of the atom's cells
+  std::vector<int32_t> box(6 * (size_t)c->natoms, 0), map;
+  std::vector<int64_t> off(c->natoms + 1, 0);
+  for (int I = 0; I < c->natoms; ++I) {
+    int lo[3] = {1 << 30, 1 << 30, 1 << 30}, hi[3] = {-1, -1, -1};
+    auto ijk = [&](int32_t cl, int d) {
+      return d == 0 ? cl % c->ncell[0]
+                    : d == 1 ? (cl / c->ncell[0]) % c->ncell[1] : cl / (c->ncell[0] * c->ncell[1]);
+    };
+    for (int32_t q = ptr[I]; q < ptr[I + 1]; ++q)
+      for (int d = 0; d < 3; ++d) {
+        lo[d] = std::min(lo[d], ijk(cells[q], d));
+        hi[d] = std::max(hi[d], ijk(cells[q], d));
+      }
+    int64_t n = ptr[I + 1] > ptr[I] ? 1 : 0;
+    for (int d = 0; d < 3 && n; ++d) {
+      box[6 * I + d] = lo[d];
+      box[6 * I + 3 + d] = hi[d] - lo[d] + 1;
+      n *= hi[d] - lo[d] + 1;
+    }
+    off[I + 1] = off[I] + n;
+    map.resize(off[I + 1], -1);
+    for (int32_t q = ptr[I]; q < ptr[I + 1]; ++q)
+      map[off[I] + (ijk(cells[q], 0) - lo[0]) +
+          (int64_t)box[6 * I + 3] * ((ijk(cells[q], 1) - lo[1]) +
+                                     (int64_t)box[6 * I + 4] * (ijk(cells[q], 2) - lo[2]))] = q;
+  }
+  if ((s = upload(c, &S.d_box, box)) || (s = upload(c, &S.d_map, map)) ||
+      (s = upload(c, &S.d_off, off)))
+    return s;
+  // bricks
+  std::vector<int32_t> bptr, batom;
+  box_atoms(c, ptr, cells, BK, bptr, batom);
+  std::vector<int64_t> ksoff(bptr.size(), 0);
+  for (size_t b = 0; b + 1 < bptr.size(); ++b)
+    ksoff[b + 1] = ksoff[b] + cdiv((int64_t)(bptr[b + 1] - bptr[b]) * nf, 4);
+  S.n_brick = (int64_t)bptr.size() - 1;
+  S.brick_tile = 256 * ksoff.back();
+  if ((s = upload(c, &S.d_bk_ptr, bptr)) || (s = upload(c, &S.d_bk_atom, batom)) ||
+      (s = upload(c, &S.d_bk_off, ksoff)))
+    return s;
+  // boxes
+  box_atoms(c, ptr, cells, BX, bptr, batom);
+  std::vector<int32_t> rboff(bptr.size(), 0), rbbox;
+  for (size_t b = 0; b + 1 < bptr.size(); ++b) {
+    const int n = (int)cdiv((int64_t)(bptr[b + 1] - bptr[b]) * nf, 16);
+    rboff[b + 1] = rboff[b] + n;
+    rbbox.insert(rbbox.end(), n, (int32_t)b);
+  }
+  S.n_box = (int64_t)bptr.size() - 1;
+  S.n_boxpairs = (int64_t)batom.size();
+  S.n_rb = rboff.back();
+  S.h_rboff = rboff;
+  if ((s = efe_alloc(c, (void **)&S.d_live, std::max<int64_t>(S.n_rb, 1) * 4))) return s;
+  S.box_tile = S.n_rb * (BX * BX * BX / 4) * 64;
+  std::vector<int32_t> aptr(c->natoms + 1, 0), apos(batom.size());
+  for (int32_t a : batom) aptr[a + 1]++;
+  for (int I = 0; I < c->natoms; ++I) aptr[I + 1] += aptr[I];
+  std::vector<int32_t> fill(aptr.begin(), aptr.end() - 1);
+  for (size_t q = 0; q < batom.size(); ++q) apos[fill[batom[q]]++] = (int32_t)q;
+  if ((s = upload(c, &S.d_bx_ptr, bptr)) || (s = upload(c, &S.d_bx_atom, batom)) ||
+      (s = upload(c, &S.d_rboff, rboff)) || (s = upload(c, &S.d_rbbox, rbbox)) ||
+      (s = upload(c, &S.d_at_ptr, aptr)) || (s = upload(c, &S.d_at_pos, apos)))
+    return s;
+  return EFE_OK;
+}
+
+Entries entries(const efe_ctx *c, const CoupleSet &S, const double *epair, const double *bam,
+                const int32_t *lmap) {
+  return {node_grid(c), {S.d_box, S.d_map, S.d_off}, S.nf, c->nloc, epair, bam, lmap};
+}
+}  // namespace
+
+// Work items of the box products: four consecutive 16-row blocks of a box, E
+// blocks first, then P^C blocks, as (box, first block); the last three lists
+// are E only, P^C only and both.
+efe_status efe_couple_setup(efe_ctx *c, const std::vector<int32_t> &eptr,
+                            const std::vector<int32_t> &ecells) {
+  efe_status s;
+  CoupleSet &E = c->cpl_e, &K = c->cpl_k;
+  const std::vector<int32_t> none(c->natoms + 1, 0);
+  if ((s = build_set(c, c->nf > 0 ? eptr : none, ecells, std::max(c->nf, 1), E))) return s;
+  if ((s = build_set(c, c->nproj ? c->kb_ptr : none, c->kb_cells, 1, K))) return s;
+  std::vector<int32_t> items[3];
+  for (int64_t b = 0; b < E.n_box; ++b) {
+    const int ne = E.h_rboff[b + 1] - E.h_rboff[b], nk = K.h_rboff[b + 1] - K.h_rboff[b];
+    for (int which = 0; which < 3; ++which) {
+      const int r0 = which == 1 ? ne : 0, r1 = which == 0 ? ne : ne + nk;
+      for (int r = r0; r < r1; r += 4) {
+        items[which].push_back((int32_t)b);
+        items[which].push_back(r);
+      }
+    }
+  }
+  for (int which = 0; which < 3; ++which) {
+    c->n_items[which] = (int64_t)items[which].size() / 2;
+    if ((s = upload(c, &c->d_items[which], items[which]))) return s;
+  }
+  if (c->nproj) {
+    if ((s = efe_alloc(c, (void **)&K.d_T1, std::max<int64_t>(K.brick_tile, 1) * 8))) return s;
+    if ((s = efe_alloc(c, (void **)&K.d_T2, std::max<int64_t>(K.box_tile, 1) * 8))) return s;
+  }
+  return EFE_OK;
+}
+
+// blocks of P^C (once, when the projectors are known)
+efe_status efe_couple_projectors(efe_ctx *c) {
+  CoupleSet &K = c->cpl_k;
+  if (!c->nproj || K.n_boxpairs == 0) return EFE_OK;
+  const Entries e = entries(c, K, nullptr, c->d_Pc_am, c->d_kbpair_lmap);
+  k_tiles_brick<<<K.n_brick, 256, 0, c->stream>>>(e, K.d_bk_ptr, K.d_bk_atom, K.d_bk_off, K.d_T1,
+                                                 nullptr);
+  k_tiles_box<<<K.n_rb, 256, 0, c->stream>>>(e, K.d_bx_ptr, K.d_bx_atom, K.d_rboff, K.d_rbbox,
+                                            K.d_T2, nullptr, K.d_live);
+  HIPCHK(c, hipGetLastError());
+  return EFE_OK;
+}
+
+// blocks of E from the per-cell E_c (d_Epair), H^E_ee and the matrix of the
+// coefficients, for a new potential
+efe_status efe_couple_build(efe_ctx *c, bool want32) {
+  efe_status s;
+  CoupleSet &E = c->cpl_e;
+  const int64_t ne = c->n_enr;
+  const int nx = c->nf + (c->nproj ? 1 : 0);
+  const int64_t n = (int64_t)c->natoms * nx;
+  if (n == 0) return EFE_OK;
+  if (!c->d_S && (s = efe_alloc(c, (void **)&c->d_S, n * n * 8))) return s;
+  if (c->nf > 0 && E.n_boxpairs > 0) {
+    if (!E.d_T1 && (s = efe_alloc(c, (void **)&E.d_T1, E.brick_tile * 8))) return s;
+    if (!E.d_T2 && (s = efe_alloc(c, (void **)&E.d_T2, E.box_tile * 8))) return s;
+    if (want32 && !E.d_T1f && (s = efe_alloc(c, (void **)&E.d_T1f, E.brick_tile * 4))) return s;
+    if (want32 && !E.d_T2f && (s = efe_alloc(c, (void **)&E.d_T2f, E.box_tile * 4))) return s;
+    // B + E first, for H^E_ee, then E over it
+    const Entries both = entries(c, E, c->d_Epair, c->d_B_am, c->d_cpair_lmap);
+    k_tiles_box<<<E.n_rb, 256, 0, c->stream>>>(both, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
+                                              E.d_T2, nullptr, E.d_live);
+    k_hee_box<<<E.n_rb, 256, 0, c->stream>>>(both, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
+                                            E.d_T2, c->d_C_am, ne, c->d_Hee);
+    const Entries e = entries(c, E, c->d_Epair, nullptr, c->d_cpair_lmap);
+    k_tiles_box<<<E.n_rb, 256, 0, c->stream>>>(e, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
+                                              E.d_T2, want32 ? E.d_T2f : nullptr, E.d_live);
+    k_tiles_brick<<<E.n_brick, 256, 0, c->stream>>>(e, E.d_bk_ptr, E.d_bk_atom, E.d_bk_off, E.d_T1,
+                                                   want32 ? E.d_T1f : nullptr);
+    if ((s = efe_symmetrize(c, ne, c->d_Hee))) return s;
+  }
+  k_coef_matrix<<<cdiv(n * n, 256), 256, 0, c->stream>>>(c->natoms, c->nf, nx, c->d_Hee, c->d_Ptil,
+                                                        c->d_D, c->d_S);
+  HIPCHK(c, hipGetLastError());
+  return EFE_OK;
+}
+
+void efe_couple_free(efe_ctx *c) {
+  for (CoupleSet *S : {&c->cpl_e, &c->cpl_k}) {
+    void *ptrs[] = {S->d_box,   S->d_map,   S->d_off,    S->d_bk_ptr, S->d_bk_atom, S->d_bk_off,
+                    S->d_bx_ptr, S->d_bx_atom, S->d_rboff, S->d_rbbox, S->d_at_ptr, S->d_at_pos,
+                    S->d_T1,    S->d_T2,    S->d_T1f,    S->d_T2f,  S->d_live};
+    for (void *p : ptrs)
+      if (p) (void)hipFree(p);
+  }
+  for (int32_t *p : c->d_items)
+    if (p) (void)hipFree(p);
+}

@@ -210,45 +210,6 @@ static void build_support(const efe_ctx *c, double rc, SupportTables &T) {
     }
 }
 
-// Work items of the atom-major reductions over support nodes: every atom's
-// (node-sorted) support list cut at multiples of `region` node indices and
-// at `maxlen` entries, as (atom, first, end) triples.  Region r goes to XCD
-// r % 8 (round robin keeps the dense middle of a cluster spread over all
-// XCDs) and each XCD's items are stored together, region by region, so that
-// the items of a region run on one XCD and re-read its rows from that XCD's
-// L2.  items_off[x] .. items_off[x+1] are XCD x's items.
-static void build_items(int natoms, int64_t n_nodes, const std::vector<int32_t> &ptr,
-                        const std::vector<int32_t> &snode, int32_t region, int32_t maxlen,
-                        std::vector<int32_t> &items, int64_t items_off[9]) {
-  struct It { int32_t reg, atom, s0, s1; };
-  std::vector<It> v;
-  for (int I = 0; I < natoms; ++I) {
-    int32_t s = ptr[I];
-    while (s < ptr[I + 1]) {
-      const int32_t reg = snode[s] / region;
-      int32_t e = s + 1;
-      while (e < ptr[I + 1] && e - s < maxlen && snode[e] / region == reg) ++e;
-      v.push_back({reg, I, s, e});
-      s = e;
-    }
-  }
-  (void)n_nodes;
-  std::stable_sort(v.begin(), v.end(), [](const It &a, const It &b) {
-    return a.reg % 8 != b.reg % 8 ? a.reg % 8 < b.reg % 8 : a.reg < b.reg;
-  });
-  items.clear();
-  size_t k = 0;
-  for (int x = 0; x < 8; ++x) {
-    items_off[x] = (int64_t)items.size() / 3;
-    for (; k < v.size() && v[k].reg % 8 == x; ++k) {
-      items.push_back(v[k].atom);
-      items.push_back(v[k].s0);
-      items.push_back(v[k].s1);
-    }
-  }
-  items_off[8] = (int64_t)items.size() / 3;
-}
-
 // (cell, I, J) for every cell and every pair of atoms from lists A and B whose
 // supports contain the cell.
 static void build_triples(const efe_ctx *c, const SupportTables &A, const SupportTables &B,
@@ -419,9 +380,7 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
     // coupling pairs: per atom every cell that holds one of its support nodes
     // (its support cells and the layer of cells around them, where C is
     // non-zero on shared nodes although phi vanishes), with the local-to-
-    // support map and the support pair of the cell (-1 for the outer layer);
-    // then their cell-major view (atom-major pairs are sorted by atom, so a
-    // cell's pairs come out in ascending atom order)
+    // support map and the support pair of the cell (-1 for the outer layer)
     {
       std::vector<int32_t> cptr(c->natoms + 1, 0), catom, ccell, cspair, clmap;
       std::vector<int32_t> pos(c->n_nodes, -1), cmark(c->n_cells, -1);
@@ -466,25 +425,11 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
         for (int32_t sI = E.snode_ptr[I]; sI < E.snode_ptr[I + 1]; ++sI) pos[E.snode[sI]] = -1;
       }
       c->ncpairs = (int64_t)catom.size();
-      std::vector<int32_t> eptr(c->n_cells + 1, 0), epair(ccell.size()), cpos(ccell.size());
-      for (int32_t cc : ccell) eptr[cc + 1]++;
-      for (int64_t cc = 0; cc < c->n_cells; ++cc) eptr[cc + 1] += eptr[cc];
-      std::vector<int32_t> fill(eptr.begin(), eptr.end() - 1);
-      for (size_t q = 0; q < ccell.size(); ++q) {
-        const int32_t at = fill[ccell[q]]++;
-        epair[at] = (int32_t)q;
-        cpos[q] = at;
-      }
-      std::vector<int64_t> noff(c->n_cells + 1, 0);
+      std::vector<int32_t> percell(c->n_cells, 0);
+      for (int32_t cc : ccell) percell[cc]++;
       int maxr = 0;
-      for (int64_t cc = 0; cc < c->n_cells; ++cc) {
-        const int64_t ne = (int64_t)(eptr[cc + 1] - eptr[cc]) * c->nf;
-        const int64_t nep = (ne + 15) / 16 * 16;
-        noff[cc + 1] = noff[cc] + nep;
-        maxr = std::max<int>(maxr, (int)(nep / 16));
-      }
+      for (int32_t n : percell) maxr = std::max(maxr, (n * c->nf + 15) / 16);
       c->max_rbe = maxr;
-      c->n_epad = noff[c->n_cells];
       if ((int64_t)maxr * 16 > EFE_MAX_CELL_ENR) {
         c->err = "more than " + std::to_string(EFE_MAX_CELL_ENR) +
                  " enrichment functions couple to one cell";
@@ -494,17 +439,10 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
       TRY(upload(c, &c->d_cpair_atom, catom));
       TRY(upload(c, &c->d_cpair_spair, cspair));
       TRY(upload(c, &c->d_cpair_lmap, clmap));
-      TRY(upload(c, &c->d_cpair_ptr, cptr));
-      TRY(upload(c, &c->d_cell_eptr, eptr));
-      TRY(upload(c, &c->d_cell_epair, epair));
-      TRY(upload(c, &c->d_cpair_cpos, cpos));
-      TRY(upload(c, &c->d_cell_noff, noff));
+      TRY(upload(c, &c->d_cpair_cell, ccell));
+      TRY(efe_couple_setup(c, cptr, ccell));
       HIPCHK(c, hipStreamSynchronize(c->stream));
     }
-    std::vector<int32_t> items;
-    build_items(c->natoms, c->n_nodes, E.snode_ptr, E.snode, 512, 1024, items, c->enr_items_off);
-    c->n_enr_items = (int64_t)items.size() / 3;
-    TRY(upload(c, &c->d_enr_items, items));
     std::vector<int32_t> trip;
     if (c->nf > 0) build_triples(c, E, E, trip);
     c->ntrip = (int64_t)trip.size() / 3;
@@ -512,19 +450,11 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
 
     c->nkbpairs = (int64_t)K.cells.size();
     c->n_kbnodes = (int64_t)K.snode.size();
-    c->nnz_kbnm = (int64_t)K.nm_atom.size();
     TRY(upload(c, &c->d_kbpair_atom, K.pair_atom));
     TRY(upload(c, &c->d_kbpair_cell, K.pair_cell));
     TRY(upload(c, &c->d_kbpair_lmap, K.lmap));
     TRY(upload(c, &c->d_kbnode_ptr, K.snode_ptr));
     TRY(upload(c, &c->d_kbnode, K.snode));
-    TRY(upload(c, &c->d_kbnm_ptr, K.nm_ptr));
-    TRY(upload(c, &c->d_kbnm_atom, K.nm_atom));
-    TRY(upload(c, &c->d_kbnm_src, K.nm_src));
-    std::vector<int32_t> kbitems;
-    build_items(c->natoms, c->n_nodes, K.snode_ptr, K.snode, 512, 1024, kbitems, c->kb_items_off);
-    c->n_kb_items = (int64_t)kbitems.size() / 3;
-    TRY(upload(c, &c->d_kb_items, kbitems));
     std::vector<int32_t> kbtrip;
     if (c->nproj > 0 && c->nf > 0) build_triples(c, K, E, kbtrip);
     c->nkbtrip = (int64_t)kbtrip.size() / 3;
@@ -607,16 +537,14 @@ extern "C" void efe_destroy(efe_ctx *c) {
                   c->d_trip,      c->d_Mpp,
                   c->d_Mee,       c->d_Hpp_kin,      c->d_Hpp,        c->d_Mee_inv,
                   c->d_kbpair_atom, c->d_kbpair_cell, c->d_kbpair_lmap, c->d_kbnode_ptr,
-                  c->d_kbnode,    c->d_Pc_am,        c->d_kbnm_ptr,   c->d_kbnm_atom,
-                  c->d_kbnm_src,  c->d_Pc_nm,        c->d_kbtrip,     c->d_Pphi,
+                  c->d_kbnode,    c->d_Pc_am,        c->d_kbtrip,     c->d_Pphi,
                   c->d_D,         c->d_vq,           c->d_Htile64,    c->d_Htile32,
-                  c->d_Htile16,   c->d_enr_items,    c->d_kb_items,   c->d_g_ptr,
+                  c->d_Htile16,   c->d_g_ptr,
                   c->d_g_atom,    c->d_nm_gslot,     c->d_Cg,         c->d_Bg,
-                  c->d_cell_eptr, c->d_cell_epair,   c->d_cpair_cpos, c->d_cell_noff,
-                  c->d_Bkin_pair, c->d_B_pair,       c->d_Et64,       c->d_Ee64,
-                  c->d_Et32,      c->d_Ee32,         c->d_Hee,
-                  c->d_Ptil,      c->d_cpair_ptr,    c->d_cpair_atom, c->d_cpair_spair,
-                  c->d_cpair_lmap, c->d_s1,          c->d_tpm};
+                  c->d_Bkin_pair, c->d_B_pair,       c->d_Hee,
+                  c->d_Ptil,      c->d_cpair_atom, c->d_cpair_spair,
+                  c->d_cpair_lmap, c->d_s1,          c->d_tpm, c->d_Epair, c->d_cpair_cell, c->d_S};
+  efe_couple_free(c);
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   for (auto &b : c->ws)

@@ -26,6 +26,43 @@ static inline MeshGeo mesh_geo(const efe_ctx *c) {
   return g;
 }
 
+// Node grid of the mesh, and its boxes of EFE_BOX^3 or EFE_BRICK^3 nodes.
+struct NodeGrid {
+  int n1[3];
+  int p, P;
+  int nc[3];
+};
+
+static inline NodeGrid node_grid(const efe_ctx *c) {
+  NodeGrid g;
+  for (int d = 0; d < 3; ++d) {
+    g.n1[d] = (int)c->n1[d];
+    g.nc[d] = c->ncell[d];
+  }
+  g.p = c->p;
+  g.P = c->P;
+  return g;
+}
+
+// first node of box b (edge e)
+__device__ inline void box_origin(const NodeGrid &g, int e, int64_t b, int o[3]) {
+  const int nx = (g.n1[0] + e - 1) / e, ny = (g.n1[1] + e - 1) / e;
+  o[0] = (int)(b % nx) * e;
+  o[1] = (int)((b / nx) % ny) * e;
+  o[2] = (int)(b / ((int64_t)nx * ny)) * e;
+}
+
+// node r of a box in the row order of its blocks (bricks of 4 x 4 x 4, x
+// fastest inside and between); false outside the interior
+__device__ inline bool box_node(const NodeGrid &g, int e, const int o[3], int r, int ijk[3]) {
+  const int s = r / 64, q = r % 64, ne = e / EFE_BRICK;
+  ijk[0] = o[0] + EFE_BRICK * (s % ne) + q % 4;
+  ijk[1] = o[1] + EFE_BRICK * ((s / ne) % ne) + (q / 4) % 4;
+  ijk[2] = o[2] + EFE_BRICK * (s / (ne * ne)) + q / 16;
+  return ijk[0] > 0 && ijk[0] < g.n1[0] - 1 && ijk[1] > 0 && ijk[1] < g.n1[1] - 1 && ijk[2] > 0 &&
+         ijk[2] < g.n1[2] - 1;
+}
+
 // Position of Gauss point q of cell `cell`.
 __device__ inline void quad_point(const MeshGeo &g, const double *__restrict__ xq1, int cell, int q,
                                   double x[3]) {

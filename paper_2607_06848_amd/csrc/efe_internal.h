@@ -24,14 +24,38 @@ struct DevBuf {
   size_t bytes = 0;
 };
 
+// edges, in nodes, of the bricks and boxes of the coupling blocks (couple.hip)
+constexpr int EFE_BRICK = 4, EFE_BOX = 8;
+
+// coupling blocks of one set of functions, nf per atom (couple.hip)
+struct CoupleSet {
+  int nf = 1;
+  int32_t *d_box = nullptr, *d_map = nullptr;   // (atom, cell) -> pair
+  int64_t *d_off = nullptr;
+  // bricks: atoms, prefix of their 4-wide k steps; boxes: atoms, prefix of
+  // their 16-row blocks, block -> box; per atom the places of its box entries
+  int32_t *d_bk_ptr = nullptr, *d_bk_atom = nullptr;
+  int64_t *d_bk_off = nullptr;
+  int32_t *d_bx_ptr = nullptr, *d_bx_atom = nullptr, *d_rboff = nullptr, *d_rbbox = nullptr;
+  int32_t *d_at_ptr = nullptr, *d_at_pos = nullptr;
+  int64_t n_brick = 0, n_box = 0, n_boxpairs = 0, n_rb = 0, brick_tile = 0, box_tile = 0;
+  uint32_t *d_live = nullptr;                   // per 16-row block: chunks of 16 nodes with entries
+  std::vector<int32_t> h_rboff;
+  double *d_T1 = nullptr, *d_T2 = nullptr;      // brick and box blocks
+  float *d_T1f = nullptr, *d_T2f = nullptr;
+};
+
 // tensor-product cell operator (cell_tp.hip)
 struct TpArgs {
   const double *X, *vq, *s1, *mask1;   // s1: per-axis row factors of X
   const int32_t *cells;                // nullptr: every cell
   double *Yc, *Y;
-  int64_t ldx, ldy, ncells, n1x, n1y;
+  int64_t ldx, ldy, ldc, ncells, n1x, n1y;
   int ncols, ncx, ncy;
   double alpha;
+  // pair form: unit (pair, k), E_c = B_c - H_c C_c^T
+  const int32_t *lmap, *spair;
+  const double *C, *B;
   const double *m;                     // 1-D matrices of the axes
 };
 
@@ -95,24 +119,20 @@ struct efe_ctx {
   double *d_Cg = nullptr, *d_Bg = nullptr;
   // coupling pairs (atom, cell): every cell holding one of the atom's support
   // nodes (atom-major, by cell), with the support pair of the cell (-1 for
-  // the layer outside the support) and the local-to-support map; their
-  // cell-major view: per cell its pairs (ascending atom), per pair its
-  // cell-major position, per cell the prefix of its padded enrichment row
-  // count (functions x atoms rounded up to 16), which places its tiles
+  // the layer outside the support) and the local-to-support map
   int64_t ncpairs = 0;
-  int32_t *d_cpair_atom = nullptr, *d_cpair_spair = nullptr, *d_cpair_lmap = nullptr;
-  int32_t *d_cpair_ptr = nullptr, *d_cpair_cpos = nullptr;
-  int32_t *d_cell_eptr = nullptr, *d_cell_epair = nullptr;
-  int64_t *d_cell_noff = nullptr;
+  int32_t *d_cpair_cell = nullptr, *d_cpair_atom = nullptr, *d_cpair_spair = nullptr,
+          *d_cpair_lmap = nullptr;
   int max_rbe = 0;                                     // max padded rows / 16 over cells
-  int64_t n_epad = 0;                                  // sum of padded rows
-  // per-pair cell blocks [pair][l][k]: kinetic part of B (setup), B (per potential)
-  double *d_Bkin_pair = nullptr, *d_B_pair = nullptr;
-  // coupling of the orthogonalized basis per cell, E_c = B_c - C_c H_c, in the
-  // MFMA operand layouts: Et = E_c^T tiles (rows: cell nodes, k: the cell's
-  // enrichment functions), Ee = E_c tiles (rows: enrichment functions, k: nodes)
-  double *d_Et64 = nullptr, *d_Ee64 = nullptr;
-  float *d_Et32 = nullptr, *d_Ee32 = nullptr;
+  // per-pair cell blocks [pair][l][k]: kinetic part of B (setup), B and the
+  // coupling E_c = B_c - C_c H_c of the orthogonalized basis (per potential)
+  double *d_Bkin_pair = nullptr, *d_B_pair = nullptr, *d_Epair = nullptr;
+  // coupling blocks over boxes of nodes: enrichment, projectors; work items of
+  // the box products (E only, P^C only, both); matrix of the coefficients
+  CoupleSet cpl_e, cpl_k;
+  int32_t *d_items[3] = {nullptr, nullptr, nullptr};
+  int64_t n_items[3] = {0, 0, 0};
+  double *d_S = nullptr;
   double *d_Hee = nullptr;                             // H^E_ee without projectors
   double *d_Ptil = nullptr;                            // P^phi - P^C C^T, [nproj][n_enr]
   // (cell, I, J) triples of atoms sharing a support cell
@@ -121,10 +141,6 @@ struct efe_ctx {
   double *d_Mpp = nullptr, *d_Mee = nullptr, *d_Hpp_kin = nullptr, *d_Hpp = nullptr;
   double *d_Mee_inv = nullptr;                         // [natoms][nf][nf]
   double amplification = 1.0;                          // efe_enrichment_amplification
-  // (atom, first, end) work items over the support lists, ordered by node region
-  int64_t n_enr_items = 0, n_kb_items = 0;
-  int64_t enr_items_off[9] = {0}, kb_items_off[9] = {0};   // per-XCD ranges
-  int32_t *d_enr_items = nullptr, *d_kb_items = nullptr;
 
   // Kleinman-Bylander projectors (one per atom)
   int64_t nkbpairs = 0;
@@ -132,9 +148,6 @@ struct efe_ctx {
   int64_t n_kbnodes = 0;
   int32_t *d_kbnode_ptr = nullptr, *d_kbnode = nullptr;
   double *d_Pc_am = nullptr;
-  int64_t nnz_kbnm = 0;
-  int32_t *d_kbnm_ptr = nullptr, *d_kbnm_atom = nullptr, *d_kbnm_src = nullptr;
-  double *d_Pc_nm = nullptr;
   int64_t nkbtrip = 0;
   int32_t *d_kbtrip = nullptr;                         // (cell, I_kb, J_enr)
   double *d_Pphi = nullptr, *d_D = nullptr;            // [nproj][n_enr], [nproj]
@@ -164,6 +177,8 @@ struct efe_ctx {
   size_t arena_spare = 0;   // bytes of the region no required slot needs (efe_ws_try)
   static constexpr int kArenaSlots = 64;
   size_t arena_off[kArenaSlots] = {0}, arena_len[kArenaSlots] = {0};
+
+  int32_t col_chunk = 160;    // columns per filter chunk (EFE_COL_CHUNK; less in a tight arena)
 
   // SCF state (scf.hip)
   void *scf = nullptr;
@@ -203,18 +218,6 @@ void efe_set_global_error(const std::string &msg);
 efe_status efe_ws(efe_ctx *ctx, int slot, size_t bytes, void **p);
 
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
-// Work-groups are dealt round-robin over the eight XCDs (block b runs on XCD
-// b % 8).  XcdSplit maps a block to (XCD, slot) and a per-XCD range of work
-// items, so that a chosen set of items runs on one XCD and shares its L2.
-struct XcdSplit {
-  int64_t off[9];
-  __host__ __device__ int64_t max_len() const {
-    int64_t m = 0;
-    for (int x = 0; x < 8; ++x) m = off[x + 1] - off[x] > m ? off[x + 1] - off[x] : m;
-    return m;
-  }
-};
 
 // Column chunk of the wide-block passes (filter, Rayleigh-Ritz H V, density):
 // the cell GEMM's column tile, and the width the per-pass workspaces are
@@ -265,7 +268,18 @@ size_t efe_syev_iwork(int64_t n);
 efe_status efe_tp_setup(efe_ctx *ctx, const std::vector<double> &xq, const std::vector<double> &wq,
                         const std::vector<double> &N1, const std::vector<double> &wg);
 efe_status efe_tp_apply(efe_ctx *ctx, const double *X, int64_t ldx, bool minv, int ncols,
-                        double *Yc, double *Y, int64_t ldy, double alpha);
+                        double *Yc, int64_t ldc, double *Y, int64_t ldy, double alpha);
+// E_c = B_c - H_c C_c^T of every coupling pair into d_Epair
+efe_status efe_tp_pairs(efe_ctx *ctx);
+// coupling blocks (couple.hip): lists from the coupling pairs (per atom its
+// cells), blocks of the projectors (once), blocks of E, H^E_ee and the matrix
+// of the coefficients (per potential; d_Epair, d_B_am and, in d_Hee, H^phiphi)
+efe_status efe_couple_setup(efe_ctx *ctx, const std::vector<int32_t> &eptr,
+                            const std::vector<int32_t> &ecells);
+efe_status efe_couple_projectors(efe_ctx *ctx);
+efe_status efe_couple_build(efe_ctx *ctx, bool want32);
+void efe_couple_free(efe_ctx *ctx);
+efe_status efe_symmetrize(efe_ctx *ctx, int64_t n, double *A);
 // workspace slot that may be missing: nullptr (no error) when it does not fit
 double *efe_ws_try(efe_ctx *ctx, int slot, size_t bytes);
 
@@ -277,9 +291,9 @@ struct ApplyEpilogue {
   double alpha = 1.0, beta = 0.0, gamma = 0.0;
   const double *Z1 = nullptr, *Z2 = nullptr, *G = nullptr, *Cl = nullptr;
 };
-// Y = H^E X with X given as (XC scaled row-wise by `scale` if non-NULL, XE);
-// prec selects the cell GEMM precision; epi (may be NULL) the epilogue.
-efe_status efe_apply_H_internal(efe_ctx *ctx, const double *XC, int64_t ldx, const double *scale,
+// Y = H^E X, or with minv H^E (M~^E)^-1 X, X given as (XC, XE); prec selects
+// the precision of the cell and coupling products; epi (may be NULL) the epilogue.
+efe_status efe_apply_H_internal(efe_ctx *ctx, const double *XC, int64_t ldx, bool minv,
                                 const double *XE, int64_t lde, double *Y, int64_t ldy, int ncols,
                                 int prec, const ApplyEpilogue *epi = nullptr);
 efe_status efe_apply_M_internal(efe_ctx *ctx, const double *X, int64_t ldx, double *Y,

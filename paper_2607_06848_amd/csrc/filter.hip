@@ -7,8 +7,8 @@
 //   Z_k = (2 s_k/e) H M~^-1 Z_{k-1} - (2 c s_k/e) Z_{k-1} - s_{k-1} s_k Z_{k-2}
 //         + (2 s_k/e) G C_{k-1}(Lambda)
 //   V  <- M~^-1 Z_m + V C_m(Lambda)
-// The CFE part of M~^-1 (1/m) is folded into the gather of the H apply; the
-// enrichment part is a batched nf x nf block product.  Z_k overwrites Z_{k-2}.
+// M~^-1 is folded into the H apply: its CFE part (1/m) into the reading of the
+// rows, its enrichment part (nf x nf blocks) into the coefficients.  Z_k overwrites Z_{k-2}.
 #include <cmath>
 #include <vector>
 
@@ -123,7 +123,7 @@ static efe_status filter_chunk(efe_ctx *c, double *V, const double *lambda, int3
     k_copy_in<<<nb, T, 0, c->stream>>>(rows, ncols, V, ld, Za, ncols);
     double *Yp = nullptr, *Yc = Za, *Yn = Zb;
     for (int k = 1; k <= m; ++k) {
-      if ((s = efe_apply_H_internal(c, Yc, ncols, nullptr, Yc + nn * ncols, ncols, W, ncols, ncols,
+      if ((s = efe_apply_H_internal(c, Yc, ncols, false, Yc + nn * ncols, ncols, W, ncols, ncols,
                                     prm->prec)))
         return s;
       if ((s = efe_enr_block_inv(c, W + nn * ncols, ncols, XE, ncols, ncols))) return s;
@@ -143,13 +143,12 @@ static efe_status filter_chunk(efe_ctx *c, double *V, const double *lambda, int3
 
   k_cheb_table<<<cdiv(ncols, 64), 64, 0, c->stream>>>(m, ncols, lambda, cc, e, dsig, Cl);
   // G = H V - M V Lambda (MV staged in Zb)
-  if ((s = efe_apply_H_internal(c, V, ld, nullptr, V + nn * ld, ld, W, ncols, ncols, EFE_FP64)))
+  if ((s = efe_apply_H_internal(c, V, ld, false, V + nn * ld, ld, W, ncols, ncols, EFE_FP64)))
     return s;
   if ((s = efe_apply_M_internal(c, V, ld, Zb, ncols, ncols))) return s;
   double *Zc = Za, *Zp = Zb;
   k_residual_init<<<nb, T, 0, c->stream>>>(rows, ncols, W, Zb, lambda, sig[1] / e, G, Zc, Zp);
   for (int k = 2; k <= m; ++k) {
-    if ((s = efe_enr_block_inv(c, Zc + nn * ncols, ncols, XE, ncols, ncols))) return s;
     // the recurrence's H applies run in the requested precision (G stays
     // FP64); its three affine terms enter the assembly itself: Z_k is
     // written in place of Z_{k-2}, starting from the terms and accumulating
@@ -163,8 +162,8 @@ static efe_status filter_chunk(efe_ctx *c, double *V, const double *lambda, int3
     ep.G = G;
     ep.Cl = Cl + (int64_t)(k - 1) * ncols;
     const int t = efe_timer_begin(c, EFE_T_RECUR);
-    if ((s = efe_apply_H_internal(c, Zc, ncols, c->d_minv, XE, ncols, Zp, ncols, ncols, prm->prec,
-                                  &ep)))
+    if ((s = efe_apply_H_internal(c, Zc, ncols, true, Zc + nn * ncols, ncols, Zp, ncols, ncols,
+                                  prm->prec, &ep)))
       return s;
     efe_timer_end(c, EFE_T_RECUR, t);
     std::swap(Zc, Zp);
@@ -197,8 +196,8 @@ efe_status efe_filter_check(efe_ctx *c, double *V, const double *lambda, int32_t
 efe_status efe_filter_run(efe_ctx *c, double *V, const double *lambda, int32_t ncols, int64_t ld,
                           const efe_cheb_params *prm) {
   efe_status s;
-  for (int32_t j0 = 0; j0 < ncols; j0 += EFE_COL_CHUNK) {
-    const int32_t nc = std::min<int32_t>(EFE_COL_CHUNK, ncols - j0);
+  for (int32_t j0 = 0; j0 < ncols; j0 += c->col_chunk) {
+    const int32_t nc = std::min<int32_t>(c->col_chunk, ncols - j0);
     if ((s = filter_chunk(c, V + j0, lambda ? lambda + j0 : nullptr, nc, ld, prm))) return s;
   }
   return EFE_OK;
@@ -339,7 +338,7 @@ extern "C" efe_status efe_spectrum_upper_bound(efe_ctx *c, const double *v0, int
   k_scale_by_inv_sqrt<<<cdiv(rows, T), T, 0, c->stream>>>(rows, &nrm[steps], u, Vb, nullptr);
   for (int j = 0; j < steps; ++j) {
     double *v = Vb + (int64_t)j * rows;
-    if ((s = efe_apply_H_internal(c, v, 1, nullptr, v + nn, 1, u, 1, 1, EFE_FP64))) return s;
+    if ((s = efe_apply_H_internal(c, v, 1, false, v + nn, 1, u, 1, 1, EFE_FP64))) return s;
     // alpha_j = v^T H v
     k_dot<<<nbk, T, 0, c->stream>>>(rows, v, u, nullptr, &alpha[j]);
     if ((s = efe_apply_Minv_internal(c, u, 1, x, 1, 1))) return s;

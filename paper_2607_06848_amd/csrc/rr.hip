@@ -82,7 +82,7 @@ extern "C" efe_status efe_rayleigh_ritz(efe_ctx *c, double *V, int32_t N, int64_
   // W = H V, chunk by chunk
   for (int32_t j0 = 0; j0 < N; j0 += EFE_COL_CHUNK) {
     const int32_t nc = std::min<int32_t>(EFE_COL_CHUNK, N - j0);
-    if ((s = efe_apply_H_internal(c, V + j0, ld, nullptr, V + nn * ld + j0, ld, W + j0, N, nc,
+    if ((s = efe_apply_H_internal(c, V + j0, ld, false, V + nn * ld + j0, ld, W + j0, N, nc,
                                   EFE_FP64)))
       return s;
   }

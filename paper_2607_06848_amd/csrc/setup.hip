@@ -307,14 +307,6 @@ __global__ void k_scale_by_minv(int64_t n_snodes, int nf, const int32_t *__restr
   C[i] = b[i] * minv[snode[i / nf]];
 }
 
-// node-major copy: dst[e*nf + k] = src[nm_src[e]*nf + k]
-__global__ void k_to_node_major(int64_t nnz, int nf, const int32_t *__restrict__ nm_src,
-                                const double *__restrict__ src, double *__restrict__ dst) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= nnz * nf) return;
-  dst[i] = src[(int64_t)nm_src[i / nf] * nf + i % nf];
-}
-
 // group-major copy: dst[(slot nf + k) 8 + n % 8] = src[nm_src[e] nf + k] for
 // every node-major entry e of node n (slot = its atom's place in the union of
 // the atoms of the 8-node group of n); entries not written stay zero
@@ -424,156 +416,46 @@ __global__ __launch_bounds__(256) void k_mee_rows(int nf, int64_t n_enr, const i
 
 // ------------------------------------------------------------ coupling
 // The orthogonalized basis couples the enrichment rows to the CFE rows
-// through H^ec = B - C H^cc (Sec. II.B: N^E = phi - C N^C).  Per cell,
-// E_c = B_c - C_c H_c (n_e x nloc: the cell's enrichment functions against
-// its nodes), formed here in FP64 so that the cancellation between B and
-// C H happens before any rounding to a reduced precision.  One work-group
-// takes a cell and 16 of its enrichment functions: C_c^T (nloc x 16) in LDS as
-// the B operand, the cell Hamiltonian's MFMA tiles as the A operand, each wave
-// a row block of H_c C_c^T.  The results go to both operand layouts of the
-// apply (E_c^T rows = nodes, E_c rows = functions; zero padding included).
+// through H^ec = B - C H^cc (Sec. II.B: N^E = phi - C N^C).  Per (atom, cell)
+// pair, E_c = B_c - C_c H_c, formed in FP64 so that the cancellation between B
+// and C H happens before any rounding to a reduced precision.  This is the
+// dense form for Gauss rules that the tensor products of cell_tp.hip do not
+// take: C_c^T (nloc x nf, padded to 16) in LDS as the B operand, the cell
+// Hamiltonian's MFMA tiles as the A operand, each wave a row block of H_c C_c^T.
 __global__ __launch_bounds__(256) void k_build_E(
-    int nloc, int RB, int KS, int nf, int max_cb, const double *__restrict__ Ht,
-    const int32_t *__restrict__ cell_eptr, const int32_t *__restrict__ cell_epair,
-    const int64_t *__restrict__ cell_noff, const int32_t *__restrict__ lmap,
+    int nloc, int RB, int KS, int nf, const double *__restrict__ Ht,
+    const int32_t *__restrict__ cell_of, const int32_t *__restrict__ lmap,
     const int32_t *__restrict__ spair, const double *__restrict__ C_am,
-    const double *__restrict__ B_pair,
-    double *__restrict__ Et, double *__restrict__ Ee, float *__restrict__ Et32,
-    float *__restrict__ Ee32) {
+    const double *__restrict__ B_pair, double *__restrict__ E) {
   __shared__ double Cs[EFE_MAXLOC + 16][16];
-  const int64_t cell = blockIdx.x / max_cb;
-  const int cb = blockIdx.x % max_cb;
-  const int32_t p0 = cell_eptr[cell];
-  const int ne = (cell_eptr[cell + 1] - p0) * nf;
-  if (16 * cb >= ne) return;
-  const int nep = (ne + 15) / 16 * 16, kse_n = nep / 4;
-  const int64_t noff = cell_noff[cell];
+  const int64_t pr = blockIdx.x;
+  const int64_t cell = cell_of[pr];
+  const int32_t sp = spair[pr];
   for (int i = threadIdx.x; i < 4 * KS * 16; i += 256) {
-    const int l = i / 16, j = i % 16, e = 16 * cb + j;
+    const int l = i / 16, k = i % 16;
     double v = 0.0;
-    if (l < nloc && e < ne) {
-      const int32_t pr = cell_epair[p0 + e / nf];
-      const int32_t sn = lmap[(int64_t)pr * nloc + l];
-      if (sn >= 0) v = C_am[(int64_t)sn * nf + e % nf];
+    if (l < nloc && k < nf) {
+      const int32_t sn = lmap[pr * nloc + l];
+      if (sn >= 0) v = C_am[(int64_t)sn * nf + k];
     }
-    Cs[l][j] = v;
+    Cs[l][k] = v;
   }
   __syncthreads();
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
   for (int rb = wave; rb < RB; rb += 4) {
-    const double *hp = Ht + ((int64_t)cell * RB + rb) * KS * 64 + lane;
+    const double *hp = Ht + (cell * RB + rb) * KS * 64 + lane;
     v4d_p acc = {0.0, 0.0, 0.0, 0.0};
     for (int ks = 0; ks < KS; ++ks)
       acc = __builtin_amdgcn_mfma_f64_16x16x4f64(hp[(int64_t)ks * 64], Cs[4 * ks + lk][li], acc,
                                                  0, 0, 0);
-    // accumulator v of lane l: node row 16 rb + 4 v + l/16, function 16 cb + l%16
+    // accumulator v of lane l: node row 16 rb + 4 v + l/16, function l%16
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int l = 16 * rb + 4 * v + lk, e = 16 * cb + li;
-      double val = 0.0;
-      if (l < nloc && e < ne) {
-        const int32_t pr = cell_epair[p0 + e / nf], sp = spair[pr];
-        // B_c vanishes on the layer of cells outside the support
-        const double bv = sp >= 0 ? B_pair[((int64_t)sp * nloc + l) * nf + e % nf] : 0.0;
-        val = bv - acc[v];
-      }
-      // E_c^T tile: row l (block rb), k index e
-      const int64_t ot = 16 * (int64_t)RB * noff + ((int64_t)rb * kse_n + e / 4) * 64 +
-                         (l % 16) + 16 * (e % 4);
-      Et[ot] = val;
-      if (Et32) Et32[ot] = (float)val;
-      // E_c tile: row e (block e/16), k index l (k steps cover 4 KS nodes)
-      if (l < 4 * KS) {
-        const int64_t oe = 4 * (int64_t)KS * noff + ((int64_t)(e / 16) * KS + l / 4) * 64 +
-                           (e % 16) + 16 * (l % 4);
-        Ee[oe] = val;
-        if (Ee32) Ee32[oe] = (float)val;
-      }
-    }
-  }
-}
-
-// Rows of the enrichment block of the orthogonalized Hamiltonian without the
-// projectors, H^E_ee = H^phiphi - C B^T - E C^T (the expansion of T^T Hhat T
-// with E = B - C H^cc), first part: Hee = H^phiphi - C B^T, row f = (I, k)
-// summed over the support nodes of atom I and, at each node, the atoms whose
-// support holds it (B vanishes off the support).
-__global__ __launch_bounds__(256) void k_hee_rows(int nf, int64_t n_enr,
-                                                  const int32_t *__restrict__ snode_ptr,
-                                                  const int32_t *__restrict__ snode,
-                                                  const int32_t *__restrict__ nm_ptr,
-                                                  const int32_t *__restrict__ nm_atom,
-                                                  const int32_t *__restrict__ nm_src,
-                                                  const double *__restrict__ C_am,
-                                                  const double *__restrict__ B_am,
-                                                  const double *__restrict__ Hpp,
-                                                  double *__restrict__ Hee) {
-  extern __shared__ double acc[];
-  const int64_t f = blockIdx.x;
-  const int I = f / nf, k = f % nf;
-  for (int64_t i = threadIdx.x; i < n_enr; i += blockDim.x) acc[i] = 0.0;
-  __syncthreads();
-  for (int32_t s = snode_ptr[I] + threadIdx.x; s < snode_ptr[I + 1]; s += blockDim.x) {
-    const int32_t j = snode[s];
-    const double cf = C_am[(int64_t)s * nf + k];
-    for (int32_t ee = nm_ptr[j]; ee < nm_ptr[j + 1]; ++ee) {
-      const int J = nm_atom[ee];
-      const int64_t src = nm_src[ee];
-      for (int l = 0; l < nf; ++l) atomicAdd(&acc[J * nf + l], cf * B_am[src * nf + l]);
-    }
-  }
-  __syncthreads();
-  for (int64_t i = threadIdx.x; i < n_enr; i += blockDim.x)
-    Hee[f * n_enr + i] = Hpp[f * n_enr + i] - acc[i];
-}
-
-// Second part: Hee -= E C^T = sum over cells of E_c C_c^T (E is non-zero on
-// the cells that hold an atom's support nodes, one layer beyond its support,
-// so the product is taken cell by cell).  One work-group takes a cell and 16
-// of its enrichment functions e2: C_c^T (nodes x 16) in LDS as the B operand,
-// the E_c tiles as the A operand, each wave the row blocks e1 = wave + 4 i;
-// every 16 x 16 block is added into Hee atomically.
-__global__ __launch_bounds__(256) void k_hee_cells(
-    int nloc, int KS, int nf, int max_cb, int64_t n_enr, const int32_t *__restrict__ cell_eptr,
-    const int32_t *__restrict__ cell_epair, const int64_t *__restrict__ cell_noff,
-    const int32_t *__restrict__ cpair_atom, const int32_t *__restrict__ lmap,
-    const double *__restrict__ C_am, const double *__restrict__ Ee, double *__restrict__ Hee) {
-  __shared__ double Cs[EFE_MAXLOC + 16][16];
-  const int64_t cell = blockIdx.x / max_cb;
-  const int cb = blockIdx.x % max_cb;
-  const int32_t p0 = cell_eptr[cell];
-  const int ne = (cell_eptr[cell + 1] - p0) * nf;
-  if (16 * cb >= ne) return;
-  const int RBE = (ne + 15) / 16;
-  const int64_t noff = cell_noff[cell];
-  for (int i = threadIdx.x; i < 4 * KS * 16; i += 256) {
-    const int l = i / 16, j = i % 16, e = 16 * cb + j;
-    double v = 0.0;
-    if (l < nloc && e < ne) {
-      const int32_t pr = cell_epair[p0 + e / nf];
-      const int32_t sn = lmap[(int64_t)pr * nloc + l];
-      if (sn >= 0) v = C_am[(int64_t)sn * nf + e % nf];
-    }
-    Cs[l][j] = v;
-  }
-  __syncthreads();
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
-  const int e2 = 16 * cb + li;
-  const int64_t f2 = e2 < ne ? (int64_t)cpair_atom[cell_epair[p0 + e2 / nf]] * nf + e2 % nf : 0;
-  for (int b1 = wave; b1 < RBE; b1 += 4) {
-    const double *ap = Ee + 4 * (int64_t)KS * noff + (int64_t)b1 * KS * 64 + lane;
-    v4d_p acc = {0.0, 0.0, 0.0, 0.0};
-    for (int ks = 0; ks < KS; ++ks)
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[(int64_t)ks * 64], Cs[4 * ks + lk][li], acc,
-                                                 0, 0, 0);
-    // accumulator v of lane l: function e1 = 16 b1 + 4 v + l/16, e2 = 16 cb + l%16
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int e1 = 16 * b1 + 4 * v + lk;
-      if (e1 < ne && e2 < ne) {
-        const int64_t f1 = (int64_t)cpair_atom[cell_epair[p0 + e1 / nf]] * nf + e1 % nf;
-        atomicAdd(&Hee[f1 * n_enr + f2], -acc[v]);
-      }
+      const int l = 16 * rb + 4 * v + lk;
+      if (l >= nloc || li >= nf) continue;
+      // B_c vanishes on the layer of cells outside the support
+      const double bv = sp >= 0 ? B_pair[((int64_t)sp * nloc + l) * nf + li] : 0.0;
+      E[(pr * nloc + l) * nf + li] = bv - acc[v];
     }
   }
 }
@@ -982,7 +864,6 @@ efe_status efe_build_enrichment(efe_ctx *c) {
   // projectors
   const int np = c->nproj;
   if ((s = efe_alloc(c, (void **)&c->d_Pc_am, c->n_kbnodes * 8))) return s;
-  if ((s = efe_alloc(c, (void **)&c->d_Pc_nm, c->nnz_kbnm * 8))) return s;
   if ((s = efe_alloc(c, (void **)&c->d_Pphi, (int64_t)np * ne * 8))) return s;
   if ((s = efe_alloc(c, (void **)&c->d_D, np * 8))) return s;
   HIPCHK(c, hipMemsetAsync(c->d_Pc_am, 0, c->n_kbnodes * 8, c->stream));
@@ -992,8 +873,6 @@ efe_status efe_build_enrichment(efe_ctx *c) {
     k_kb_pc<<<c->nkbpairs, 256, 0, c->stream>>>(g, c->kb_width, c->kb_rcut, c->d_xq1, c->d_W3,
                                                 c->d_N3, c->d_xyz, c->d_kbpair_atom,
                                                 c->d_kbpair_cell, c->d_kbpair_lmap, c->d_Pc_am);
-    k_to_node_major<<<cdiv(c->nnz_kbnm, 256), 256, 0, c->stream>>>(c->nnz_kbnm, 1, c->d_kbnm_src,
-                                                                   c->d_Pc_am, c->d_Pc_nm);
     if (c->nkbtrip > 0)
       k_kb_pphi<<<c->nkbtrip, 256, 0, c->stream>>>(g, e, c->kb_width, c->kb_rcut, c->d_xq1,
                                                    c->d_W3, c->d_xyz, c->d_nu, c->d_kbtrip, ne,
@@ -1005,6 +884,17 @@ efe_status efe_build_enrichment(efe_ctx *c) {
     k_ptilde<<<np, 256, ne * 8, c->stream>>>(nf, ne, c->d_kbnode_ptr, c->d_kbnode, c->d_Pc_am,
                                              c->d_nm_ptr, c->d_nm_atom, c->d_nm_src, c->d_C_am,
                                              c->d_Pphi, c->d_Ptil);
+  HIPCHK(c, hipGetLastError());
+  // the projectors' part P~^T D P~ of H^E_ee does not depend on the potential
+  if (np > 0 && ne > 0 &&
+      (s = efe_dgemm(c, true, false, ne, ne, np, 1.0, c->d_Ptil, ne, c->d_Ptil, ne, 1.0,
+                     c->d_Hpp_kin, ne, c->d_D)))
+    return s;
+  return efe_couple_projectors(c);
+}
+
+efe_status efe_symmetrize(efe_ctx *c, int64_t n, double *A) {
+  k_symmetrize<<<cdiv(n * n, 256), 256, 0, c->stream>>>(n, A);
   HIPCHK(c, hipGetLastError());
   return EFE_OK;
 }
@@ -1026,18 +916,22 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
   const int64_t tiles = c->n_cells * c->RB * c->KS * 64;
   if (!c->d_vq && (s = efe_alloc(c, (void **)&c->d_vq, c->n_qpts * 8))) return s;
   k_copy<<<cdiv(c->n_qpts, 256), 256, 0, c->stream>>>(c->n_qpts, vq, c->d_vq);
-  if (!c->d_Htile64 && (s = efe_alloc(c, (void **)&c->d_Htile64, tiles * 8))) return s;
   const bool want32 = precisions & (1 << EFE_FP32);
   const bool want16 = precisions & (1 << EFE_BF16);
-  if (want32 && !c->d_Htile32 && (s = efe_alloc(c, (void **)&c->d_Htile32, tiles * 4))) return s;
+  // dense cell Hamiltonians where an apply takes them: Gauss rules without
+  // tensor products, and the BF16 copies
+  const bool dense = !c->tp || want16;
+  if (dense && !c->d_Htile64 && (s = efe_alloc(c, (void **)&c->d_Htile64, tiles * 8))) return s;
+  if (want32 && !c->tp && !c->d_Htile32 && (s = efe_alloc(c, (void **)&c->d_Htile32, tiles * 4))) return s;
   const int64_t tiles16 = c->n_cells * c->RB * c->KS32 * 64 * 8;
   if (want16 && !c->d_Htile16 && (s = efe_alloc(c, (void **)&c->d_Htile16, tiles16 * 2))) return s;
   const int KQ8 = (int)cdiv(cdiv(c->nqp, 4), 8) * 8;   // quadrature k steps, padded
   const size_t shm = (size_t)KQ8 * 64 * 8;
   if (shm > 64 * 1024) EFE_FAIL(c, EFE_EINVAL, "too many Gauss points per cell");
-  k_build_hcell<<<c->n_cells * c->RB, 256, shm, c->stream>>>(
-      c->nloc, c->nqp, c->RB, c->KS, KQ8, c->d_N3, c->d_W3, c->d_K, c->d_vq, c->d_Htile64,
-      want32 ? c->d_Htile32 : nullptr);
+  if (dense)
+    k_build_hcell<<<c->n_cells * c->RB, 256, shm, c->stream>>>(
+        c->nloc, c->nqp, c->RB, c->KS, KQ8, c->d_N3, c->d_W3, c->d_K, c->d_vq, c->d_Htile64,
+        want32 && !c->tp ? c->d_Htile32 : nullptr);
   if (want16)
     k_tile_bf16<<<cdiv(tiles16, 256), 256, 0, c->stream>>>(c->n_cells, c->RB, c->KS, c->KS32,
                                                            c->d_Htile64, c->d_Htile16);
@@ -1047,12 +941,8 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
     const int64_t ns = c->n_snodes * nf;
     const size_t pb = (size_t)c->npairs * c->nloc * nf * 8;   // support pairs
     if (!c->d_B_pair && (s = efe_alloc(c, (void **)&c->d_B_pair, pb))) return s;
-    if (!c->d_Hee && (s = efe_alloc(c, (void **)&c->d_Hee, ne * ne * 8))) return s;
-    const int64_t tT = 16 * (int64_t)c->RB * c->n_epad, tE = 4 * (int64_t)c->KS * c->n_epad;
-    if (!c->d_Et64 && (s = efe_alloc(c, (void **)&c->d_Et64, tT * 8))) return s;
-    if (!c->d_Ee64 && (s = efe_alloc(c, (void **)&c->d_Ee64, tE * 8))) return s;
-    if (want32 && !c->d_Et32 && (s = efe_alloc(c, (void **)&c->d_Et32, tT * 4))) return s;
-    if (want32 && !c->d_Ee32 && (s = efe_alloc(c, (void **)&c->d_Ee32, tE * 4))) return s;
+    if (!c->d_Epair && (s = efe_alloc(c, (void **)&c->d_Epair, (size_t)c->ncpairs * c->nloc * nf * 8)))
+      return s;
     k_copy<<<cdiv(ns, 256), 256, 0, c->stream>>>(ns, c->d_Bkin_am, c->d_B_am);
     const int KQ = (int)cdiv(c->nqp, 4);
     k_enr_pair_proj_v<<<c->npairs, 256, (size_t)KQ * 64 * 8, c->stream>>>(
@@ -1064,20 +954,22 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
                                                        c->d_nu, c->d_trip, c->d_vq, ne, nullptr,
                                                        c->d_Hpp);
     k_symmetrize<<<cdiv(ne * ne, 256), 256, 0, c->stream>>>(ne, c->d_Hpp);
-    // coupling of the orthogonalized basis: E_c per cell, then
-    // H^E_ee = H^phiphi - C B^T - sum_c E_c C_c^T
-    k_build_E<<<c->n_cells * c->max_rbe, 256, 0, c->stream>>>(
-        c->nloc, c->RB, c->KS, nf, c->max_rbe, c->d_Htile64, c->d_cell_eptr, c->d_cell_epair,
-        c->d_cell_noff, c->d_cpair_lmap, c->d_cpair_spair, c->d_C_am, c->d_B_pair, c->d_Et64,
-        c->d_Ee64, want32 ? c->d_Et32 : nullptr, want32 ? c->d_Ee32 : nullptr);
-    k_hee_rows<<<ne, 256, ne * 8, c->stream>>>(nf, ne, c->d_snode_ptr, c->d_snode, c->d_nm_ptr,
-                                               c->d_nm_atom, c->d_nm_src, c->d_C_am, c->d_B_am,
-                                               c->d_Hpp, c->d_Hee);
-    k_hee_cells<<<c->n_cells * c->max_rbe, 256, 0, c->stream>>>(
-        c->nloc, c->KS, nf, c->max_rbe, ne, c->d_cell_eptr, c->d_cell_epair, c->d_cell_noff,
-        c->d_cpair_atom, c->d_cpair_lmap, c->d_C_am, c->d_Ee64, c->d_Hee);
-    k_symmetrize<<<cdiv(ne * ne, 256), 256, 0, c->stream>>>(ne, c->d_Hee);
+    // coupling of the orthogonalized basis, E_c per (atom, cell) pair
+    if (c->tp) {
+      if ((s = efe_tp_pairs(c))) return s;
+    } else {
+      k_build_E<<<c->ncpairs, 256, 0, c->stream>>>(c->nloc, c->RB, c->KS, nf, c->d_Htile64,
+                                                   c->d_cpair_cell, c->d_cpair_lmap,
+                                                   c->d_cpair_spair, c->d_C_am, c->d_B_pair,
+                                                   c->d_Epair);
+    }
   }
+  if (ne) {
+    if (!c->d_Hee && (s = efe_alloc(c, (void **)&c->d_Hee, ne * ne * 8))) return s;
+    k_copy<<<cdiv(ne * ne, 256), 256, 0, c->stream>>>(
+        ne * ne, nf > 0 && c->npairs > 0 ? c->d_Hpp : c->d_Hpp_kin, c->d_Hee);
+  }
+  if ((s = efe_couple_build(c, want32))) return s;
   HIPCHK(c, hipGetLastError());
   c->have_potential = true;
   return EFE_OK;
