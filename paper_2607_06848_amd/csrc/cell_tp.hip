@@ -20,14 +20,9 @@
 #include <vector>
 
 #include "efe_device.h"
+#include "line_ops.h"
 
 namespace {
-// 1-D matrices of one axis in even/odd form: with H = ceil(P/2), Q = floor(P/2),
-// e[q H + i] = (M[q][i] + M[q][P-1-i]) / 2 (M itself for i or q the middle),
-// o[q Q + i] = (M[q][i] - M[q][P-1-i]) / 2; the transposed product reads the
-// same numbers transposed.
-constexpr int TP_MAT = 25;   // doubles per matrix: e (16), o (9)
-
 // vectors per work-group: U P threads share U P^3 doubles of LDS.  Chosen so
 // that U P fills whole waves (P = 4: 64, P = 6: 192, P = 3: 192 threads) or
 // nearly (P = 5: 120 of 128, P = 7: 112 of 128), a node's piece of U columns
@@ -35,46 +30,8 @@ constexpr int TP_MAT = 25;   // doubles per matrix: e (16), o (9)
 // more work-groups fit a CU's LDS (P = 7: 44 KB each).
 constexpr int tp_units(int P) { return P == 7 ? 16 : P == 6 ? 32 : P == 5 ? 24 : P == 4 ? 16 : 64; }
 
-// The matrices are read through the scalar cache.  fresh() hides where the
-// pointer comes from, so that every phase loads its own 50 numbers again
-// instead of keeping all six matrices in scalar registers (which spilled).
 // waves per SIMD the registers leave (two planes of P^2 doubles are live)
 constexpr int tp_waves(int P) { return P >= 6 ? 2 : P == 5 ? 3 : 4; }
-
-typedef const __attribute__((address_space(4))) double cdouble;
-__device__ __forceinline__ cdouble *fresh(cdouble *m) {
-  asm volatile("" : "+s"(m));
-  return m;
-}
-
-// y = M x (T: M^T x) for matrix k of the table (axis, or 3 + axis)
-template <int P, bool T>
-__device__ __forceinline__ void mul1d(cdouble *m, int k, const double (&x)[P], double (&y)[P]) {
-  cdouble *e = m + k * TP_MAT, *o = e + 16;
-  constexpr int H = (P + 1) / 2, Q = P / 2;
-  double xe[H], xo[Q > 0 ? Q : 1];
-#pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    xe[i] = x[i] + x[P - 1 - i];
-    xo[i] = x[i] - x[P - 1 - i];
-  }
-  if (H > Q) xe[Q] = x[Q];
-#pragma unroll
-  for (int q = 0; q < H; ++q) {
-    double s = (T ? e[q] : e[q * H]) * xe[0];
-#pragma unroll
-    for (int i = 1; i < H; ++i) s = fma(T ? e[i * H + q] : e[q * H + i], xe[i], s);
-    if (q < Q) {
-      double d = (T ? o[q] : o[q * Q]) * xo[0];
-#pragma unroll
-      for (int i = 1; i < Q; ++i) d = fma(T ? o[i * Q + q] : o[q * Q + i], xo[i], d);
-      y[q] = s + d;
-      y[P - 1 - q] = s - d;
-    } else {
-      y[q] = s;
-    }
-  }
-}
 
 // A work-group takes U (cell, column) units; thread (s, u) owns plane s of
 // unit u, P^2 values in registers, and contracts the two axes inside its
@@ -288,21 +245,11 @@ void lagrange_derivative(const std::vector<double> &x, std::vector<double> &D) {
     }
 }
 
-void even_odd(int P, const std::vector<double> &M, double *e, double *o) {
-  const int H = (P + 1) / 2, Q = P / 2;
-  for (int q = 0; q < H; ++q)
-    for (int i = 0; i < H; ++i)
-      e[q * H + i] = i < Q ? 0.5 * (M[q * P + i] + M[q * P + P - 1 - i]) : M[q * P + i];
-  for (int q = 0; q < H && H > Q; ++q)   // middle row: M[mid][i] = M[mid][P-1-i]
-    for (int i = 0; i < Q; ++i)
-      if (q == Q) e[q * H + i] = 0.5 * (M[q * P + i] + M[q * P + P - 1 - i]);
-  for (int q = 0; q < Q; ++q)
-    for (int i = 0; i < Q; ++i) o[q * Q + i] = 0.5 * (M[q * P + i] - M[q * P + P - 1 - i]);
-}
 }  // namespace
 
 efe_status efe_tp_setup(efe_ctx *c, const std::vector<double> &xq, const std::vector<double> &wq,
-                        const std::vector<double> &N1, const std::vector<double> &wg) {
+                        const std::vector<double> &N1, const std::vector<double> &D1,
+                        const std::vector<double> &wg) {
   c->tp = c->nq == c->P && c->P >= 2;
   const int P = c->P;
   // separable factors of the lumped mass: 1 (0 on the boundary), then 1/m
@@ -319,6 +266,27 @@ efe_status efe_tp_setup(efe_ctx *c, const std::vector<double> &xq, const std::ve
   efe_status st;
   if ((st = efe_alloc(c, (void **)&c->d_s1, s1.size() * 8))) return st;
   HIPCHK(c, hipMemcpyAsync(c->d_s1, s1.data(), s1.size() * 8, hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  // 1-D mass and stiffness of the Gauss rule on the nodes (any nq): the cell
+  // stiffness is K x M x M + M x K x M + M x M x K
+  std::vector<double> mk(6 * TP_MAT, 0.0), M(P * P), K(P * P);
+  for (int d = 0; d < 3 && P >= 2; ++d) {
+    const double h2 = 0.5 * c->h[d];
+    for (int i = 0; i < P; ++i)
+      for (int j = 0; j < P; ++j) {
+        double m = 0.0, k = 0.0;
+        for (int q = 0; q < c->nq; ++q) {
+          m += wq[q] * N1[q * P + i] * N1[q * P + j];
+          k += wq[q] * D1[q * P + i] * D1[q * P + j];
+        }
+        M[i * P + j] = h2 * m;
+        K[i * P + j] = k / h2;
+      }
+    even_odd(P, M, &mk[d * TP_MAT], &mk[d * TP_MAT + 16]);
+    even_odd(P, K, &mk[(3 + d) * TP_MAT], &mk[(3 + d) * TP_MAT + 16]);
+  }
+  if ((st = efe_alloc(c, (void **)&c->d_mk, mk.size() * 8))) return st;
+  HIPCHK(c, hipMemcpyAsync(c->d_mk, mk.data(), mk.size() * 8, hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (!c->tp) return EFE_OK;
   std::vector<double> D, Nd(P * P), S(P * P), tab(6 * TP_MAT, 0.0);

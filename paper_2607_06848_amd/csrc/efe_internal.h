@@ -156,6 +156,7 @@ struct efe_ctx {
   // row factors [2][n1x + n1y + n1z] (interior mask, 1/m)
   bool tp = false;
   double *d_tpm = nullptr, *d_s1 = nullptr;
+  double *d_mk = nullptr;   // 1-D mass and stiffness per axis (Poisson)
 
   // potential-dependent operators
   bool have_potential = false;
@@ -266,7 +267,8 @@ size_t efe_syev_iwork(int64_t n);
 // tensor-product cell operator (cell_tp.hip): the products of every cell into
 // Yc [cell][local node][column], or (Yc = nullptr) added to Y times alpha
 efe_status efe_tp_setup(efe_ctx *ctx, const std::vector<double> &xq, const std::vector<double> &wq,
-                        const std::vector<double> &N1, const std::vector<double> &wg);
+                        const std::vector<double> &N1, const std::vector<double> &D1,
+                        const std::vector<double> &wg);
 efe_status efe_tp_apply(efe_ctx *ctx, const double *X, int64_t ldx, bool minv, int ncols,
                         double *Yc, int64_t ldc, double *Y, int64_t ldy, double alpha);
 // E_c = B_c - H_c C_c^T of every coupling pair into d_Epair

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "efe_device.h"
+#include "line_ops.h"
 
 #define KB_HA_PER_K 3.166811563e-6
 
@@ -24,8 +25,7 @@ struct ScfState {
   double *rho_in = nullptr, *rho_out = nullptr, *v_in = nullptr, *phiq = nullptr;
   double *phi_rem = nullptr, *phi_out = nullptr;                      // [n_nodes]
   double *Kdiag = nullptr;                                            // [n_nodes]
-  double *cg = nullptr;                                               // r, z, p, Ap, b
-  double *Ktile = nullptr;   // cell stiffness in the 16x16x4 MFMA operand layout
+  double *cg = nullptr;                                               // r, z, p (two), b
   double *part = nullptr;    // per-work-group partial sums of the CG reductions
   double *ycell = nullptr;   // K x cell by cell, before the gather to nodes
   double *hist = nullptr;                                             // Anderson X, F ring
@@ -51,7 +51,7 @@ void efe_scf_free(efe_ctx *c) {
   ScfState &s = *(ScfState *)c->scf;
   void *ptrs[] = {s.rho_at, s.phi_at, s.v_short, s.rho_in, s.rho_out, s.v_in, s.phiq,
                   s.phi_rem, s.phi_out, s.Kdiag, s.cg, s.hist, s.scal, s.f, s.cell_ptr,
-                  s.cell_atom, s.Ktile, s.part, s.ycell, s.kdiag_k, s.u_k, s.uq_k};
+                  s.cell_atom, s.part, s.ycell, s.kdiag_k, s.u_k, s.uq_k};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   delete (ScfState *)c->scf;
@@ -249,144 +249,296 @@ __global__ __launch_bounds__(256) void k_load_vector(int nloc, int nqp, const in
   }
 }
 
-typedef double v4d_s __attribute__((ext_vector_type(4)));
+// ---- K x cell by cell, K_c = K x M x M + M x K x M + M x M x K with the 1-D
+// mass M and stiffness K of every axis, as contractions along the lines of a
+// cell: a work-group holds 256 / P^2 cells in LDS, thread = (cell, line); along
+// x it forms M x and K x, along y M M x and K M x + M K x, along z the result.
+// For one vector the tensor form needs 14 P^4 flops a cell in place of 2 P^6:
+// 23 us for 4,096 cells at P = 7, bound by latency and the 42 MB it moves.
+//
+// CG (Jacobi preconditioner) runs two kernels an iteration, this one and
+// k_cg_update.  No iteration needs a scalar on the host: every work-group adds
+// the per-work-group partial sums of the dot products itself, in the same
+// order (the result does not depend on timing), and all of them see the same
+// stopping test, so iterations queued after the last one do nothing and the
+// loop ends after the same iteration as one that tests r.r each time.  An
+// iteration takes 45 us for 4,096 cells and 22 us for 64 (107 and 42 us with
+// matrix products, five kernels and a separate p).
+//   sc[0] done flag, sc[1] iterations, sc[2] squared stopping threshold, sc[3] b.b
+//   part[0], part[1]: [r.r, r.z][CG_NP] of even and odd iterations; part[2]: p.Ap
+constexpr int CG_NP = 768;   // three work-groups a CU (their LDS)
 
-// Cell stiffness in the operand layout of v_mfma_f64_16x16x4:
-// Kt[rb][ks][lane] = K[16 rb + lane%16][4 ks + lane/16] (zero past nloc)
-__global__ void k_tile_K(int nloc, int RB, int KS, const double *__restrict__ K,
-                         double *__restrict__ Kt) {
-  const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)RB * KS * 64) return;
-  const int l = (int)(idx % 64);
-  const int ks = (int)((idx / 64) % KS), rb = (int)(idx / (64 * (int64_t)KS));
-  const int row = 16 * rb + l % 16, col = 4 * ks + l / 16;
-  Kt[idx] = (row < nloc && col < nloc) ? K[(int64_t)row * nloc + col] : 0.0;
-}
-
-// K x_c for every cell in one launch, on FP64 MFMA: a work-group takes 16
-// cells, whose gathered x form the 16 columns of the B operand (in LDS,
-// zero on boundary nodes and past nloc), and four row blocks of the shared
-// cell stiffness (A operand, MFMA layout), one per wave; the products are
-// written cell by cell and summed into the nodes by k_stiff_gather.
-constexpr int STIFF_CELLS = 16;
-__global__ __launch_bounds__(256) void k_stiff_apply_all(int64_t ncells, int nloc, int RB, int KS,
-                                                         const int32_t *__restrict__ c2g,
-                                                         const double *__restrict__ Kt,
-                                                         const double *__restrict__ x,
-                                                         const double *__restrict__ minv,
-                                                         double *__restrict__ ycell,
-                                                         const double *__restrict__ done) {
-  extern __shared__ double xs[];   // [STIFF_CELLS][4 KS + 1]
-  if (done && *done != 0.0) return;
-  const int KP1 = 4 * KS + 1;      // odd row stride: the 16 cells hit different banks
-  const int64_t c0 = (int64_t)blockIdx.x * STIFF_CELLS;
-  const int ncb = (int)min<int64_t>(STIFF_CELLS, ncells - c0);
-  for (int i = threadIdx.x; i < STIFF_CELLS * KP1; i += blockDim.x) {
-    const int cc = i / KP1, l = i % KP1;
-    double v = 0.0;
-    if (cc < ncb && l < nloc) {
-      const int32_t node = c2g[(c0 + cc) * nloc + l];
-      if (minv[node] != 0.0) v = x[node];
+// sums of the CG_NP values at a and at b (256 or more threads)
+__device__ inline double2 cg_sums(const double *__restrict__ a, const double *__restrict__ b,
+                                  double *red) {
+  const int t = threadIdx.x;
+  double x = 0.0, y = 0.0;
+  if (t < 256) {
+    x = (a[t] + a[t + 256]) + a[t + 512];
+    y = (b[t] + b[t + 256]) + b[t + 512];
+    for (int o = 32; o > 0; o >>= 1) {
+      x += __shfl_xor(x, o);
+      y += __shfl_xor(y, o);
     }
-    xs[i] = v;
+    if (t % 64 == 0) {
+      red[t / 64] = x;
+      red[4 + t / 64] = y;
+    }
   }
   __syncthreads();
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
-  // one row block per wave; the work-groups of blockIdx.y share the gather
-  const int rb = 4 * blockIdx.y + wave;
-  if (rb < RB) {
-    // four accumulators (k step mod 4) quarter the dependent MFMA chain; the
-    // A fragments of eight k steps are loaded ahead of their MFMAs
-    v4d_s acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = acc0, acc2 = acc0, acc3 = acc0;
-    const double *kt = Kt + (int64_t)rb * KS * 64 + lane;
-    const double *xb = xs + li * KP1 + lk;
-    int ks = 0;
-    for (; ks + 7 < KS; ks += 8) {
-      double a[8];
+  const double2 r = make_double2((red[0] + red[1]) + (red[2] + red[3]),
+                                 (red[4] + red[5]) + (red[6] + red[7]));
+  __syncthreads();
+  return r;
+}
+
+// sum over the work-group in a fixed order (every thread gets it)
+template <int NT>
+__device__ inline double wg_sum(double x, double *red) {
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+  if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = x;
+  __syncthreads();
+  double s = 0.0;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) a[u] = kt[(int64_t)(ks + u) * 64];
+  for (int i = 0; i < NT / 64; ++i) s += red[i];
+  __syncthreads();
+  return s;
+}
+
+struct StiffArgs {
+  const double *mk, *x, *z, *m;
+  double *p, *ycell, *part, *sc;
+  double shift;
+  int64_t ncells, n1x, n1y;
+  int ncx, ncy, it;
+};
+
+// it < 0: ycell = K_c x only.  Else iteration it of CG: p = z + beta x with x
+// the previous p (written once per node, by the cell that holds it off its far
+// faces), and the partial sums of p.(K + shift diag(m)) p.
+template <int P>
+__global__ __launch_bounds__(256) void k_stiff_cells(StiffArgs a) {
+  constexpr int PP = P * P, N = P * P * P, CW = 256 / PP;
+  __shared__ double X[CW * N], A[CW * N], B[CW * N], red[8];
+  const int t = threadIdx.x;
+  double beta = 0.0;
+  if (a.it >= 0) {
+    const double *cur = a.part + (a.it & 1) * 2 * CG_NP;
+    const double2 s = cg_sums(cur, cur + CG_NP, red);
+    if (s.x <= a.sc[2]) {
+      if (blockIdx.x == 0 && t == 0) a.sc[0] = 1.0;
+      return;
+    }
+    if (a.it > 0) {
+      const double *old = a.part + (1 - (a.it & 1)) * 2 * CG_NP;
+      beta = s.y / cg_sums(old, old + CG_NP, red).y;
+    }
+  }
+  cdouble *const m0 = (cdouble *)(uintptr_t)a.mk;
+  double acc = 0.0;
+  const int c = t / PP, line = t % PP, l0 = line % P, l1 = line / P;
+  for (int64_t cb = blockIdx.x * (int64_t)CW; cb < a.ncells; cb += (int64_t)gridDim.x * CW) {
+    const int nc = (int)min<int64_t>(CW, a.ncells - cb);
+    __syncthreads();
+    for (int i = t; i < CW * N; i += 256) {
+      const int cc = i / N, l = i % N;
+      double v = 0.0;
+      if (cc < nc) {
+        const int cell = (int)cb + cc;
+        const int cx = cell % a.ncx, cy = (cell / a.ncx) % a.ncy, cz = cell / (a.ncx * a.ncy);
+        const int i0 = l % P, i1 = (l / P) % P, i2 = l / PP;
+        const int64_t node = cx * (P - 1) + i0 +
+                             a.n1x * (cy * (P - 1) + i1 + a.n1y * (int64_t)(cz * (P - 1) + i2));
+        if (a.it < 0) {
+          v = a.x[node];
+        } else {
+          v = a.z[node] + (a.it > 0 ? beta * a.x[node] : 0.0);
+          if (i0 < P - 1 && i1 < P - 1 && i2 < P - 1) {
+            a.p[node] = v;
+            if (a.shift != 0.0) acc += a.shift * a.m[node] * v * v;
+          }
+        }
+      }
+      X[i] = v;
+    }
+    __syncthreads();
+    const bool on = c < nc && c < CW;
+    double v[P], y[P], w[P], q[P];
+    cdouble *m = fresh(m0);
+    if (on) {
+      const int o = c * N + PP * l1 + P * l0;   // line (y, z) = (l0, l1)
 #pragma unroll
-      for (int u = 0; u < 8; u += 4) {
-        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], xb[4 * (ks + u)], acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u + 1], xb[4 * (ks + u + 1)], acc1, 0, 0, 0);
-        acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u + 2], xb[4 * (ks + u + 2)], acc2, 0, 0, 0);
-        acc3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u + 3], xb[4 * (ks + u + 3)], acc3, 0, 0, 0);
+      for (int i = 0; i < P; ++i) v[i] = X[o + i];
+      mul1d<P, false>(m, 0, v, y);
+      mul1d<P, false>(m, 3, v, w);
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        A[o + i] = y[i];
+        B[o + i] = w[i];
       }
     }
-    for (; ks < KS; ++ks)
-      acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(kt[(int64_t)ks * 64], xb[4 * ks], acc0, 0, 0, 0);
-    const v4d_s acc = (acc0 + acc1) + (acc2 + acc3);
-    // accumulator v of lane l: local row 16 rb + 4 v + l/16 of cell l%16
+    __syncthreads();
+    m = fresh(m0);
+    if (on) {
+      const int o = c * N + PP * l1 + l0;       // line (x, z)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = 16 * rb + 4 * v + lk;
-      if (li < ncb && row < nloc) ycell[(c0 + li) * nloc + row] = acc[v];
+      for (int i = 0; i < P; ++i) v[i] = A[o + P * i];
+      mul1d<P, false>(m, 1, v, y);
+      mul1d<P, false>(m, 4, v, w);
+#pragma unroll
+      for (int i = 0; i < P; ++i) v[i] = B[o + P * i];
+      mul1d<P, false>(m, 1, v, q);
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        A[o + P * i] = y[i];
+        B[o + P * i] = w[i] + q[i];
+      }
     }
+    __syncthreads();
+    m = fresh(m0);
+    if (on) {
+      const int o = c * N + P * l1 + l0;        // line (x, y)
+#pragma unroll
+      for (int i = 0; i < P; ++i) v[i] = A[o + PP * i];
+      mul1d<P, false>(m, 5, v, y);
+#pragma unroll
+      for (int i = 0; i < P; ++i) v[i] = B[o + PP * i];
+      mul1d<P, false>(m, 2, v, w);
+      double *yc = a.ycell + (cb + c) * N + line;
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        const double r = y[i] + w[i];
+        yc[PP * i] = r;
+        if (a.it >= 0) acc += X[o + PP * i] * r;
+      }
+    }
+  }
+  if (a.it >= 0) {
+    __syncthreads();
+    const double s = wg_sum<256>(acc, red);
+    if (t == 0) a.part[4 * CG_NP + blockIdx.x] = s;
   }
 }
 
-// y[node] = sum of ycell over the (up to 8) cells holding the node, in a
-// fixed order (no atomics); zero on boundary nodes.  Node (i, j, k) lies in
-// cells i/p - 1 and i/p along x when i is a multiple of p (inside the mesh),
-// else in cell i/p only; likewise along y and z.  With part, the work-group
-// also leaves its partial sum of x.y there (the p.Ap of CG).
+// sum of ycell over the (up to 8) cells holding an interior node, in a fixed
+// order (no atomics).  Node (i, j, k) lies in cells i/p - 1 and i/p along x
+// when i is a multiple of p, else in cell i/p only; likewise along y and z.
 struct GridDims {
-  int64_t n1x, n1y, n1z;
+  uint32_t n1x, n1y, n1z;
   int ncx, ncy, ncz, p, P, nloc;
 };
-__global__ __launch_bounds__(256) void k_stiff_gather(GridDims d, const double *__restrict__ ycell,
-                                                      const double *__restrict__ minv,
-                                                      const double *__restrict__ x,
-                                                      double *__restrict__ y,
-                                                      double *__restrict__ part,
-                                                      const double *__restrict__ done,
-                                                      double shift,
-                                                      const double *__restrict__ m) {
-  __shared__ double red[256];
-  if (done && *done != 0.0) return;
-  const int64_t n = d.n1x * d.n1y * d.n1z;
-  double acc = 0.0;
-  for (int64_t node = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; node < n;
-       node += (int64_t)gridDim.x * blockDim.x) {
-    double v = 0.0;
-    if (minv[node] != 0.0) {
-      const int64_t gi = node % d.n1x, gj = (node / d.n1x) % d.n1y, gk = node / (d.n1x * d.n1y);
-      int cs[3][2], ls[3][2], nc[3];
-      const int64_t g3[3] = {gi, gj, gk};
-      const int ncl[3] = {d.ncx, d.ncy, d.ncz};
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        const int cc = (int)(g3[t] / d.p), a = (int)(g3[t] % d.p);
-        nc[t] = 0;
-        if (a == 0 && cc > 0) {
-          cs[t][nc[t]] = cc - 1;
-          ls[t][nc[t]++] = d.p;
-        }
-        if (cc < ncl[t]) {
-          cs[t][nc[t]] = cc;
-          ls[t][nc[t]++] = a;
-        }
+__device__ inline double cell_sum(const GridDims &d, uint32_t node,
+                                  const double *__restrict__ ycell) {
+  const uint32_t jk = node / d.n1x, gi = node - jk * d.n1x, gk = jk / d.n1y, gj = jk - gk * d.n1y;
+  const int cx = (int)(gi / (uint32_t)d.p), cy = (int)(gj / (uint32_t)d.p),
+            cz = (int)(gk / (uint32_t)d.p);
+  const int lx = (int)gi - cx * d.p, ly = (int)gj - cy * d.p, lz = (int)gk - cz * d.p;
+  double v = 0.0;
+  for (int z = lz == 0 ? -1 : 0; z <= 0; ++z)
+    for (int y = ly == 0 ? -1 : 0; y <= 0; ++y)
+      for (int x = lx == 0 ? -1 : 0; x <= 0; ++x) {
+        const int64_t cell = cx + x + (int64_t)d.ncx * (cy + y + (int64_t)d.ncy * (cz + z));
+        v += ycell[cell * d.nloc + (x ? d.p : lx) + d.P * ((y ? d.p : ly) + d.P * (z ? d.p : lz))];
       }
-      for (int z = 0; z < nc[2]; ++z)
-        for (int yy = 0; yy < nc[1]; ++yy)
-          for (int xx = 0; xx < nc[0]; ++xx) {
-            const int64_t cell = cs[0][xx] + (int64_t)d.ncx * (cs[1][yy] + (int64_t)d.ncy * cs[2][z]);
-            const int l = ls[0][xx] + d.P * (ls[1][yy] + d.P * ls[2][z]);
-            v += ycell[cell * d.nloc + l];
-          }
-      if (shift != 0.0) v += shift * m[node] * x[node];
+  return v;
+}
+
+// start of CG: r = b - (K + shift diag(m)) phi with the cell sums of K phi in
+// ycell, z = r / diag, and the partial sums of b.b, r.r and r.z (zero on the
+// boundary)
+__global__ __launch_bounds__(256) void k_cg_init(GridDims d, const double *__restrict__ ycell,
+                                                 const double *__restrict__ minv,
+                                                 const double *__restrict__ m, double shift,
+                                                 const double *__restrict__ diag,
+                                                 const double *__restrict__ b,
+                                                 const double *__restrict__ phi,
+                                                 double *__restrict__ r, double *__restrict__ z,
+                                                 double *__restrict__ part) {
+  __shared__ double red[8];
+  const uint32_t n = d.n1x * d.n1y * d.n1z;
+  double bb = 0.0, rr = 0.0, rz = 0.0;
+  for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) {
+    double ri = 0.0, zi = 0.0;
+    if (minv[i] != 0.0) {
+      double y = cell_sum(d, i, ycell);
+      if (shift != 0.0) y += shift * m[i] * phi[i];
+      ri = b[i] - y;
+      zi = ri / diag[i];
     }
-    y[node] = v;
-    if (part) acc += x[node] * v;
+    r[i] = ri;
+    z[i] = zi;
+    bb += b[i] * b[i];
+    rr += ri * ri;
+    rz += ri * zi;
   }
-  if (part) {
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-      __syncthreads();
+  const double s0 = wg_sum<256>(rr, red), s1 = wg_sum<256>(rz, red), s2 = wg_sum<256>(bb, red);
+  if (threadIdx.x == 0) {
+    part[blockIdx.x] = s0;
+    part[CG_NP + blockIdx.x] = s1;
+    part[4 * CG_NP + blockIdx.x] = s2;
+  }
+}
+
+// b.b and the stopping threshold before the first iteration (start), or the
+// stopping test after a batch of iterations
+__global__ __launch_bounds__(256) void k_cg_check(const double *__restrict__ part, int it,
+                                                  double rtol, bool start, double *sc) {
+  __shared__ double red[8];
+  const double *cur = part + (it & 1) * 2 * CG_NP;
+  const double2 s = cg_sums(cur, part + 4 * CG_NP, red);
+  if (threadIdx.x != 0) return;
+  if (start) {
+    const double tb = rtol * sqrt(s.y);
+    sc[1] = 0.0;
+    sc[2] = tb * tb;
+    sc[3] = s.y;
+  }
+  sc[0] = s.x <= sc[2] ? 1.0 : 0.0;
+}
+
+// alpha = r.z / p.Ap; phi += alpha p, r -= alpha Ap with Ap summed from the
+// cells on the way, z = r / diag (interior); partial sums of r.r and r.z of the
+// next iteration (copies of this one's once the test is met)
+__global__ __launch_bounds__(512) void k_cg_update(GridDims d, const double *__restrict__ ycell,
+                                                   const double *__restrict__ minv,
+                                                   const double *__restrict__ m, double shift,
+                                                   const double *__restrict__ diag,
+                                                   const double *__restrict__ p,
+                                                   double *__restrict__ phi,
+                                                   double *__restrict__ r, double *__restrict__ z,
+                                                   double *__restrict__ part, int it,
+                                                   double *__restrict__ sc) {
+  __shared__ double red[8];
+  const double *cur = part + (it & 1) * 2 * CG_NP;
+  double *nxt = part + (1 - (it & 1)) * 2 * CG_NP;
+  const double2 s = cg_sums(cur, cur + CG_NP, red);
+  if (s.x <= sc[2]) {
+    if (threadIdx.x == 0) {
+      nxt[blockIdx.x] = cur[blockIdx.x];
+      nxt[CG_NP + blockIdx.x] = cur[CG_NP + blockIdx.x];
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+    return;
+  }
+  const double alpha = s.y / cg_sums(cur, part + 4 * CG_NP, red).y;
+  const uint32_t n = d.n1x * d.n1y * d.n1z;
+  double rr = 0.0, rz = 0.0;
+  for (uint32_t i = blockIdx.x * 512u + threadIdx.x; i < n; i += gridDim.x * 512u) {
+    if (minv[i] == 0.0) continue;   // p, r and z stay zero there
+    double y = cell_sum(d, i, ycell);
+    if (shift != 0.0) y += shift * m[i] * p[i];
+    phi[i] += alpha * p[i];
+    const double ri = r[i] - alpha * y;
+    const double zi = ri / diag[i];
+    r[i] = ri;
+    z[i] = zi;
+    rr += ri * ri;
+    rz += ri * zi;
+  }
+  const double t0 = wg_sum<512>(rr, red), t1 = wg_sum<512>(rz, red);
+  if (threadIdx.x == 0) {
+    nxt[blockIdx.x] = t0;
+    nxt[CG_NP + blockIdx.x] = t1;
+    if (blockIdx.x == 0) sc[1] += 1.0;
   }
 }
 
@@ -627,113 +779,10 @@ __global__ void k_wdot(int64_t n, int nqp, const double *__restrict__ W3,
   if (threadIdx.x == 0) atomicAdd(out, red[0]);
 }
 
-// y = a x + b y (vectors)
-__global__ void k_axpby(int64_t n, double a, const double *__restrict__ x, double b,
-                        double *__restrict__ y) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) y[i] = a * x[i] + b * y[i];
-}
-
-// z = r / d
-__global__ void k_precond(int64_t n, const double *__restrict__ r, const double *__restrict__ d,
-                          const double *__restrict__ minv, double *__restrict__ z) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) z[i] = minv[i] == 0.0 ? 0.0 : r[i] / d[i];
-}
-
 __global__ void k_sub(int64_t n, const double *__restrict__ a, const double *__restrict__ b,
                       double *__restrict__ c) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < n) c[i] = a[i] - b[i];
-}
-
-// ---- Poisson CG with its scalars on the device.  sc[0] r.z, sc[1] p.Ap,
-// sc[2] r.r, sc[3] new r.z, sc[4] done flag, sc[5] iterations, sc[6] the
-// squared stopping threshold, sc[7] beta.  Every kernel of an iteration
-// returns at once when the flag is set, so the host can queue iterations in
-// batches and still stop after the same iteration as a loop that tests r.r
-// each time.  The reductions go through CG_NB per-work-group partial sums
-// that are added in a fixed order (no atomics: the result does not depend
-// on timing).
-constexpr int CG_NB = 1024;
-
-__device__ inline double block_sum(double v, double *red) {
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  return red[0];
-}
-
-// sum of part[0 .. CG_NB) by one work-group of 256 threads, fixed order
-__device__ inline double sum_parts(const double *__restrict__ part, double *red) {
-  double a = 0.0;
-  for (int i = threadIdx.x; i < CG_NB; i += 256) a += part[i];
-  const double t = block_sum(a, red);
-  __syncthreads();
-  return t;
-}
-
-// alpha = r.z / p.Ap (every work-group adds the p.Ap partials itself, in the
-// same order); phi += alpha p, r -= alpha Ap, z = r / diag (interior);
-// partial sums of r.r and r.z
-__global__ __launch_bounds__(256) void k_cg_update(int64_t n, const double *__restrict__ p,
-                                                   const double *__restrict__ Ap,
-                                                   const double *__restrict__ d,
-                                                   const double *__restrict__ minv,
-                                                   double *__restrict__ phi, double *__restrict__ r,
-                                                   double *__restrict__ z, double *__restrict__ part,
-                                                   const double *__restrict__ sc) {
-  __shared__ double red[256];
-  if (sc[4] != 0.0) return;
-  const double alpha = sc[0] / sum_parts(part, red);
-  double rr = 0.0, rz = 0.0;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    phi[i] += alpha * p[i];
-    const double ri = r[i] - alpha * Ap[i];
-    r[i] = ri;
-    const double zi = minv[i] == 0.0 ? 0.0 : ri / d[i];
-    z[i] = zi;
-    rr += ri * ri;
-    rz += ri * zi;
-  }
-  const double t1 = block_sum(rr, red);
-  __syncthreads();
-  const double t2 = block_sum(rz, red);
-  if (threadIdx.x == 0) {
-    part[CG_NB + blockIdx.x] = t1;
-    part[2 * CG_NB + blockIdx.x] = t2;
-  }
-}
-
-// end of an iteration: r.r and the new r.z from their partials, the
-// iteration count, the stopping test, beta, and r.z for the next iteration
-__global__ __launch_bounds__(256) void k_cg_next(const double *__restrict__ part,
-                                                 double *__restrict__ sc) {
-  __shared__ double red[256];
-  if (sc[4] != 0.0) return;
-  const double rr = sum_parts(part + CG_NB, red);
-  const double rz = sum_parts(part + 2 * CG_NB, red);
-  if (threadIdx.x == 0) {
-    sc[2] = rr;
-    sc[3] = rz;
-    sc[5] += 1.0;
-    if (rr <= sc[6]) sc[4] = 1.0;
-    sc[7] = rz / sc[0];
-    sc[0] = rz;
-  }
-}
-
-// p = z + beta p
-__global__ void k_cg_pupdate(int64_t n, const double *__restrict__ z, double *__restrict__ p,
-                             const double *__restrict__ sc) {
-  if (sc[4] != 0.0) return;
-  const double beta = sc[7];
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) p[i] = z[i] + beta * p[i];
 }
 
 // slot j <- slot j + 1 for j < m, element by element (each thread reads a
@@ -824,11 +873,8 @@ static efe_status scf_init(efe_ctx *c) {
     if ((st = efe_alloc(c, (void **)pp, nn * 8))) return st;
   if ((st = efe_alloc(c, (void **)&s.cg, 5 * nn * 8))) return st;
   if ((st = efe_alloc(c, (void **)&s.scal, 256 * 8))) return st;
-  if ((st = efe_alloc(c, (void **)&s.part, 3 * CG_NB * 8))) return st;
+  if ((st = efe_alloc(c, (void **)&s.part, 5 * CG_NP * 8))) return st;
   if ((st = efe_alloc(c, (void **)&s.ycell, (size_t)c->n_cells * c->nloc * 8))) return st;
-  const int64_t kt = (int64_t)c->RB * c->KS * 64;
-  if ((st = efe_alloc(c, (void **)&s.Ktile, kt * 8))) return st;
-  k_tile_K<<<cdiv(kt, 256), 256, 0, c->stream>>>(c->nloc, c->RB, c->KS, c->d_K, s.Ktile);
   HIPCHK(c, hipMemsetAsync(s.phi_rem, 0, nn * 8, c->stream));
   HIPCHK(c, hipMemsetAsync(s.Kdiag, 0, nn * 8, c->stream));
   HIPCHK(c, hipMemsetAsync(s.scal, 0, 256 * 8, c->stream));
@@ -887,33 +933,18 @@ static efe_status scf_init(efe_ctx *c) {
   return EFE_OK;
 }
 
-// y = (K + shift diag(m)) x on interior nodes (sc: CG scalars whose done
-// flag turns the launches into no-ops; part: also the per-work-group
-// partials of x.y)
-static efe_status stiff_apply(efe_ctx *c, const double *x, double *y, const double *sc = nullptr,
-                              double *part = nullptr, double shift = 0.0) {
-  ScfState &s = S(c);
-  const size_t shm = (size_t)STIFF_CELLS * (4 * c->KS + 1) * 8;
-  const dim3 grid((unsigned)cdiv(c->n_cells, STIFF_CELLS), (unsigned)cdiv(c->RB, 4));
-  k_stiff_apply_all<<<grid, 256, shm, c->stream>>>(c->n_cells, c->nloc, c->RB, c->KS, c->d_c2g,
-                                                   s.Ktile, x, c->d_minv, s.ycell,
-                                                   sc ? sc + 4 : nullptr);
-  const GridDims d{c->n1[0], c->n1[1], c->n1[2], c->ncell[0], c->ncell[1], c->ncell[2],
-                   c->p,     c->P,     c->nloc};
-  k_stiff_gather<<<CG_NB, 256, 0, c->stream>>>(d, s.ycell, c->d_minv, x, y, part,
-                                               sc ? sc + 4 : nullptr, shift, c->d_m_int);
+// K_c x of every cell into ycell, or one CG iteration's first half
+static efe_status stiff_cells(efe_ctx *c, const StiffArgs &a, int nwg) {
+  const unsigned g = (unsigned)nwg;
+  switch (c->P) {
+    case 2: k_stiff_cells<2><<<g, 256, 0, c->stream>>>(a); break;
+    case 3: k_stiff_cells<3><<<g, 256, 0, c->stream>>>(a); break;
+    case 4: k_stiff_cells<4><<<g, 256, 0, c->stream>>>(a); break;
+    case 5: k_stiff_cells<5><<<g, 256, 0, c->stream>>>(a); break;
+    case 6: k_stiff_cells<6><<<g, 256, 0, c->stream>>>(a); break;
+    default: k_stiff_cells<7><<<g, 256, 0, c->stream>>>(a); break;
+  }
   HIPCHK(c, hipGetLastError());
-  return EFE_OK;
-}
-
-static efe_status dot_host(efe_ctx *c, int64_t n, const double *a, const double *b, double *res) {
-  ScfState &s = S(c);
-  double *slot = s.scal + 64;
-  HIPCHK(c, hipMemsetAsync(slot, 0, 8, c->stream));
-  k_wdot<<<(unsigned)std::min<int64_t>(cdiv(n, 256), 1024), 256, 0, c->stream>>>(n, 1, nullptr, a,
-                                                                                b, slot);
-  HIPCHK(c, hipMemcpyAsync(res, slot, 8, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
   return EFE_OK;
 }
 
@@ -925,50 +956,55 @@ static efe_status cg_solve(efe_ctx *c, const double *fq, const double *sub, doub
                            int *iters) {
   ScfState &s = S(c);
   const int64_t nn = c->n_nodes;
-  double *r = s.cg, *z = s.cg + nn, *p = s.cg + 2 * nn, *Ap = s.cg + 3 * nn, *b = s.cg + 4 * nn;
+  double *r = s.cg, *z = s.cg + nn, *p0 = s.cg + 2 * nn, *p1 = s.cg + 3 * nn, *b = s.cg + 4 * nn;
   efe_status st;
-  const int T = 256;
-  HIPCHK(c, hipMemsetAsync(b, 0, nn * 8, c->stream));
+  HIPCHK(c, hipMemsetAsync(p0, 0, 3 * nn * 8, c->stream));   // both p, and b
   k_load_vector<<<c->n_cells, 256, 0, c->stream>>>(c->nloc, c->nqp, c->d_c2g, c->d_N3, c->d_W3, fq,
                                                    sub, c->d_minv, scale, b);
-  if ((st = stiff_apply(c, phi, Ap, nullptr, nullptr, shift))) return st;
-  k_sub<<<cdiv(nn, T), T, 0, c->stream>>>(nn, b, Ap, r);
-  k_precond<<<cdiv(nn, T), T, 0, c->stream>>>(nn, r, diag, c->d_minv, z);
-  HIPCHK(c, hipMemcpyAsync(p, z, nn * 8, hipMemcpyDeviceToDevice, c->stream));
-  double rz, bb, rr;
-  if ((st = dot_host(c, nn, r, z, &rz))) return st;
-  if ((st = dot_host(c, nn, b, b, &bb))) return st;
-  if ((st = dot_host(c, nn, r, r, &rr))) return st;
-  const double bn = sqrt(bb);
+  const GridDims d{(uint32_t)c->n1[0], (uint32_t)c->n1[1], (uint32_t)c->n1[2],
+                   c->ncell[0],        c->ncell[1],        c->ncell[2],
+                   c->p,               c->P,               c->nloc};
+  double *sc = s.scal + 96;
+  StiffArgs a{c->d_mk, phi,   nullptr, c->d_m_int,  nullptr,    s.ycell,     s.part, sc,
+              shift,   c->n_cells, c->n1[0], c->n1[1], c->ncell[0], c->ncell[1], -1};
+  const int nwg = (int)std::min<int64_t>(CG_NP, cdiv(c->n_cells, 256 / (c->P * c->P)));
+  const int nup = (int)std::min<int64_t>(CG_NP, cdiv(nn, 512));
+  // partial sums that no work-group writes count as zero
+  HIPCHK(c, hipMemsetAsync(s.part, 0, 5 * CG_NP * 8, c->stream));
+  if ((st = stiff_cells(c, a, nwg))) return st;
+  k_cg_init<<<nup, 256, 0, c->stream>>>(d, s.ycell, c->d_minv, c->d_m_int, shift, diag, b, phi, r, z,
+                                       s.part);
+  k_cg_check<<<1, 256, 0, c->stream>>>(s.part, 0, rtol, true, sc);
+  HIPCHK(c, hipMemsetAsync(s.part + 4 * CG_NP, 0, CG_NP * 8, c->stream));
+  // iterations in batches of 16 with the scalars on the device; the loop
+  // stops after the first iteration that meets sqrt(r.r) <= rtol |b|
+  double hs[4] = {0, 0, 0, 0};
   int it = 0;
-  if (bn == 0.0) {   // zero source: zero solution
+  a.z = z;
+  while (it < maxit) {
+    const int batch = std::min(16, maxit - it);
+    for (int q = 0; q < batch; ++q) {
+      a.it = it + q;
+      a.x = a.it & 1 ? p1 : p0;      // the previous p
+      a.p = a.it & 1 ? p0 : p1;
+      if ((st = stiff_cells(c, a, nwg))) return st;
+      k_cg_update<<<nup, 512, 0, c->stream>>>(d, s.ycell, c->d_minv, c->d_m_int, shift, diag, a.p,
+                                             phi, r, z, s.part, a.it, sc);
+    }
+    it += batch;
+    k_cg_check<<<1, 256, 0, c->stream>>>(s.part, it, rtol, false, sc);
+    HIPCHK(c, hipGetLastError());
+    HIPCHK(c, hipMemcpyAsync(hs, sc, 4 * 8, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (hs[0] != 0.0 || hs[3] == 0.0) break;
+  }
+  *iters = (int)hs[1];
+  if (hs[3] == 0.0) {   // zero source: zero solution
     HIPCHK(c, hipMemsetAsync(phi, 0, nn * 8, c->stream));
     *iters = 0;
     return EFE_OK;
   }
-  // iterations in batches of 16 with the scalars on the device; the loop
-  // stops after the first iteration that meets sqrt(r.r) <= rtol |b|
-  double *sc = s.scal + 96;
-  const double init[8] = {rz, 0.0, 0.0, 0.0, sqrt(rr) > rtol * bn ? 0.0 : 1.0, 0.0,
-                          (rtol * bn) * (rtol * bn), 0.0};   // read by the copy until the sync below
-  HIPCHK(c, hipMemcpyAsync(sc, init, sizeof(init), hipMemcpyHostToDevice, c->stream));
-  double hs[6] = {0, 0, 0, 0, 0, 0};
-  while (it < maxit) {
-    const int batch = std::min(16, maxit - it);
-    for (int q = 0; q < batch; ++q) {
-      if ((st = stiff_apply(c, p, Ap, sc, s.part, shift))) return st;   // Ap and the p.Ap partials
-      k_cg_update<<<CG_NB, T, 0, c->stream>>>(nn, p, Ap, diag, c->d_minv, phi, r, z, s.part, sc);
-      k_cg_next<<<1, T, 0, c->stream>>>(s.part, sc);
-      k_cg_pupdate<<<cdiv(nn, T), T, 0, c->stream>>>(nn, z, p, sc);
-    }
-    HIPCHK(c, hipGetLastError());
-    HIPCHK(c, hipMemcpyAsync(hs, sc, 6 * 8, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    it = (int)hs[5];
-    if (hs[4] != 0.0) break;
-  }
-  *iters = it;
-  if (hs[4] == 0.0) EFE_FAIL(c, EFE_ENOTCONV, "CG did not converge");
+  if (hs[0] == 0.0) EFE_FAIL(c, EFE_ENOTCONV, "CG did not converge");
   return EFE_OK;
 }
 

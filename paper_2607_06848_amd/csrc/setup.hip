@@ -783,7 +783,7 @@ efe_status efe_build_reference(efe_ctx *c) {
   c->KS = c->KP / 4;
   c->RB = (int)cdiv(c->nloc, 16);
   c->KS32 = (int)cdiv(c->nloc, 32);
-  return efe_tp_setup(c, xq, wq, N1, wg);
+  return efe_tp_setup(c, xq, wq, N1, D1, wg);
 }
 
 efe_status efe_build_enrichment(efe_ctx *c) {
