@@ -211,77 +211,226 @@ extern "C" efe_status efe_cheb_filter(efe_ctx *c, double *V, const double *lambd
 }
 
 // ------------------------------------------------------------------ Lanczos
-// out[0] = sum_r x_r y_r ; out[1] = x^T M~ x (CFE: m x^2, enrichment blocks)
-__global__ void k_dot(int64_t n, const double *__restrict__ x, const double *__restrict__ y,
-                      const double *__restrict__ w, double *__restrict__ out) {
-  __shared__ double red[256];
-  double acc = 0.0;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    acc += x[i] * y[i] * (w ? w[i] : 1.0);
-  red[threadIdx.x] = acc;
+// Vectors are rows long: CFE rows first, then the enrichment rows of every
+// atom.  The inner product is that of M~: m on CFE rows, the atom blocks of
+// M^ee on enrichment rows.  Work-groups 0 .. nbc - 1 take CFE rows, the others
+// atoms, 16 lanes each (one thread per atom left 50 us of dependent loads).
+// Dot products go through LZ_NP per-work-group partial sums, which every
+// work-group of the next kernel adds itself in the same order: no atomics, no
+// extra launches (one launch per dot product, 231 of them in 20 steps, took
+// 7.6 of the 64-atom bound's 16.9 ms).
+constexpr int LZ_NP = 512, LZ_T = 256;
+
+__device__ inline double lz_block_sum(double x, double *red) {
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+  if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = x;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+  const double s = (red[0] + red[1]) + (red[2] + red[3]);
+  __syncthreads();
+  return s;
+}
+
+// total of one row of partial sums (every thread gets it)
+__device__ inline double lz_total(const double *__restrict__ part, double *red) {
+  return lz_block_sum(part[threadIdx.x] + part[threadIdx.x + LZ_T], red);
+}
+
+struct LzArgs {
+  int64_t nn, n_enr;
+  int natoms, nf, nbc;
+  const double *m, *minv, *Mee, *inv;
+};
+
+// loop of a CFE work-group over its rows, and of an atom work-group over its
+// atoms: f(I, k) with k the lane's function (every lane of a group runs it)
+template <class F>
+__device__ inline void lz_rows(const LzArgs &a, F &&f) {
+  if ((int)blockIdx.x >= a.nbc) return;
+  for (int64_t i = blockIdx.x * (int64_t)LZ_T + threadIdx.x; i < a.nn; i += (int64_t)a.nbc * LZ_T)
+    f(i);
+}
+template <class F>
+__device__ inline void lz_atoms(const LzArgs &a, F &&f) {
+  if ((int)blockIdx.x < a.nbc) return;
+  const int per = LZ_T / 16, g = (int)blockIdx.x - a.nbc, ng = (int)gridDim.x - a.nbc;
+  for (int I = g * per + (int)threadIdx.x / 16; I < a.natoms; I += ng * per)
+    f(I, (int)threadIdx.x % 16);
+}
+// (M^ee_II x)_k from the lanes' x (zero in lanes k >= nf)
+__device__ inline double lz_block_row(const LzArgs &a, int I, int k, double x) {
+  double s = 0.0;
+  for (int l = 0; l < a.nf; ++l) {
+    const double xl = __shfl(x, l, 16);
+    if (k < a.nf) s += a.Mee[((int64_t)I * a.nf + k) * a.n_enr + (int64_t)I * a.nf + l] * xl;
   }
-  if (threadIdx.x == 0) atomicAdd(out, red[0]);
+  return s;
 }
 
-// sum over atoms of x_I^T Mee_II y_I
-__global__ void k_enr_block_dot(int natoms, int nf, int64_t n_enr, const double *__restrict__ Mee,
-                                const double *__restrict__ x, const double *__restrict__ y,
-                                double *__restrict__ out) {
-  const int I = blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= natoms) return;
-  double acc = 0.0;
-  for (int k = 0; k < nf; ++k)
-    for (int l = 0; l < nf; ++l)
-      acc += x[I * nf + k] * Mee[(int64_t)(I * nf + k) * n_enr + I * nf + l] * y[I * nf + l];
-  atomicAdd(out, acc);
+// y = x without its boundary rows; partial sums of y.M~ y
+__global__ __launch_bounds__(LZ_T) void k_lz_start(LzArgs a, const double *__restrict__ x,
+                                                   double *__restrict__ y,
+                                                   double *__restrict__ part) {
+  __shared__ double red[4];
+  double s = 0.0;
+  lz_rows(a, [&](int64_t i) {
+    const double v = a.minv[i] == 0.0 ? 0.0 : x[i];
+    y[i] = v;
+    s += a.m[i] * v * v;
+  });
+  lz_atoms(a, [&](int I, int k) {
+    const int64_t r = a.nn + (int64_t)I * a.nf + k;
+    const double v = k < a.nf ? x[r] : 0.0;
+    if (k < a.nf) y[r] = v;
+    s += v * lz_block_row(a, I, k, v);
+  });
+  const double t = lz_block_sum(s, red);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-// Lanczos vector update: w = u - alpha v - beta_prev v_prev; scalars on device
-// sc = [alpha_j, beta_j, beta_{j-1}, ...]: out = (u - a v - b vp)
-__global__ void k_lanczos_update(int64_t n, const double *__restrict__ u,
-                                 const double *__restrict__ v, const double *__restrict__ vp,
-                                 const double *__restrict__ alpha, const double *__restrict__ bprev,
-                                 double *__restrict__ w) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  w[i] = u[i] - (*alpha) * v[i] - (bprev ? *bprev : 0.0) * vp[i];
+// y = x / b with b = sqrt of the summed partials, which is kept in beta_out
+__global__ __launch_bounds__(LZ_T) void k_lz_scale(int64_t n, const double *__restrict__ part,
+                                                   const double *__restrict__ x,
+                                                   double *__restrict__ y,
+                                                   double *__restrict__ beta_out) {
+  __shared__ double red[4];
+  const double b = sqrt(lz_total(part, red));
+  if (blockIdx.x == 0 && threadIdx.x == 0 && beta_out) *beta_out = b;
+  for (int64_t i = blockIdx.x * (int64_t)LZ_T + threadIdx.x; i < n; i += (int64_t)gridDim.x * LZ_T)
+    y[i] = x[i] / b;
 }
 
-__global__ void k_mask_copy(int64_t n_nodes, int64_t rows, const double *__restrict__ minv,
-                            const double *__restrict__ x, double *__restrict__ y) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= rows) return;
-  y[i] = (i < n_nodes && minv[i] == 0.0) ? 0.0 : x[i];
+// partial sums of v.u
+__global__ __launch_bounds__(LZ_T) void k_lz_dot(int64_t n, const double *__restrict__ v,
+                                                 const double *__restrict__ u,
+                                                 double *__restrict__ part) {
+  __shared__ double red[4];
+  double s = 0.0;
+  for (int64_t i = blockIdx.x * (int64_t)LZ_T + threadIdx.x; i < n; i += (int64_t)gridDim.x * LZ_T)
+    s += v[i] * u[i];
+  const double t = lz_block_sum(s, red);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-__global__ void k_scale_by_inv_sqrt(int64_t n, const double *__restrict__ nrm2,
-                                    const double *__restrict__ x, double *__restrict__ y,
-                                    double *__restrict__ beta_out) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const double b = sqrt(*nrm2);
-  if (i == 0 && beta_out) *beta_out = b;
-  if (i < n) y[i] = x[i] / b;
+// w = M~^-1 u - alpha v_j - beta_{j-1} v_{j-1} (alpha from the partials, kept in
+// alpha_out) and the partial sums of v_i.M~ w for i = i0 .. i0 + LZ_G - 1 <= j;
+// write = false: w is there already
+constexpr int LZ_G = 8;
+__global__ __launch_bounds__(LZ_T) void k_lz_step(LzArgs a, int j, int i0, bool write,
+                                                  const double *__restrict__ Vb, int64_t ldv,
+                                                  const double *__restrict__ u,
+                                                  const double *__restrict__ apart,
+                                                  const double *__restrict__ beta,
+                                                  double *__restrict__ alpha_out, double *w,
+                                                  double *__restrict__ part) {
+  __shared__ double red[4];
+  const double al = write ? lz_total(apart, red) : 0.0;
+  if (write && blockIdx.x == 0 && threadIdx.x == 0) *alpha_out = al;
+  const double be = write && j > 0 ? *beta : 0.0;
+  const double *v = Vb + j * ldv, *vp = j > 0 ? v - ldv : v;
+  const int ng = min(LZ_G, j + 1 - i0);
+  double s[LZ_G];
+#pragma unroll
+  for (int g = 0; g < LZ_G; ++g) s[g] = 0.0;
+  lz_rows(a, [&](int64_t i) {
+    double wi;
+    if (write) {
+      wi = a.minv[i] * u[i] - al * v[i] - be * vp[i];
+      w[i] = wi;
+    } else {
+      wi = w[i];
+    }
+    const double mw = a.m[i] * wi;
+#pragma unroll
+    for (int g = 0; g < LZ_G; ++g)
+      if (g < ng) s[g] += Vb[(i0 + g) * ldv + i] * mw;
+  });
+  lz_atoms(a, [&](int I, int k) {
+    const int64_t r = a.nn + (int64_t)I * a.nf + k;
+    const bool on = k < a.nf;
+    double wi = 0.0;
+    if (write) {
+      const double uk = on ? u[r] : 0.0;
+      for (int l = 0; l < a.nf; ++l) {
+        const double ul = __shfl(uk, l, 16);
+        if (on) wi += a.inv[((int64_t)I * a.nf + k) * a.nf + l] * ul;
+      }
+      if (on) {
+        wi = wi - al * v[r] - be * vp[r];
+        w[r] = wi;
+      }
+    } else if (on) {
+      wi = w[r];
+    }
+    const double mw = lz_block_row(a, I, k, wi);
+#pragma unroll
+    for (int g = 0; g < LZ_G; ++g)
+      if (g < ng && on) s[g] += Vb[(i0 + g) * ldv + r] * mw;
+  });
+#pragma unroll
+  for (int g = 0; g < LZ_G; ++g) {
+    if (g >= ng) break;
+    const double t = lz_block_sum(s[g], red);
+    if (threadIdx.x == 0) part[(int64_t)(i0 + g) * LZ_NP + blockIdx.x] = t;
+  }
 }
 
-// theta_max of the k x k tridiagonal (alpha, beta) by Sturm bisection, plus |beta_k|
-__global__ void k_tridiag_bound(int k, const double *__restrict__ alpha,
-                                const double *__restrict__ beta, double *__restrict__ out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// w -= sum_{i <= j} c_i v_i (classical Gram-Schmidt against the Lanczos basis)
+// with c_i from the partials; partial sums of w.M~ w
+constexpr int LZ_MAXC = 1000;
+__global__ __launch_bounds__(LZ_T) void k_lz_reorth(LzArgs a, int j, const double *__restrict__ Vb,
+                                                    int64_t ldv, const double *__restrict__ cpart,
+                                                    double *w, double *__restrict__ part) {
+  __shared__ double red[4], c[LZ_MAXC];
+  // one wave per coefficient
+  for (int i = threadIdx.x / 64; i <= j; i += LZ_T / 64) {
+    double s = 0.0;
+    for (int q = threadIdx.x % 64; q < LZ_NP; q += 64) s += cpart[(int64_t)i * LZ_NP + q];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (threadIdx.x % 64 == 0) c[i] = s;
+  }
+  __syncthreads();
+  double s = 0.0;
+  lz_rows(a, [&](int64_t r) {
+    double acc = 0.0;
+#pragma unroll 4
+    for (int i = 0; i <= j; ++i) acc += c[i] * Vb[i * ldv + r];
+    const double wr = w[r] - acc;
+    w[r] = wr;
+    s += a.m[r] * wr * wr;
+  });
+  lz_atoms(a, [&](int I, int k) {
+    const int64_t r = a.nn + (int64_t)I * a.nf + k;
+    double wr = 0.0;
+    if (k < a.nf) {
+      double acc = 0.0;
+#pragma unroll 4
+      for (int i = 0; i <= j; ++i) acc += c[i] * Vb[i * ldv + r];
+      wr = w[r] - acc;
+      w[r] = wr;
+    }
+    s += wr * lz_block_row(a, I, k, wr);
+  });
+  const double t = lz_block_sum(s, red);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
+}
+
+// theta_max of the k x k tridiagonal (alpha, beta), plus |beta_k|: the smallest
+// double with every eigenvalue below it by Sturm counts, 64 probes at a time
+// (one wave; one probe at a time took 95 us)
+__global__ __launch_bounds__(64) void k_tridiag_bound(int k, const double *__restrict__ alpha,
+                                                      const double *__restrict__ beta,
+                                                      double *__restrict__ out) {
   double lo = 1e300, hi = -1e300;
   for (int i = 0; i < k; ++i) {
     double r = (i > 0 ? fabs(beta[i - 1]) : 0.0) + (i < k - 1 ? fabs(beta[i]) : 0.0);
     lo = fmin(lo, alpha[i] - r);
     hi = fmax(hi, alpha[i] + r);
   }
-  // number of eigenvalues below x
   for (int it = 0; it < 200; ++it) {
-    const double x = 0.5 * (lo + hi);
-    if (!(x > lo && x < hi)) break;
+    const double mid = 0.5 * (lo + hi);
+    if (!(mid > lo && mid < hi)) break;
+    // lane l probes lo + (l + 1)/65 (hi - lo), clamped between the ends
+    const double x = fmin(fmax(lo + (hi - lo) * ((threadIdx.x + 1) / 65.0), lo), hi);
     int cnt = 0;
     double d = 1.0;
     for (int i = 0; i < k; ++i) {
@@ -290,20 +439,27 @@ __global__ void k_tridiag_bound(int k, const double *__restrict__ alpha,
       if (d == 0.0) d = -1e-300;
       if (d < 0.0) ++cnt;
     }
-    if (cnt >= k) hi = x;   // all eigenvalues below x
-    else lo = x;
+    // lanes whose probe has every eigenvalue below it
+    const uint64_t above = __ballot(cnt >= k);
+    const int first = above ? __ffsll((unsigned long long)above) - 1 : 64;
+    const double nhi = first < 64 ? __shfl(x, first) : hi, nlo = first > 0 ? __shfl(x, first - 1) : lo;
+    if (nhi == hi && nlo == lo) {   // the probes fell on the ends: halve
+      double dm = 1.0;
+      int c = 0;
+      for (int i = 0; i < k; ++i) {
+        const double b2 = i > 0 ? beta[i - 1] * beta[i - 1] : 0.0;
+        dm = alpha[i] - mid - (i > 0 ? b2 / dm : 0.0);
+        if (dm == 0.0) dm = -1e-300;
+        if (dm < 0.0) ++c;
+      }
+      if (c >= k) hi = mid;
+      else lo = mid;
+      continue;
+    }
+    hi = nhi;
+    lo = nlo;
   }
-  out[0] = hi + fabs(beta[k - 1]);
-}
-
-// w -= sum_{i <= j} c_i V_i (classical Gram-Schmidt against the Lanczos basis)
-__global__ void k_reorth(int64_t n, int j, const double *__restrict__ V, int64_t ldv,
-                         const double *__restrict__ c, double *__restrict__ w) {
-  const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (r >= n) return;
-  double acc = 0.0;
-  for (int i = 0; i <= j; ++i) acc += c[i] * V[(int64_t)i * ldv + r];
-  w[r] -= acc;
+  if (threadIdx.x == 0) out[0] = hi + fabs(beta[k - 1]);
 }
 
 extern "C" efe_status efe_spectrum_upper_bound(efe_ctx *c, const double *v0, int32_t steps,
@@ -316,46 +472,35 @@ extern "C" efe_status efe_spectrum_upper_bound(efe_ctx *c, const double *v0, int
   double *buf, *sc;
   // the Lanczos basis V_0 .. V_{steps-1}, then u (= H v), w, x (= M~^-1 u)
   if ((s = efe_ws(c, 20, (size_t)rows * (steps + 3) * 8, (void **)&buf))) return s;
-  const size_t nsc = (size_t)steps * steps + 4 * (size_t)steps + 8;
+  const size_t npart = (size_t)(steps + 2) * LZ_NP, nsc = 2 * (size_t)steps + 8 + npart;
   if ((s = efe_ws(c, 21, nsc * 8, (void **)&sc))) return s;
   double *Vb = buf, *u = buf + (int64_t)steps * rows, *w = u + rows, *x = w + rows;
-  double *alpha = sc, *beta = sc + steps, *nrm = sc + 2 * steps;   // nrm: steps + 1 slots
-  double *coef = sc + 4 * steps + 8;                               // steps x steps
+  double *alpha = sc, *beta = sc + steps, *res = sc + 2 * steps;
+  double *part = sc + 2 * steps + 8;                 // one row: v.u, or norms
+  double *cpart = part + 2 * LZ_NP;                  // a row per basis vector
   HIPCHK(c, hipMemsetAsync(sc, 0, nsc * 8, c->stream));
-  const int T = 256;
-  const int nbk = (int)std::min<int64_t>(cdiv(rows, T), 1024);
-  // copy of v0 without its boundary rows
-  k_mask_copy<<<cdiv(rows, T), T, 0, c->stream>>>(nn, rows, c->d_minv, v0, u);
-  // inner product of the M~ norm: m x y on CFE rows + atom blocks
-  auto mdot = [&](const double *a, const double *b, double *out) -> efe_status {
-    k_dot<<<nbk, T, 0, c->stream>>>(nn, a, b, c->d_m_int, out);
-    if (ne) k_enr_block_dot<<<cdiv(c->natoms, 64), 64, 0, c->stream>>>(c->natoms, c->nf, ne, c->d_Mee,
-                                                                       a + nn, b + nn, out);
-    HIPCHK(c, hipGetLastError());
-    return EFE_OK;
-  };
-  if ((s = mdot(u, u, &nrm[steps]))) return s;
-  k_scale_by_inv_sqrt<<<cdiv(rows, T), T, 0, c->stream>>>(rows, &nrm[steps], u, Vb, nullptr);
+  const int nbe = ne ? (int)std::min<int64_t>(cdiv(c->natoms, LZ_T / 16), LZ_NP / 8) : 0;
+  const int nbc = (int)std::min<int64_t>(cdiv(nn, LZ_T), LZ_NP - LZ_NP / 8), nb = nbc + nbe;
+  const LzArgs a{nn,      ne,         ne ? c->natoms : 0, c->nf, nbc, c->d_m_int,
+                 c->d_minv, c->d_Mee, c->d_Mee_inv};
+  double *npart_ = part + LZ_NP;
+  k_lz_start<<<nb, LZ_T, 0, c->stream>>>(a, v0, u, npart_);
+  k_lz_scale<<<nb, LZ_T, 0, c->stream>>>(rows, npart_, u, Vb, nullptr);
   for (int j = 0; j < steps; ++j) {
     double *v = Vb + (int64_t)j * rows;
     if ((s = efe_apply_H_internal(c, v, 1, false, v + nn, 1, u, 1, 1, EFE_FP64))) return s;
-    // alpha_j = v^T H v
-    k_dot<<<nbk, T, 0, c->stream>>>(rows, v, u, nullptr, &alpha[j]);
-    if ((s = efe_apply_Minv_internal(c, u, 1, x, 1, 1))) return s;
-    k_lanczos_update<<<cdiv(rows, T), T, 0, c->stream>>>(
-        rows, x, v, j > 0 ? v - rows : v, &alpha[j], j > 0 ? &beta[j - 1] : nullptr, w);
-    // once more against the whole basis
-    double *cj = coef + (int64_t)j * steps;
-    for (int i = 0; i <= j; ++i)
-      if ((s = mdot(Vb + (int64_t)i * rows, w, &cj[i]))) return s;
-    k_reorth<<<cdiv(rows, T), T, 0, c->stream>>>(rows, j, Vb, rows, cj, w);
-    if ((s = mdot(w, w, &nrm[j]))) return s;
+    // alpha_j = v^T H v; w = M~^-1 H v - alpha v - beta v_prev and its products
+    // with the basis, once more against the whole basis, its norm
+    k_lz_dot<<<nb, LZ_T, 0, c->stream>>>(rows, v, u, part);
+    for (int i0 = 0; i0 <= j; i0 += LZ_G)
+      k_lz_step<<<nb, LZ_T, 0, c->stream>>>(a, j, i0, i0 == 0, Vb, rows, u, part,
+                                           j > 0 ? &beta[j - 1] : nullptr, &alpha[j], w, cpart);
+    k_lz_reorth<<<nb, LZ_T, 0, c->stream>>>(a, j, Vb, rows, cpart, w, npart_);
     // v_{j+1} = w / beta_j (the last one is not kept)
     double *vn = j + 1 < steps ? Vb + (int64_t)(j + 1) * rows : x;
-    k_scale_by_inv_sqrt<<<cdiv(rows, T), T, 0, c->stream>>>(rows, &nrm[j], w, vn, &beta[j]);
+    k_lz_scale<<<nb, LZ_T, 0, c->stream>>>(rows, npart_, w, vn, &beta[j]);
   }
-  double *res = sc + 4 * steps + 4;
-  k_tridiag_bound<<<1, 1, 0, c->stream>>>(steps, alpha, beta, res);
+  k_tridiag_bound<<<1, 64, 0, c->stream>>>(steps, alpha, beta, res);
   HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipMemcpyAsync(b_out, res, 8, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
