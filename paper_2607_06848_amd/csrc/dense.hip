@@ -435,50 +435,78 @@ __global__ void k_round_pairs(int nb, int *__restrict__ pairs) {
 
 // the 2 JB x 2 JB subproblem of pair k: eigenvectors into U[k] (row-major
 // 64 x 64), by cyclic Jacobi sweeps with a parallel (round-robin) ordering of
-// the 32 index pairs of each step
-__global__ __launch_bounds__(256) void k_jacobi_sub(int64_t np, const double *__restrict__ A,
-                                                    int64_t lda, const int *__restrict__ pairs,
-                                                    double *__restrict__ U, int max_sweeps,
-                                                    double thr) {
-  __shared__ double S[J2][J2 + 1], Q[J2][J2 + 1];
-  __shared__ double cs[J2 / 2], sn[J2 / 2];
-  __shared__ int ip[J2 / 2], jp[J2 / 2];
-  __shared__ double red[256];
+// the 32 index pairs of each step.  A chain of 63 dependent steps a sweep, so
+// what counts is the time of one step: 1,024 threads, two barriers, and LDS
+// traffic of S only.  S takes both sides of a step's rotations at once, one
+// 2 x 2 block a thread.  The rows of the eigenvectors stay in registers: lane g
+// of 16 holds the columns in pair slots 2 g and 2 g + 1 of its row, the slots'
+// contents move one place per step (circle method), which is a shift among 16
+// lanes, and a rotation only needs its slot's c and s.  (256 threads updating
+// rows of S, columns of S and Q in LDS took 1.2 us a step, N = 160: 613 us a
+// launch.)
+__device__ __forceinline__ double dpp_from_right(double v) {   // lane i gets lane i + 1 of its 16
+  const long long u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, 0x101, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), 0x101, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double dpp_from_left(double v) {    // lane i gets lane i - 1 of its 16
+  const long long u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, 0x111, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), 0x111, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// indices in slot t of step `step`: top (index 0 stays in slot 0) and bottom
+__device__ __forceinline__ int slot_top(int step, int t) {
+  const int x = step + t - 1;
+  return t == 0 ? 0 : 1 + (x >= J2 - 1 ? x - (J2 - 1) : x);
+}
+__device__ __forceinline__ int slot_bottom(int step, int t) {
+  const int x = step + (J2 - 2) - t;
+  return 1 + (x >= J2 - 1 ? x - (J2 - 1) : x);
+}
+
+__global__ __launch_bounds__(1024) void k_jacobi_sub(int64_t np, const double *__restrict__ A,
+                                                     int64_t lda, const int *__restrict__ pairs,
+                                                     double *__restrict__ U, int max_sweeps,
+                                                     double thr) {
+  static_assert(J2 == 64, "slots and lanes are laid out for 64 indices");
+  __shared__ double S[J2][J2 + 1];
+  __shared__ double cs[J2 / 2], sn[J2 / 2], ss[J2 / 2];
+  __shared__ double red[16];
   const int k = blockIdx.x, t = threadIdx.x;
   const int p = pairs[2 * k], q = pairs[2 * k + 1];
-  for (int e = t; e < J2 * J2; e += 256) {
+  for (int e = t; e < J2 * J2; e += 1024) {
     const int r = e / J2, cc = e % J2;
     const int64_t gr = r < JB ? (int64_t)p * JB + r : (int64_t)q * JB + r - JB;
     const int64_t gc = cc < JB ? (int64_t)p * JB + cc : (int64_t)q * JB + cc - JB;
     S[r][cc] = A[gr * lda + gc];
-    Q[r][cc] = r == cc ? 1.0 : 0.0;
   }
+  const int w1 = t / 32, w2 = t % 32;      // block of S
+  const int row = t / 16, g = t % 16;      // row and slot pairs of Q
+  double T0 = slot_top(0, 2 * g) == row, T1 = slot_top(0, 2 * g + 1) == row;
+  double B0 = slot_bottom(0, 2 * g) == row, B1 = slot_bottom(0, 2 * g + 1) == row;
   __syncthreads();
   for (int sw = 0; sw < max_sweeps; ++sw) {
     // off-diagonal size of S
     double off = 0.0;
-    for (int e = t; e < J2 * J2; e += 256) {
+    for (int e = t; e < J2 * J2; e += 1024) {
       const double v = S[e / J2][e % J2];
       if (e / J2 != e % J2) off += v * v;
     }
-    red[t] = off;
+    for (int o = 32; o > 0; o >>= 1) off += __shfl_xor(off, o);
+    if (t % 64 == 0) red[t / 64] = off;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (t < s) red[t] += red[t + s];
-      __syncthreads();
-    }
-    const double offs = red[0];
+    double offs = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) offs += red[i];
     __syncthreads();
     if (!(offs > thr)) break;
     for (int step = 0; step < J2 - 1; ++step) {
       if (t < J2 / 2) {
-        // round-robin pairing of 64 indices: index 0 fixed
-        const int m = J2 - 1;
-        int a = t == 0 ? 0 : 1 + (step + t - 1) % m;
-        int b = t == 0 ? 1 + (step + m - 1) % m : 1 + (step + m - t - 1) % m;
+        const int a = slot_top(step, t), b = slot_bottom(step, t);
         const int i = min(a, b), j = max(a, b);
-        ip[t] = i;
-        jp[t] = j;
         const double aij = S[i][j], aii = S[i][i], ajj = S[j][j];
         double c = 1.0, s = 0.0;
         if (aij != 0.0) {
@@ -489,84 +517,110 @@ __global__ __launch_bounds__(256) void k_jacobi_sub(int64_t np, const double *__
         }
         cs[t] = c;
         sn[t] = s;
+        ss[t] = a < b ? s : -s;            // for (top, bottom) in place of (i, j)
       }
       __syncthreads();
-      // rows i, j of S
-      for (int e = t; e < (J2 / 2) * J2; e += 256) {
-        const int w = e / J2, col = e % J2;
-        const int i = ip[w], j = jp[w];
-        const double c = cs[w], s = sn[w];
-        const double si = S[i][col], sj = S[j][col];
-        S[i][col] = c * si - s * sj;
-        S[j][col] = s * si + c * sj;
+      {
+        // rows, then columns, of the 2 x 2 block of pairs w1 and w2
+        const int a1 = slot_top(step, w1), b1 = slot_bottom(step, w1);
+        const int a2 = slot_top(step, w2), b2 = slot_bottom(step, w2);
+        const int i1 = min(a1, b1), j1 = max(a1, b1), i2 = min(a2, b2), j2 = max(a2, b2);
+        const double c1 = cs[w1], s1 = sn[w1], c2 = cs[w2], s2 = sn[w2];
+        const double ii = S[i1][i2], ij = S[i1][j2], ji = S[j1][i2], jj = S[j1][j2];
+        const double ri = c1 * ii - s1 * ji, rj = c1 * ij - s1 * jj;
+        const double qi = s1 * ii + c1 * ji, qj = s1 * ij + c1 * jj;
+        S[i1][i2] = c2 * ri - s2 * rj;
+        S[i1][j2] = s2 * ri + c2 * rj;
+        S[j1][i2] = c2 * qi - s2 * qj;
+        S[j1][j2] = s2 * qi + c2 * qj;
       }
-      __syncthreads();
-      // columns i, j of S and of Q
-      for (int e = t; e < (J2 / 2) * J2; e += 256) {
-        const int w = e / J2, row = e % J2;
-        const int i = ip[w], j = jp[w];
-        const double c = cs[w], s = sn[w];
-        const double si = S[row][i], sj = S[row][j];
-        S[row][i] = c * si - s * sj;
-        S[row][j] = s * si + c * sj;
-        const double qi = Q[row][i], qj = Q[row][j];
-        Q[row][i] = c * qi - s * qj;
-        Q[row][j] = s * qi + c * qj;
+      {
+        const double c0 = cs[2 * g], s0 = ss[2 * g], c1 = cs[2 * g + 1], s1 = ss[2 * g + 1];
+        const double t0 = c0 * T0 - s0 * B0, b0 = s0 * T0 + c0 * B0;
+        const double t1 = c1 * T1 - s1 * B1, b1 = s1 * T1 + c1 * B1;
+        const double right = dpp_from_right(t0), left = dpp_from_left(b1);
+        T0 = g == 0 ? t0 : t1;
+        B0 = g == 0 ? t1 : left;
+        T1 = g == 15 ? b1 : right;
+        B1 = b0;
       }
       __syncthreads();
     }
   }
-  for (int e = t; e < J2 * J2; e += 256) U[(int64_t)k * J2 * J2 + e] = Q[e / J2][e % J2];
+  // a whole number of sweeps: the slots are where they began
+  double *u = U + (int64_t)k * J2 * J2 + row * J2;
+  u[slot_top(0, 2 * g)] = T0;
+  u[slot_top(0, 2 * g + 1)] = T1;
+  u[slot_bottom(0, 2 * g)] = B0;
+  u[slot_bottom(0, 2 * g + 1)] = B1;
 }
 
-// B[rows of pair k] = U_k^T A[rows of pair k] (all columns): one work-group
-// per (pair, 64 columns), one thread per column, the 64 x 64 U_k in LDS
-__global__ __launch_bounds__(64) void k_jacobi_rows(int64_t np, const double *__restrict__ A,
-                                                    int64_t lda, const int *__restrict__ pairs,
-                                                    const double *__restrict__ U,
-                                                    double *__restrict__ B) {
-  __shared__ double Us[J2][J2 + 1];
+// B[rows of pair k] = U_k^T A[rows of pair k] on the matrix cores: one
+// work-group per (pair, 64 columns), one wave per 16 rows; operands come from
+// memory in the layout of v_mfma_f64_16x16x4
+__global__ __launch_bounds__(256) void k_jacobi_rows(const double *__restrict__ A, int64_t lda,
+                                                     const int *__restrict__ pairs,
+                                                     const double *__restrict__ U,
+                                                     double *__restrict__ B) {
   const int k = blockIdx.y;
   const int p = pairs[2 * k], q = pairs[2 * k + 1];
-  for (int e = threadIdx.x; e < J2 * J2; e += 64) Us[e / J2][e % J2] = U[(int64_t)k * J2 * J2 + e];
-  __syncthreads();
-  const int64_t col = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (col >= np) return;
-  double a[J2];
-  for (int r = 0; r < J2; ++r) {
-    const int64_t gr = r < JB ? (int64_t)p * JB + r : (int64_t)q * JB + r - JB;
-    a[r] = A[gr * lda + col];
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
+  const int64_t c0 = (int64_t)blockIdx.x * 64 + li;
+  const double *u = U + (int64_t)k * J2 * J2 + 16 * wave + li;
+  v4d_g acc[4];
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb) acc[cb] = (v4d_g){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int ks = 0; ks < J2 / 4; ++ks) {
+    const int m = 4 * ks + lk;
+    const int64_t gr = m < JB ? (int64_t)p * JB + m : (int64_t)q * JB + m - JB;
+    const double a = u[m * J2];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+      acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, A[gr * lda + c0 + 16 * cb], acc[cb], 0, 0, 0);
   }
-  for (int r = 0; r < J2; ++r) {
-    double s = 0.0;
-    for (int m = 0; m < J2; ++m) s += Us[m][r] * a[m];
-    const int64_t gr = r < JB ? (int64_t)p * JB + r : (int64_t)q * JB + r - JB;
-    B[gr * lda + col] = s;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int m = 16 * wave + 4 * v + lk;
+    const int64_t gr = m < JB ? (int64_t)p * JB + m : (int64_t)q * JB + m - JB;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) B[gr * lda + c0 + 16 * cb] = acc[cb][v];
   }
 }
 
-// X[:, cols of pair k] = B[:, cols of pair k] U_k, one thread per row
-__global__ __launch_bounds__(64) void k_jacobi_cols(int64_t nrows, const double *__restrict__ B,
-                                                    int64_t ldb, const int *__restrict__ pairs,
-                                                    const double *__restrict__ U,
-                                                    double *__restrict__ X, int64_t ldx) {
-  __shared__ double Us[J2][J2 + 1];
+// X[:, columns of pair k] = B[:, columns of pair k] U_k for (B0, X0), and for
+// (B1, X1) in the second layer of the grid: one work-group per (64 rows, pair)
+__global__ __launch_bounds__(256) void k_jacobi_cols(const double *__restrict__ B0,
+                                                     const double *__restrict__ B1, int64_t ld,
+                                                     const int *__restrict__ pairs,
+                                                     const double *__restrict__ U,
+                                                     double *__restrict__ X0,
+                                                     double *__restrict__ X1) {
   const int k = blockIdx.y;
   const int p = pairs[2 * k], q = pairs[2 * k + 1];
-  for (int e = threadIdx.x; e < J2 * J2; e += 64) Us[e / J2][e % J2] = U[(int64_t)k * J2 * J2 + e];
-  __syncthreads();
-  const int64_t row = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (row >= nrows) return;
-  double b[J2];
-  for (int cc = 0; cc < J2; ++cc) {
-    const int64_t gc = cc < JB ? (int64_t)p * JB + cc : (int64_t)q * JB + cc - JB;
-    b[cc] = B[row * ldb + gc];
+  const double *B = blockIdx.z ? B1 : B0;
+  double *X = blockIdx.z ? X1 : X0;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
+  const int64_t r0 = (int64_t)blockIdx.x * 64 + 16 * wave;
+  const double *u = U + (int64_t)k * J2 * J2 + li;
+  v4d_g acc[4];
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb) acc[cb] = (v4d_g){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int ks = 0; ks < J2 / 4; ++ks) {
+    const int m = 4 * ks + lk;
+    const int64_t gc = m < JB ? (int64_t)p * JB + m : (int64_t)q * JB + m - JB;
+    const double a = B[(r0 + li) * ld + gc];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+      acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, u[m * J2 + 16 * cb], acc[cb], 0, 0, 0);
   }
-  for (int cc = 0; cc < J2; ++cc) {
-    double s = 0.0;
-    for (int m = 0; m < J2; ++m) s += b[m] * Us[m][cc];
-    const int64_t gc = cc < JB ? (int64_t)p * JB + cc : (int64_t)q * JB + cc - JB;
-    X[row * ldx + gc] = s;
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb) {
+    const int m = 16 * cb + li;
+    const int64_t gc = m < JB ? (int64_t)p * JB + m : (int64_t)q * JB + m - JB;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) X[(r0 + 4 * v + lk) * ld + gc] = acc[cb][v];
   }
 }
 
@@ -647,7 +701,7 @@ static int jacobi_blocks(int64_t n) {
 
 size_t efe_syev_work(int64_t n) {
   const int64_t np = (int64_t)jacobi_blocks(n) * JB;
-  return (size_t)(3 * np * np + (np / J2) * J2 * J2 + 2);
+  return (size_t)(4 * np * np + (np / J2) * J2 * J2 + 2);
 }
 
 size_t efe_syev_iwork(int64_t n) {
@@ -666,7 +720,7 @@ efe_status efe_syev_jacobi(efe_ctx *c, int64_t n, const double *H, int64_t ldh, 
   const int nb = jacobi_blocks(n);
   const int64_t np = (int64_t)nb * JB;
   const int npair = nb / 2;
-  double *A = work, *B = A + np * np, *V = B + np * np, *U = V + np * np;
+  double *A = work, *B = A + np * np, *V = B + np * np, *Vn = V + np * np, *U = Vn + np * np;
   double *off = U + (int64_t)npair * J2 * J2;
   // a bound above every eigenvalue (Gershgorin through the Frobenius norm)
   HIPCHK(c, hipMemsetAsync(off, 0, 2 * 8, c->stream));
@@ -695,15 +749,12 @@ efe_status efe_syev_jacobi(efe_ctx *c, int64_t n, const double *H, int64_t ldh, 
     prev = h2[0];
     for (int r = 0; r < nb - 1; ++r) {
       const int *pr = iwork + (int64_t)r * 2 * npair;
-      k_jacobi_sub<<<npair, 256, 0, c->stream>>>(np, A, np, pr, U, 8, 1e-30 * hn2);
-      // B = U^T A on the paired rows (every row belongs to one pair)
-      k_jacobi_rows<<<dim3((unsigned)cdiv(np, 64), npair), 64, 0, c->stream>>>(np, A, np, pr, U, B);
-      // A = B U, V = V U on the paired columns
-      k_jacobi_cols<<<dim3((unsigned)cdiv(np, 64), npair), 64, 0, c->stream>>>(np, B, np, pr, U, A,
-                                                                              np);
-      k_jacobi_cols<<<dim3((unsigned)cdiv(np, 64), npair), 64, 0, c->stream>>>(np, V, np, pr, U, B,
-                                                                              np);
-      std::swap(V, B);
+      k_jacobi_sub<<<npair, 1024, 0, c->stream>>>(np, A, np, pr, U, 8, 1e-30 * hn2);
+      // B = U^T A on the paired rows (every row belongs to one pair), then
+      // A = B U and V = V U on the paired columns (np is a multiple of 64)
+      k_jacobi_rows<<<dim3((unsigned)(np / 64), npair), 256, 0, c->stream>>>(A, np, pr, U, B);
+      k_jacobi_cols<<<dim3((unsigned)(np / 64), npair, 2), 256, 0, c->stream>>>(B, V, np, pr, U, A, Vn);
+      std::swap(V, Vn);
     }
   }
   if (sweeps_out) *sweeps_out = sw;
