@@ -48,7 +48,6 @@ constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + MLP_H * MLP_IN, OFF_W2 = OFF_B1 + ML
               N_PARAMS = OFF_B4 + 1;
 constexpr double RHO_FLOOR = 1e-12;
 constexpr int TP = 64;      // points per work-group tile of the MLP kernels
-constexpr int WLD = 132;    // LDS row stride of the transposed weights (float4 aligned)
 }  // namespace
 
 __device__ inline double dist2_nofma(double x0, double x1, double x2, const double *a) {
@@ -135,193 +134,327 @@ __global__ __launch_bounds__(256) void k_descriptors(int64_t npts, const double 
 // ------------------------------------------------------------------ MLP
 __device__ inline float sigm(float z) { return 1.0f / (1.0f + __expf(-z)); }
 
-// Fused forward pass of a 64-point tile: activations stay in LDS (transposed,
-// [neuron][point]); each layer's W^T is staged in LDS; every thread owns 4
-// neurons x 8 points.  acts (optional) receives the pre-activations z1..z3.
-__global__ __launch_bounds__(256) void k_mlp_fwd(int64_t npts, const float *__restrict__ prm,
-                                                 const float *__restrict__ X,
-                                                 float *__restrict__ y, float *__restrict__ acts) {
-  extern __shared__ float sm[];
-  float *Wt = sm;                 // [128][WLD]
-  float *Ht = sm + MLP_H * WLD;   // [128][TP]
-  const int t = threadIdx.x;
-  const int64_t p0 = blockIdx.x * (int64_t)TP;
-  const int np = (int)min<int64_t>(TP, npts - p0);
-  for (int i = t; i < TP * MLP_IN; i += 256) {
-    const int p = i / MLP_IN, k = i % MLP_IN;
-    Ht[k * TP + p] = p < np ? X[p0 * MLP_IN + i] : 0.0f;
-  }
-  const int jg = t & 31, pg = t >> 5;
-  for (int l = 0; l < 3; ++l) {
-    const int K = l == 0 ? MLP_IN : MLP_H;
-    const float *W = prm + (l == 0 ? OFF_W1 : l == 1 ? OFF_W2 : OFF_W3);
-    const float *b = prm + (l == 0 ? OFF_B1 : l == 1 ? OFF_B2 : OFF_B3);
-    for (int i = t; i < MLP_H * K; i += 256) {
-      const int j = i / K, k = i % K;
-      Wt[k * WLD + j] = W[i];
-    }
-    __syncthreads();
-    float acc[8][4];
+// The layers run on v_mfma_f32_16x16x4 with neurons as rows and points as
+// columns, a wave per 16 neurons.  A wave's weights
+// stay in its registers for the whole launch and the work-groups loop over
+// 64-point tiles, so the only traffic is a tile's activations through LDS; the
+// scalar products this replaces ran at 20 TFLOP/s (forward) and staged 64 KB of
+// weights per tile and layer.  65,536 points: forward 68 us (before 241), the
+// backward layers 73, 68 and 20 us (329, 329 and 241), where the matrix cores
+// alone would take 32, 29, 29 and 4 us; the activations and their exponentials
+// are the rest.  v_mfma_f32_16x16x4 adds its four products one after the other
+// as fused multiply-adds, so sums taken in the order of k are those of a scalar
+// loop, bit for bit.  Two work-groups a CU (forward) need the weights in 128
+// registers; at 256 a group had the CU to itself and took 105 us.
+typedef float v4m __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4m mfma4(float a, float b, v4m c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// LDS row strides of [neuron][point] tiles.  Backward: 16 neurons x 4 points (a
+// gradient's operand) and, with the contraction index in the order kidx, 4
+// neurons x 16 points (the other operand) hit 64 different banks; forward: the
+// same for 4 consecutive neurons x 16 points.
+constexpr int BS = TP + 4, FS = TP + 16;
+__device__ __forceinline__ int kidx(int s, int lk) { return 16 * (s / 4) + 4 * lk + s % 4; }
+
+// A scalar base pointer: left alone, each of a loop's addresses becomes a running
+// 64-bit pointer in vector registers, which the weights need.
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T *uniform(T *p) {
+  auto *g = (__attribute__((address_space(1))) T *)p;
+  asm volatile("" : "+s"(g));
+  return g;
+}
+
+// Forward pass of 64-point tiles, one layer after the other.  acts (optional)
+// receives the pre-activations z1..z3.  Wave w holds the weights of neurons
+// 16 w ..; a layer's output replaces its input in LDS.
+template <int K>
+__device__ __forceinline__ void fwd_weights(const float *__restrict__ W, int n, int lk,
+                                            float (&w)[(K + 3) / 4]) {
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const float bj = b[4 * jg + jj];
-#pragma unroll
-      for (int p = 0; p < 8; ++p) acc[p][jj] = bj;
-    }
-    for (int k = 0; k < K; ++k) {
-      const float4 w = *(const float4 *)&Wt[k * WLD + 4 * jg];
-      const float4 ha = *(const float4 *)&Ht[k * TP + 8 * pg];
-      const float4 hb = *(const float4 *)&Ht[k * TP + 8 * pg + 4];
-      const float h[8] = {ha.x, ha.y, ha.z, ha.w, hb.x, hb.y, hb.z, hb.w};
-      const float wv[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int p = 0; p < 8; ++p)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) acc[p][jj] = fmaf(h[p], wv[jj], acc[p][jj]);
-    }
-    __syncthreads();
-    if (acts) {
-#pragma unroll
-      for (int p = 0; p < 8; ++p)
-        if (8 * pg + p < np)
-          *(float4 *)&acts[(int64_t)l * npts * MLP_H + (p0 + 8 * pg + p) * MLP_H + 4 * jg] =
-              make_float4(acc[p][0], acc[p][1], acc[p][2], acc[p][3]);
-    }
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      float s[8];
-#pragma unroll
-      for (int p = 0; p < 8; ++p) s[p] = acc[p][jj] * sigm(acc[p][jj]);
-      *(float4 *)&Ht[(4 * jg + jj) * TP + 8 * pg] = make_float4(s[0], s[1], s[2], s[3]);
-      *(float4 *)&Ht[(4 * jg + jj) * TP + 8 * pg + 4] = make_float4(s[4], s[5], s[6], s[7]);
-    }
-    __syncthreads();
-  }
-  if (t < np) {
-    float s = prm[OFF_B4];
-    for (int k = 0; k < MLP_H; ++k) s = fmaf(prm[OFF_W4 + k], Ht[k * TP + t], s);
-    y[p0 + t] = s;
+  for (int s = 0; s < (K + 3) / 4; ++s) {
+    const int k = 4 * s + lk;
+    const float x = W[n * K + min(k, K - 1)];
+    w[s] = k < K ? x : 0.0f;
   }
 }
 
-// Output layer backward: dz3 = dy W4 silu'(z3); gW4 += dy silu(z3), gb4 += dy.
-__global__ __launch_bounds__(256) void k_mlp_bwd_head(int64_t npts, const float *__restrict__ prm,
-                                                      const float *__restrict__ dy,
-                                                      const float *__restrict__ z3,
-                                                      float *__restrict__ dz3,
-                                                      float *__restrict__ grads) {
-  const int t = threadIdx.x, k = t & (MLP_H - 1), half = t >> 7;
-  const float w4 = prm[OFF_W4 + k];
-  float gw = 0.0f, gb = 0.0f;
-  for (int64_t p = blockIdx.x * 2 + half; p < npts; p += (int64_t)gridDim.x * 2) {
-    const float d = dy[p], z = z3[p * MLP_H + k];
-    const float s = sigm(z);
-    gw = fmaf(d, z * s, gw);
-    dz3[p * MLP_H + k] = d * w4 * (s * (1.0f + z * (1.0f - s)));
-    if (k == 0) gb += d;
+// the same for K = 128 from consecutive loads, transposed through the wave's part
+// of H (64 scattered loads took 10 us longer)
+__device__ __forceinline__ void fwd_weights_h(const float *__restrict__ W, float *H, int wave,
+                                              int li, int lk, float (&w)[MLP_H / 4]) {
+  float *A = H + wave * 16 * BS;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int r = 0; r < 16; r += 4)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        A[(r + lk) * BS + 4 * li + i] = W[(16 * wave + r + lk) * MLP_H + 64 * h + 4 * li + i];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 16; ++s) w[16 * h + s] = A[li * BS + 4 * s + lk];
+    __syncthreads();
   }
-  atomicAdd(&grads[OFF_W4 + k], gw);
-  if (k == 0) atomicAdd(&grads[OFF_B4], gb);
 }
 
-// Backward of one hidden layer z = W h + b over 64-point tiles (grid-stride):
-// gW += dz^T h and gb += sum dz accumulate in registers and are added to
-// grads once per work-group; for KIN = 128 also dz_prev = (dz W) silu'(z_prev).
-// hin is the standardized input X (KIN = 25) or z_prev (KIN = 128).
-template <int KIN>
-__global__ __launch_bounds__(256) void k_mlp_bwd_layer(int64_t npts, const float *__restrict__ prm,
-                                                       int offW, int offB,
-                                                       const float *__restrict__ dz,
-                                                       const float *__restrict__ hin,
-                                                       float *__restrict__ dzprev,
-                                                       float *__restrict__ grads) {
-  extern __shared__ float sm[];
-  constexpr bool PREV = KIN == MLP_H;
-  float *Ws = sm;                                // [128][128] row-major (PREV only)
-  float *Ds = sm + (PREV ? MLP_H * MLP_H : 0);   // [TP][128]
-  float *Hs = Ds + TP * MLP_H;                   // [TP][128], zero beyond KIN
-  const int t = threadIdx.x;
-  if (PREV)
-    for (int i = t; i < MLP_H * MLP_H; i += 256) Ws[i] = prm[offW + i];
-  const int jg = t >> 4, kg = t & 15;            // gW block: j 8jg.., k 8kg..
-  float gw[8][8];
+// z (neurons n0 + 4 lk + v, points 16 c + li) = W h + b, the products of a sum
+// in the order of k.  H is [neuron k][point] with row stride FS; SWZ: 16-point
+// blocks permuted by hcol, so that the rows 4 lk + v that a layer's output
+// stores together lie in different banks, as the rows 4 s + lk read here do.
+__device__ __forceinline__ int hcol(int c, int row4) { return 16 * (c ^ (row4 & 3)); }
+template <int K, bool SWZ>
+__device__ __forceinline__ void fwd_layer(const float (&w)[(K + 3) / 4], const float *b,
+                                          const float *H, int li, int lk, v4m (&z)[4]) {
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
+  for (int c = 0; c < 4; ++c) z[c] = *(const v4m *)b;
+  int o = lk * FS + li;
+  asm volatile("" : "+v"(o));   // row addresses formed here, not kept
 #pragma unroll
-    for (int c = 0; c < 8; ++c) gw[a][c] = 0.0f;
-  float gb = 0.0f;
+  for (int s = 0; s < (K + 3) / 4; ++s) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      z[c] = mfma4(w[s], H[o + 4 * s * FS + (SWZ ? hcol(c, s) : 16 * c)], z[c]);
+    // keeps the LDS reads near their use: hoisted, they push the weights to scratch
+    if (s % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+__global__ __launch_bounds__(512, 4) void k_mlp_fwd(int64_t npts, const float *__restrict__ prm,
+                                                    const float *__restrict__ X,
+                                                    float *__restrict__ y,
+                                                    float *__restrict__ acts) {
+  constexpr int KX = 32, NX = TP * KX / 512;   // padded inputs, those a thread brings
+  __shared__ float Hx[KX * FS];
+  __shared__ float H[MLP_H * FS];
+  __shared__ __align__(16) float bs[4][MLP_H];          // b1, b2, b3, w4
+  const int t = threadIdx.x, wave = t / 64, lane = t % 64, li = lane % 16, lk = lane / 16;
+  const int n0 = 16 * wave + 4 * lk;
+  float w1[7], w2[32], w3[32];
+  fwd_weights<MLP_IN>(prm + OFF_W1, 16 * wave + li, lk, w1);
+  fwd_weights_h(prm + OFF_W2, H, wave, li, lk, w2);
+  fwd_weights_h(prm + OFF_W3, H, wave, li, lk, w3);
+  if (t < MLP_H) {
+    bs[0][t] = prm[OFF_B1 + t];
+    bs[1][t] = prm[OFF_B2 + t];
+    bs[2][t] = prm[OFF_B3 + t];
+    bs[3][t] = prm[OFF_W4 + t];
+  }
   const int64_t ntiles = (npts + TP - 1) / TP;
+  float xr[NX];
+  auto load = [&](int64_t tile) {
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+      const int e = t + 512 * i;
+      auto *a = uniform(X + tile * TP * MLP_IN);
+      const int last = (int)min<int64_t>(TP, npts - tile * TP) - 1;
+      xr[i] = a[(unsigned)(min(e / KX, last) * MLP_IN + min(e % KX, MLP_IN - 1))];
+    }
+  };
+  load(min((int64_t)blockIdx.x, ntiles - 1));
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int64_t p0 = tile * TP;
     const int np = (int)min<int64_t>(TP, npts - p0);
-    __syncthreads();
-    for (int i = t; i < TP * MLP_H; i += 256) {
-      const int p = i >> 7, k = i & (MLP_H - 1);
-      Ds[i] = p < np ? dz[(p0 + p) * MLP_H + k] : 0.0f;
-      float h = 0.0f;
-      if (p < np && k < KIN) {
-        const float v = hin[(p0 + p) * KIN + k];
-        h = PREV ? v * sigm(v) : v;
-      }
-      Hs[i] = h;
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+      const int e = t + 512 * i, p = e / KX, k = e % KX;
+      Hx[k * FS + p] = p < np && k < MLP_IN ? xr[i] : 0.0f;
     }
     __syncthreads();
-    for (int p = 0; p < np; ++p) {
-      const float4 da = *(const float4 *)&Ds[p * MLP_H + 8 * jg];
-      const float4 db = *(const float4 *)&Ds[p * MLP_H + 8 * jg + 4];
-      const float4 ha = *(const float4 *)&Hs[p * MLP_H + 8 * kg];
-      const float4 hb = *(const float4 *)&Hs[p * MLP_H + 8 * kg + 4];
-      const float dv[8] = {da.x, da.y, da.z, da.w, db.x, db.y, db.z, db.w};
-      const float hv[8] = {ha.x, ha.y, ha.z, ha.w, hb.x, hb.y, hb.z, hb.w};
+    load(min(tile + (int64_t)gridDim.x, ntiles - 1));
+    v4m z[4];
+    auto finish = [&](int l) {
 #pragma unroll
-      for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) gw[a][c] = fmaf(dv[a], hv[c], gw[a][c]);
-    }
-    if (t < MLP_H)
-      for (int p = 0; p < np; ++p) gb += Ds[p * MLP_H + t];
-    if (PREV) {
-      const int pg = t >> 5, kq = t & 31;          // 8 points x 4 inputs
-      float acc[8][4];
-#pragma unroll
-      for (int p = 0; p < 8; ++p)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[p][c] = 0.0f;
-      for (int j = 0; j < MLP_H; ++j) {
-        const float4 w = *(const float4 *)&Ws[j * MLP_H + 4 * kq];
-        const float wv[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-          const float d = Ds[(8 * pg + p) * MLP_H + j];
-#pragma unroll
-          for (int c = 0; c < 4; ++c) acc[p][c] = fmaf(d, wv[c], acc[p][c]);
+      for (int c = 0; c < 4; ++c) {
+        const int p = 16 * c + li;
+        if (acts) {
+          auto *a = uniform(acts + ((int64_t)l * npts + p0 + 16 * c) * MLP_H);
+          if (p < np) *(__attribute__((address_space(1))) v4m *)&a[(unsigned)(li * MLP_H + n0)] = z[c];
         }
-      }
 #pragma unroll
-      for (int p = 0; p < 8; ++p) {
-        if (8 * pg + p < np) {
-          const int64_t o = (p0 + 8 * pg + p) * MLP_H + 4 * kq;
-          const float4 z = *(const float4 *)&hin[o];
-          const float zv[4] = {z.x, z.y, z.z, z.w};
-          float r[4];
+        for (int v = 0; v < 4; ++v) z[c][v] *= sigm(z[c][v]);
+        int o = n0 * FS + hcol(c, lk) + li;
+        asm volatile("" : "+v"(o));   // formed here, not kept
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const float s = sigm(zv[c]);
-            r[c] = acc[p][c] * (s * (1.0f + zv[c] * (1.0f - s)));
-          }
-          *(float4 *)&dzprev[o] = make_float4(r[0], r[1], r[2], r[3]);
-        }
+        for (int v = 0; v < 4; ++v) H[o + v * FS] = z[c][v];
+        __builtin_amdgcn_sched_barrier(0);
       }
+    };
+    fwd_layer<MLP_IN, false>(w1, &bs[0][n0], Hx, li, lk, z);
+    finish(0);
+    __syncthreads();
+    fwd_layer<MLP_H, true>(w2, &bs[1][n0], H, li, lk, z);
+    __syncthreads();
+    finish(1);
+    __syncthreads();
+    fwd_layer<MLP_H, true>(w3, &bs[2][n0], H, li, lk, z);
+    __syncthreads();
+    finish(2);
+    __syncthreads();
+    // output layer, a wave's 16 points: one row of a product
+    if (wave < TP / 16) {
+      v4m o = {prm[OFF_B4], 0.f, 0.f, 0.f};
+      const float on = li == 0 ? 1.0f : 0.0f;
+#pragma unroll 8
+      for (int s = 0; s < MLP_H / 4; ++s)
+        o = mfma4(on * bs[3][4 * s + lk], H[(4 * s + lk) * FS + hcol(wave, s) + li], o);
+      const int p = 16 * wave + li;
+      if (lk == 0 && p < np) y[p0 + p] = o[0];
     }
   }
+}
+
+// Backward of one hidden layer z = W h + b, h = silu(z_prev) (KIN = 128) or the
+// standardized input (KIN = 25), over 64-point tiles: gW += dz^T h and gb += sum
+// dz in registers, added to grads once per work-group; dz_prev = (dz W)
+// silu'(z_prev) for KIN = 128.  HEAD: dz = dy W4 silu'(z) is formed here from z
+// (the last layer's), with gW4 += dy silu(z) and gb4 += dy.  Eight waves, wave w
+// on neurons 16 w ..: their dz and h on the way into LDS, rows of gW, and rows of
+// dz_prev with W^T in registers.  A thread's tile values are those of its
+// dz_prev, so silu'(z_prev) never leaves its registers.  The tiles alternate
+// between two LDS buffers with one barrier a tile, so one wave's products run
+// beside another's activations, and the next tile's loads beside both.
+template <int KIN, bool HEAD>
+__global__ __launch_bounds__(512) void k_mlp_bwd_layer(int64_t npts, const float *__restrict__ prm,
+                                                       int offW, int offB,
+                                                       const float *__restrict__ dzin,
+                                                       const float *__restrict__ dy,
+                                                       const float *__restrict__ hin,
+                                                       float *__restrict__ dzprev,
+                                                       float *__restrict__ grads) {
+  constexpr bool PREV = KIN == MLP_H;
+  constexpr int KB = (KIN + 15) / 16;          // 16-column blocks of gW
+  constexpr int KE = PREV ? 0 : TP * 32 / 512; // inputs a thread brings
+  extern __shared__ float sm[];
+  constexpr int NB = (MLP_H + 16 * KB) * BS;   // dz [neuron][point], h [input][point]
+  const int t = threadIdx.x, wave = t / 64, lane = t % 64, li = lane % 16, lk = lane / 16;
+  const int n0 = 16 * wave + 4 * lk;           // this thread's neurons, at points 16 c + li
+  float wt[PREV ? 32 : 1];                     // W^T: rows 16 wave + li, columns kidx
+  if constexpr (PREV)
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
+    for (int s = 0; s < 32; ++s) wt[s] = prm[offW + kidx(s, lk) * MLP_H + 16 * wave + li];
+  v4m gw[KB];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int k = 8 * kg + c;
-      if (k < KIN) atomicAdd(&grads[offW + (8 * jg + a) * KIN + k], gw[a][c]);
+  for (int c = 0; c < KB; ++c) gw[c] = (v4m){0.f, 0.f, 0.f, 0.f};
+  v4m gb = {0.f, 0.f, 0.f, 0.f}, g4 = gb, w4 = gb;
+  float gb4 = 0.0f;
+  if constexpr (HEAD)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) w4[v] = prm[OFF_W4 + n0 + v];
+  v4m dr[4], hr[PREV ? 4 : 1];
+  float yr[HEAD ? 4 : 1], xr[PREV ? 1 : KE];
+  const int64_t ntiles = (npts + TP - 1) / TP;
+  auto load = [&](int64_t tile) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int64_t p = min(tile * TP + 16 * c + li, npts - 1);
+      dr[c] = *(const v4m *)&dzin[p * MLP_H + n0];
+      if constexpr (HEAD) yr[c] = dy[p];
+      if constexpr (PREV) hr[c] = *(const v4m *)&hin[p * MLP_H + n0];
     }
-  if (t < MLP_H) atomicAdd(&grads[offB + t], gb);
+#pragma unroll
+    for (int i = 0; i < KE; ++i) {
+      const int e = t + 512 * i;
+      xr[i] = hin[min(tile * TP + e / 32, npts - 1) * KIN + min(e % 32, KIN - 1)];
+    }
+  };
+  load(blockIdx.x);
+  int par = 0;
+  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x, par ^= 1) {
+    const int64_t p0 = tile * TP;
+    const int np = (int)min<int64_t>(TP, npts - p0);
+    float *D = sm + par * NB, *H = D + MLP_H * BS;
+    v4m sp[PREV ? 4 : 1];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int p = 16 * c + li;
+      const bool on = p < np;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float d = on ? dr[c][v] : 0.0f;
+        if constexpr (HEAD) {
+          const float s = sigm(d), u = on ? yr[c] : 0.0f;
+          g4[v] = fmaf(u, d * s, g4[v]);
+          d = u * w4[v] * (s * (1.0f + d * (1.0f - s)));
+        }
+        gb[v] += d;
+        D[(n0 + v) * BS + p] = d;
+        if constexpr (PREV) {
+          const float z = on ? hr[c][v] : 0.0f, s = sigm(z);
+          H[(n0 + v) * BS + p] = z * s;
+          sp[c][v] = s * (1.0f + z * (1.0f - s));
+        }
+      }
+      if constexpr (HEAD) gb4 += on ? yr[c] : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < KE; ++i) {
+      const int e = t + 512 * i, p = e / 32, k = e % 32;
+      H[k * BS + p] = p < np && k < KIN ? xr[i] : 0.0f;
+    }
+    __syncthreads();
+    load(min(tile + (int64_t)gridDim.x, ntiles - 1));
+    if constexpr (PREV) {
+      v4m acc[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = (v4m){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 32; ++s)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          acc[c] = mfma4(wt[s], D[kidx(s, lk) * BS + 16 * c + li], acc[c]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int p = 16 * c + li;
+        if (p < np) *(v4m *)&dzprev[(p0 + p) * MLP_H + n0] = acc[c] * sp[c];
+      }
+    }
+    // gW rows 16 wave .., columns 16 c ..: the sum over the points
+#pragma unroll 4
+    for (int s = 0; s < TP / 4; ++s) {
+      const float a = D[(16 * wave + li) * BS + 4 * s + lk];
+#pragma unroll
+      for (int c = 0; c < KB; ++c) gw[c] = mfma4(a, H[(16 * c + li) * BS + 4 * s + lk], gw[c]);
+    }
+  }
+  __syncthreads();
+  // through LDS, so that a wave's atomics hit consecutive addresses and the
+  // work-groups, which end together, start at different ones
+#pragma unroll
+  for (int c = 0; c < KB; ++c)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int k = 16 * c + li;
+      if (k < KIN) sm[(n0 + v) * KIN + k] = gw[c][v];
+    }
+  float *ge = sm + MLP_H * KIN;
+#pragma unroll
+  for (int o = 1; o < 16; o *= 2) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      gb[v] += __shfl_xor(gb[v], o);
+      if (HEAD) g4[v] += __shfl_xor(g4[v], o);
+    }
+    if (HEAD) gb4 += __shfl_xor(gb4, o);
+  }
+  if (li == 0)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      ge[n0 + v] = gb[v];
+      if (HEAD) ge[MLP_H + n0 + v] = g4[v];
+    }
+  if (HEAD && t == 0) ge[2 * MLP_H] = gb4;
+  __syncthreads();
+  constexpr int NW = MLP_H * KIN;
+  int i = (int)((int64_t)blockIdx.x * NW / gridDim.x) + t;
+  for (int e = t; e < NW; e += 512, i += 512) {
+    if (i >= NW) i -= NW;
+    atomicAdd(&grads[offW + i], sm[i]);
+  }
+  if (t < MLP_H) atomicAdd(&grads[offB + t], ge[t]);
+  if (HEAD && t <= MLP_H) atomicAdd(&grads[OFF_W4 + t], ge[MLP_H + t]);   // b4 follows W4
 }
 
 // sums[0] += sum w, sums[1] += sum w (y - t)^2 (FP64)
@@ -437,29 +570,26 @@ efe_status gfail(efe_status code, const std::string &msg) {
       return gfail(EFE_EHIP, std::string(#call) + " failed: " + hipGetErrorString(e_)); \
   } while (0)
 
-constexpr size_t FWD_LDS = (size_t)(MLP_H * WLD + MLP_H * TP) * sizeof(float);
-constexpr size_t BWD_LDS_128 = (size_t)(MLP_H * MLP_H + 2 * TP * MLP_H) * sizeof(float);
-constexpr size_t BWD_LDS_25 = (size_t)(2 * TP * MLP_H) * sizeof(float);
+constexpr size_t BWD_LDS_128 = 2 * (size_t)(2 * MLP_H * BS) * sizeof(float);
+constexpr size_t BWD_LDS_25 = 2 * (size_t)((MLP_H + 32) * BS) * sizeof(float);
 
 efe_status lds_attrs() {
   static bool done = false;
   if (done) return EFE_OK;
-  GCHK(hipFuncSetAttribute((const void *)k_mlp_fwd, hipFuncAttributeMaxDynamicSharedMemorySize,
-                           (int)FWD_LDS));
-  GCHK(hipFuncSetAttribute((const void *)k_mlp_bwd_layer<MLP_H>,
-                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)BWD_LDS_128));
-  GCHK(hipFuncSetAttribute((const void *)k_mlp_bwd_layer<MLP_IN>,
-                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)BWD_LDS_25));
+  const void *big[] = {(const void *)k_mlp_bwd_layer<MLP_H, true>,
+                       (const void *)k_mlp_bwd_layer<MLP_H, false>,
+                       (const void *)k_mlp_bwd_layer<MLP_IN, false>};
+  for (const void *f : big)
+    GCHK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BWD_LDS_128));
   done = true;
   return EFE_OK;
 }
 
 efe_status mlp_forward(hipStream_t s, const float *prm, const float *feat, int64_t npts, float *out,
                        float *acts) {
-  efe_status st;
-  if ((st = lds_attrs())) return st;
   if (npts == 0) return EFE_OK;
-  k_mlp_fwd<<<cdiv(npts, TP), 256, FWD_LDS, s>>>(npts, prm, feat, out, acts);
+  // two work-groups a CU
+  k_mlp_fwd<<<(int)std::min<int64_t>(cdiv(npts, TP), 512), 512, 0, s>>>(npts, prm, feat, out, acts);
   GCHK(hipGetLastError());
   return EFE_OK;
 }
@@ -511,13 +641,13 @@ extern "C" efe_status efe_mlp_backward(void *stream, const float *params, const 
   const float *z1 = acts, *z2 = acts + zs, *z3 = acts + 2 * zs;
   float *A = work, *B = work + zs;
   k_fill_f32<<<cdiv(N_PARAMS, 256), 256, 0, s>>>(N_PARAMS, grads, 0.0f);
-  const int gh = (int)std::min<int64_t>(cdiv(npts, 2), 512);
-  k_mlp_bwd_head<<<gh, 256, 0, s>>>(npts, params, dout, z3, A, grads);
   const int gl = (int)std::min<int64_t>(cdiv(npts, TP), 256);
-  k_mlp_bwd_layer<MLP_H><<<gl, 256, BWD_LDS_128, s>>>(npts, params, OFF_W3, OFF_B3, A, z2, B, grads);
-  k_mlp_bwd_layer<MLP_H><<<gl, 256, BWD_LDS_128, s>>>(npts, params, OFF_W2, OFF_B2, B, z1, A, grads);
-  k_mlp_bwd_layer<MLP_IN><<<gl, 256, BWD_LDS_25, s>>>(npts, params, OFF_W1, OFF_B1, A, feat, nullptr,
-                                                      grads);
+  k_mlp_bwd_layer<MLP_H, true><<<gl, 512, BWD_LDS_128, s>>>(npts, params, OFF_W3, OFF_B3, z3, dout,
+                                                           z2, A, grads);
+  k_mlp_bwd_layer<MLP_H, false><<<gl, 512, BWD_LDS_128, s>>>(npts, params, OFF_W2, OFF_B2, A, nullptr,
+                                                            z1, B, grads);
+  k_mlp_bwd_layer<MLP_IN, false><<<gl, 512, BWD_LDS_25, s>>>(npts, params, OFF_W1, OFF_B1, B, nullptr,
+                                                            feat, nullptr, grads);
   GCHK(hipGetLastError());
   return EFE_OK;
 }
