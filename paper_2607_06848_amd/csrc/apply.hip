@@ -647,6 +647,61 @@ void k_box_gather(GatherArgs<T> a) {
   }
 }
 
+// The same where k_box_gather has too few work-groups to hide its chain of
+// chunks (FEW_GROUPS): one work-group per 16-row block and 16 columns, one wave
+// per 64 nodes (a brick) with all its operands requested at once, straight from
+// memory; the eight sums meet in LDS in a fixed order.  27 boxes and 8 vectors:
+// 7.1 us, 15.7 in chunks; 64 boxes with 1 and 37 vectors 8.3 us on average, 20.8
+// and 32 in chunks.
+template <typename T>
+__global__ __launch_bounds__(512) void k_box_gather_few(GatherArgs<T> a) {
+  typedef CellMfma<T> M;
+  typedef typename M::acc_t acc_t;
+  constexpr int NB = EFE_BOX * EFE_BOX * EFE_BOX, KS = NB / 4, KW = KS / 8;
+  __shared__ double red[8][256];
+  const int box = a.items[2 * (blockIdx.x / 4)], r = a.items[2 * (blockIdx.x / 4) + 1] + (int)(blockIdx.x % 4);
+  const int ne = a.E.rboff[box + 1] - a.E.rboff[box], nk = a.K.rboff[box + 1] - a.K.rboff[box];
+  if (r >= ne + (sizeof(T) == 8 ? nk : 0)) return;
+  const bool isE = r < ne;
+  const int64_t rb = isE ? a.E.rboff[box] + r : a.K.rboff[box] + r - ne;
+  const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t / 64), lane = t % 64;
+  const int li = lane % 16, lk = lane / 16;
+  const int c0 = (int)blockIdx.y * 16, col = min(c0 + li, a.ncols - 1);
+  const uint32_t live = (isE ? a.E.live[rb] : a.K.live[rb]) >> (4 * wave) & 15;
+  acc_t acc = (acc_t){0, 0, 0, 0};
+  if (live) {
+    const T *tp = (isE ? a.E.tile : (const T *)a.K.tile) + (rb * KS + wave * KW) * 64 + lane;
+    int o[3], ijk[3];
+    box_origin(a.g, EFE_BOX, box, o);
+    T av[KW];
+    double x[KW], m[KW];
+#pragma unroll
+    for (int s = 0; s < KW; ++s) {
+      const bool in = box_node(a.g, EFE_BOX, o, 4 * (KW * wave + s) + lk, ijk);
+      const int32_t node = in ? ijk[0] + a.g.n1[0] * (ijk[1] + a.g.n1[1] * ijk[2]) : 0;
+      av[s] = tp[s * 64];
+      x[s] = a.X[(int64_t)node * a.ldx + col];
+      const double w = a.scaled ? a.minv[node] : 1.0;
+      m[s] = in ? w : 0.0;
+    }
+#pragma unroll
+    for (int s = 0; s < KW; ++s)
+      if (live >> (s / 4) & 1)
+        acc = M::op(av[s], m[s] != 0.0 ? (T)(m[s] * x[s]) : (T)0, acc);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[wave][M::row(v, lk) * 16 + li] = (double)acc[v];
+  __syncthreads();
+  if (t >= 256 || c0 + t % 16 >= a.ncols) return;
+  const int nf = isE ? a.E.nf : 1, f = 16 * (isE ? r : r - ne) + t / 16;
+  const int32_t *ptr = isE ? a.E.ptr : a.K.ptr;
+  if (f >= (ptr[box + 1] - ptr[box]) * nf) return;
+  double s = 0.0;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) s += red[w][t];
+  a.Yp[((isE ? 0 : a.prow) + (int64_t)ptr[box] * nf + f) * a.ldp + c0 + t % 16] = s;
+}
+
 // Coefficients of one apply, interleaved atom by atom: rows (I, k) of Q, k <
 // nf the enrichment rows of the vectors (times the atom's block of
 // (M~^ee)^-1 when inv is given), k = nf (with projectors) P^C_I s X^C; R = E s
@@ -863,7 +918,11 @@ __device__ __forceinline__ void brick_product(const T *tp, int K, const int32_t 
   }
 }
 
-template <typename T, int CBM>
+// FEW (one column block): what the nodes add to the products is requested
+// first, all of it at once, instead of cell after cell behind the products (17^3
+// nodes and 8 vectors: 9.4 us, before 15.0).  With bricks enough to cover those
+// waits the registers cost more (0.91 M nodes, one vector: 203 us against 175).
+template <typename T, int CBM, bool FEW = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 void k_node_update(NodeArgs<T> a) {
   __shared__ __align__(16) double Xs[2 * 256 * CBM];
@@ -876,6 +935,33 @@ void k_node_update(NodeArgs<T> a) {
   const double *const Qc = a.Q + c0;
   const int t = threadIdx.x, wave = t / 64, lane = t % 64, li = lane % 16, lk = lane / 16;
   const NodeGrid &g = a.g;
+  double pre[FEW ? 4 : 1][9];
+  if constexpr (FEW) {
+    static_assert(CBM == 1, "the wide tiles read their terms in pairs");
+    int o[3];
+    box_origin(g, EFE_BRICK, b, o);
+    const int gi = o[0] + lk, gk = o[2] + wave;
+    const int cx = gi / g.p, cz = gk / g.p, lx = gi - cx * g.p, lz = gk - cz * g.p;
+    const bool inxz = gi > 0 && gi < g.n1[0] - 1 && gk > 0 && gk < g.n1[2] - 1;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int gj = o[1] + v, cy = gj / g.p, ly = gj - cy * g.p;
+#pragma unroll
+      for (int n = 0; n < 9; ++n) pre[v][n] = 0.0;
+      if (!inxz || gj <= 0 || gj >= g.n1[1] - 1 || li >= ncols) continue;
+      if (a.Yc)
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+          const int x = n & 1, y = n >> 1 & 1, z = n >> 2;
+          if ((x && lx) || (y && ly) || (z && lz)) continue;
+          const int64_t cell = cx - x + g.nc[0] * (cy - y + (int64_t)g.nc[1] * (cz - z));
+          const int l = (x ? g.p : lx) + g.P * ((y ? g.p : ly) + g.P * (z ? g.p : lz));
+          pre[v][n] = a.Yc[(cell * (g.P * g.P * g.P) + l) * a.ldc + c0 + li];
+        }
+      const int64_t row = ((int64_t)gi + (int64_t)g.n1[0] * (gj + (int64_t)g.n1[1] * gk)) * a.ldy + c0;
+      pre[v][8] = epi_terms(a.e, row + li, c0 + li);
+    }
+  }
   v4d acc[CBM];
 #pragma unroll
   for (int cb = 0; cb < CBM; ++cb) acc[cb] = (v4d){0.0, 0.0, 0.0, 0.0};
@@ -923,7 +1009,13 @@ void k_node_update(NodeArgs<T> a) {
     const int64_t row = ((int64_t)gi + (int64_t)g.n1[0] * (gj + (int64_t)g.n1[1] * gk)) * a.ldy + c0;
     const bool inner = gi > 0 && gi < g.n1[0] - 1 && gj > 0 && gj < g.n1[1] - 1 && gk > 0 &&
                        gk < g.n1[2] - 1;
-    if constexpr (CBM == 1) {
+    if constexpr (FEW) {
+      if (li >= ncols) continue;
+      double s = acc[0][v];   // the cells in the order of their numbers
+#pragma unroll
+      for (int n = 7; n >= 0; --n) s += pre[v][n];
+      a.Y[row + li] = inner ? e.alpha * s + pre[v][8] : 0.0;
+    } else if constexpr (CBM == 1) {
       if (li >= ncols) continue;
       double s = acc[0][v];
       if (a.Yc && inner) {
@@ -1081,9 +1173,19 @@ static int tile_blocks(int ncols) {
   return n == 1 ? 1 : (n + 1) / 2 * 2;
 }
 
+// Few work-groups (small meshes) leave the chip waiting on one chain of loads
+// each; 16-column parts make more of them, with shorter chains, and the blocks
+// that the parts read again are in the caches.  FEW_GROUPS is two work-groups a
+// CU.
+constexpr int64_t FEW_GROUPS = 512;
+
 template <typename T>
 static void launch_box_gather(efe_ctx *c, const GatherArgs<T> &a, int64_t n) {
   if (n == 0) return;
+  if (n < FEW_GROUPS) {
+    k_box_gather_few<T><<<dim3(4 * n, cdiv(a.ncols, 16)), 512, 0, c->stream>>>(a);
+    return;
+  }
 #define GO(B) k_box_gather<T, B><<<n, 256, 0, c->stream>>>(a)
   switch (tile_blocks(a.ncols)) {
     case 1: GO(1); break;
@@ -1103,9 +1205,14 @@ static void launch_node_update(efe_ctx *c, NodeArgs<T> a, const T *tile) {
   // 64-column parts: their 95 registers leave five waves a SIMD to cover the
   // reads (64 atoms, 160 vectors: 1.61 ms, against 1.71 in 32-column parts, 1.9
   // in one 160-column part with two waves)
-  const int B = std::min(tile_blocks(a.ncols), 4);
+  const bool few = c->cpl_e.n_brick * cdiv(a.ncols, 64) < 2 * FEW_GROUPS;
+  const int B = few ? 1 : std::min(tile_blocks(a.ncols), 4);
   a.nparts = (int)cdiv(a.ncols, 16 * B);
   const int64_t n = c->cpl_e.n_brick * a.nparts;
+  if (few) {
+    k_node_update<T, 1, true><<<n, 256, 0, c->stream>>>(a);
+    return;
+  }
 #define GO(B) k_node_update<T, B><<<n, 256, 0, c->stream>>>(a)
   switch (B) {
     case 1: GO(1); break;
