@@ -22,9 +22,7 @@
 namespace {
 constexpr int BK = EFE_BRICK, BX = EFE_BOX;   // edges of a brick and of a box, in nodes
 
-// Sum over the (up to eight) cells of an interior node that form a pair with
-// atom I of val(pair, local node), x fastest; first: stop at the first pair
-// whose value exists (assembled quantities).
+// (atom, cell) -> pair
 struct PairMap {
   const int32_t *box, *map;   // per atom: x0 y0 z0 nx ny nz and the place of its table
   const int64_t *off;
@@ -35,17 +33,6 @@ __device__ inline int pair_of(const PairMap &m, int I, int cx, int cy, int cz) {
   const int x = cx - b[0], y = cy - b[1], z = cz - b[2];
   if (x < 0 || y < 0 || z < 0 || x >= b[3] || y >= b[4] || z >= b[5]) return -1;
   return m.map[m.off[I] + x + b[3] * (y + (int64_t)b[4] * z)];
-}
-
-template <class F>
-__device__ inline void over_cells(const NodeGrid &g, const int ijk[3], F &&f) {
-  const int cx = ijk[0] / g.p, cy = ijk[1] / g.p, cz = ijk[2] / g.p;
-  const int lx = ijk[0] - cx * g.p, ly = ijk[1] - cy * g.p, lz = ijk[2] - cz * g.p;
-  for (int z = lz == 0 ? -1 : 0; z <= 0; ++z)
-    for (int y = ly == 0 ? -1 : 0; y <= 0; ++y)
-      for (int x = lx == 0 ? -1 : 0; x <= 0; ++x)
-        f(cx + x, cy + y, cz + z,
-          (x ? g.p : lx) + g.P * ((y ? g.p : ly) + g.P * (z ? g.p : lz)));
 }
 
 // What the blocks hold: E (epair: E_c per coupling pair), E + B (bam too) or
@@ -59,24 +46,85 @@ struct Entries {
   const int32_t *lmap;    // [pair][local node] -> support node
 };
 
-__device__ inline double entry(const Entries &s, int I, int k, const int ijk[3]) {
-  double v = 0.0, b = 0.0;
-  bool have = s.bam == nullptr;
-  over_cells(s.g, ijk, [&](int cx, int cy, int cz, int l) {
-    const int pr = pair_of(s.m, I, cx, cy, cz);
-    if (pr < 0) return;
-    const int64_t o = (int64_t)pr * s.nloc + l;
-    if (s.epair) v += s.epair[o * s.nf + k];
-    if (!have) {
-      const int32_t sn = s.lmap[o];
-      if (sn >= 0) {
-        b = s.bam[(int64_t)sn * s.nf + k];
-        have = true;
-      }
-    }
-  });
-  return v + b;
+// The pairs that a box of edge e can meet, atom by atom, in LDS: nc^3 cells from
+// the one before the box's first node.  Reading box, table and pair behind each
+// other for every entry instead made the three builds of E for 64 atoms take 5.2
+// ms (now 2.1).
+__host__ __device__ constexpr int box_cells(int e, int p) { return (e - 1 + p - 1) / p + 2; }
+
+__device__ __forceinline__ void box_pairs(const Entries &s, const int32_t *atom, int na,
+                                          const int o[3], int nc, int32_t *tab) {
+  const int n3 = nc * nc * nc;
+  for (int i = threadIdx.x; i < na * n3; i += blockDim.x) {
+    const int c = i % n3;
+    tab[i] = pair_of(s.m, atom[i / n3], o[0] / s.g.p - 1 + c % nc, o[1] / s.g.p - 1 + c / nc % nc,
+                     o[2] / s.g.p - 1 + c / (nc * nc));
+  }
 }
+
+// The (up to eight) cells of a node: place in an atom's part of the table (-1:
+// not a cell of the node) and the node's number there.  The cells come in the
+// order of their numbers from n = 7 down.
+struct NodeCells {
+  int at[8], l[8];
+  __device__ __forceinline__ NodeCells(const NodeGrid &g, const int o[3], const int ijk[3], int nc,
+                                       bool in) {
+    int cd[3], ld[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int c = ijk[d] / g.p;
+      ld[d] = ijk[d] - c * g.p;
+      cd[d] = c - (o[d] / g.p - 1);
+    }
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      const int x = n & 1, y = n >> 1 & 1, z = n >> 2;
+      const bool on = in && !(x && ld[0]) && !(y && ld[1]) && !(z && ld[2]);
+      at[n] = on ? cd[0] - x + nc * (cd[1] - y + nc * (cd[2] - z)) : -1;
+      l[n] = (x ? g.p : ld[0]) + g.P * ((y ? g.p : ld[1]) + g.P * (z ? g.p : ld[2]));
+    }
+  }
+};
+
+// An entry in two parts, so that several are on their way at once: request()
+// the per-cell values (and the support node), then value()
+struct EntryLoad {
+  double e[8], b;
+  int32_t sn;
+  __device__ __forceinline__ void request(const Entries &s, const NodeCells &c, const int32_t *tab,
+                                          int k) {
+    int64_t o[8];
+    int32_t q[8];
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      const int pr = c.at[n] >= 0 ? tab[c.at[n]] : -1;
+      o[n] = pr >= 0 ? (int64_t)pr * s.nloc + c.l[n] : -1;
+      e[n] = 0.0;
+      q[n] = -1;
+    }
+    if (s.epair)
+#pragma unroll
+      for (int n = 0; n < 8; ++n)
+        if (o[n] >= 0) e[n] = s.epair[o[n] * s.nf + k];
+    sn = -1;
+    if (s.bam) {
+#pragma unroll
+      for (int n = 0; n < 8; ++n)
+        if (o[n] >= 0) q[n] = s.lmap[o[n]];
+#pragma unroll
+      for (int n = 0; n < 8; ++n) sn = q[n] >= 0 ? q[n] : sn;
+    }
+  }
+  __device__ __forceinline__ void request_support(const Entries &s, int k) {
+    b = sn >= 0 ? s.bam[(int64_t)sn * s.nf + k] : 0.0;
+  }
+  __device__ __forceinline__ double value() const {
+    double v = 0.0;
+#pragma unroll
+    for (int n = 7; n >= 0; --n) v += e[n];
+    return v + b;
+  }
+};
 
 // Bricks: tile[rb][ks][lane] = entry(function 4 ks + lane/16, node 16 rb + row
 // of the lane), the A operand of v_mfma_*_16x16x4.  The FP32 copy has rows
@@ -92,16 +140,40 @@ __global__ __launch_bounds__(256) void k_tiles_brick(Entries s, const int32_t *_
   if (na == 0) return;
   const int K = na * s.nf, KS = (K + 3) / 4;
   const int rb = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
+  const int nc = box_cells(BK, s.g.p), n3 = nc * nc * nc;
+  extern __shared__ int32_t tab[];   // 16 atoms
   int o[3], ijk[3];
   box_origin(s.g, BK, b, o);
   const bool in = box_node(s.g, BK, o, 16 * rb + li, ijk);
+  const NodeCells cells(s.g, o, ijk, nc, in);
   const int64_t base = 256 * off[b] + (int64_t)rb * KS * 64;
   const int lp = 16 * lk + 4 * (li % 4) + li / 4;
-  for (int ks = 0; ks < KS; ++ks) {
-    const int f = 4 * ks + lk;
-    const double v = in && f < K ? entry(s, atom[a0 + f / s.nf], f % s.nf, ijk) : 0.0;
-    T64[base + (int64_t)ks * 64 + lane] = v;
-    if (T32) T32[base + (int64_t)ks * 64 + lp] = (float)v;
+  constexpr int U = 2;
+  for (int q0 = 0; q0 < na; q0 += 16) {
+    const int nq = min(16, na - q0), f0 = q0 * s.nf, ks1 = min(KS, (f0 + 16 * s.nf) / 4);
+    __syncthreads();
+    box_pairs(s, atom + a0 + q0, nq, o, nc, tab);
+    __syncthreads();
+    for (int ks = f0 / 4; ks < ks1; ks += U) {
+      EntryLoad v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int f = min(4 * (ks + u) + lk, f0 + nq * s.nf - 1) - f0;
+        v[u].request(s, cells, tab + f / s.nf * n3, f % s.nf);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int f = min(4 * (ks + u) + lk, f0 + nq * s.nf - 1) - f0;
+        v[u].request_support(s, f % s.nf);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (ks + u >= ks1) continue;
+        const double x = 4 * (ks + u) + lk < K ? v[u].value() : 0.0;
+        T64[base + (int64_t)(ks + u) * 64 + lane] = x;
+        if (T32) T32[base + (int64_t)(ks + u) * 64 + lp] = (float)x;
+      }
+    }
   }
 }
 
@@ -115,24 +187,37 @@ __global__ __launch_bounds__(256) void k_tiles_box(Entries s, const int32_t *__r
                                                    float *__restrict__ T32,
                                                    uint32_t *__restrict__ live) {
   __shared__ uint32_t mask;
-  if (threadIdx.x == 0) mask = 0;
-  __syncthreads();
+  extern __shared__ int32_t tab[];   // the atoms of 16 functions
   const int64_t row = blockIdx.x;
   const int b = rbbox[row], rb = (int)row - rboff[b];
-  const int a0 = ptr[b], K = (ptr[b + 1] - a0) * s.nf;
+  const int a0 = ptr[b], na = ptr[b + 1] - a0, K = na * s.nf;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
-  const int f = 16 * rb + li;
-  const int I = f < K ? atom[a0 + f / s.nf] : 0, k = f % s.nf;
+  const int f = 16 * rb + li, q0 = 16 * rb / s.nf, k = f % s.nf;
+  const int nc = box_cells(BX, s.g.p), n3 = nc * nc * nc;
   int o[3], ijk[3];
   box_origin(s.g, BX, b, o);
-  constexpr int KS = BX * BX * BX / 4;
-  for (int ks = wave; ks < KS; ks += 4) {
-    const bool in = box_node(s.g, BX, o, 4 * ks + lk, ijk);
-    const double v = in && f < K ? entry(s, I, k, ijk) : 0.0;
-    const int64_t at = (row * KS + ks) * 64 + lane;
-    T64[at] = v;
-    if (T32) T32[at] = (float)v;
-    if (__ballot(v != 0.0) && lane == 0) atomicOr(&mask, 1u << (ks / 4));
+  if (threadIdx.x == 0) mask = 0;
+  box_pairs(s, atom + a0 + q0, min((16 * rb + 15) / s.nf + 1, na) - q0, o, nc, tab);
+  __syncthreads();
+  const int32_t *const ft = tab + (f / s.nf - q0) * n3;
+  constexpr int KS = BX * BX * BX / 4, U = 2;
+  for (int ks = wave; ks < KS; ks += 4 * U) {
+    EntryLoad v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = box_node(s.g, BX, o, 4 * (ks + 4 * u) + lk, ijk);
+      v[u].request(s, NodeCells(s.g, o, ijk, nc, in && f < K), ft, k);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u].request_support(s, k);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double x = v[u].value();
+      const int64_t at = (row * KS + ks + 4 * u) * 64 + lane;
+      T64[at] = x;
+      if (T32) T32[at] = (float)x;
+      if (__ballot(x != 0.0) && lane == 0) atomicOr(&mask, 1u << ((ks + 4 * u) / 4));
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) live[row] = mask;
@@ -142,43 +227,81 @@ __global__ __launch_bounds__(256) void k_tiles_box(Entries s, const int32_t *__r
 // H^E_ee = H^phiphi - C B^T - E C^T: the symmetric part of H^phiphi - (B + E)
 // C^T (H^phiphi - C B^T - E C^T is symmetric), as products of the box blocks
 // of B + E with C.  One work-group takes a box and 16 functions of C (its
-// nodes x 16 in LDS as the B operand), each wave every fourth row block; the
-// 16 x 16 results are added into Hee atomically.
+// nodes x 16 in LDS as the B operand), each wave every fourth row block, and
+// only the chunks of 16 nodes in which both have entries; the 16 x 16 results
+// are added into Hee atomically (64 atoms: 2.6 ms; 4.2 with all chunks; 32
+// functions a work-group read B + E half as often but leave one work-group a CU,
+// whose fill of C nothing covers, 3.1).
 typedef double v4d_c __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void k_hee_box(Entries s, const int32_t *__restrict__ ptr,
                                                  const int32_t *__restrict__ atom,
                                                  const int32_t *__restrict__ rboff,
                                                  const int32_t *__restrict__ rbbox,
                                                  const double *__restrict__ T,
+                                                 const uint32_t *__restrict__ live,
                                                  const double *__restrict__ C_am, int64_t n_enr,
                                                  double *__restrict__ Hee) {
-  constexpr int NB = BX * BX * BX, KS = NB / 4;
+  constexpr int NB = BX * BX * BX, KS = NB / 4, U = 2;
   __shared__ double Cs[NB][16];
+  __shared__ uint32_t cmask;
+  extern __shared__ int32_t tab[];
   const int64_t row = blockIdx.x;
   const int b = rbbox[row], cb = (int)row - rboff[b], nrb = rboff[b + 1] - rboff[b];
-  const int a0 = ptr[b], K = (ptr[b + 1] - a0) * s.nf;
+  const int a0 = ptr[b], na = ptr[b + 1] - a0, K = na * s.nf, q0 = 16 * cb / s.nf;
+  const int nc = box_cells(BX, s.g.p), n3 = nc * nc * nc;
   int o[3];
   box_origin(s.g, BX, b, o);
   Entries c = s;
   c.epair = nullptr;
   c.bam = C_am;
-  for (int i = threadIdx.x; i < NB * 16; i += 256) {
-    const int f = 16 * cb + i % 16;
-    int ijk[3];
-    const bool in = box_node(s.g, BX, o, i / 16, ijk);
-    Cs[i / 16][i % 16] = in && f < K ? entry(c, atom[a0 + f / s.nf], f % s.nf, ijk) : 0.0;
-  }
+  if (threadIdx.x == 0) cmask = 0;
+  box_pairs(s, atom + a0 + q0, min((16 * cb + 15) / s.nf + 1, na) - q0, o, nc, tab);
   __syncthreads();
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
   const int f2 = 16 * cb + li;
+  const int32_t *const ft = tab + (f2 / s.nf - q0) * n3;
+  for (int ks = wave; ks < KS; ks += 4 * U) {
+    EntryLoad v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      int ijk[3];
+      const bool in = box_node(s.g, BX, o, 4 * (ks + 4 * u) + lk, ijk);
+      v[u].request(c, NodeCells(s.g, o, ijk, nc, in && f2 < K), ft, f2 % s.nf);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u].request_support(c, f2 % s.nf);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double x = v[u].value();
+      Cs[4 * (ks + 4 * u) + lk][li] = x;
+      if (__ballot(x != 0.0) && lane == 0) atomicOr(&cmask, 1u << ((ks + 4 * u) / 4));
+    }
+  }
+  __syncthreads();
+  const uint32_t cm = __builtin_amdgcn_readfirstlane(cmask);
   const int64_t g2 = f2 < K ? (int64_t)atom[a0 + f2 / s.nf] * s.nf + f2 % s.nf : 0;
-  for (int rb = wave; rb < nrb; rb += 4) {
+  for (int rb = __builtin_amdgcn_readfirstlane(wave); rb < nrb; rb += 4) {
+    uint32_t left = live[rboff[b] + rb] & cm;
+    if (left == 0) continue;
     const double *tp = T + ((int64_t)(rboff[b] + rb) * KS) * 64 + lane;
     v4d_c acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
-    for (int ks = 0; ks < KS; ++ks)
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tp[(int64_t)ks * 64], Cs[4 * ks + lk][li], acc, 0,
-                                                 0, 0);
+    double a[4], nx[4];
+    int ch = __builtin_ctz(left);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = tp[(4 * ch + i) * 64];
+    while (true) {
+      left &= left - 1;
+      const int n = left ? __builtin_ctz(left) : ch;   // the last one requests itself again
+#pragma unroll
+      for (int i = 0; i < 4; ++i) nx[i] = tp[(4 * n + i) * 64];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], Cs[4 * (4 * ch + i) + lk][li], acc, 0, 0, 0);
+      if (!left) break;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = nx[i];
+      ch = n;
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int f1 = 16 * rb + 4 * v + lk;
@@ -332,6 +455,15 @@ Entries entries(const efe_ctx *c, const CoupleSet &S, const double *epair, const
                 const int32_t *lmap) {
   return {node_grid(c), {S.d_box, S.d_map, S.d_off}, S.nf, c->nloc, epair, bam, lmap};
 }
+// LDS of the pair tables: 16 atoms of a brick, the atoms of 16 functions of a box
+size_t brick_lds(const efe_ctx *c) {
+  const int n = box_cells(BK, c->p);
+  return 16 * (size_t)(n * n * n) * 4;
+}
+size_t box_lds(const efe_ctx *c, int nf) {
+  const int n = box_cells(BX, c->p);
+  return std::min(16, 14 / nf + 2) * (size_t)(n * n * n) * 4;
+}
 }  // namespace
 
 // Work items of the box products: four consecutive 16-row blocks of a box, E
@@ -371,9 +503,9 @@ efe_status efe_couple_projectors(efe_ctx *c) {
   CoupleSet &K = c->cpl_k;
   if (!c->nproj || K.n_boxpairs == 0) return EFE_OK;
   const Entries e = entries(c, K, nullptr, c->d_Pc_am, c->d_kbpair_lmap);
-  k_tiles_brick<<<K.n_brick, 256, 0, c->stream>>>(e, K.d_bk_ptr, K.d_bk_atom, K.d_bk_off, K.d_T1,
+  k_tiles_brick<<<K.n_brick, 256, brick_lds(c), c->stream>>>(e, K.d_bk_ptr, K.d_bk_atom, K.d_bk_off, K.d_T1,
                                                  nullptr);
-  k_tiles_box<<<K.n_rb, 256, 0, c->stream>>>(e, K.d_bx_ptr, K.d_bx_atom, K.d_rboff, K.d_rbbox,
+  k_tiles_box<<<K.n_rb, 256, box_lds(c, 1), c->stream>>>(e, K.d_bx_ptr, K.d_bx_atom, K.d_rboff, K.d_rbbox,
                                             K.d_T2, nullptr, K.d_live);
   HIPCHK(c, hipGetLastError());
   return EFE_OK;
@@ -396,14 +528,16 @@ efe_status efe_couple_build(efe_ctx *c, bool want32) {
     if (want32 && !E.d_T2f && (s = efe_alloc(c, (void **)&E.d_T2f, E.box_tile * 4))) return s;
     // B + E first, for H^E_ee, then E over it
     const Entries both = entries(c, E, c->d_Epair, c->d_B_am, c->d_cpair_lmap);
-    k_tiles_box<<<E.n_rb, 256, 0, c->stream>>>(both, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
+    k_tiles_box<<<E.n_rb, 256, box_lds(c, c->nf), c->stream>>>(both, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
                                               E.d_T2, nullptr, E.d_live);
-    k_hee_box<<<E.n_rb, 256, 0, c->stream>>>(both, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
-                                            E.d_T2, c->d_C_am, ne, c->d_Hee);
+    HIPCHK(c, hipFuncSetAttribute((const void *)k_hee_box, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)box_lds(c, c->nf)));
+    k_hee_box<<<E.n_rb, 256, box_lds(c, c->nf), c->stream>>>(both, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
+                                            E.d_T2, E.d_live, c->d_C_am, ne, c->d_Hee);
     const Entries e = entries(c, E, c->d_Epair, nullptr, c->d_cpair_lmap);
-    k_tiles_box<<<E.n_rb, 256, 0, c->stream>>>(e, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
+    k_tiles_box<<<E.n_rb, 256, box_lds(c, c->nf), c->stream>>>(e, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
                                               E.d_T2, want32 ? E.d_T2f : nullptr, E.d_live);
-    k_tiles_brick<<<E.n_brick, 256, 0, c->stream>>>(e, E.d_bk_ptr, E.d_bk_atom, E.d_bk_off, E.d_T1,
+    k_tiles_brick<<<E.n_brick, 256, brick_lds(c), c->stream>>>(e, E.d_bk_ptr, E.d_bk_atom, E.d_bk_off, E.d_T1,
                                                    want32 ? E.d_T1f : nullptr);
     if ((s = efe_symmetrize(c, ne, c->d_Hee))) return s;
   }
