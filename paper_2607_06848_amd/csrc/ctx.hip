@@ -447,6 +447,22 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
     if (c->nf > 0) build_triples(c, E, E, trip);
     c->ntrip = (int64_t)trip.size() / 3;
     TRY(upload(c, &c->d_trip, trip));
+    // (first triple, atoms, block, block) of every cell: a cell's triples are
+    // its atoms squared, and blocks hold up to EFE_PPV_F functions (k_enr_ppv)
+    std::vector<int32_t> ppv;
+    for (int64_t t0 = 0, t1; t0 < c->ntrip; t0 = t1) {
+      for (t1 = t0; t1 < c->ntrip && trip[3 * t1] == trip[3 * t0];) ++t1;
+      int n = 1;
+      while ((int64_t)n * n < t1 - t0) ++n;
+      const int nblk = (int)cdiv(n, EFE_PPV_F / c->nf);
+      for (int a = 0; a < nblk; ++a)
+        for (int b = a; b < nblk; ++b) {
+          const int32_t it[4] = {(int32_t)t0, n, a, b};
+          ppv.insert(ppv.end(), it, it + 4);
+        }
+    }
+    c->n_ppv = (int64_t)ppv.size() / 4;
+    TRY(upload(c, &c->d_ppv, ppv));
 
     c->nkbpairs = (int64_t)K.cells.size();
     c->n_kbnodes = (int64_t)K.snode.size();
@@ -534,7 +550,7 @@ extern "C" void efe_destroy(efe_ctx *c) {
                   c->d_pair_cell, c->d_pair_lmap,    c->d_snode_ptr,  c->d_snode,
                   c->d_nu,        c->d_b_am,         c->d_C_am,       c->d_Bkin_am,
                   c->d_B_am,      c->d_nm_ptr,       c->d_nm_atom,    c->d_nm_src,
-                  c->d_trip,      c->d_Mpp,
+                  c->d_trip,      c->d_ppv,        c->d_Mpp,
                   c->d_Mee,       c->d_Hpp_kin,      c->d_Hpp,        c->d_Mee_inv,
                   c->d_kbpair_atom, c->d_kbpair_cell, c->d_kbpair_lmap, c->d_kbnode_ptr,
                   c->d_kbnode,    c->d_Pc_am,        c->d_kbtrip,     c->d_Pphi,

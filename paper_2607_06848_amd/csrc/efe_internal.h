@@ -13,6 +13,7 @@
 #include "../../include/efe.h"
 
 #define EFE_MAXP 6
+#define EFE_PPV_F 96   // functions of a block of atoms in H^phiphi
 #define EFE_MAXQ 7
 #define EFE_MAXLOC ((EFE_MAXP + 1) * (EFE_MAXP + 1) * (EFE_MAXP + 1))
 // enrichment functions that may couple to one cell (padded to 16): 85 atoms
@@ -138,6 +139,8 @@ struct efe_ctx {
   // (cell, I, J) triples of atoms sharing a support cell
   int64_t ntrip = 0;
   int32_t *d_trip = nullptr;
+  int64_t n_ppv = 0;
+  int32_t *d_ppv = nullptr;        // work items over the triples of a cell
   double *d_Mpp = nullptr, *d_Mee = nullptr, *d_Hpp_kin = nullptr, *d_Hpp = nullptr;
   double *d_Mee_inv = nullptr;                         // [natoms][nf][nf]
   double amplification = 1.0;                          // efe_enrichment_amplification
