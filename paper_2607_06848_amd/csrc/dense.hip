@@ -510,10 +510,20 @@ __global__ __launch_bounds__(1024) void k_jacobi_sub(int64_t np, const double *_
         const double aij = S[i][j], aii = S[i][i], ajj = S[j][j];
         double c = 1.0, s = 0.0;
         if (aij != 0.0) {
-          const double tau = (ajj - aii) / (2.0 * aij);
-          const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-          c = 1.0 / sqrt(1.0 + tt * tt);
-          s = tt * c;
+          // the smaller of the two angles, through 1/R, R = hypot(d, 2 aij): c^2 =
+          // (1 + |d|/R) / 2, |s| = |aij| / (R c).  Two reciprocal roots behind
+          // each other, where the tangent takes three divisions and two roots,
+          // most of a step's time.  Scaled so that no square leaves the range.
+          double d = ajj - aii, a2 = 2.0 * aij;
+          const bool plus = d == 0.0 || (d > 0.0) == (a2 > 0.0);
+          const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(a2)));
+          d = fabs(ldexp(d, -ex));
+          a2 = fabs(ldexp(a2, -ex));
+          const double r = rsqrt(fma(d, d, a2 * a2));
+          const double c2 = fma(0.5 * d, r, 0.5), ic = rsqrt(c2);
+          c = c2 * ic;
+          s = 0.5 * a2 * r * ic;
+          if (!plus) s = -s;
         }
         cs[t] = c;
         sn[t] = s;
