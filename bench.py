@@ -12,8 +12,8 @@ each step filters a fresh copy of it.
 
 Headline value: DoF * vector * degree / s over the timed steps (DoF =
 interior CFE nodes + enrichment rows), whole-job wall time of the K steps.
-Also reported: the roofline of the dominant kernel (the cell GEMM colour
-pass, timed with HIP events on the library stream), per-kernel times, and
+Also reported: the roofline of the dominant kernel (the node update, timed
+with HIP events on the library stream), per-kernel times, and
 the CPU oracle on a bounded sample (extrapolated to the full apply).
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--prec fp64|fp32|bf16]
@@ -35,9 +35,9 @@ PEAK = {"fp64": 78.6e12, "fp32": 157.3e12, "bf16": 2.5e15, "hbm": 8.0e12}
 PREC = {"fp64": 0, "fp32": 1, "bf16": 2}
 STEP_TIMERS = ("t_filter_ms", "t_rr_ms", "t_poisson_ms", "t_density_ms", "t_operators_ms",
                "t_bound_ms", "t_energy_ms", "t_other_ms")
-COL_CHUNK = 160   # column chunk of the filter and of one cell GEMM launch
-CELL_KERNEL = {"fp64": "k_cell3<double, 1, 10, true>", "fp32": "k_cell3<float, 2, 10, true>",
-               "bf16": "k_cell_bf16<32>"}
+COL_CHUNK = 160   # column chunk of the filter and of one apply
+NODE_KERNEL = {"fp64": "k_node_update<double, 4, false>", "fp32": "k_node_update<float, 4, false>",
+               "bf16": "k_node_update<double, 4, false>"}
 
 
 def log(*a):
@@ -50,7 +50,7 @@ def measured_traffic(kernel, workload):
     the same counter's reading for a 1 GiB device copy), or None when the
     summary is missing or was taken from a different source of the kernel."""
     import hashlib
-    path = os.path.join(ROOT, "profiles", f"cell_gemm_{workload}_traffic.json")
+    path = os.path.join(ROOT, "profiles", f"node_update_{workload}_traffic.json")
     src = os.path.join(ROOT, "paper_2607_06848_amd", "csrc", "apply.hip")
     try:
         with open(path) as f:
@@ -112,9 +112,8 @@ def cpu_baseline(w):
 
 def profile_applies(w, prec, k):
     """A short program for hardware-counter runs: K H^E applies of one column
-    chunk of the workload's block (its first min(N, 160) columns: the width
-    one cell-GEMM launch takes) under the local pseudopotential, then one
-    plain device copy of 1 GiB."""
+    chunk of the workload's block (its first min(N, 160) columns) under the
+    local pseudopotential, then one plain device copy of 1 GiB."""
     import torch
     from paper_2607_06848_amd import efe
     from paper_2607_06848_amd import workloads as wl
@@ -375,9 +374,9 @@ def filter_bench(args, w):
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     timers = {k: ctx.timing_get(k) for k in ("cell", "pre", "post", "recur", "apply")}
-    names = {"cell": "cell GEMM colour pass", "pre": "projector pass + Y^C start values",
-             "post": "enrichment rows", "recur": "recurrence step (fused apply)",
-             "apply": "plain H apply (G)"}
+    names = {"cell": "cell products", "pre": "node update",
+             "post": "coefficients (gather, sums, dense part)",
+             "recur": "recurrence step (fused apply)", "apply": "H apply"}
     ctx.timing(False)
     amp = ctx.amplification()
     ncp, maxe = ctx.coupling()
@@ -388,16 +387,17 @@ def filter_bench(args, w):
                for k, (c, ms) in timers.items()}
     log(f"step {ms_step:.1f} ms; " + ", ".join(f"{k} {v['ms_avg']:.3f} ms x {v['launches']}"
                                               for k, v in kernels.items()))
-    # roofline of the cell GEMM colour pass: one launch multiplies one
-    # colour's cells (n_cells / 8 on average) into the chunk's columns: the
-    # cell Hamiltonians (2 nloc^2 per cell and vector) and the coupling blocks
-    # E_c and E_c^T (4 nf nloc per coupling pair and vector)
-    ncell_l, cell_ms = timers["cell"]
-    nf = ctx.n_enr // max(ctx.natoms, 1)
-    flops_per_launch = (2.0 * ctx.nloc ** 2 * ctx.n_cells + 4.0 * nf * ctx.nloc * ncp) * n / 8.0
-    avg_cell_s = cell_ms * 1e-3 / max(ncell_l, 1)
-    achieved = flops_per_launch / avg_cell_s
-    peak = PEAK[args.prec]
+    # roofline of the node update: it reads the cells' products (nloc rows a
+    # cell) and, in a recurrence step, Z_{k-1}, Z_{k-2} and G, and writes Y^C.
+    # The coupling blocks, which the column parts of a brick share, and the
+    # coefficient rows come on top and are not counted.
+    nupd, upd_ms = timers["pre"]
+    nrec = timers["recur"][0]
+    rows_moved = ctx.nloc * ctx.n_cells + ctx.n_nodes * (1.0 + 3.0 * nrec / max(nupd, 1))
+    bytes_per_launch = 8.0 * n * rows_moved
+    avg_upd_s = upd_ms * 1e-3 / max(nupd, 1)
+    achieved = bytes_per_launch / avg_upd_s
+    peak = PEAK["hbm"]
     full_pass_s = (t1 - t0) / args.steps * w["nvec"] / n
     return {
         "metric": "Cheb-filter DoF*vec*deg/s",
@@ -410,7 +410,7 @@ def filter_bench(args, w):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": {"fp64": "f64", "fp32": "f32 cell GEMM / f64", "bf16": "bf16 cell GEMM / f64"}[
+        "dtype": {"fp64": "f64", "fp32": "f32 coupling / f64", "bf16": "bf16 cell GEMM / f64"}[
             args.prec],
         "data": "synthetic",
         "config": {"workload": f"{w['name']}: {len(w['xyz'])}-atom jittered cubic Gaussian-"
@@ -423,12 +423,12 @@ def filter_bench(args, w):
                    "full_block_pass_s": full_pass_s,
                    "full_block_pass_rule": f"{w['nvec']} / {n} chunk passes back to back",
                    "kernels": kernels},
-        "roofline": {"bound": "mfma", "kernel": CELL_KERNEL[args.prec] + " (one colour pass)",
-                     "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
+        "roofline": {"bound": "hbm", "kernel": NODE_KERNEL[args.prec],
+                     "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TB/s",
                      "frac": achieved / peak,
-                     "traffic": measured_traffic(CELL_KERNEL[args.prec], w["name"]),
-                     "launch_ms": avg_cell_s * 1e3, "flops_per_launch": flops_per_launch,
-                     "share_of_step": cell_ms / ((t1 - t0) * 1e3)},
+                     "traffic": measured_traffic(NODE_KERNEL[args.prec], w["name"]),
+                     "launch_ms": avg_upd_s * 1e3, "bytes_per_launch": bytes_per_launch,
+                     "share_of_step": upd_ms / ((t1 - t0) * 1e3)},
         **({} if args.no_cpu else {"cpu_baseline": _cpu(w)}),
     }
 

@@ -42,8 +42,10 @@ typedef int32_t efe_status;
 #define EFE_ENUMERIC -5   /* numerical breakdown (Cholesky, non-finite data) */
 #define EFE_ESTATE   -6   /* call out of order (e.g. no potential set)       */
 
-/* Precision of the filter's cell GEMMs and projector updates (Sec. III.B runs
- * in FP64; FP32 and BF16 keep FP64 eigen-residual, output and Rayleigh-Ritz). */
+/* Precision of the filter's enrichment coupling (FP32: its two products with
+ * the nodes) or plain cell products (FP32 for Gauss rules without tensor
+ * products, BF16); Sec. III.B runs in FP64, and eigen-residual, output and
+ * Rayleigh-Ritz stay FP64. */
 #define EFE_FP64 0
 #define EFE_FP32 1
 #define EFE_BF16 2
@@ -198,17 +200,19 @@ efe_status efe_local_potential(efe_ctx *ctx, double *vq);
 efe_status efe_set_potential(efe_ctx *ctx, const double *vq, int32_t precisions);
 
 /* Y = H^E X for ncols vectors (device blocks, rows x ld).  Blocks wider than
- * 160 vectors are applied 160 columns at a time.  The apply runs the per-cell
- * form of T^T Hhat T: the cell GEMM takes [H_c | E_c^T] on the cell's nodes
- * and enrichment rows, E_c on its nodes for the enrichment rows.  EFE_EINVAL
- * if n_nodes x 160 reaches 2^31 (32-bit offsets of the cell GEMM's gathers);
- * efe_setup_mesh refuses systems with more than 768 enrichment functions
+ * 160 vectors are applied 160 columns at a time.  The apply runs T^T Hhat T
+ * with the orthogonalized coupling E = B - C H^cc: cell products by 1-D
+ * contractions (dense cell matrices where nq != p + 1), and E and P^C as dense
+ * blocks over boxes of nodes.  The cells' products take n_cells x nloc x
+ * min(ncols, 160) doubles of workspace; without room for them they are added
+ * colour by colour.  EFE_EINVAL if n_nodes x 160 reaches 2^31 (32-bit offsets
+ * of the dense cell products); efe_setup_mesh refuses systems with more than 768 enrichment functions
  * coupled to one cell. */
 efe_status efe_apply_H(efe_ctx *ctx, const double *X, double *Y, int32_t ncols, int64_t ld);
-/* Y = H^E X with the cell GEMMs in the given precision (EFE_FP64, or EFE_FP32
- * / EFE_BF16 with FP32 accumulation; the matrices must have been built by
- * efe_set_potential).  The coupling blocks E_c are formed in FP64 and rounded
- * with the cell matrices; projector and enrichment-block products stay FP64.
+/* Y = H^E X in the given precision (EFE_FP64, or EFE_FP32 / EFE_BF16 with
+ * FP32 accumulation; the reduced-precision blocks must have been built by
+ * efe_set_potential).  The coupling blocks are formed in FP64 and rounded;
+ * tensor-product cells, projector and enrichment-block products stay FP64.
  * EFE_BF16 takes plain CFE systems only (EFE_EINVAL with enrichment). */
 efe_status efe_apply_H_prec(efe_ctx *ctx, const double *X, double *Y, int32_t ncols, int64_t ld,
                             int32_t prec);
@@ -228,8 +232,8 @@ typedef struct {
   int32_t degree;     /* m >= 1 */
   double a, b, a_min; /* unwanted interval (a, b); a_min <= lowest eigenvalue < a */
   int32_t mode;       /* EFE_FILTER_RESIDUAL or EFE_FILTER_STANDARD */
-  int32_t prec;       /* EFE_FP64, EFE_FP32, EFE_BF16: operands of the cell GEMMs of
-                       * the recurrence; projectors, enrichment rows, G and
+  int32_t prec;       /* EFE_FP64, EFE_FP32, EFE_BF16: operands of the coupling and
+                       * dense cell products of the recurrence; projectors, enrichment rows, G and
                        * V_out stay FP64 */
 } efe_cheb_params;
 
@@ -243,7 +247,7 @@ efe_status efe_enrichment_amplification(const efe_ctx *ctx, double *amp);
 
 /* Largest amplification for which the filter accepts EFE_BF16: the BF16 unit
  * round-off 2^-8 times A must stay below 1, i.e. A <= 256.  Beyond it the
- * rounding of the cell GEMM operands, magnified by (M~^E)^-1, is as large as
+ * rounding of the cell operands, magnified by (M~^E)^-1, is as large as
  * the filtered residual itself and the filter output carries no digits. */
 #define EFE_BF16_MAX_AMPLIFICATION 256.0
 
@@ -267,7 +271,9 @@ efe_status efe_cheb_filter(efe_ctx *ctx, double *V, const double *lambda, int32_
  * GPU it runs on until the process ends (its address on a device is taken
  * when the first context on that device is set up).  No device memory is
  * allocated or freed.  EFE_EINVAL when the call's workspaces (about
- * 4 x rows x min(ncols, 160) doubles plus the apply's) exceed the region;
+ * 4 x rows x min(ncols, 160) doubles plus copies of the rows and one partial
+ * row per coupling pair) exceed the region; an accepted call whose slots are
+ * larger than that runs in narrower column chunks;
  * EFE_ESTATE if the region is unavailable on the context's device.  Every call
  * on a GPU shares that GPU's region and leaves its contents behind: calls that
  * overlap on one GPU (other streams, other host threads) race and must not
@@ -278,7 +284,7 @@ efe_status efe_cheb_filter_noalloc(efe_ctx *ctx, double *V, const double *lambda
 
 /* Rayleigh-Ritz in FP64 (Eq. projectedKSEig): S = V^T M V, Hp = V^T H V,
  * Hp R = S R Lambda with R^T S R = I (dense generalized eigensolve on the
- * GPU: Cholesky of S, reduction, divide and conquer), V <- V R.
+ * GPU: Cholesky of S, reduction, block Jacobi), V <- V R.
  * lambda (device, ncols) ascending; resnorm (device, ncols, may be NULL)
  * = ||H v_j - lambda_j M v_j||_2.  Boundary rows of V are set to zero.
  * Any block width: H V is formed in column chunks, the rotation in row
@@ -413,18 +419,19 @@ efe_status efe_scf_step(efe_ctx *ctx, double *V, int32_t ncols, int64_t ld, doub
  * events on the context's stream around the tracked launches; 0 stops.
  * efe_timing_get returns, for a kernel class, the number of recorded launches
  * and their summed duration in milliseconds (synchronizes the stream):
- *   0 one colour pass of the cell GEMM
- *   1 projector coefficients and the Y^C start values of an H apply
- *   2 enrichment rows of an H apply (partial sums and dense blocks)
+ *   0 cell products of an H apply (one launch; per colour where they are
+ *     added to Y^C)
+ *   1 node update of an H apply (sums the cells, coupling, recurrence terms)
+ *   2 coefficients of an H apply (box products, sums, dense part, Y^E)
  *   3 whole H apply of a recurrence step (the recurrence fused into it)
  *   4 whole H apply                      5 whole Rayleigh-Ritz
- *   6 colour pass, blocks of <= 16 vectors (e.g. the Lanczos vector)
+ *   6 cell products, blocks of <= 16 vectors (e.g. the Lanczos vector)
  *   7 whole H apply, blocks of <= 16 vectors
  * Classes 0 and 4 count blocks wider than 16 vectors only. */
 efe_status efe_timing(efe_ctx *ctx, int32_t enable);
 efe_status efe_timing_get(efe_ctx *ctx, int32_t which, int64_t *launches, double *total_ms);
 
-/* Layout check of the matrix-core instructions the cell GEMMs use (test
+/* Layout check of the matrix-core instructions the block products use (test
  * support): one wave forms D = A B with A 16 x K, B K x 16 (device, FP64,
  * row-major; K = 4 for which = 0 FP64 and 1 FP32, K = 32 for 2 BF16) through
  * the lane mappings of the kernels, D 16 x 16 row-major (device). */

@@ -26,10 +26,9 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 typedef double v2d __attribute__((ext_vector_type(2)));
 
 // Streams that a launch reads or writes once and that are far larger than the
-// caches (cell matrices, the recurrence blocks, Y of a colour pass, the
-// enrichment partial rows) go with the non-temporal hint, so that they do not
-// evict what is re-read through L2 (the gathered cell rows, the projector
-// support rows).  The hint changes cache policy only, not the values.
+// caches (the cells' products, the recurrence blocks, the coupling blocks, the
+// partial rows) go with the non-temporal hint, so that they do not evict what
+// is re-read through L2 (the rows of a box, the coefficient rows).  The hint changes cache policy only, not the values.
 template <typename T>
 __device__ inline T ld_nt(const T *p) {
   return __builtin_nontemporal_load(p);
@@ -52,34 +51,27 @@ __device__ inline void st_nt2(double2 v, double *p) {
 // columns per pass, three per lane).  For every atom of the group's union
 // the nine X^E rows are read once and applied to all eight nodes with the
 // group-major coefficients (uniform over the wave, so they come through the
-// scalar cache): Xh = s X^C - C^T X^E and Y^C = B^T X^E.
+// scalar cache): Xh = X^C - C^T X^E, boundary rows 0.
 constexpr int PRE_Q = 3;
 __global__ __launch_bounds__(256) void k_pre(int64_t n_nodes, int ncols, const double *__restrict__ XC,
-                                             int64_t ldx, const double *__restrict__ scale,
-                                             const double *__restrict__ minv,
+                                             int64_t ldx, const double *__restrict__ minv,
                                              const double *__restrict__ XE, int64_t lde,
                                              const int32_t *__restrict__ g_ptr,
                                              const int32_t *__restrict__ g_atom,
-                                             const double *__restrict__ Cg,
-                                             const double *__restrict__ Bg, int nf,
-                                             double *__restrict__ Xh, int64_t ldh,
-                                             double *Y, int64_t ldy) {
+                                             const double *__restrict__ Cg, int nf,
+                                             double *__restrict__ Xh, int64_t ldh) {
   const int64_t grp =
       (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
   const int lane = threadIdx.x % 64;
   const int64_t n0 = grp * 8;
   if (n0 >= n_nodes) return;
   const int nn = (int)min<int64_t>(8, n_nodes - n0);
-  double s[8];
   bool inner[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    inner[j] = j < nn && minv[n0 + j] != 0.0;
-    s[j] = j < nn ? (scale ? scale[n0 + j] : 1.0) : 0.0;
-  }
+  for (int j = 0; j < 8; ++j) inner[j] = j < nn && minv[n0 + j] != 0.0;
   const int32_t a0 = g_ptr[grp], a1 = g_ptr[grp + 1];
   for (int c0 = 0; c0 < ncols; c0 += 64 * PRE_Q) {
-    double xh[PRE_Q][8], y[PRE_Q][8];
+    double xh[PRE_Q][8];
 #pragma unroll
     for (int q = 0; q < PRE_Q; ++q) {
       const int col = c0 + 64 * q + lane;
@@ -88,13 +80,12 @@ __global__ __launch_bounds__(256) void k_pre(int64_t n_nodes, int ncols, const d
         // unconditional loads at clamped addresses keep every load of the
         // group in flight at once; the select drops what they brought in
         const double xv = XC[(n0 + min(j, nn - 1)) * ldx + min(col, ncols - 1)];
-        xh[q][j] = (inner[j] && col < ncols) ? s[j] * xv : 0.0;
-        y[q][j] = 0.0;
+        xh[q][j] = (inner[j] && col < ncols) ? xv : 0.0;
       }
     }
     for (int32_t a = a0; a < a1; ++a) {
       const double *xe = XE + (int64_t)g_atom[a] * nf * lde;
-      const double *cg = Cg + (int64_t)a * nf * 8, *bg = Bg + (int64_t)a * nf * 8;
+      const double *cg = Cg + (int64_t)a * nf * 8;
       for (int k = 0; k < nf; ++k) {
         double v[PRE_Q];
 #pragma unroll
@@ -104,12 +95,9 @@ __global__ __launch_bounds__(256) void k_pre(int64_t n_nodes, int ncols, const d
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-          const double cj = cg[k * 8 + j], bj = bg[k * 8 + j];
+          const double cj = cg[k * 8 + j];
 #pragma unroll
-          for (int q = 0; q < PRE_Q; ++q) {
-            xh[q][j] -= cj * v[q];
-            y[q][j] += bj * v[q];
-          }
+          for (int q = 0; q < PRE_Q; ++q) xh[q][j] -= cj * v[q];
         }
       }
     }
@@ -121,7 +109,6 @@ __global__ __launch_bounds__(256) void k_pre(int64_t n_nodes, int ncols, const d
       for (int j = 0; j < 8; ++j) {
         if (j >= nn) continue;
         Xh[(n0 + j) * ldh + col] = inner[j] ? xh[q][j] : 0.0;
-        if (Y) Y[(n0 + j) * ldy + col] = inner[j] ? y[q][j] : 0.0;
       }
     }
   }
@@ -1386,10 +1373,9 @@ efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, bool 
 efe_status efe_transform_cfe(efe_ctx *c, const double *X, int64_t ldx, double *Xh, int64_t ldh,
                              int ncols) {
   if (ncols <= 0) return EFE_OK;
-  k_pre<<<cdiv(c->n_nodes, 32), 256, 0, c->stream>>>(c->n_nodes, ncols, X, ldx, nullptr, c->d_minv,
+  k_pre<<<cdiv(c->n_nodes, 32), 256, 0, c->stream>>>(c->n_nodes, ncols, X, ldx, c->d_minv,
                                                      X + c->n_nodes * ldx, ldx, c->d_g_ptr,
-                                                     c->d_g_atom, c->d_Cg, c->d_Bg, c->nf, Xh, ldh,
-                                                     nullptr, 0);
+                                                     c->d_g_atom, c->d_Cg, c->nf, Xh, ldh);
   HIPCHK(c, hipGetLastError());
   return EFE_OK;
 }
@@ -1446,8 +1432,8 @@ extern "C" efe_status efe_set_potential(efe_ctx *c, const double *vq, int32_t pr
   return efe_build_operators(c, vq, precisions);
 }
 
-// wide blocks go through the apply in column chunks of the cell GEMM's
-// register tile, so its workspaces stay n_nodes x 160
+// wide blocks go through the apply in column chunks of the widest register
+// tile, so its workspaces stay n_nodes x 160
 static efe_status apply_H_chunked(efe_ctx *c, const double *X, double *Y, int32_t ncols,
                                   int64_t ld, int prec) {
   efe_status s;

@@ -556,7 +556,7 @@ extern "C" void efe_destroy(efe_ctx *c) {
                   c->d_kbnode,    c->d_Pc_am,        c->d_kbtrip,     c->d_Pphi,
                   c->d_D,         c->d_vq,           c->d_Htile64,    c->d_Htile32,
                   c->d_Htile16,   c->d_g_ptr,
-                  c->d_g_atom,    c->d_nm_gslot,     c->d_Cg,         c->d_Bg,
+                  c->d_g_atom,    c->d_nm_gslot,     c->d_Cg,
                   c->d_Bkin_pair, c->d_B_pair,       c->d_Hee,
                   c->d_Ptil,      c->d_cpair_atom, c->d_cpair_spair,
                   c->d_cpair_lmap, c->d_s1,          c->d_tpm, c->d_mk, c->d_Epair, c->d_cpair_cell, c->d_S};

@@ -17,7 +17,7 @@
 #define EFE_MAXQ 7
 #define EFE_MAXLOC ((EFE_MAXP + 1) * (EFE_MAXP + 1) * (EFE_MAXP + 1))
 // enrichment functions that may couple to one cell (padded to 16): 85 atoms
-// of 9 (the cell GEMM keeps their row numbers in LDS)
+// of 9 (a limit of the interface)
 #define EFE_MAX_CELL_ENR 768
 
 struct DevBuf {
@@ -117,7 +117,7 @@ struct efe_ctx {
   // support holds one of its nodes (slots), and C, B per slot as [slot][k][8]
   int64_t n_gslots = 0;
   int32_t *d_g_ptr = nullptr, *d_g_atom = nullptr, *d_nm_gslot = nullptr;
-  double *d_Cg = nullptr, *d_Bg = nullptr;
+  double *d_Cg = nullptr;
   // coupling pairs (atom, cell): every cell holding one of the atom's support
   // nodes (atom-major, by cell), with the support pair of the cell (-1 for
   // the layer outside the support) and the local-to-support map
@@ -167,7 +167,7 @@ struct efe_ctx {
   double *d_Htile64 = nullptr;                         // MFMA-tiled cell Hamiltonians
   float *d_Htile32 = nullptr;
   uint16_t *d_Htile16 = nullptr;
-  int RB = 0, KS = 0, KP = 0;                          // tile geometry of the cell GEMM
+  int RB = 0, KS = 0, KP = 0;                          // tile geometry of the dense cell products
   int KS32 = 0;                                        // 32-wide k steps of the BF16 tiles
   bool have32 = false, have16 = false;                 // reduced-precision tiles built
 
@@ -224,7 +224,7 @@ efe_status efe_ws(efe_ctx *ctx, int slot, size_t bytes, void **p);
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Column chunk of the wide-block passes (filter, Rayleigh-Ritz H V, density):
-// the cell GEMM's column tile, and the width the per-pass workspaces are
+// the widest column tile of the block products, and the width the per-pass workspaces are
 // sized for.
 constexpr int32_t EFE_COL_CHUNK = 160;
 
@@ -319,13 +319,13 @@ efe_status efe_enr_block_inv(efe_ctx *ctx, const double *XE, int64_t ldx, double
 
 // ------------------------------------------------------------------ timing
 // Optional HIP-event timing of the hot-path kernels (efe_timing).
-#define EFE_T_CELL 0     // one colour pass of the cell GEMM
-#define EFE_T_PRE 1      // projector pass and Y^C initialization of an H apply
-#define EFE_T_POST 2     // enrichment rows of an H apply (reduction and dense blocks)
+#define EFE_T_CELL 0     // cell products of an H apply
+#define EFE_T_PRE 1      // node update of an H apply
+#define EFE_T_POST 2     // coefficients of an H apply (gather, sums, dense part)
 #define EFE_T_RECUR 3    // residual recurrence update
 #define EFE_T_APPLY 4    // a whole H apply
 #define EFE_T_RR 5       // a whole Rayleigh-Ritz
-#define EFE_T_CELL_NARROW 6    // colour pass of a block of <= 16 vectors
+#define EFE_T_CELL_NARROW 6    // cell products of a block of <= 16 vectors
 #define EFE_T_APPLY_NARROW 7   // H apply of a block of <= 16 vectors
 #define EFE_T_N 8
 int efe_timer_begin(efe_ctx *ctx, int which);

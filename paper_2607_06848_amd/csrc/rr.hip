@@ -1,7 +1,7 @@
 // Rayleigh-Ritz in FP64 (Eq. projectedKSEig) with the exact overlap M^E
 // (Sec. III.B: the approximate inverse is used only inside the filter).
 //
-//   W  = H V                      (column chunks of the cell GEMM's width)
+//   W  = H V                      (column chunks of 160)        
 //   S  = V^T M V  (lumped mass on CFE rows, M^ee on enrichment rows)
 //   Hp = V^T W
 //   S = L L^T, A = L^-1 Hp L^-T, A = Q Lambda Q^T (block Jacobi), R = L^-T Q:

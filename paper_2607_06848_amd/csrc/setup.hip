@@ -917,7 +917,7 @@ efe_status efe_build_reference(efe_ctx *c) {
   (void)hipFree(dD1);
   (void)hipFree(dwq);
   (void)hipFree(dwg);
-  // MFMA tile geometry of the cell GEMM
+  // MFMA tile geometry of the dense cell products
   c->KP = (int)cdiv(c->nloc, 4) * 4;
   c->KS = c->KP / 4;
   c->RB = (int)cdiv(c->nloc, 16);
@@ -939,10 +939,8 @@ efe_status efe_build_enrichment(efe_ctx *c) {
   if ((s = efe_alloc(c, (void **)&c->d_B_am, ns * 8))) return s;
   const int64_t ng = c->n_gslots * nf * 8;
   if ((s = efe_alloc(c, (void **)&c->d_Cg, ng * 8))) return s;
-  if ((s = efe_alloc(c, (void **)&c->d_Bg, ng * 8))) return s;
   if (ng) {
     HIPCHK(c, hipMemsetAsync(c->d_Cg, 0, ng * 8, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->d_Bg, 0, ng * 8, c->stream));
   }
   if ((s = efe_alloc(c, (void **)&c->d_Mpp, ne * ne * 8))) return s;
   if ((s = efe_alloc(c, (void **)&c->d_Mee, ne * ne * 8))) return s;
