@@ -857,6 +857,7 @@ struct NodeArgs {
   double *Y;
   int64_t ldy;
   bool vec;
+  int first;                       // first column of part 0
 };
 
 constexpr int NODE_SEG = 512;      // functions whose row numbers sit in LDS
@@ -917,7 +918,7 @@ void k_node_update(NodeArgs<T> a) {
   // the column parts of a brick, and neighbouring bricks, run on one XCD
   int64_t b = blockIdx.x;
   if (gridDim.x % 8 == 0) b = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
-  const int c0 = (int)(b % a.nparts) * 16 * CBM, ncols = min(a.ncols - c0, 16 * CBM);
+  const int c0 = a.first + (int)(b % a.nparts) * 16 * CBM, ncols = min(a.ncols - c0, 16 * CBM);
   b /= a.nparts;
   const double *const Qc = a.Q + c0;
   const int t = threadIdx.x, wave = t / 64, lane = t % 64, li = lane % 16, lk = lane / 16;
@@ -1193,20 +1194,24 @@ static void launch_node_update(efe_ctx *c, NodeArgs<T> a, const T *tile) {
   // reads (64 atoms, 160 vectors: 1.61 ms, against 1.71 in 32-column parts, 1.9
   // in one 160-column part with two waves)
   const bool few = c->cpl_e.n_brick * cdiv(a.ncols, 64) < 2 * FEW_GROUPS;
-  const int B = few ? 1 : std::min(tile_blocks(a.ncols), 4);
-  a.nparts = (int)cdiv(a.ncols, 16 * B);
-  const int64_t n = c->cpl_e.n_brick * a.nparts;
   if (few) {
-    k_node_update<T, 1, true><<<n, 256, 0, c->stream>>>(a);
+    a.nparts = (int)cdiv(a.ncols, 16);
+    k_node_update<T, 1, true><<<c->cpl_e.n_brick * a.nparts, 256, 0, c->stream>>>(a);
     return;
   }
-#define GO(B) k_node_update<T, B><<<n, 256, 0, c->stream>>>(a)
-  switch (B) {
-    case 1: GO(1); break;
-    case 2: GO(2); break;
-    default: GO(4);
+  // what is left of 64-column parts goes on its own in the narrowest tile that
+  // holds it (500 atoms, 160 vectors: 14.9 ms, 15.9 as a third 64-column part
+  // whose products are half empty; 64 atoms 1.62, 1.64)
+  for (a.first = 0; a.first < a.ncols; a.first += 64 * a.nparts) {
+    const int left = a.ncols - a.first, B = std::min(tile_blocks(left), 4);
+    a.nparts = std::max(left / 64, 1);
+    const int64_t n = c->cpl_e.n_brick * a.nparts;
+    switch (B) {
+      case 1: k_node_update<T, 1><<<n, 256, 0, c->stream>>>(a); break;
+      case 2: k_node_update<T, 2><<<n, 256, 0, c->stream>>>(a); break;
+      default: k_node_update<T, 4><<<n, 256, 0, c->stream>>>(a);
+    }
   }
-#undef GO
 }
 
 efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, bool minv,

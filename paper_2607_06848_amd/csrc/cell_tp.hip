@@ -46,7 +46,7 @@ constexpr int tp_waves(int P) { return P >= 6 ? 2 : P == 5 ? 3 : 4; }
 // Units are laid out column group by column group (U columns each; the last
 // group may be narrower and then a work-group holds several cells), so that
 // ragged widths and single vectors fill the work-groups as full ones do.
-template <int P, bool PAIR>
+template <int P>
 __global__ __launch_bounds__(tp_units(P) * P) __attribute__((amdgpu_waves_per_eu(tp_waves(P))))
 void k_cell_tp(TpArgs a) {
   constexpr int U = tp_units(P), PP = P * P, N = P * P * P;
@@ -64,7 +64,7 @@ void k_cell_tp(TpArgs a) {
   const int64_t uc = live ? unit : a.ncells * w - 1;
   const int pos = w == U ? (int)(blk - g * a.ncells) : (int)(uc / w);
   const int jc = w == U ? u : (int)(uc - (int64_t)pos * w);
-  const int cell = PAIR || a.cells ? a.cells[pos] : pos;
+  const int cell = a.cells ? a.cells[pos] : pos;
   const int cx = cell % a.ncx, cy = (cell / a.ncx) % a.ncy, cz = cell / (a.ncx * a.ncy);
   const int64_t row0 = cx * (P - 1) + a.n1x * (cy * (P - 1) + a.n1y * (cz * (P - 1) + (int64_t)s));
   cdouble *const m0 = (cdouble *)(uintptr_t)a.m;
@@ -74,29 +74,18 @@ void k_cell_tp(TpArgs a) {
     double fx[P];
     const double *sy = a.s1 + a.n1x + cy * (P - 1);
     double sz = 1.0;
-    if constexpr (PAIR) {
-      const int32_t *lm = a.lmap + (int64_t)pos * N + s * PP;
+    const double *x = a.X + row0 * a.ldx + g * U + jc;
 #pragma unroll
-      for (int i = 0; i < PP; ++i) {
-        const int32_t sn = lm[i];
-        f[i] = sn >= 0 ? a.C[(int64_t)sn * a.ncols + jc] : 0.0;
-      }
+    for (int b = 0; b < P; ++b)
 #pragma unroll
-      for (int i = 0; i < P; ++i) fx[i] = 1.0;
-    } else {
-      const double *x = a.X + row0 * a.ldx + g * U + jc;
+      for (int i = 0; i < P; ++i) f[b * P + i] = x[(b * a.n1x + i) * a.ldx];
+    const double *sx = a.s1 + cx * (P - 1);
+    sz = a.s1[a.n1x + a.n1y + cz * (P - 1) + s];
 #pragma unroll
-      for (int b = 0; b < P; ++b)
-#pragma unroll
-        for (int i = 0; i < P; ++i) f[b * P + i] = x[(b * a.n1x + i) * a.ldx];
-      const double *sx = a.s1 + cx * (P - 1);
-      sz = a.s1[a.n1x + a.n1y + cz * (P - 1) + s];
-#pragma unroll
-      for (int i = 0; i < P; ++i) fx[i] = sx[i];
-    }
+    for (int i = 0; i < P; ++i) fx[i] = sx[i];
 #pragma unroll
     for (int b = 0; b < P; ++b) {
-      const double fy = PAIR ? 1.0 : sy[b] * sz;
+      const double fy = sy[b] * sz;
       double v[P], y[P];
 #pragma unroll
       for (int i = 0; i < P; ++i) v[i] = f[b * P + i] * (fx[i] * fy);
@@ -180,24 +169,7 @@ void k_cell_tp(TpArgs a) {
   __syncthreads();
   m = fresh(m0);
   if (!live) return;
-  if constexpr (PAIR) {
-    // B_c vanishes on the layer of cells outside the support
-    const int32_t sp = a.spair[pos];
-    const double *B = a.B + ((int64_t)max(sp, 0) * N + s * PP) * a.ncols + jc;
-    double *E = a.Yc + ((int64_t)pos * N + s * PP) * a.ncols + jc;
-#pragma unroll
-    for (int b = 0; b < P; ++b) {
-      double v[P], y[P];
-#pragma unroll
-      for (int i = 0; i < P; ++i) v[i] = L[((s * P + b) * P + i) * U + u];
-      mul1d<P, true>(m, 0, v, y);
-#pragma unroll
-      for (int i = 0; i < P; ++i) {
-        const int o = (b * P + i) * a.ncols;
-        E[o] = (sp >= 0 ? B[o] : 0.0) - y[i];
-      }
-    }
-  } else if (a.Yc) {
+  if (a.Yc) {
     double *yc = a.Yc + ((int64_t)pos * N + s * PP) * a.ldc + g * U + jc;
 #pragma unroll
     for (int b = 0; b < P; ++b) {
@@ -344,48 +316,14 @@ efe_status efe_tp_apply(efe_ctx *c, const double *X, int64_t ldx, bool minv, int
     const int t = efe_timer_begin(c, ncols <= 16 ? EFE_T_CELL_NARROW : EFE_T_CELL);
     const unsigned nb = (unsigned)nblk, th = (unsigned)(U * c->P);
     switch (c->P) {
-      case 2: k_cell_tp<2, false><<<nb, th, 0, c->stream>>>(a); break;
-      case 3: k_cell_tp<3, false><<<nb, th, 0, c->stream>>>(a); break;
-      case 4: k_cell_tp<4, false><<<nb, th, 0, c->stream>>>(a); break;
-      case 5: k_cell_tp<5, false><<<nb, th, 0, c->stream>>>(a); break;
-      case 6: k_cell_tp<6, false><<<nb, th, 0, c->stream>>>(a); break;
-      case 7: k_cell_tp<7, false><<<nb, th, 0, c->stream>>>(a); break;
+      case 2: k_cell_tp<2><<<nb, th, 0, c->stream>>>(a); break;
+      case 3: k_cell_tp<3><<<nb, th, 0, c->stream>>>(a); break;
+      case 4: k_cell_tp<4><<<nb, th, 0, c->stream>>>(a); break;
+      case 5: k_cell_tp<5><<<nb, th, 0, c->stream>>>(a); break;
+      case 6: k_cell_tp<6><<<nb, th, 0, c->stream>>>(a); break;
+      case 7: k_cell_tp<7><<<nb, th, 0, c->stream>>>(a); break;
     }
     efe_timer_end(c, ncols <= 16 ? EFE_T_CELL_NARROW : EFE_T_CELL, t);
-  }
-  HIPCHK(c, hipGetLastError());
-  return EFE_OK;
-}
-
-efe_status efe_tp_pairs(efe_ctx *c) {
-  TpArgs a{};
-  a.ncols = c->nf;
-  a.Yc = c->d_Epair;
-  a.vq = c->d_vq;
-  a.s1 = a.mask1 = c->d_s1;
-  a.ncx = c->ncell[0];
-  a.ncy = c->ncell[1];
-  a.n1x = c->n1[0];
-  a.n1y = c->n1[1];
-  a.m = c->d_tpm;
-  a.cells = c->d_cpair_cell;
-  a.ncells = c->ncpairs;
-  a.lmap = c->d_cpair_lmap;
-  a.spair = c->d_cpair_spair;
-  a.C = c->d_C_am;
-  a.B = c->d_B_pair;
-  const int U = tp_units(c->P);
-  static_assert(tp_units(7) > 9, "the functions of a pair fit one column group");
-  const int64_t nblk = cdiv(a.ncells * a.ncols, U);
-  if (nblk > 0x7fffffffLL) EFE_FAIL(c, EFE_EINVAL, "pair grid too large");
-  const unsigned nb = (unsigned)nblk, th = (unsigned)(U * c->P);
-  switch (c->P) {
-    case 2: k_cell_tp<2, true><<<nb, th, 0, c->stream>>>(a); break;
-    case 3: k_cell_tp<3, true><<<nb, th, 0, c->stream>>>(a); break;
-    case 4: k_cell_tp<4, true><<<nb, th, 0, c->stream>>>(a); break;
-    case 5: k_cell_tp<5, true><<<nb, th, 0, c->stream>>>(a); break;
-    case 6: k_cell_tp<6, true><<<nb, th, 0, c->stream>>>(a); break;
-    case 7: k_cell_tp<7, true><<<nb, th, 0, c->stream>>>(a); break;
   }
   HIPCHK(c, hipGetLastError());
   return EFE_OK;

@@ -35,7 +35,7 @@ __device__ inline int pair_of(const PairMap &m, int I, int cx, int cy, int cz) {
   return m.map[m.off[I] + x + b[3] * (y + (int64_t)b[4] * z)];
 }
 
-// What the blocks hold: E (epair: E_c per coupling pair), E + B (bam too) or
+// What the blocks hold: E (epair: E_c per coupling pair), C (bam) or
 // P^C (epair nullptr: bam is the assembled P^C, nf = 1).
 struct Entries {
   NodeGrid g;
@@ -223,15 +223,13 @@ __global__ __launch_bounds__(256) void k_tiles_box(Entries s, const int32_t *__r
   if (threadIdx.x == 0) live[row] = mask;
 }
 
-// Enrichment block of the orthogonalized Hamiltonian without the projectors,
-// H^E_ee = H^phiphi - C B^T - E C^T: the symmetric part of H^phiphi - (B + E)
-// C^T (H^phiphi - C B^T - E C^T is symmetric), as products of the box blocks
-// of B + E with C.  One work-group takes a box and 16 functions of C (its
-// nodes x 16 in LDS as the B operand), each wave every fourth row block, and
-// only the chunks of 16 nodes in which both have entries; the 16 x 16 results
-// are added into Hee atomically (64 atoms: 2.6 ms; 4.2 with all chunks; 32
-// functions a work-group read B + E half as often but leave one work-group a CU,
-// whose fill of C nothing covers, 3.1).
+// Second part of H^E_ee = H^phiphi - C B^T - E C^T (the first: k_hee_rows,
+// setup.hip): -E C^T as products of the box blocks of E with C.  One work-group
+// takes a box and 16 functions of C (its nodes x 16 in LDS as the B operand), each
+// wave every fourth row block, and only the chunks of 16 nodes in which both have
+// entries; the 16 x 16 results are added into Hee atomically (64 atoms: 2.6 ms;
+// 4.2 with all chunks; 32 functions a work-group read E half as often but leave
+// one work-group a CU, whose fill of C nothing covers, 3.1).
 typedef double v4d_c __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void k_hee_box(Entries s, const int32_t *__restrict__ ptr,
                                                  const int32_t *__restrict__ atom,
@@ -526,17 +524,14 @@ efe_status efe_couple_build(efe_ctx *c, bool want32) {
     if (!E.d_T2 && (s = efe_alloc(c, (void **)&E.d_T2, E.box_tile * 8))) return s;
     if (want32 && !E.d_T1f && (s = efe_alloc(c, (void **)&E.d_T1f, E.brick_tile * 4))) return s;
     if (want32 && !E.d_T2f && (s = efe_alloc(c, (void **)&E.d_T2f, E.box_tile * 4))) return s;
-    // B + E first, for H^E_ee, then E over it
-    const Entries both = entries(c, E, c->d_Epair, c->d_B_am, c->d_cpair_lmap);
-    k_tiles_box<<<E.n_rb, 256, box_lds(c, c->nf), c->stream>>>(both, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
-                                              E.d_T2, nullptr, E.d_live);
+    const size_t lds = box_lds(c, c->nf);
     HIPCHK(c, hipFuncSetAttribute((const void *)k_hee_box, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)box_lds(c, c->nf)));
-    k_hee_box<<<E.n_rb, 256, box_lds(c, c->nf), c->stream>>>(both, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
-                                            E.d_T2, E.d_live, c->d_C_am, ne, c->d_Hee);
+                                  (int)lds));
     const Entries e = entries(c, E, c->d_Epair, nullptr, c->d_cpair_lmap);
-    k_tiles_box<<<E.n_rb, 256, box_lds(c, c->nf), c->stream>>>(e, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
-                                              E.d_T2, want32 ? E.d_T2f : nullptr, E.d_live);
+    k_tiles_box<<<E.n_rb, 256, lds, c->stream>>>(e, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
+                                                E.d_T2, want32 ? E.d_T2f : nullptr, E.d_live);
+    k_hee_box<<<E.n_rb, 256, lds, c->stream>>>(e, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
+                                              E.d_T2, E.d_live, c->d_C_am, ne, c->d_Hee);
     k_tiles_brick<<<E.n_brick, 256, brick_lds(c), c->stream>>>(e, E.d_bk_ptr, E.d_bk_atom, E.d_bk_off, E.d_T1,
                                                    want32 ? E.d_T1f : nullptr);
     if ((s = efe_symmetrize(c, ne, c->d_Hee))) return s;

@@ -436,6 +436,16 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
         s = EFE_EINVAL;
         goto fail;
       }
+      // the pairs cell by cell
+      std::vector<int32_t> eptr(c->n_cells + 1, 0), epair(ccell.size());
+      for (int32_t cc : ccell) eptr[cc + 1]++;
+      for (int64_t k = 0; k < c->n_cells; ++k) eptr[k + 1] += eptr[k];
+      {
+        std::vector<int32_t> fill(eptr.begin(), eptr.end() - 1);
+        for (size_t q = 0; q < ccell.size(); ++q) epair[fill[ccell[q]]++] = (int32_t)q;
+      }
+      TRY(upload(c, &c->d_cell_eptr, eptr));
+      TRY(upload(c, &c->d_cell_epair, epair));
       TRY(upload(c, &c->d_cpair_atom, catom));
       TRY(upload(c, &c->d_cpair_spair, cspair));
       TRY(upload(c, &c->d_cpair_lmap, clmap));
@@ -558,7 +568,7 @@ extern "C" void efe_destroy(efe_ctx *c) {
                   c->d_Htile16,   c->d_g_ptr,
                   c->d_g_atom,    c->d_nm_gslot,     c->d_Cg,
                   c->d_Bkin_pair, c->d_B_pair,       c->d_Hee,
-                  c->d_Ptil,      c->d_cpair_atom, c->d_cpair_spair,
+                  c->d_Ptil,      c->d_cpair_atom, c->d_cpair_spair, c->d_cell_eptr, c->d_cell_epair,
                   c->d_cpair_lmap, c->d_s1,          c->d_tpm, c->d_mk, c->d_Epair, c->d_cpair_cell, c->d_S};
   efe_couple_free(c);
   for (void *p : ptrs)

@@ -54,9 +54,6 @@ struct TpArgs {
   int64_t ldx, ldy, ldc, ncells, n1x, n1y;
   int ncols, ncx, ncy;
   double alpha;
-  // pair form: unit (pair, k), E_c = B_c - H_c C_c^T
-  const int32_t *lmap, *spair;
-  const double *C, *B;
   const double *m;                     // 1-D matrices of the axes
 };
 
@@ -122,6 +119,7 @@ struct efe_ctx {
   // nodes (atom-major, by cell), with the support pair of the cell (-1 for
   // the layer outside the support) and the local-to-support map
   int64_t ncpairs = 0;
+  int32_t *d_cell_eptr = nullptr, *d_cell_epair = nullptr;   // coupling pairs cell by cell
   int32_t *d_cpair_cell = nullptr, *d_cpair_atom = nullptr, *d_cpair_spair = nullptr,
           *d_cpair_lmap = nullptr;
   int max_rbe = 0;                                     // max padded rows / 16 over cells
@@ -275,7 +273,6 @@ efe_status efe_tp_setup(efe_ctx *ctx, const std::vector<double> &xq, const std::
 efe_status efe_tp_apply(efe_ctx *ctx, const double *X, int64_t ldx, bool minv, int ncols,
                         double *Yc, int64_t ldc, double *Y, int64_t ldy, double alpha);
 // E_c = B_c - H_c C_c^T of every coupling pair into d_Epair
-efe_status efe_tp_pairs(efe_ctx *ctx);
 // coupling blocks (couple.hip): lists from the coupling pairs (per atom its
 // cells), blocks of the projectors (once), blocks of E, H^E_ee and the matrix
 // of the coefficients (per potential; d_Epair, d_B_am and, in d_Hee, H^phiphi)

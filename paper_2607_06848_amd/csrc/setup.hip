@@ -553,50 +553,100 @@ __global__ __launch_bounds__(256) void k_mee_rows(int nf, int64_t n_enr, const i
     Mee[f * n_enr + i] = Mpp[f * n_enr + i] - acc[i];
 }
 
-// ------------------------------------------------------------ coupling
-// The orthogonalized basis couples the enrichment rows to the CFE rows
-// through H^ec = B - C H^cc (Sec. II.B: N^E = phi - C N^C).  Per (atom, cell)
-// pair, E_c = B_c - C_c H_c, formed in FP64 so that the cancellation between B
-// and C H happens before any rounding to a reduced precision.  This is the
-// dense form for Gauss rules that the tensor products of cell_tp.hip do not
-// take: C_c^T (nloc x nf, padded to 16) in LDS as the B operand, the cell
-// Hamiltonian's MFMA tiles as the A operand, each wave a row block of H_c C_c^T.
-__global__ __launch_bounds__(256) void k_build_E(
-    int nloc, int RB, int KS, int nf, const double *__restrict__ Ht,
-    const int32_t *__restrict__ cell_of, const int32_t *__restrict__ lmap,
-    const int32_t *__restrict__ spair, const double *__restrict__ C_am,
-    const double *__restrict__ B_pair, double *__restrict__ E) {
-  __shared__ double Cs[EFE_MAXLOC + 16][16];
-  const int64_t pr = blockIdx.x;
-  const int64_t cell = cell_of[pr];
-  const int32_t sp = spair[pr];
-  for (int i = threadIdx.x; i < 4 * KS * 16; i += 256) {
-    const int l = i / 16, k = i % 16;
+// Coupling of the orthogonalized basis, E_c = B_c - C_c H_c of every (atom, cell)
+// pair (Sec. II.B: N^E = phi - C N^C), in FP64 from the dense cell Hamiltonians.
+// 1-D contractions do it in 1.3 ms for 64 atoms, but B - C H cancels most of its
+// digits, what is left enters G and with it every step of a filter, and the
+// output of degree 40 moved by 6e-9.  One work-group takes a cell and 32 of its
+// enrichment functions: C_c^T (nodes x 32) in LDS, each wave every eighth 16 rows
+// of H_c, whose fragments feed two products (64 atoms: 7.8 ms; 12.8 with a
+// work-group a pair).
+__global__ __launch_bounds__(512) void k_build_E(
+    int nloc, int RB, int KS, int nf, int max_cb, const double *__restrict__ Ht,
+    const int32_t *__restrict__ eptr, const int32_t *__restrict__ epair,
+    const int32_t *__restrict__ lmap, const int32_t *__restrict__ spair,
+    const double *__restrict__ C_am, const double *__restrict__ B_pair, double *__restrict__ E) {
+  __shared__ double Cs[2][EFE_MAXLOC + 16][16];
+  const int64_t cell = blockIdx.x / max_cb;
+  const int cb = blockIdx.x % max_cb;
+  const int32_t p0 = eptr[cell];
+  const int ne = (eptr[cell + 1] - p0) * nf;
+  if (32 * cb >= ne) return;
+  for (int i = threadIdx.x; i < 4 * KS * 32; i += 512) {
+    const int l = i / 32, j = i % 32, e = 32 * cb + j;
     double v = 0.0;
-    if (l < nloc && k < nf) {
-      const int32_t sn = lmap[pr * nloc + l];
-      if (sn >= 0) v = C_am[(int64_t)sn * nf + k];
+    if (l < nloc && e < ne) {
+      const int32_t sn = lmap[(int64_t)epair[p0 + e / nf] * nloc + l];
+      if (sn >= 0) v = C_am[(int64_t)sn * nf + e % nf];
     }
-    Cs[l][k] = v;
+    Cs[j / 16][l][j % 16] = v;
   }
   __syncthreads();
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
-  for (int rb = wave; rb < RB; rb += 4) {
+  for (int rb = wave; rb < RB; rb += 8) {
     const double *hp = Ht + (cell * RB + rb) * KS * 64 + lane;
-    v4d_p acc = {0.0, 0.0, 0.0, 0.0};
-    for (int ks = 0; ks < KS; ++ks)
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(hp[(int64_t)ks * 64], Cs[4 * ks + lk][li], acc,
-                                                 0, 0, 0);
+    v4d_p acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll 8
+    for (int ks = 0; ks < KS; ++ks) {
+      const double h = hp[(int64_t)ks * 64];
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(h, Cs[b][4 * ks + lk][li], acc[b], 0, 0, 0);
+    }
     // accumulator v of lane l: node row 16 rb + 4 v + l/16, function l%16
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int l = 16 * rb + 4 * v + lk;
-      if (l >= nloc || li >= nf) continue;
-      // B_c vanishes on the layer of cells outside the support
-      const double bv = sp >= 0 ? B_pair[((int64_t)sp * nloc + l) * nf + li] : 0.0;
-      E[(pr * nloc + l) * nf + li] = bv - acc[v];
+    for (int b = 0; b < 2; ++b) {
+      const int e = 32 * cb + 16 * b + li;
+      if (e >= ne) continue;
+      const int64_t pr = epair[p0 + e / nf];
+      const int32_t sp = spair[pr];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int l = 16 * rb + 4 * v + lk;
+        if (l >= nloc) continue;
+        // B_c vanishes on the layer of cells outside the support
+        const double bv = sp >= 0 ? B_pair[((int64_t)sp * nloc + l) * nf + e % nf] : 0.0;
+        E[(pr * nloc + l) * nf + e % nf] = bv - acc[b][v];
+      }
     }
   }
+}
+
+// Rows of the enrichment block of the orthogonalized Hamiltonian without the
+// projectors, H^E_ee = H^phiphi - C B^T - E C^T (the expansion of T^T Hhat T
+// with E = B - C H^cc), first part: Hee = H^phiphi - C B^T, row f = (I, k)
+// summed over the support nodes of atom I and, at each node, the atoms whose
+// support holds it (B vanishes off the support).  C B^T cancels nearly all of
+// H^phiphi and what is left is magnified by (M~^ee)^-1, so a filter's output
+// follows the rounding of this sum: over boxes of nodes (couple.hip) it takes 3.3
+// ms instead of 14.1 for 64 atoms, but moves the output of degree 40 by 1.5e-9.
+__global__ __launch_bounds__(256) void k_hee_rows(int nf, int64_t n_enr,
+                                                  const int32_t *__restrict__ snode_ptr,
+                                                  const int32_t *__restrict__ snode,
+                                                  const int32_t *__restrict__ nm_ptr,
+                                                  const int32_t *__restrict__ nm_atom,
+                                                  const int32_t *__restrict__ nm_src,
+                                                  const double *__restrict__ C_am,
+                                                  const double *__restrict__ B_am,
+                                                  const double *__restrict__ Hpp,
+                                                  double *__restrict__ Hee) {
+  extern __shared__ double acc[];
+  const int64_t f = blockIdx.x;
+  const int I = f / nf, k = f % nf;
+  for (int64_t i = threadIdx.x; i < n_enr; i += blockDim.x) acc[i] = 0.0;
+  __syncthreads();
+  for (int32_t s = snode_ptr[I] + threadIdx.x; s < snode_ptr[I + 1]; s += blockDim.x) {
+    const int32_t j = snode[s];
+    const double cf = C_am[(int64_t)s * nf + k];
+    for (int32_t ee = nm_ptr[j]; ee < nm_ptr[j + 1]; ++ee) {
+      const int J = nm_atom[ee];
+      const int64_t src = nm_src[ee];
+      for (int l = 0; l < nf; ++l) atomicAdd(&acc[J * nf + l], cf * B_am[src * nf + l]);
+    }
+  }
+  __syncthreads();
+  for (int64_t i = threadIdx.x; i < n_enr; i += blockDim.x)
+    Hee[f * n_enr + i] = Hpp[f * n_enr + i] - acc[i];
 }
 
 // Projector rows in the orthogonalized basis: P~^phi = P^phi - P^C C^T
@@ -1055,9 +1105,9 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
   k_copy<<<cdiv(c->n_qpts, 256), 256, 0, c->stream>>>(c->n_qpts, vq, c->d_vq);
   const bool want32 = precisions & (1 << EFE_FP32);
   const bool want16 = precisions & (1 << EFE_BF16);
-  // dense cell Hamiltonians where an apply takes them: Gauss rules without
-  // tensor products, and the BF16 copies
-  const bool dense = !c->tp || want16;
+  // dense cell Hamiltonians: for E_c, and where an apply takes them (Gauss rules
+  // without tensor products, and the BF16 copies)
+  const bool dense = !c->tp || want16 || (nf > 0 && c->npairs > 0);
   if (dense && !c->d_Htile64 && (s = efe_alloc(c, (void **)&c->d_Htile64, tiles * 8))) return s;
   if (want32 && !c->tp && !c->d_Htile32 && (s = efe_alloc(c, (void **)&c->d_Htile32, tiles * 4))) return s;
   const int64_t tiles16 = c->n_cells * c->RB * c->KS32 * 64 * 8;
@@ -1105,19 +1155,18 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
                                                 c->d_ppv, c->d_trip, c->d_vq, ne, c->d_Hpp);
     k_symmetrize<<<cdiv(ne * ne, 256), 256, 0, c->stream>>>(ne, c->d_Hpp);
     // coupling of the orthogonalized basis, E_c per (atom, cell) pair
-    if (c->tp) {
-      if ((s = efe_tp_pairs(c))) return s;
-    } else {
-      k_build_E<<<c->ncpairs, 256, 0, c->stream>>>(c->nloc, c->RB, c->KS, nf, c->d_Htile64,
-                                                   c->d_cpair_cell, c->d_cpair_lmap,
-                                                   c->d_cpair_spair, c->d_C_am, c->d_B_pair,
-                                                   c->d_Epair);
-    }
+    k_build_E<<<c->n_cells * cdiv(c->max_rbe, 2), 512, 0, c->stream>>>(
+        c->nloc, c->RB, c->KS, nf, (int)cdiv(c->max_rbe, 2), c->d_Htile64, c->d_cell_eptr,
+        c->d_cell_epair, c->d_cpair_lmap, c->d_cpair_spair, c->d_C_am, c->d_B_pair, c->d_Epair);
   }
   if (ne) {
     if (!c->d_Hee && (s = efe_alloc(c, (void **)&c->d_Hee, ne * ne * 8))) return s;
-    k_copy<<<cdiv(ne * ne, 256), 256, 0, c->stream>>>(
-        ne * ne, nf > 0 && c->npairs > 0 ? c->d_Hpp : c->d_Hpp_kin, c->d_Hee);
+    if (nf > 0 && c->npairs > 0)
+      k_hee_rows<<<ne, 256, ne * 8, c->stream>>>(nf, ne, c->d_snode_ptr, c->d_snode, c->d_nm_ptr,
+                                                 c->d_nm_atom, c->d_nm_src, c->d_C_am, c->d_B_am,
+                                                 c->d_Hpp, c->d_Hee);
+    else
+      k_copy<<<cdiv(ne * ne, 256), 256, 0, c->stream>>>(ne * ne, c->d_Hpp_kin, c->d_Hee);
   }
   if ((s = efe_couple_build(c, want32))) return s;
   HIPCHK(c, hipGetLastError());
