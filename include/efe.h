@@ -437,6 +437,13 @@ efe_status efe_timing_get(efe_ctx *ctx, int32_t which, int64_t *launches, double
  * the lane mappings of the kernels, D 16 x 16 row-major (device). */
 efe_status efe_probe_mfma(int32_t which, const double *A, const double *B, double *D);
 
+/* Device memory of the context: *held (may be NULL) receives the bytes it holds
+ * now; limit >= 0 sets a bound on them (0: none, the default), beyond which an
+ * allocation fails as one that the device cannot serve.  When an allocation
+ * fails, the context first gives back what it can do without (the cells'
+ * products of an apply, the inputs of the operators) and tries again. */
+efe_status efe_memory(efe_ctx *ctx, int64_t limit, int64_t *held);
+
 /* Message of the last failure on this context ("" if none); with ctx == NULL
  * the message of the last failed efe_setup_mesh on the calling thread. */
 const char *efe_last_error(const efe_ctx *ctx);

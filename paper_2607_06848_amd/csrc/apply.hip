@@ -1267,10 +1267,10 @@ efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, bool 
   //    (rows of whole 64-byte pieces where there is room: 37 vectors on 4,096
   //    cells 346 us, 451 with pieces of neighbouring rows in one)
   int64_t ldc = ncols <= 16 ? ncols : (ncols + 7) & ~7;
-  double *Yc = tp ? efe_ws_try(c, 15, (size_t)c->n_cells * c->nloc * ldc * 8) : nullptr;
+  double *Yc = tp ? efe_ws_try(c, (size_t)c->n_cells * c->nloc * ldc * 8) : nullptr;
   if (tp && !Yc && ldc > ldq) {
     ldc = ldq;
-    Yc = efe_ws_try(c, 15, (size_t)c->n_cells * c->nloc * ldc * 8);
+    Yc = efe_ws_try(c, (size_t)c->n_cells * c->nloc * ldc * 8);
   }
   if (Yc && (s = efe_tp_apply(c, XC, ldx, minv, ncols, Yc, ldc, nullptr, 0, 0.0))) return s;
   // 2. coefficients: [E ; P^C] s X^C by boxes, their sums, the dense part (Y^E

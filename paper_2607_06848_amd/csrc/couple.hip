@@ -547,9 +547,7 @@ void efe_couple_free(efe_ctx *c) {
     void *ptrs[] = {S->d_box,   S->d_map,   S->d_off,    S->d_bk_ptr, S->d_bk_atom, S->d_bk_off,
                     S->d_bx_ptr, S->d_bx_atom, S->d_rboff, S->d_rbbox, S->d_at_ptr, S->d_at_pos,
                     S->d_T1,    S->d_T2,    S->d_T1f,    S->d_T2f,  S->d_live};
-    for (void *p : ptrs)
-      if (p) (void)hipFree(p);
+    for (void *p : ptrs) efe_free(c, p);
   }
-  for (int32_t *p : c->d_items)
-    if (p) (void)hipFree(p);
+  for (int32_t *p : c->d_items) efe_free(c, p);
 }

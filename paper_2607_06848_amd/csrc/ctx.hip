@@ -10,12 +10,59 @@
 
 #include "efe_internal.h"
 
-efe_status efe_alloc(efe_ctx *ctx, void **p, size_t bytes) {
+static hipError_t device_alloc(efe_ctx *ctx, void **p, size_t bytes) {
   *p = nullptr;
-  if (bytes == 0) bytes = 16;
-  hipError_t e = hipMalloc(p, bytes);
+  if (ctx->mem_limit && ctx->held + bytes > ctx->mem_limit) return hipErrorOutOfMemory;
+  const hipError_t e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
+    *p = nullptr;
+    return e;
+  }
+  ctx->allocs[*p] = bytes;
+  ctx->held += bytes;
+  return e;
+}
+
+void efe_free(efe_ctx *ctx, void *p) {
+  if (!p) return;
+  const auto it = ctx->allocs.find(p);
+  if (it != ctx->allocs.end()) {
+    ctx->held -= it->second;
+    ctx->allocs.erase(it);
+  }
+  (void)hipFree(p);
+}
+
+// Give back what no later call needs to find: the cells' products (an apply
+// without them adds the cells colour by colour) and what only the building of
+// operators reads (E_c per pair; the dense cell Hamiltonians where applies take
+// tensor products).  True if anything was freed.
+static bool release_spare(efe_ctx *ctx) {
+  DevBuf *y = (int)ctx->ws.size() > EFE_WS_SPARE ? &ctx->ws[EFE_WS_SPARE] : nullptr;
+  const bool ops = !ctx->building && (ctx->d_Epair || (ctx->tp && ctx->d_Htile64));
+  if (!(y && y->p) && !ops) return false;
+  if (hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
+  if (y && y->p) {
+    efe_free(ctx, y->p);
+    *y = DevBuf();
+  }
+  if (ops) {
+    efe_free(ctx, ctx->d_Epair);
+    ctx->d_Epair = nullptr;
+    if (ctx->tp) {
+      efe_free(ctx, ctx->d_Htile64);
+      ctx->d_Htile64 = nullptr;
+    }
+  }
+  return true;
+}
+
+efe_status efe_alloc(efe_ctx *ctx, void **p, size_t bytes) {
+  if (bytes == 0) bytes = 16;
+  hipError_t e = device_alloc(ctx, p, bytes);
+  if (e == hipErrorOutOfMemory && release_spare(ctx)) e = device_alloc(ctx, p, bytes);
+  if (e != hipSuccess) {
     ctx->err = "hipMalloc of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(e);
     return EFE_ENOMEM;
   }
@@ -44,7 +91,7 @@ efe_status efe_ws(efe_ctx *ctx, int slot, size_t bytes, void **p) {
   if (b.bytes < bytes) {
     if (b.p) {
       HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-      HIPCHK(ctx, hipFree(b.p));
+      efe_free(ctx, b.p);
     }
     b.p = nullptr;
     b.bytes = 0;
@@ -56,20 +103,52 @@ efe_status efe_ws(efe_ctx *ctx, int slot, size_t bytes, void **p) {
   return EFE_OK;
 }
 
-double *efe_ws_try(efe_ctx *ctx, int slot, size_t bytes) {
+// The old buffer stays until a larger one exists, so that narrower applies keep
+// theirs, and a size that the device refused is not asked for on every apply.
+// Nothing is allocated while the stream is being captured.
+double *efe_ws_try(efe_ctx *ctx, size_t bytes) {
+  const int slot = EFE_WS_SPARE;
   void *p = nullptr;
   if (ctx->arena) {
     // only out of what the call's other slots leave
     if (ctx->arena_len[slot] == 0) {
       if (bytes + 256 > ctx->arena_spare) return nullptr;
       ctx->arena_spare -= bytes + 256;
+    } else if (ctx->arena_len[slot] < bytes) {
+      return nullptr;
     }
     return efe_ws(ctx, slot, bytes, &p) == EFE_OK ? (double *)p : nullptr;
   }
-  if (efe_ws(ctx, slot, bytes, &p) == EFE_OK) return (double *)p;
-  (void)hipGetLastError();
-  ctx->err.clear();
-  return nullptr;
+  if ((int)ctx->ws.size() <= slot) ctx->ws.resize(slot + 1);
+  DevBuf &b = ctx->ws[slot];
+  if (b.bytes >= bytes) return (double *)b.p;
+  if (bytes >= ctx->ws_refused) return nullptr;
+  hipStreamCaptureStatus cap;
+  if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (cap != hipStreamCaptureStatusNone) return nullptr;
+  if (device_alloc(ctx, &p, bytes) != hipSuccess ||
+      (b.p && hipStreamSynchronize(ctx->stream) != hipSuccess)) {
+    efe_free(ctx, p);
+    ctx->ws_refused = bytes;
+    return nullptr;
+  }
+  efe_free(ctx, b.p);
+  b.p = p;
+  b.bytes = bytes;
+  return (double *)p;
+}
+
+extern "C" efe_status efe_memory(efe_ctx *ctx, int64_t limit, int64_t *held) {
+  if (!ctx) return EFE_EINVAL;
+  if (limit >= 0) {
+    ctx->mem_limit = (size_t)limit;
+    ctx->ws_refused = SIZE_MAX;
+  }
+  if (held) *held = (int64_t)ctx->held;
+  return EFE_OK;
 }
 
 template <class T>
@@ -571,10 +650,8 @@ extern "C" void efe_destroy(efe_ctx *c) {
                   c->d_Ptil,      c->d_cpair_atom, c->d_cpair_spair, c->d_cell_eptr, c->d_cell_epair,
                   c->d_cpair_lmap, c->d_s1,          c->d_tpm, c->d_mk, c->d_Epair, c->d_cpair_cell, c->d_S};
   efe_couple_free(c);
-  for (void *p : ptrs)
-    if (p) (void)hipFree(p);
-  for (auto &b : c->ws)
-    if (b.p) (void)hipFree(b.p);
+  for (void *p : ptrs) efe_free(c, p);
+  for (auto &b : c->ws) efe_free(c, b.p);
   for (auto &v : c->tev)
     for (hipEvent_t e : v) (void)hipEventDestroy(e);
   delete c;

@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "../../include/efe.h"
@@ -169,8 +170,17 @@ struct efe_ctx {
   int KS32 = 0;                                        // 32-wide k steps of the BF16 tiles
   bool have32 = false, have16 = false;                 // reduced-precision tiles built
 
-  // workspaces (grown on demand)
+  // device memory of the context: every allocation with its size, their sum,
+  // the caller's bound (0: none; efe_memory)
+  std::unordered_map<void *, size_t> allocs;
+  size_t held = 0, mem_limit = 0;
+  // new operators are being built: their inputs must not be given back
+  bool building = false;
+
+  // workspaces (grown on demand); smallest request for the optional one that
+  // the device refused since the last potential
   std::vector<DevBuf> ws;
+  size_t ws_refused = SIZE_MAX;
   // while an entry point that allocates nothing runs, workspace slots are
   // carved out of the caller-fixed region [arena, arena + arena_cap) instead
   // (slot -> offset, bytes; reset for every call)
@@ -210,6 +220,7 @@ struct efe_ctx {
   } while (0)
 
 efe_status efe_alloc(efe_ctx *ctx, void **p, size_t bytes);
+void efe_free(efe_ctx *ctx, void *p);
 // per-device address of the static scratch region of efe_cheb_filter_noalloc
 // (noalloc.hip), taken once per device at context setup
 efe_status efe_scratch_attach(efe_ctx *ctx);
@@ -282,8 +293,10 @@ efe_status efe_couple_projectors(efe_ctx *ctx);
 efe_status efe_couple_build(efe_ctx *ctx, bool want32);
 void efe_couple_free(efe_ctx *ctx);
 efe_status efe_symmetrize(efe_ctx *ctx, int64_t n, double *A);
-// workspace slot that may be missing: nullptr (no error) when it does not fit
-double *efe_ws_try(efe_ctx *ctx, int slot, size_t bytes);
+// the workspace that may be missing (the cells' products): nullptr (no error)
+// when it does not fit
+constexpr int EFE_WS_SPARE = 15;
+double *efe_ws_try(efe_ctx *ctx, size_t bytes);
 
 // operator applications (apply.hip)
 // Affine epilogue of an H apply (the Chebyshev recurrence fused into the

@@ -52,8 +52,7 @@ void efe_scf_free(efe_ctx *c) {
   void *ptrs[] = {s.rho_at, s.phi_at, s.v_short, s.rho_in, s.rho_out, s.v_in, s.phiq,
                   s.phi_rem, s.phi_out, s.Kdiag, s.cg, s.hist, s.scal, s.f, s.cell_ptr,
                   s.cell_atom, s.part, s.ycell, s.kdiag_k, s.u_k, s.uq_k};
-  for (void *p : ptrs)
-    if (p) (void)hipFree(p);
+  for (void *p : ptrs) efe_free(c, p);
   delete (ScfState *)c->scf;
   c->scf = nullptr;
 }
@@ -1414,7 +1413,7 @@ extern "C" efe_status efe_scf_step(efe_ctx *c, double *V, int32_t N, int64_t ld,
   auto t3 = std::chrono::steady_clock::now();
   const int m = prm->mix_history;
   if (!s.hist || s.hist_m != m) {
-    if (s.hist) (void)hipFree(s.hist);
+    efe_free(c, s.hist);
     s.hist = nullptr;
     if ((st = efe_alloc(c, (void **)&s.hist, (size_t)2 * (m + 1) * nq * 8))) return st;
     s.hist_m = m;

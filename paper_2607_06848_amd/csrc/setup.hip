@@ -963,10 +963,10 @@ efe_status efe_build_reference(efe_ctx *c) {
       c->n1[0], c->n1[1], c->n1[2], c->p, dwg, c->h[0], c->h[1], c->h[2], c->d_m, c->d_minv, c->d_m_int);
   HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  (void)hipFree(dN1);
-  (void)hipFree(dD1);
-  (void)hipFree(dwq);
-  (void)hipFree(dwg);
+  efe_free(c, dN1);
+  efe_free(c, dD1);
+  efe_free(c, dwq);
+  efe_free(c, dwg);
   // MFMA tile geometry of the dense cell products
   c->KP = (int)cdiv(c->nloc, 4) * 4;
   c->KS = c->KP / 4;
@@ -1034,7 +1034,7 @@ efe_status efe_build_enrichment(efe_ctx *c) {
     int hfail = 0;
     HIPCHK(c, hipMemcpyAsync(&hfail, dfail, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    (void)hipFree(dfail);
+    efe_free(c, dfail);
     if (hfail) EFE_FAIL(c, EFE_ENUMERIC, "singular atom block of M^ee");
     double *damp;
     if ((s = efe_alloc(c, (void **)&damp, (size_t)c->natoms * 8))) return s;
@@ -1044,7 +1044,7 @@ efe_status efe_build_enrichment(efe_ctx *c) {
     HIPCHK(c, hipMemcpyAsync(amp.data(), damp, (size_t)c->natoms * 8, hipMemcpyDeviceToHost,
                              c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    (void)hipFree(damp);
+    efe_free(c, damp);
     c->amplification = 1.0;
     for (double a : amp) c->amplification = std::max(c->amplification, a);
   }
@@ -1096,6 +1096,12 @@ efe_status efe_launch_local_potential(efe_ctx *c, double *vq) {
 
 efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
   efe_status s;
+  struct Building {   // until the call returns
+    efe_ctx *c;
+    explicit Building(efe_ctx *x) : c(x) { c->building = true; }
+    ~Building() { c->building = false; }
+  } building(c);
+  c->ws_refused = SIZE_MAX;
   const MeshGeo g = mesh_geo(c);
   const EnrParam e = enr_param(c);
   const int nf = c->nf;

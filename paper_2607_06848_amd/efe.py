@@ -157,6 +157,7 @@ _SIGS = {
     "efe_timing_get": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, c_int64_p, c_double_p]),
     "efe_probe_mfma": (ctypes.c_int32, [ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
                                         ctypes.c_void_p]),
+    "efe_memory": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int64, c_int64_p]),
     "efe_last_error": (ctypes.c_char_p, [ctypes.c_void_p]),
     "efe_destroy": (None, [ctypes.c_void_p]),
 }
@@ -260,6 +261,13 @@ class Context:
     def _check(self, st):
         if st != 0:
             raise EFEError(st, lib().efe_last_error(self.h).decode())
+
+    def memory(self, limit=None):
+        """Device bytes the context holds; `limit` (0: none) bounds them from now on."""
+        held = ctypes.c_int64()
+        self._check(lib().efe_memory(self.h, -1 if limit is None else int(limit),
+                                     ctypes.byref(held)))
+        return held.value
 
     def close(self):
         if getattr(self, "h", None):

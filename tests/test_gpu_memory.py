@@ -1,0 +1,123 @@
+"""Device memory of a context (efe_memory): what it can do without is given back
+when an allocation needs the room, and every call gives the same result with the
+workspaces it can have as without them."""
+import numpy as np
+import pytest
+
+from paper_2607_06848_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def make(p=4, nq=None, ncell=8, **kw):
+    rng = np.random.default_rng(5)
+    w = dict(wl.PSP, lo=(0.0,) * 3, hi=(12.0,) * 3, ncell=(ncell,) * 3, p=p, nq=nq or p + 1,
+             xyz=rng.uniform(4.5, 7.5, (3, 3)), enr_lmax=1, enr_rcut=3.0, kb_rcut=3.0,
+             Zs=np.full(3, 4.0))
+    w.update(kw)
+    return w
+
+
+def block(ctx, cols, seed):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    V = torch.rand(ctx.rows, cols, dtype=torch.float64, device="cuda", generator=g) - 0.5
+    V[:ctx.n_nodes] *= torch.from_numpy(1.0 - ctx.tables()["boundary"]).cuda()[:, None]
+    return V
+
+
+def rel(a, b):
+    return float((a - b).abs().max() / b.abs().max())
+
+
+# roundings of one apply: as in the cell operator's test, on coupled rows too
+APPLY_TOL = 100 * 2.0 ** -53 * 8
+
+
+def test_held_counts_and_bound():
+    from paper_2607_06848_amd import efe
+    ctx = efe.Context(make())
+    h0 = ctx.memory()
+    ctx.set_potential(ctx.local_potential())
+    h1 = ctx.memory()
+    assert 0 < h0 < h1
+    X = block(ctx, 40, 1)
+    ctx.memory(h0)                       # no room, whatever is given back
+    with pytest.raises(efe.EFEError) as e:
+        ctx.rayleigh_ritz(X.clone())
+    assert e.value.status == -2
+    ctx.memory(0)
+    h2 = ctx.memory()
+    assert h0 < h2 < h1
+    ctx.rayleigh_ritz(X)
+    assert ctx.memory() > h2
+    ctx.set_potential(ctx.local_potential())
+    ctx.close()
+
+
+@pytest.mark.parametrize("cols", [3, 40])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_apply_without_cell_products(cols, prec):
+    """The cells' products refused: eight launches of cells in place of one, with
+    the coupling of enrichment and projectors beside them."""
+    from paper_2607_06848_amd import efe
+    ctx = efe.Context(make())
+    ctx.set_potential(ctx.local_potential(), 1 << efe.EFE_FP32)
+    X = block(ctx, cols, 2)
+    kind = "cell" if cols > 16 else "cell_narrow"
+    ctx.timing(True)
+    ref = ctx.apply_H_prec(X, prec)
+    assert ctx.timing_get(kind)[0] == 1
+    ctx.close()
+    ctx = efe.Context(make())
+    ctx.set_potential(ctx.local_potential(), 1 << efe.EFE_FP32)
+    yc = ctx.n_cells * ctx.nloc * cols * 8
+    ctx.memory(ctx.memory() + yc // 2)   # the other workspaces are far smaller
+    ctx.timing(True)
+    got = [ctx.apply_H_prec(X, prec) for _ in range(2)]
+    assert ctx.timing_get(kind)[0] == 16
+    assert rel(got[0], ref) < APPLY_TOL and rel(got[1], ref) < APPLY_TOL
+    # narrower applies find room, and keep it beside the refusal of the wide one
+    narrow = [ctx.apply_H_prec(X[:, :1].contiguous(), prec), ctx.apply_H_prec(X, prec)]
+    assert rel(narrow[0], ref[:, :1]) < APPLY_TOL and rel(narrow[1], ref) < APPLY_TOL
+    ctx.timing(True)
+    ctx.apply_H_prec(X[:, :1].contiguous(), prec)
+    assert ctx.timing_get("cell_narrow")[0] == 1
+    ctx.close()
+
+
+def test_spare_memory_makes_room():
+    """A block that fits only once the cells' products and the inputs of the
+    operators are given back; the next potential and the next apply follow."""
+    import torch
+    from paper_2607_06848_amd import efe
+    w = make()
+    ctx = efe.Context(w)
+    vq = ctx.local_potential()
+    ctx.set_potential(vq)
+    V0 = block(ctx, 60, 3)
+    X = block(ctx, 160, 4)
+    ref = ctx.apply_H(X)
+    before = ctx.memory()
+    V = V0.clone()
+    lam_ref, _ = ctx.rayleigh_ritz(V)
+    ctx.close()
+    ctx = efe.Context(w)
+    ctx.set_potential(vq)
+    base = ctx.memory()
+    ctx.apply_H(X)
+    assert ctx.memory() == before
+    # the Rayleigh-Ritz workspaces alone: more than what is left
+    ctx.memory(before + (1 << 20))
+    V = V0.clone()
+    lam, _ = ctx.rayleigh_ritz(V)
+    assert ctx.memory() <= before + (1 << 20)
+    # the Ritz value parity bound
+    assert float((lam - lam_ref).abs().max()) < 1e-9 * float(lam_ref.abs().max())
+    assert rel(ctx.apply_H(X), ref) < APPLY_TOL
+    ctx.memory(0)
+    ctx.set_potential(vq)
+    assert rel(ctx.apply_H(X), ref) < APPLY_TOL
+    assert ctx.memory() > base
+    torch.cuda.synchronize()
+    ctx.close()
