@@ -509,6 +509,21 @@ efe_status efe_couple_projectors(efe_ctx *c) {
   return EFE_OK;
 }
 
+// memory of efe_couple_build
+efe_status efe_couple_alloc(efe_ctx *c, bool want32) {
+  efe_status s;
+  CoupleSet &E = c->cpl_e;
+  const int64_t n = (int64_t)c->natoms * (c->nf + (c->nproj ? 1 : 0));
+  if (n == 0) return EFE_OK;
+  if (!c->d_S && (s = efe_alloc(c, (void **)&c->d_S, n * n * 8))) return s;
+  if (c->nf == 0 || E.n_boxpairs == 0) return EFE_OK;
+  if (!E.d_T1 && (s = efe_alloc(c, (void **)&E.d_T1, E.brick_tile * 8))) return s;
+  if (!E.d_T2 && (s = efe_alloc(c, (void **)&E.d_T2, E.box_tile * 8))) return s;
+  if (want32 && !E.d_T1f && (s = efe_alloc(c, (void **)&E.d_T1f, E.brick_tile * 4))) return s;
+  if (want32 && !E.d_T2f && (s = efe_alloc(c, (void **)&E.d_T2f, E.box_tile * 4))) return s;
+  return EFE_OK;
+}
+
 // blocks of E from the per-cell E_c (d_Epair), H^E_ee and the matrix of the
 // coefficients, for a new potential
 efe_status efe_couple_build(efe_ctx *c, bool want32) {
@@ -518,12 +533,7 @@ efe_status efe_couple_build(efe_ctx *c, bool want32) {
   const int nx = c->nf + (c->nproj ? 1 : 0);
   const int64_t n = (int64_t)c->natoms * nx;
   if (n == 0) return EFE_OK;
-  if (!c->d_S && (s = efe_alloc(c, (void **)&c->d_S, n * n * 8))) return s;
   if (c->nf > 0 && E.n_boxpairs > 0) {
-    if (!E.d_T1 && (s = efe_alloc(c, (void **)&E.d_T1, E.brick_tile * 8))) return s;
-    if (!E.d_T2 && (s = efe_alloc(c, (void **)&E.d_T2, E.box_tile * 8))) return s;
-    if (want32 && !E.d_T1f && (s = efe_alloc(c, (void **)&E.d_T1f, E.brick_tile * 4))) return s;
-    if (want32 && !E.d_T2f && (s = efe_alloc(c, (void **)&E.d_T2f, E.box_tile * 4))) return s;
     const size_t lds = box_lds(c, c->nf);
     HIPCHK(c, hipFuncSetAttribute((const void *)k_hee_box, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds));

@@ -290,6 +290,7 @@ efe_status efe_tp_apply(efe_ctx *ctx, const double *X, int64_t ldx, bool minv, i
 efe_status efe_couple_setup(efe_ctx *ctx, const std::vector<int32_t> &eptr,
                             const std::vector<int32_t> &ecells);
 efe_status efe_couple_projectors(efe_ctx *ctx);
+efe_status efe_couple_alloc(efe_ctx *ctx, bool want32);
 efe_status efe_couple_build(efe_ctx *ctx, bool want32);
 void efe_couple_free(efe_ctx *ctx);
 efe_status efe_symmetrize(efe_ctx *ctx, int64_t n, double *A);

@@ -1107,8 +1107,9 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
   const int nf = c->nf;
   const int64_t ne = c->n_enr;
   const int64_t tiles = c->n_cells * c->RB * c->KS * 64;
+  // every allocation before the first launch: a call that fails for memory
+  // leaves the operators of the potential before it whole
   if (!c->d_vq && (s = efe_alloc(c, (void **)&c->d_vq, c->n_qpts * 8))) return s;
-  k_copy<<<cdiv(c->n_qpts, 256), 256, 0, c->stream>>>(c->n_qpts, vq, c->d_vq);
   const bool want32 = precisions & (1 << EFE_FP32);
   const bool want16 = precisions & (1 << EFE_BF16);
   // dense cell Hamiltonians: for E_c, and where an apply takes them (Gauss rules
@@ -1121,6 +1122,15 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
   const int KQ8 = (int)cdiv(cdiv(c->nqp, 4), 8) * 8;   // quadrature k steps, padded
   const size_t shm = (size_t)KQ8 * 64 * 8;
   if (shm > 64 * 1024) EFE_FAIL(c, EFE_EINVAL, "too many Gauss points per cell");
+  if (nf > 0 && c->npairs > 0) {
+    const size_t pb = (size_t)c->npairs * c->nloc * nf * 8;   // support pairs
+    if (!c->d_B_pair && (s = efe_alloc(c, (void **)&c->d_B_pair, pb))) return s;
+    if (!c->d_Epair && (s = efe_alloc(c, (void **)&c->d_Epair, (size_t)c->ncpairs * c->nloc * nf * 8)))
+      return s;
+  }
+  if (ne && !c->d_Hee && (s = efe_alloc(c, (void **)&c->d_Hee, ne * ne * 8))) return s;
+  if ((s = efe_couple_alloc(c, want32))) return s;
+  k_copy<<<cdiv(c->n_qpts, 256), 256, 0, c->stream>>>(c->n_qpts, vq, c->d_vq);
   if (dense)
     k_build_hcell<<<c->n_cells * c->RB, 256, shm, c->stream>>>(
         c->nloc, c->nqp, c->RB, c->KS, KQ8, c->d_N3, c->d_W3, c->d_K, c->d_vq, c->d_Htile64,
@@ -1132,10 +1142,6 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
   c->have16 = want16;
   if (nf > 0 && c->npairs > 0) {
     const int64_t ns = c->n_snodes * nf;
-    const size_t pb = (size_t)c->npairs * c->nloc * nf * 8;   // support pairs
-    if (!c->d_B_pair && (s = efe_alloc(c, (void **)&c->d_B_pair, pb))) return s;
-    if (!c->d_Epair && (s = efe_alloc(c, (void **)&c->d_Epair, (size_t)c->ncpairs * c->nloc * nf * 8)))
-      return s;
     k_copy<<<cdiv(ns, 256), 256, 0, c->stream>>>(ns, c->d_Bkin_am, c->d_B_am);
     const int KQ = (int)cdiv(c->nqp, 4);
 #define GO(P)                                                                                  \
@@ -1166,7 +1172,6 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
         c->d_cell_epair, c->d_cpair_lmap, c->d_cpair_spair, c->d_C_am, c->d_B_pair, c->d_Epair);
   }
   if (ne) {
-    if (!c->d_Hee && (s = efe_alloc(c, (void **)&c->d_Hee, ne * ne * 8))) return s;
     if (nf > 0 && c->npairs > 0)
       k_hee_rows<<<ne, 256, ne * 8, c->stream>>>(nf, ne, c->d_snode_ptr, c->d_snode, c->d_nm_ptr,
                                                  c->d_nm_atom, c->d_nm_src, c->d_C_am, c->d_B_am,

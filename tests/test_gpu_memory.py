@@ -121,3 +121,26 @@ def test_spare_memory_makes_room():
     assert ctx.memory() > base
     torch.cuda.synchronize()
     ctx.close()
+
+
+def test_potential_refused_for_memory():
+    """A potential that fails for memory leaves the operators of the one before."""
+    from paper_2607_06848_amd import efe
+    ctx = efe.Context(make())
+    vq = ctx.local_potential()
+    ctx.set_potential(vq)
+    X = block(ctx, 20, 6)
+    ref = ctx.apply_H(X)
+    # room for nothing: the FP32 blocks of the second call are refused
+    ctx.memory(1)
+    with pytest.raises(efe.EFEError) as e:
+        ctx.set_potential(2.0 * vq + 0.5, 1 << efe.EFE_FP32)
+    assert e.value.status == -2
+    ctx.memory(0)
+    assert rel(ctx.apply_H(X), ref) < APPLY_TOL
+    with pytest.raises(efe.EFEError) as e:
+        ctx.apply_H_prec(X, efe.EFE_FP32)
+    assert e.value.status == -6
+    ctx.set_potential(2.0 * vq + 0.5, 1 << efe.EFE_FP32)
+    assert rel(ctx.apply_H(X), ref) > 1e-3
+    ctx.close()
