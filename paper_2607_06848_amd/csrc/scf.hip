@@ -324,7 +324,7 @@ __global__ __launch_bounds__(256) void k_stiff_cells(StiffArgs a) {
   if (a.it >= 0) {
     const double *cur = a.part + (a.it & 1) * 2 * CG_NP;
     const double2 s = cg_sums(cur, cur + CG_NP, red);
-    if (s.x <= a.sc[2]) {
+    if (a.sc[0] != 0.0 || s.x <= a.sc[2]) {
       if (blockIdx.x == 0 && t == 0) a.sc[0] = 1.0;
       return;
     }
@@ -479,7 +479,9 @@ __global__ __launch_bounds__(256) void k_cg_init(GridDims d, const double *__res
 }
 
 // b.b and the stopping threshold before the first iteration (start), or the
-// stopping test after a batch of iterations
+// stopping test after a batch of iterations.  A source that is not a number
+// counts as met at the start: no iteration runs, and phi keeps its values for
+// the next source.
 __global__ __launch_bounds__(256) void k_cg_check(const double *__restrict__ part, int it,
                                                   double rtol, bool start, double *sc) {
   __shared__ double red[8];
@@ -488,11 +490,13 @@ __global__ __launch_bounds__(256) void k_cg_check(const double *__restrict__ par
   if (threadIdx.x != 0) return;
   if (start) {
     const double tb = rtol * sqrt(s.y);
+    sc[0] = s.x > tb * tb ? 0.0 : 1.0;
     sc[1] = 0.0;
     sc[2] = tb * tb;
     sc[3] = s.y;
+  } else if (s.x <= sc[2]) {
+    sc[0] = 1.0;
   }
-  sc[0] = s.x <= sc[2] ? 1.0 : 0.0;
 }
 
 // alpha = r.z / p.Ap; phi += alpha p, r -= alpha Ap with Ap summed from the
@@ -511,7 +515,7 @@ __global__ __launch_bounds__(512) void k_cg_update(GridDims d, const double *__r
   const double *cur = part + (it & 1) * 2 * CG_NP;
   double *nxt = part + (1 - (it & 1)) * 2 * CG_NP;
   const double2 s = cg_sums(cur, cur + CG_NP, red);
-  if (s.x <= sc[2]) {
+  if (sc[0] != 0.0 || s.x <= sc[2]) {
     if (threadIdx.x == 0) {
       nxt[blockIdx.x] = cur[blockIdx.x];
       nxt[CG_NP + blockIdx.x] = cur[CG_NP + blockIdx.x];
