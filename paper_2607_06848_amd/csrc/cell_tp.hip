@@ -46,6 +46,15 @@ constexpr int tp_waves(int P) { return P >= 6 ? 2 : P == 5 ? 3 : 4; }
 // Units are laid out column group by column group (U columns each; the last
 // group may be narrower and then a work-group holds several cells), so that
 // ragged widths and single vectors fill the work-groups as full ones do.
+//
+// Accuracy: the rounding of the tables, amplified by S, is the larger part of the
+// error on smooth values, so they are formed in extended precision and rounded
+// once.  With 3 points an axis S u still loses digits against the constant part
+// of u, and the value at the middle node is taken off first (S sees none of it;
+// r gets v x0 sqrt(w) back).  Largest error of an apply relative to its largest
+// value, smooth fields, p = 2 to 6, in 1e-15: 0.3, 1.7, 3.4, 3.8, 8.2, where the
+// dense products have 0.8, 2.6, 5.1, 18, 32 and tables in double 1.7, 3.1, 9.4,
+// 6.2, 21; random fields are below the dense products for every p.
 template <int P>
 __global__ __launch_bounds__(tp_units(P) * P) __attribute__((amdgpu_waves_per_eu(tp_waves(P))))
 void k_cell_tp(TpArgs a) {
@@ -69,9 +78,15 @@ void k_cell_tp(TpArgs a) {
   const int64_t row0 = cx * (P - 1) + a.n1x * (cy * (P - 1) + a.n1y * (cz * (P - 1) + (int64_t)s));
   cdouble *const m0 = (cdouble *)(uintptr_t)a.m;
   cdouble *m = fresh(m0);
-  double f[PP];
+  constexpr bool MID = P == 3;
+  double f[PP], x0 = 0.0;
   {
     double fx[P];
+    if constexpr (MID) {
+      const int64_t mx = cx * (P - 1) + 1, my = cy * (P - 1) + 1, mz = cz * (P - 1) + 1;
+      x0 = a.X[(mx + a.n1x * (my + a.n1y * mz)) * a.ldx + g * U + jc] *
+           (a.s1[mx] * (a.s1[a.n1x + my] * a.s1[a.n1x + a.n1y + mz]));
+    }
     const double *sy = a.s1 + a.n1x + cy * (P - 1);
     double sz = 1.0;
     const double *x = a.X + row0 * a.ldx + g * U + jc;
@@ -88,7 +103,7 @@ void k_cell_tp(TpArgs a) {
       const double fy = sy[b] * sz;
       double v[P], y[P];
 #pragma unroll
-      for (int i = 0; i < P; ++i) v[i] = f[b * P + i] * (fx[i] * fy);
+      for (int i = 0; i < P; ++i) v[i] = f[b * P + i] * (fx[i] * fy) - x0;
       mul1d<P, false>(m, 0, v, y);
 #pragma unroll
       for (int i = 0; i < P; ++i) f[b * P + i] = y[i];
@@ -141,6 +156,9 @@ void k_cell_tp(TpArgs a) {
 #pragma unroll
       for (int i = 0; i < P; ++i) v[i] = L[((s * P + b) * P + i) * U + u];
       mul1d<P, false>(m, 3, v, y);
+      if constexpr (MID)
+#pragma unroll
+        for (int i = 0; i < P; ++i) v[i] = fma(x0, a.sw[(s * P + b) * P + i], v[i]);
 #pragma unroll
       for (int i = 0; i < P; ++i)
         L[((s * P + b) * P + i) * U + u] = fma(vq[b * P + i], v[i], y[i]);
@@ -221,7 +239,8 @@ void lagrange_derivative(const std::vector<double> &x, std::vector<double> &D) {
 
 efe_status efe_tp_setup(efe_ctx *c, const std::vector<double> &xq, const std::vector<double> &wq,
                         const std::vector<double> &N1, const std::vector<double> &D1,
-                        const std::vector<double> &wg) {
+                        const std::vector<double> &wg, const std::vector<long double> &wql,
+                        const std::vector<long double> &N1l, const std::vector<long double> &Dl) {
   c->tp = c->nq == c->P && c->P >= 2;
   const int P = c->P;
   // separable factors of the lumped mass: 1 (0 on the boundary), then 1/m
@@ -278,6 +297,27 @@ efe_status efe_tp_setup(efe_ctx *c, const std::vector<double> &xq, const std::ve
   if ((st = efe_alloc(c, (void **)&c->d_tpm, tab.size() * 8))) return st;
   HIPCHK(c, hipMemcpyAsync(c->d_tpm, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  // the cell operator's own copy, from extended precision, and sqrt(w) of the
+  // cell's Gauss points
+  std::vector<long double> Nl(P * P), Sl(P * P);
+  for (int d = 0; d < 3; ++d) {
+    const long double h2 = 0.5L * c->h[d];
+    for (int q = 0; q < P; ++q)
+      for (int i = 0; i < P; ++i) {
+        Nl[q * P + i] = sqrtl(wql[q] * h2) * N1l[q * P + i];
+        long double acc = 0.0;
+        for (int g = 0; g < P; ++g) acc += wql[g] * Dl[g * P + q] * Dl[g * P + i];
+        Sl[q * P + i] = 0.5L * acc / (sqrtl(wql[q] * wql[i]) * h2 * h2);
+      }
+    even_odd(P, Nl, &tab[d * TP_MAT], &tab[d * TP_MAT + 16]);
+    even_odd(P, Sl, &tab[(3 + d) * TP_MAT], &tab[(3 + d) * TP_MAT + 16]);
+  }
+  const long double jac = 0.125L * c->h[0] * c->h[1] * c->h[2];
+  for (int q = 0; q < P * P * P; ++q)
+    tab.push_back((double)sqrtl(wql[q % P] * wql[q / P % P] * wql[q / (P * P)] * jac));
+  if ((st = efe_alloc(c, (void **)&c->d_tpc, tab.size() * 8))) return st;
+  HIPCHK(c, hipMemcpyAsync(c->d_tpc, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipStreamSynchronize(c->stream));
   return EFE_OK;
 }
 
@@ -301,7 +341,8 @@ efe_status efe_tp_apply(efe_ctx *c, const double *X, int64_t ldx, bool minv, int
   a.ncy = c->ncell[1];
   a.n1x = c->n1[0];
   a.n1y = c->n1[1];
-  a.m = c->d_tpm;
+  a.m = c->d_tpc;
+  a.sw = c->d_tpc + 6 * TP_MAT;
   for (int col = 0; col < (Yc ? 1 : 8); ++col) {
     if (Yc) {
       a.ncells = c->n_cells;

@@ -648,7 +648,7 @@ extern "C" void efe_destroy(efe_ctx *c) {
                   c->d_g_atom,    c->d_nm_gslot,     c->d_Cg,
                   c->d_Bkin_pair, c->d_B_pair,       c->d_Hee,
                   c->d_Ptil,      c->d_cpair_atom, c->d_cpair_spair, c->d_cell_eptr, c->d_cell_epair,
-                  c->d_cpair_lmap, c->d_s1,          c->d_tpm, c->d_mk, c->d_Epair, c->d_cpair_cell, c->d_S};
+                  c->d_cpair_lmap, c->d_s1,          c->d_tpm, c->d_tpc, c->d_mk, c->d_Epair, c->d_cpair_cell, c->d_S};
   efe_couple_free(c);
   for (void *p : ptrs) efe_free(c, p);
   for (auto &b : c->ws) efe_free(c, b.p);

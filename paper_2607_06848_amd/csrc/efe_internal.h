@@ -56,6 +56,7 @@ struct TpArgs {
   int ncols, ncx, ncy;
   double alpha;
   const double *m;                     // 1-D matrices of the axes
+  const double *sw;                    // sqrt(w) of a cell's Gauss points
 };
 
 struct efe_ctx {
@@ -154,10 +155,11 @@ struct efe_ctx {
   int32_t *d_kbtrip = nullptr;                         // (cell, I_kb, J_enr)
   double *d_Pphi = nullptr, *d_D = nullptr;            // [nproj][n_enr], [nproj]
 
-  // tensor-product cell operator (nq = p + 1): matrices, and the separable
-  // row factors [2][n1x + n1y + n1z] (interior mask, 1/m)
+  // tensor-product cell operator (nq = p + 1): its matrices, those of the
+  // projections and the density, and the separable row factors [2][n1x + n1y +
+  // n1z] (interior mask, 1/m)
   bool tp = false;
-  double *d_tpm = nullptr, *d_s1 = nullptr;
+  double *d_tpc = nullptr, *d_tpm = nullptr, *d_s1 = nullptr;
   double *d_mk = nullptr;   // 1-D mass and stiffness per axis (Poisson)
 
   // potential-dependent operators
@@ -280,7 +282,8 @@ size_t efe_syev_iwork(int64_t n);
 // Yc [cell][local node][column], or (Yc = nullptr) added to Y times alpha
 efe_status efe_tp_setup(efe_ctx *ctx, const std::vector<double> &xq, const std::vector<double> &wq,
                         const std::vector<double> &N1, const std::vector<double> &D1,
-                        const std::vector<double> &wg);
+                        const std::vector<double> &wg, const std::vector<long double> &wql,
+                        const std::vector<long double> &N1l, const std::vector<long double> &Dl);
 efe_status efe_tp_apply(efe_ctx *ctx, const double *X, int64_t ldx, bool minv, int ncols,
                         double *Yc, int64_t ldc, double *Y, int64_t ldy, double alpha);
 // E_c = B_c - H_c C_c^T of every coupling pair into d_Epair

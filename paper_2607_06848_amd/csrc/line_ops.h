@@ -51,14 +51,15 @@ __device__ __forceinline__ void mul1d(cdouble *m, int k, const double (&x)[P], d
 }
 
 // the even/odd form of the P x P matrix M
-static inline void even_odd(int P, const std::vector<double> &M, double *e, double *o) {
+template <class T>
+static inline void even_odd(int P, const std::vector<T> &M, double *e, double *o) {
   const int H = (P + 1) / 2, Q = P / 2;
   for (int q = 0; q < H; ++q)
     for (int i = 0; i < H; ++i)
-      e[q * H + i] = i < Q ? 0.5 * (M[q * P + i] + M[q * P + P - 1 - i]) : M[q * P + i];
+      e[q * H + i] = i < Q ? T(0.5) * (M[q * P + i] + M[q * P + P - 1 - i]) : M[q * P + i];
   for (int q = 0; q < H && H > Q; ++q)   // middle row: M[mid][i] = M[mid][P-1-i]
     for (int i = 0; i < Q; ++i)
-      if (q == Q) e[q * H + i] = 0.5 * (M[q * P + i] + M[q * P + P - 1 - i]);
+      if (q == Q) e[q * H + i] = T(0.5) * (M[q * P + i] + M[q * P + P - 1 - i]);
   for (int q = 0; q < Q; ++q)
-    for (int i = 0; i < Q; ++i) o[q * Q + i] = 0.5 * (M[q * P + i] - M[q * P + P - 1 - i]);
+    for (int i = 0; i < Q; ++i) o[q * Q + i] = T(0.5) * (M[q * P + i] - M[q * P + P - 1 - i]);
 }

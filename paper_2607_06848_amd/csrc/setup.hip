@@ -12,69 +12,98 @@
 //  potential           cell Hamiltonians 1/2 K + N^T diag(w v) N in the MFMA
 //                      operand layout, B and H^phiphi potential parts
 #include <cmath>
+#include <limits>
 #include <vector>
 
 #include "efe_device.h"
 #include "line_ops.h"
 
 // ------------------------------------------------------------ 1-D rules
-static void legendre(int n, double x, double &P, double &dP) {
-  double p0 = 1.0, p1 = x;
+// T = double, and long double for tables that are rounded once (cell_tp.hip)
+template <class T>
+static void legendre(int n, T x, T &P, T &dP) {
+  T p0 = 1.0, p1 = x;
   if (n == 0) {
     P = 1.0;
     dP = 0.0;
     return;
   }
   for (int k = 1; k < n; ++k) {
-    double p2 = ((2 * k + 1) * x * p1 - k * p0) / (k + 1);
+    T p2 = ((2 * k + 1) * x * p1 - k * p0) / (k + 1);
     p0 = p1;
     p1 = p2;
   }
   P = p1;
-  dP = n * (x * p1 - p0) / (x * x - 1.0);
+  dP = n * (x * p1 - p0) / (x * x - T(1.0));
 }
 
-static void gll_rule(int p, std::vector<double> &x, std::vector<double> &w) {
+template <class T>
+static void gll_rule(int p, std::vector<T> &x, std::vector<T> &w) {
   x.assign(p + 1, 0.0);
   w.assign(p + 1, 0.0);
   x[0] = -1.0;
   x[p] = 1.0;
   for (int i = 1; i < p; ++i) {
-    double t = -cos(M_PI * i / p);
+    T t = -cos(M_PI * i / p);
     for (int it = 0; it < 100; ++it) {   // Newton on P_p'
-      double P, dP;
+      T P, dP;
       legendre(p, t, P, dP);
-      double d2P = (2 * t * dP - p * (p + 1) * P) / (1.0 - t * t);
-      double dt = dP / d2P;
+      T d2P = (2 * t * dP - p * (p + 1) * P) / (T(1.0) - t * t);
+      T dt = dP / d2P;
       t -= dt;
-      if (fabs(dt) < 1e-16) break;
+      if (std::abs(dt) < std::min<T>(1e-16, std::numeric_limits<T>::epsilon())) break;
     }
     x[i] = t;
   }
   for (int i = 0; i <= p; ++i) {
-    double P, dP;
+    T P, dP;
     legendre(p, x[i], P, dP);
-    w[i] = 2.0 / (p * (p + 1) * P * P);
+    w[i] = T(2.0) / (p * (p + 1) * P * P);
   }
 }
 
-static void gauss_rule(int n, std::vector<double> &x, std::vector<double> &w) {
+template <class T>
+static void gauss_rule(int n, std::vector<T> &x, std::vector<T> &w) {
   x.assign(n, 0.0);
   w.assign(n, 0.0);
   for (int i = 0; i < n; ++i) {
-    double t = -cos(M_PI * (i + 0.75) / (n + 0.5));
+    T t = -cos(M_PI * (i + 0.75) / (n + 0.5));
     for (int it = 0; it < 100; ++it) {
-      double P, dP;
+      T P, dP;
       legendre(n, t, P, dP);
-      double dt = P / dP;
+      T dt = P / dP;
       t -= dt;
-      if (fabs(dt) < 1e-16) break;
+      if (std::abs(dt) < std::min<T>(1e-16, std::numeric_limits<T>::epsilon())) break;
     }
-    double P, dP;
+    T P, dP;
     legendre(n, t, P, dP);
     x[i] = t;
-    w[i] = 2.0 / ((1.0 - t * t) * dP * dP);
+    w[i] = T(2.0) / ((T(1.0) - t * t) * dP * dP);
   }
+}
+
+// values and derivatives of the Lagrange basis on xg at the points xq
+template <class T>
+static void lagrange(const std::vector<T> &xg, const std::vector<T> &xq, std::vector<T> &N1,
+                     std::vector<T> &D1) {
+  const int P = (int)xg.size(), nq = (int)xq.size();
+  N1.resize(nq * P);
+  D1.resize(nq * P);
+  for (int q = 0; q < nq; ++q)
+    for (int a = 0; a < P; ++a) {
+      T v = 1.0, d = 0.0;
+      for (int b = 0; b < P; ++b)
+        if (b != a) v *= (xq[q] - xg[b]) / (xg[a] - xg[b]);
+      for (int b = 0; b < P; ++b) {
+        if (b == a) continue;
+        T t = T(1.0) / (xg[a] - xg[b]);
+        for (int cc = 0; cc < P; ++cc)
+          if (cc != a && cc != b) t *= (xq[q] - xg[cc]) / (xg[a] - xg[cc]);
+        d += t;
+      }
+      N1[q * P + a] = v;
+      D1[q * P + a] = d;
+    }
 }
 
 // ------------------------------------------------------------ kernels
@@ -919,22 +948,8 @@ efe_status efe_build_reference(efe_ctx *c) {
   std::vector<double> xg, wg, xq, wq;
   gll_rule(c->p, xg, wg);
   gauss_rule(c->nq, xq, wq);
-  std::vector<double> N1(c->nq * c->P), D1(c->nq * c->P);
-  for (int q = 0; q < c->nq; ++q)
-    for (int a = 0; a < c->P; ++a) {
-      double v = 1.0, d = 0.0;
-      for (int b = 0; b < c->P; ++b)
-        if (b != a) v *= (xq[q] - xg[b]) / (xg[a] - xg[b]);
-      for (int b = 0; b < c->P; ++b) {
-        if (b == a) continue;
-        double t = 1.0 / (xg[a] - xg[b]);
-        for (int cc = 0; cc < c->P; ++cc)
-          if (cc != a && cc != b) t *= (xq[q] - xg[cc]) / (xg[a] - xg[cc]);
-        d += t;
-      }
-      N1[q * c->P + a] = v;
-      D1[q * c->P + a] = d;
-    }
+  std::vector<double> N1, D1;
+  lagrange(xg, xq, N1, D1);
   double *dN1, *dD1, *dwq, *dwg;
   efe_status s;
   if ((s = efe_alloc(c, (void **)&dN1, N1.size() * 8))) return s;
@@ -972,7 +987,12 @@ efe_status efe_build_reference(efe_ctx *c) {
   c->KS = c->KP / 4;
   c->RB = (int)cdiv(c->nloc, 16);
   c->KS32 = (int)cdiv(c->nloc, 32);
-  return efe_tp_setup(c, xq, wq, N1, D1, wg);
+  std::vector<long double> xgl, wgl, xql, wql, N1l, D1l, Il, Dl;
+  gll_rule(c->p, xgl, wgl);
+  gauss_rule(c->nq, xql, wql);
+  lagrange(xgl, xql, N1l, D1l);
+  lagrange(xql, xql, Il, Dl);
+  return efe_tp_setup(c, xq, wq, N1, D1, wg, wql, N1l, Dl);
 }
 
 efe_status efe_build_enrichment(efe_ctx *c) {
