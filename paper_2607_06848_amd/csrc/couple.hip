@@ -130,18 +130,17 @@ struct EntryLoad {
 // of the lane), the A operand of v_mfma_*_16x16x4.  The FP32 copy has rows
 // 4 a + b and 4 b + a exchanged, so that the accumulators of both precisions
 // hold the same nodes.  One wave per 16-row block.
-__global__ __launch_bounds__(256) void k_tiles_brick(Entries s, const int32_t *__restrict__ ptr,
-                                                     const int32_t *__restrict__ atom,
-                                                     const int64_t *__restrict__ off,
-                                                     double *__restrict__ T64,
-                                                     float *__restrict__ T32) {
-  const int64_t b = blockIdx.x;
+__device__ __forceinline__ void tiles_brick(const Entries &s, int64_t b,
+                                            const int32_t *__restrict__ ptr,
+                                            const int32_t *__restrict__ atom,
+                                            const int64_t *__restrict__ off,
+                                            double *__restrict__ T64, float *__restrict__ T32,
+                                            int32_t *tab /* 16 atoms */) {
   const int a0 = ptr[b], na = ptr[b + 1] - a0;
   if (na == 0) return;
   const int K = na * s.nf, KS = (K + 3) / 4;
   const int rb = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
   const int nc = box_cells(BK, s.g.p), n3 = nc * nc * nc;
-  extern __shared__ int32_t tab[];   // 16 atoms
   int o[3], ijk[3];
   box_origin(s.g, BK, b, o);
   const bool in = box_node(s.g, BK, o, 16 * rb + li, ijk);
@@ -178,17 +177,18 @@ __global__ __launch_bounds__(256) void k_tiles_brick(Entries s, const int32_t *_
 }
 
 // Boxes: tile[rb][ks][lane] = entry(function 16 rb + lane%16, node 4 ks +
-// lane/16); live: bit c set where the nodes 16 c .. hold a non-zero entry
-__global__ __launch_bounds__(256) void k_tiles_box(Entries s, const int32_t *__restrict__ ptr,
-                                                   const int32_t *__restrict__ atom,
-                                                   const int32_t *__restrict__ rboff,
-                                                   const int32_t *__restrict__ rbbox,
-                                                   double *__restrict__ T64,
-                                                   float *__restrict__ T32,
-                                                   uint32_t *__restrict__ live) {
-  __shared__ uint32_t mask;
-  extern __shared__ int32_t tab[];   // the atoms of 16 functions
-  const int64_t row = blockIdx.x;
+// lane/16); live: bit c set where the nodes 16 c .. hold a non-zero entry.  One
+// work-group per block and part of its nodes (1, or 4 that write a byte of live
+// each), U entries of a wave in flight.
+template <int U, int PARTS>
+__device__ __forceinline__ void tiles_box(const Entries &s, int64_t row, int part,
+                                          const int32_t *__restrict__ ptr,
+                                          const int32_t *__restrict__ atom,
+                                          const int32_t *__restrict__ rboff,
+                                          const int32_t *__restrict__ rbbox,
+                                          double *__restrict__ T64, float *__restrict__ T32,
+                                          uint32_t *__restrict__ live, uint32_t &mask,
+                                          int32_t *tab /* the atoms of 16 functions */) {
   const int b = rbbox[row], rb = (int)row - rboff[b];
   const int a0 = ptr[b], na = ptr[b + 1] - a0, K = na * s.nf;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
@@ -200,8 +200,9 @@ __global__ __launch_bounds__(256) void k_tiles_box(Entries s, const int32_t *__r
   box_pairs(s, atom + a0 + q0, min((16 * rb + 15) / s.nf + 1, na) - q0, o, nc, tab);
   __syncthreads();
   const int32_t *const ft = tab + (f / s.nf - q0) * n3;
-  constexpr int KS = BX * BX * BX / 4, U = 2;
-  for (int ks = wave; ks < KS; ks += 4 * U) {
+  constexpr int KS = BX * BX * BX / 4, KP = KS / PARTS;
+  static_assert(KS / 4 == 32 && (PARTS == 1 || PARTS == 4) && KP % (4 * U) == 0, "a byte a part");
+  for (int ks = part * KP + wave; ks < (part + 1) * KP; ks += 4 * U) {
     EntryLoad v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -216,11 +217,43 @@ __global__ __launch_bounds__(256) void k_tiles_box(Entries s, const int32_t *__r
       const int64_t at = (row * KS + ks + 4 * u) * 64 + lane;
       T64[at] = x;
       if (T32) T32[at] = (float)x;
-      if (__ballot(x != 0.0) && lane == 0) atomicOr(&mask, 1u << ((ks + 4 * u) / 4));
+      if (__ballot(x != 0.0) && lane == 0) atomicOr(&mask, 1u << ((ks + 4 * u) / 4 - KP / 4 * part));
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) live[row] = mask;
+  if (threadIdx.x != 0) return;
+  if (PARTS == 1) live[row] = mask;
+  else ((uint8_t *)live)[PARTS * row + part] = (uint8_t)mask;
+}
+
+// Both sets of one family of functions.  Few blocks (TILES_FEW): four work-groups a
+// block of a box, four entries in flight, and the bricks in the same launch, which
+// shortens the chain of loads (27 boxes: 15.6 us, 57 as below); many: two launches,
+// one work-group a block, two entries in flight, whose registers leave more waves
+// to cover the loads (64 atoms: 1.05 ms, 1.23 as above).
+constexpr int64_t TILES_FEW = 512;
+struct TileArgs {
+  Entries s;
+  const int32_t *bx_ptr, *bx_atom, *rboff, *rbbox, *bk_ptr, *bk_atom;
+  const int64_t *bk_off;
+  double *T1, *T2;
+  float *T1f, *T2f;
+  uint32_t *live;
+  int64_t n_rb;
+};
+template <int U, int PARTS, bool BRICKS>
+__global__ __launch_bounds__(256) void k_tiles(TileArgs a) {
+  __shared__ uint32_t mask;
+  extern __shared__ int32_t tab[];
+  const int64_t b = blockIdx.x, nb = PARTS * a.n_rb;
+  if constexpr (PARTS > 0)
+    if (b < nb) {
+      tiles_box<U, PARTS>(a.s, b / PARTS, (int)(b % PARTS), a.bx_ptr, a.bx_atom, a.rboff, a.rbbox,
+                          a.T2, a.T2f, a.live, mask, tab);
+      return;
+    }
+  if constexpr (BRICKS)
+    tiles_brick(a.s, b - nb, a.bk_ptr, a.bk_atom, a.bk_off, a.T1, a.T1f, tab);
 }
 
 // Second part of H^E_ee = H^phiphi - C B^T - E C^T (the first: k_hee_rows,
@@ -229,7 +262,11 @@ __global__ __launch_bounds__(256) void k_tiles_box(Entries s, const int32_t *__r
 // wave every fourth row block, and only the chunks of 16 nodes in which both have
 // entries; the 16 x 16 results are added into Hee atomically (64 atoms: 2.6 ms;
 // 4.2 with all chunks; 32 functions a work-group read E half as often but leave
-// one work-group a CU, whose fill of C nothing covers, 3.1).
+// one work-group a CU, whose fill of C nothing covers, 3.1).  gridDim.y parts of
+// the nodes: with few blocks (HEE_FEW) eight, whose loads behind each other are an
+// eighth (27 boxes: 56 us in one part); with many one, as every part adds its own
+// products atomically.
+constexpr int64_t HEE_FEW = 512;
 typedef double v4d_c __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void k_hee_box(Entries s, const int32_t *__restrict__ ptr,
                                                  const int32_t *__restrict__ atom,
@@ -258,7 +295,8 @@ __global__ __launch_bounds__(256) void k_hee_box(Entries s, const int32_t *__res
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
   const int f2 = 16 * cb + li;
   const int32_t *const ft = tab + (f2 / s.nf - q0) * n3;
-  for (int ks = wave; ks < KS; ks += 4 * U) {
+  const int ksp = KS / (int)gridDim.y, ks0 = (int)blockIdx.y * ksp;
+  for (int ks = ks0 + wave; ks < ks0 + ksp; ks += 4 * U) {
     EntryLoad v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -312,7 +350,7 @@ __global__ __launch_bounds__(256) void k_hee_box(Entries s, const int32_t *__res
 // Matrix of the dense part of an apply (apply.hip) over the coefficients
 // (I, k), k < nf the enrichment functions and (with projectors) k = nf the
 // projector of atom I: [[H^E_ee + P~^T D P~, P~^T D], [D P~, D]]; Hee holds the
-// projector term already.
+// projector term already, and is symmetrized here.
 __global__ void k_coef_matrix(int natoms, int nf, int nx, const double *__restrict__ Hee,
                               const double *__restrict__ Pt, const double *__restrict__ D,
                               double *__restrict__ S) {
@@ -323,7 +361,10 @@ __global__ void k_coef_matrix(int natoms, int nf, int nx, const double *__restri
   const int64_t I = r / nx, J = c / nx;
   const int k = (int)(r % nx), l = (int)(c % nx);
   double v;
-  if (k < nf && l < nf) v = Hee[(I * nf + k) * ne + J * nf + l];
+  if (k < nf && l < nf) {
+    const int64_t f = I * nf + k, h = J * nf + l;
+    v = 0.5 * (Hee[f * ne + h] + Hee[h * ne + f]);
+  }
   else if (k < nf) v = Pt[J * ne + I * nf + k] * D[J];
   else if (l < nf) v = Pt[I * ne + J * nf + l] * D[I];
   else v = I == J ? D[I] : 0.0;
@@ -458,9 +499,21 @@ size_t brick_lds(const efe_ctx *c) {
   const int n = box_cells(BK, c->p);
   return 16 * (size_t)(n * n * n) * 4;
 }
-size_t box_lds(const efe_ctx *c, int nf) {
-  const int n = box_cells(BX, c->p);
+size_t box_lds(int p, int nf) {
+  const int n = box_cells(BX, p);
   return std::min(16, 14 / nf + 2) * (size_t)(n * n * n) * 4;
+}
+void launch_tiles(efe_ctx *c, const CoupleSet &S, const Entries &e, bool f32) {
+  const TileArgs a{e,         S.d_bx_ptr, S.d_bx_atom, S.d_rboff, S.d_rbbox, S.d_bk_ptr,
+                   S.d_bk_atom, S.d_bk_off, S.d_T1,      S.d_T2,    f32 ? S.d_T1f : nullptr,
+                   f32 ? S.d_T2f : nullptr, S.d_live, S.n_rb};
+  const size_t l1 = brick_lds(c), l2 = box_lds(c->p, S.nf);
+  if (S.n_rb < TILES_FEW) {
+    k_tiles<4, 4, true><<<4 * S.n_rb + S.n_brick, 256, std::max(l1, l2), c->stream>>>(a);
+    return;
+  }
+  k_tiles<2, 1, false><<<S.n_rb, 256, l2, c->stream>>>(a);
+  k_tiles<2, 0, true><<<S.n_brick, 256, l1, c->stream>>>(a);
 }
 }  // namespace
 
@@ -471,6 +524,10 @@ efe_status efe_couple_setup(efe_ctx *c, const std::vector<int32_t> &eptr,
                             const std::vector<int32_t> &ecells) {
   efe_status s;
   CoupleSet &E = c->cpl_e, &K = c->cpl_k;
+  // the same bound for every context: what the lowest order and one function an
+  // atom need
+  HIPCHK(c, hipFuncSetAttribute((const void *)k_hee_box, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)box_lds(1, 1)));
   const std::vector<int32_t> none(c->natoms + 1, 0);
   if ((s = build_set(c, c->nf > 0 ? eptr : none, ecells, std::max(c->nf, 1), E))) return s;
   if ((s = build_set(c, c->nproj ? c->kb_ptr : none, c->kb_cells, 1, K))) return s;
@@ -501,10 +558,7 @@ efe_status efe_couple_projectors(efe_ctx *c) {
   CoupleSet &K = c->cpl_k;
   if (!c->nproj || K.n_boxpairs == 0) return EFE_OK;
   const Entries e = entries(c, K, nullptr, c->d_Pc_am, c->d_kbpair_lmap);
-  k_tiles_brick<<<K.n_brick, 256, brick_lds(c), c->stream>>>(e, K.d_bk_ptr, K.d_bk_atom, K.d_bk_off, K.d_T1,
-                                                 nullptr);
-  k_tiles_box<<<K.n_rb, 256, box_lds(c, 1), c->stream>>>(e, K.d_bx_ptr, K.d_bx_atom, K.d_rboff, K.d_rbbox,
-                                            K.d_T2, nullptr, K.d_live);
+  launch_tiles(c, K, e, false);
   HIPCHK(c, hipGetLastError());
   return EFE_OK;
 }
@@ -527,24 +581,16 @@ efe_status efe_couple_alloc(efe_ctx *c, bool want32) {
 // blocks of E from the per-cell E_c (d_Epair), H^E_ee and the matrix of the
 // coefficients, for a new potential
 efe_status efe_couple_build(efe_ctx *c, bool want32) {
-  efe_status s;
   CoupleSet &E = c->cpl_e;
   const int64_t ne = c->n_enr;
   const int nx = c->nf + (c->nproj ? 1 : 0);
   const int64_t n = (int64_t)c->natoms * nx;
   if (n == 0) return EFE_OK;
   if (c->nf > 0 && E.n_boxpairs > 0) {
-    const size_t lds = box_lds(c, c->nf);
-    HIPCHK(c, hipFuncSetAttribute((const void *)k_hee_box, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)lds));
     const Entries e = entries(c, E, c->d_Epair, nullptr, c->d_cpair_lmap);
-    k_tiles_box<<<E.n_rb, 256, lds, c->stream>>>(e, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
-                                                E.d_T2, want32 ? E.d_T2f : nullptr, E.d_live);
-    k_hee_box<<<E.n_rb, 256, lds, c->stream>>>(e, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox,
-                                              E.d_T2, E.d_live, c->d_C_am, ne, c->d_Hee);
-    k_tiles_brick<<<E.n_brick, 256, brick_lds(c), c->stream>>>(e, E.d_bk_ptr, E.d_bk_atom, E.d_bk_off, E.d_T1,
-                                                   want32 ? E.d_T1f : nullptr);
-    if ((s = efe_symmetrize(c, ne, c->d_Hee))) return s;
+    launch_tiles(c, E, e, want32);
+    k_hee_box<<<dim3(E.n_rb, E.n_rb < HEE_FEW ? 8 : 1), 256, box_lds(c->p, c->nf), c->stream>>>(
+        e, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox, E.d_T2, E.d_live, c->d_C_am, ne, c->d_Hee);
   }
   k_coef_matrix<<<cdiv(n * n, 256), 256, 0, c->stream>>>(c->natoms, c->nf, nx, c->d_Hee, c->d_Ptil,
                                                         c->d_D, c->d_S);

@@ -296,7 +296,6 @@ efe_status efe_couple_projectors(efe_ctx *ctx);
 efe_status efe_couple_alloc(efe_ctx *ctx, bool want32);
 efe_status efe_couple_build(efe_ctx *ctx, bool want32);
 void efe_couple_free(efe_ctx *ctx);
-efe_status efe_symmetrize(efe_ctx *ctx, int64_t n, double *A);
 // the workspace that may be missing (the cells' products): nullptr (no error)
 // when it does not fit
 constexpr int EFE_WS_SPARE = 15;

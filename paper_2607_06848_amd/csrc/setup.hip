@@ -643,7 +643,7 @@ __global__ __launch_bounds__(512) void k_build_E(
 
 // Rows of the enrichment block of the orthogonalized Hamiltonian without the
 // projectors, H^E_ee = H^phiphi - C B^T - E C^T (the expansion of T^T Hhat T
-// with E = B - C H^cc), first part: Hee = H^phiphi - C B^T, row f = (I, k)
+// with E = B - C H^cc), first part: Hee = H^phiphi (symmetrized) - C B^T, row f = (I, k)
 // summed over the support nodes of atom I and, at each node, the atoms whose
 // support holds it (B vanishes off the support).  C B^T cancels nearly all of
 // H^phiphi and what is left is magnified by (M~^ee)^-1, so a filter's output
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(256) void k_hee_rows(int nf, int64_t n_enr,
   }
   __syncthreads();
   for (int64_t i = threadIdx.x; i < n_enr; i += blockDim.x)
-    Hee[f * n_enr + i] = Hpp[f * n_enr + i] - acc[i];
+    Hee[f * n_enr + i] = 0.5 * (Hpp[f * n_enr + i] + Hpp[i * n_enr + f]) - acc[i];
 }
 
 // Projector rows in the orthogonalized basis: P~^phi = P^phi - P^C C^T
@@ -860,6 +860,20 @@ __global__ void k_fill(int64_t n, double v, double *__restrict__ x) {
 __global__ void k_copy(int64_t n, const double *__restrict__ a, double *__restrict__ b) {
   int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < n) b[i] = a[i];
+}
+
+// three copies in one launch
+__global__ void k_copy3(int64_t n0, const double *__restrict__ a0, double *__restrict__ b0,
+                        int64_t n1, const double *__restrict__ a1, double *__restrict__ b1,
+                        int64_t n2, const double *__restrict__ a2, double *__restrict__ b2) {
+  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i < n0) {
+    b0[i] = a0[i];
+  } else if ((i -= n0) < n1) {
+    b1[i] = a1[i];
+  } else if ((i -= n1) < n2) {
+    b2[i] = a2[i];
+  }
 }
 
 // Local pseudopotential at every Gauss point: sum_I -Z erf(r/rc)/r + A exp(-(r/rg)^2)
@@ -1100,12 +1114,6 @@ efe_status efe_build_enrichment(efe_ctx *c) {
   return efe_couple_projectors(c);
 }
 
-efe_status efe_symmetrize(efe_ctx *c, int64_t n, double *A) {
-  k_symmetrize<<<cdiv(n * n, 256), 256, 0, c->stream>>>(n, A);
-  HIPCHK(c, hipGetLastError());
-  return EFE_OK;
-}
-
 efe_status efe_launch_local_potential(efe_ctx *c, double *vq) {
   const MeshGeo g = mesh_geo(c);
   k_local_potential<<<cdiv(c->n_qpts, 256), 256, 0, c->stream>>>(
@@ -1134,7 +1142,8 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
   const bool want16 = precisions & (1 << EFE_BF16);
   // dense cell Hamiltonians: for E_c, and where an apply takes them (Gauss rules
   // without tensor products, and the BF16 copies)
-  const bool dense = !c->tp || want16 || (nf > 0 && c->npairs > 0);
+  const bool coupled = nf > 0 && c->npairs > 0;
+  const bool dense = !c->tp || want16 || coupled;
   if (dense && !c->d_Htile64 && (s = efe_alloc(c, (void **)&c->d_Htile64, tiles * 8))) return s;
   if (want32 && !c->tp && !c->d_Htile32 && (s = efe_alloc(c, (void **)&c->d_Htile32, tiles * 4))) return s;
   const int64_t tiles16 = c->n_cells * c->RB * c->KS32 * 64 * 8;
@@ -1142,7 +1151,7 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
   const int KQ8 = (int)cdiv(cdiv(c->nqp, 4), 8) * 8;   // quadrature k steps, padded
   const size_t shm = (size_t)KQ8 * 64 * 8;
   if (shm > 64 * 1024) EFE_FAIL(c, EFE_EINVAL, "too many Gauss points per cell");
-  if (nf > 0 && c->npairs > 0) {
+  if (coupled) {
     const size_t pb = (size_t)c->npairs * c->nloc * nf * 8;   // support pairs
     if (!c->d_B_pair && (s = efe_alloc(c, (void **)&c->d_B_pair, pb))) return s;
     if (!c->d_Epair && (s = efe_alloc(c, (void **)&c->d_Epair, (size_t)c->ncpairs * c->nloc * nf * 8)))
@@ -1150,7 +1159,10 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
   }
   if (ne && !c->d_Hee && (s = efe_alloc(c, (void **)&c->d_Hee, ne * ne * 8))) return s;
   if ((s = efe_couple_alloc(c, want32))) return s;
-  k_copy<<<cdiv(c->n_qpts, 256), 256, 0, c->stream>>>(c->n_qpts, vq, c->d_vq);
+  // the potential, and what it adds to: the kinetic parts of B and H^phiphi
+  const int64_t ns = coupled ? c->n_snodes * nf : 0, ns2 = coupled ? ne * ne : 0;
+  k_copy3<<<cdiv(c->n_qpts + ns + ns2, 256), 256, 0, c->stream>>>(
+      c->n_qpts, vq, c->d_vq, ns, c->d_Bkin_am, c->d_B_am, ns2, c->d_Hpp_kin, c->d_Hpp);
   if (dense)
     k_build_hcell<<<c->n_cells * c->RB, 256, shm, c->stream>>>(
         c->nloc, c->nqp, c->RB, c->KS, KQ8, c->d_N3, c->d_W3, c->d_K, c->d_vq, c->d_Htile64,
@@ -1160,9 +1172,7 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
                                                            c->d_Htile64, c->d_Htile16);
   c->have32 = want32;
   c->have16 = want16;
-  if (nf > 0 && c->npairs > 0) {
-    const int64_t ns = c->n_snodes * nf;
-    k_copy<<<cdiv(ns, 256), 256, 0, c->stream>>>(ns, c->d_Bkin_am, c->d_B_am);
+  if (coupled) {
     const int KQ = (int)cdiv(c->nqp, 4);
 #define GO(P)                                                                                  \
   k_enr_pair_proj_tp<P><<<c->npairs, PAIR_TP_T, 0, c->stream>>>(                               \
@@ -1181,18 +1191,16 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
             c->d_pair_lmap, c->d_vq, KQ, c->d_B_am, c->d_Bkin_pair, c->d_B_pair);
     }
 #undef GO
-    k_copy<<<cdiv(ne * ne, 256), 256, 0, c->stream>>>(ne * ne, c->d_Hpp_kin, c->d_Hpp);
     if (c->n_ppv > 0)
       k_enr_ppv<<<c->n_ppv, 256, 0, c->stream>>>(g, e, c->d_xq1, c->d_W3, c->d_xyz, c->d_nu,
                                                 c->d_ppv, c->d_trip, c->d_vq, ne, c->d_Hpp);
-    k_symmetrize<<<cdiv(ne * ne, 256), 256, 0, c->stream>>>(ne, c->d_Hpp);
     // coupling of the orthogonalized basis, E_c per (atom, cell) pair
     k_build_E<<<c->n_cells * cdiv(c->max_rbe, 2), 512, 0, c->stream>>>(
         c->nloc, c->RB, c->KS, nf, (int)cdiv(c->max_rbe, 2), c->d_Htile64, c->d_cell_eptr,
         c->d_cell_epair, c->d_cpair_lmap, c->d_cpair_spair, c->d_C_am, c->d_B_pair, c->d_Epair);
   }
   if (ne) {
-    if (nf > 0 && c->npairs > 0)
+    if (coupled)
       k_hee_rows<<<ne, 256, ne * 8, c->stream>>>(nf, ne, c->d_snode_ptr, c->d_snode, c->d_nm_ptr,
                                                  c->d_nm_atom, c->d_nm_src, c->d_C_am, c->d_B_am,
                                                  c->d_Hpp, c->d_Hee);
