@@ -588,19 +588,25 @@ __global__ __launch_bounds__(256) void k_mee_rows(int nf, int64_t n_enr, const i
 // digits, what is left enters G and with it every step of a filter, and the
 // output of degree 40 moved by 6e-9.  One work-group takes a cell and 32 of its
 // enrichment functions: C_c^T (nodes x 32) in LDS, each wave every eighth 16 rows
-// of H_c, whose fragments feed two products (64 atoms: 7.8 ms; 12.8 with a
-// work-group a pair).
+// of H_c, whose fragments feed two products (one for the last 16 functions or
+// fewer).  Bound by the reading of H_c, with one work-group a CU to cover it: eight
+// fragments are on their way while eight are multiplied, and the work-groups of a
+// cell run on one XCD, whose L2 they share (64 atoms: 3.0 ms, 7.8 with the loads
+// before their products and a cell spread over the XCDs; 27 atoms of 4 functions at
+// p = 6: 0.55 ms, 1.23, and 0.93 as 16 functions a work-group).
 __global__ __launch_bounds__(512) void k_build_E(
-    int nloc, int RB, int KS, int nf, int max_cb, const double *__restrict__ Ht,
+    int64_t ncells, int nloc, int RB, int KS, int nf, int max_cb, const double *__restrict__ Ht,
     const int32_t *__restrict__ eptr, const int32_t *__restrict__ epair,
     const int32_t *__restrict__ lmap, const int32_t *__restrict__ spair,
     const double *__restrict__ C_am, const double *__restrict__ B_pair, double *__restrict__ E) {
   __shared__ double Cs[2][EFE_MAXLOC + 16][16];
-  const int64_t cell = blockIdx.x / max_cb;
-  const int cb = blockIdx.x % max_cb;
+  const int slot = blockIdx.x / 8, cb = slot % max_cb;
+  const int64_t cell = (int64_t)(slot / max_cb) * 8 + blockIdx.x % 8;
+  if (cell >= ncells) return;
   const int32_t p0 = eptr[cell];
   const int ne = (eptr[cell + 1] - p0) * nf;
   if (32 * cb >= ne) return;
+  const bool two = ne - 32 * cb > 16;
   for (int i = threadIdx.x; i < 4 * KS * 32; i += 512) {
     const int l = i / 32, j = i % 32, e = 32 * cb + j;
     double v = 0.0;
@@ -615,12 +621,28 @@ __global__ __launch_bounds__(512) void k_build_E(
   for (int rb = wave; rb < RB; rb += 8) {
     const double *hp = Ht + (cell * RB + rb) * KS * 64 + lane;
     v4d_p acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-#pragma unroll 8
-    for (int ks = 0; ks < KS; ++ks) {
-      const double h = hp[(int64_t)ks * 64];
+    constexpr int U = 8;
+    double h0[U], h1[U];
+    auto load = [&](int k0, double (&h)[U]) {
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
-        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(h, Cs[b][4 * ks + lk][li], acc[b], 0, 0, 0);
+      for (int u = 0; u < U; ++u) h[u] = hp[(int64_t)min(k0 + u, KS - 1) * 64];
+    };
+    auto multiply = [&](int k0, const double (&h)[U]) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int ks = k0 + u;
+        if (ks >= KS) break;
+        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(h[u], Cs[0][4 * ks + lk][li], acc[0], 0, 0, 0);
+        if (two)
+          acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(h[u], Cs[1][4 * ks + lk][li], acc[1], 0, 0, 0);
+      }
+    };
+    load(0, h0);
+    for (int k0 = 0; k0 < KS; k0 += 2 * U) {
+      load(k0 + U, h1);
+      multiply(k0, h0);
+      load(k0 + 2 * U, h0);
+      multiply(k0 + U, h1);
     }
     // accumulator v of lane l: node row 16 rb + 4 v + l/16, function l%16
 #pragma unroll
@@ -1195,8 +1217,8 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
       k_enr_ppv<<<c->n_ppv, 256, 0, c->stream>>>(g, e, c->d_xq1, c->d_W3, c->d_xyz, c->d_nu,
                                                 c->d_ppv, c->d_trip, c->d_vq, ne, c->d_Hpp);
     // coupling of the orthogonalized basis, E_c per (atom, cell) pair
-    k_build_E<<<c->n_cells * cdiv(c->max_rbe, 2), 512, 0, c->stream>>>(
-        c->nloc, c->RB, c->KS, nf, (int)cdiv(c->max_rbe, 2), c->d_Htile64, c->d_cell_eptr,
+    k_build_E<<<cdiv(c->n_cells, 8) * 8 * cdiv(c->max_rbe, 2), 512, 0, c->stream>>>(
+        c->n_cells, c->nloc, c->RB, c->KS, nf, (int)cdiv(c->max_rbe, 2), c->d_Htile64, c->d_cell_eptr,
         c->d_cell_epair, c->d_cpair_lmap, c->d_cpair_spair, c->d_C_am, c->d_B_pair, c->d_Epair);
   }
   if (ne) {
