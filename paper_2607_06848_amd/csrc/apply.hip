@@ -498,7 +498,7 @@ __device__ __forceinline__ void tile_step(const T *Xs, int s, T a, int li, int l
 // blocks of one set of functions (couple.hip) as the kernels take them
 template <typename T>
 struct BoxSet {
-  const int32_t *ptr, *rboff, *atom;
+  const int32_t *ptr, *rboff, *rbbox, *atom;
   const int64_t *ksoff;
   const T *tile;
   const uint32_t *live;
@@ -518,6 +518,7 @@ struct GatherArgs {
   const int32_t *items;
   const double *X, *minv;
   int64_t ldx, ldp, prow;          // prow: first partial row of the projectors
+  int64_t nre, nrk;                // 16-row blocks of E and P^C in the list
   double *Yp;
   BoxSet<T> E;
   BoxSet<double> K;
@@ -635,22 +636,19 @@ void k_box_gather(GatherArgs<T> a) {
 }
 
 // The same where k_box_gather has too few work-groups to hide its chain of
-// chunks (FEW_GROUPS): one work-group per 16-row block and 16 columns, one wave
+// chunks (GATHER_FEW): one work-group per 16-row block and 16 columns, one wave
 // per 64 nodes (a brick) with all its operands requested at once, straight from
 // memory; the eight sums meet in LDS in a fixed order.  27 boxes and 8 vectors:
-// 7.1 us, 15.7 in chunks; 64 boxes with 1 and 37 vectors 8.3 us on average, 20.8
-// and 32 in chunks.
+// 7.1 us, 15.7 in chunks.
 template <typename T>
 __global__ __launch_bounds__(512) void k_box_gather_few(GatherArgs<T> a) {
   typedef CellMfma<T> M;
   typedef typename M::acc_t acc_t;
   constexpr int NB = EFE_BOX * EFE_BOX * EFE_BOX, KS = NB / 4, KW = KS / 8;
   __shared__ double red[8][256];
-  const int box = a.items[2 * (blockIdx.x / 4)], r = a.items[2 * (blockIdx.x / 4) + 1] + (int)(blockIdx.x % 4);
-  const int ne = a.E.rboff[box + 1] - a.E.rboff[box], nk = a.K.rboff[box + 1] - a.K.rboff[box];
-  if (r >= ne + (sizeof(T) == 8 ? nk : 0)) return;
-  const bool isE = r < ne;
-  const int64_t rb = isE ? a.E.rboff[box] + r : a.K.rboff[box] + r - ne;
+  const bool isE = (int64_t)blockIdx.x < a.nre;   // E blocks first, then P^C blocks
+  const int64_t rb = isE ? blockIdx.x : blockIdx.x - a.nre;
+  const int box = (isE ? a.E.rbbox : a.K.rbbox)[rb];
   const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t / 64), lane = t % 64;
   const int li = lane % 16, lk = lane / 16;
   const int c0 = (int)blockIdx.y * 16, col = min(c0 + li, a.ncols - 1);
@@ -680,7 +678,7 @@ __global__ __launch_bounds__(512) void k_box_gather_few(GatherArgs<T> a) {
   for (int v = 0; v < 4; ++v) red[wave][M::row(v, lk) * 16 + li] = (double)acc[v];
   __syncthreads();
   if (t >= 256 || c0 + t % 16 >= a.ncols) return;
-  const int nf = isE ? a.E.nf : 1, f = 16 * (isE ? r : r - ne) + t / 16;
+  const int nf = isE ? a.E.nf : 1, f = 16 * (int)(rb - (isE ? a.E.rboff : a.K.rboff)[box]) + t / 16;
   const int32_t *ptr = isE ? a.E.ptr : a.K.ptr;
   if (f >= (ptr[box + 1] - ptr[box]) * nf) return;
   double s = 0.0;
@@ -1151,7 +1149,7 @@ __global__ void k_copy_cols(int64_t rows, int ncols, const double *__restrict__ 
 
 template <typename T>
 static BoxSet<T> box_set(const CoupleSet &S, bool brick, const T *tile) {
-  return {brick ? S.d_bk_ptr : S.d_bx_ptr, S.d_rboff, S.d_bk_atom, S.d_bk_off, tile, S.d_live, S.nf};
+  return {brick ? S.d_bk_ptr : S.d_bx_ptr, S.d_rboff, S.d_rbbox, S.d_bk_atom, S.d_bk_off, tile, S.d_live, S.nf};
 }
 
 // column blocks of the register tile: the narrowest that holds the columns
@@ -1167,11 +1165,18 @@ static int tile_blocks(int ncols) {
 // CU.
 constexpr int64_t FEW_GROUPS = 512;
 
+// The gather in 16-column parts takes a time that grows with its work-groups, the
+// chunked one at least its chain of 32 chunks.  Coefficients of an apply (gather,
+// sums, dense part) in parts and in chunks, by work-groups: 920 (projectors only,
+// 160 vectors) 26 and 70 us, 1,390 46 and 50, 1,759 54 and 63, 2,085 55 and 55,
+// 2,146 76 and 73, 2,612 78 and 69, 13,060 230 and 142.
+constexpr int64_t GATHER_FEW = 2048;
+
 template <typename T>
 static void launch_box_gather(efe_ctx *c, const GatherArgs<T> &a, int64_t n) {
   if (n == 0) return;
-  if (n < FEW_GROUPS) {
-    k_box_gather_few<T><<<dim3(4 * n, cdiv(a.ncols, 16)), 512, 0, c->stream>>>(a);
+  if ((a.nre + a.nrk) * cdiv(a.ncols, 16) <= GATHER_FEW) {
+    k_box_gather_few<T><<<dim3(a.nre + a.nrk, cdiv(a.ncols, 16)), 512, 0, c->stream>>>(a);
     return;
   }
 #define GO(B) k_box_gather<T, B><<<n, 256, 0, c->stream>>>(a)
@@ -1305,9 +1310,12 @@ efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, bool 
       h.ncols = ncols;
       h.scaled = g.scaled;
       h.vec = g.vec;
+      h.nre = cE.n_rb;
       launch_box_gather(c, h, c->n_items[0]);
     }
     g.items = c->d_items[f32 ? 1 : 2];
+    g.nre = f32 ? 0 : cE.n_rb;
+    g.nrk = cK.n_rb;
     launch_box_gather(c, g, c->n_items[f32 ? 1 : 2]);
     SumArgs sa{cE.d_at_ptr, cE.d_at_pos, cK.d_at_ptr, cK.d_at_pos, Yp, XE, minv ? c->d_Mee_inv : nullptr,
                ncols, lde, ldq, prow, Q, R, c->nf, nx, ncols};
