@@ -700,6 +700,10 @@ struct SumArgs {
   int64_t ldp, lde, ldq, prow;
   double *Q, *R;
   int nf, nx, ncols;
+  // without enrichment the dense part is W = D P^C s X^C, done here: D and the
+  // rows of W (else NULL)
+  const double *D;
+  double *W;
 };
 
 __global__ __launch_bounds__(640) void k_coef_sum(SumArgs a) {
@@ -726,6 +730,7 @@ __global__ __launch_bounds__(640) void k_coef_sum(SumArgs a) {
   double *q = a.Q + ((int64_t)I * a.nx + k) * a.ldq + col;
   if (!isE) {
     *q = sum;
+    if (a.D) a.W[I * a.ldq + col] = a.D[I] * sum;
     return;
   }
   a.R[((int64_t)I * a.nf + k) * a.ldq + col] = sum;
@@ -765,6 +770,7 @@ __global__ __launch_bounds__(640) void k_coef_sum_narrow(SumArgs a, int cw) {
   double *q = a.Q + ((int64_t)I * a.nx + k) * a.ldq + col;
   if (!isE) {
     *q = sum;
+    if (a.D) a.W[I * a.ldq + col] = a.D[I] * sum;
     return;
   }
   a.R[((int64_t)I * a.nf + k) * a.ldq + col] = sum;
@@ -1318,7 +1324,7 @@ efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, bool 
     g.nrk = cK.n_rb;
     launch_box_gather(c, g, c->n_items[f32 ? 1 : 2]);
     SumArgs sa{cE.d_at_ptr, cE.d_at_pos, cK.d_at_ptr, cK.d_at_pos, Yp, XE, minv ? c->d_Mee_inv : nullptr,
-               ncols, lde, ldq, prow, Q, R, c->nf, nx, ncols};
+               ncols, lde, ldq, prow, Q, R, c->nf, nx, ncols, c->nf ? nullptr : c->d_D, Q + nq * ldq};
     if (ncols <= 16) {
       int cw = 1;
       while (cw < ncols) cw *= 2;
@@ -1330,10 +1336,10 @@ efe_status efe_apply_H_internal(efe_ctx *c, const double *XC, int64_t ldx, bool 
     if (ee.Z1) ee.Z1 += nn * ldy;
     if (ee.Z2) ee.Z2 += nn * ldy;
     if (ee.G) ee.G += nn * ldy;
-    if (ncols <= 16)
+    if (c->nf > 0 && ncols <= 16)
       k_coef_dense<1><<<dim3(cdiv(nq, 16), 1), 256, 0, c->stream>>>(nq, c->nf, nx, ncols, c->d_S, Q,
                                                                    ldq, R, ee, Y + nn * ldy, ldy);
-    else
+    else if (c->nf > 0)
       k_coef_dense<5><<<dim3(cdiv(nq, 16), cdiv(ncols, 80)), 256, 0, c->stream>>>(
           nq, c->nf, nx, ncols, c->d_S, Q, ldq, R, ee, Y + nn * ldy, ldy);
     efe_timer_end(c, EFE_T_POST, t);

@@ -218,85 +218,22 @@ void k_cell_tp(TpArgs a) {
   }
 }
 
-// Gauss-point basis: derivative matrix D[i][j] = L_j'(x_i) of the Lagrange
-// polynomials on the points x
-void lagrange_derivative(const std::vector<double> &x, std::vector<double> &D) {
-  const int n = (int)x.size();
-  D.assign(n * n, 0.0);
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j < n; ++j) {
-      for (int k = 0; k < n; ++k) {
-        if (k == j) continue;
-        double t = 1.0 / (x[j] - x[k]);
-        for (int l = 0; l < n; ++l)
-          if (l != j && l != k) t *= (x[i] - x[l]) / (x[j] - x[l]);
-        D[i * n + j] += t;
-      }
-    }
-}
-
-}  // namespace
-
-efe_status efe_tp_setup(efe_ctx *c, const std::vector<double> &xq, const std::vector<double> &wq,
-                        const std::vector<double> &N1, const std::vector<double> &D1,
-                        const std::vector<double> &wg, const std::vector<long double> &wql,
-                        const std::vector<long double> &N1l, const std::vector<long double> &Dl) {
-  c->tp = c->nq == c->P && c->P >= 2;
+// matrices of the projections and the density, then those of the cell operator and
+// sqrt(w), appended to `all`
+void tp_tables(const efe_ctx *c, const std::vector<double> &wq, const std::vector<double> &N1,
+               const std::vector<long double> &wql,
+               const std::vector<long double> &N1l, const std::vector<long double> &Dl,
+               std::vector<double> &all) {
   const int P = c->P;
-  // separable factors of the lumped mass: 1 (0 on the boundary), then 1/m
-  const int64_t n3 = c->n1[0] + c->n1[1] + c->n1[2];
-  std::vector<double> s1(2 * n3, 0.0);
-  int64_t o = 0;
-  for (int d = 0; d < 3; ++d)
-    for (int64_t i = 0; i < c->n1[d]; ++i, ++o) {
-      if (i == 0 || i == c->n1[d] - 1) continue;
-      const int l = (int)(i % c->p);
-      s1[o] = 1.0;
-      s1[n3 + o] = 1.0 / (0.5 * c->h[d] * (l == 0 ? wg[0] + wg[c->p] : wg[l]));
-    }
-  efe_status st;
-  if ((st = efe_alloc(c, (void **)&c->d_s1, s1.size() * 8))) return st;
-  HIPCHK(c, hipMemcpyAsync(c->d_s1, s1.data(), s1.size() * 8, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  // 1-D mass and stiffness of the Gauss rule on the nodes (any nq): the cell
-  // stiffness is K x M x M + M x K x M + M x M x K
-  std::vector<double> mk(6 * TP_MAT, 0.0), M(P * P), K(P * P);
-  for (int d = 0; d < 3 && P >= 2; ++d) {
-    const double h2 = 0.5 * c->h[d];
-    for (int i = 0; i < P; ++i)
-      for (int j = 0; j < P; ++j) {
-        double m = 0.0, k = 0.0;
-        for (int q = 0; q < c->nq; ++q) {
-          m += wq[q] * N1[q * P + i] * N1[q * P + j];
-          k += wq[q] * D1[q * P + i] * D1[q * P + j];
-        }
-        M[i * P + j] = h2 * m;
-        K[i * P + j] = k / h2;
-      }
-    even_odd(P, M, &mk[d * TP_MAT], &mk[d * TP_MAT + 16]);
-    even_odd(P, K, &mk[(3 + d) * TP_MAT], &mk[(3 + d) * TP_MAT + 16]);
-  }
-  if ((st = efe_alloc(c, (void **)&c->d_mk, mk.size() * 8))) return st;
-  HIPCHK(c, hipMemcpyAsync(c->d_mk, mk.data(), mk.size() * 8, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  if (!c->tp) return EFE_OK;
-  std::vector<double> D, Nd(P * P), S(P * P), tab(6 * TP_MAT, 0.0);
-  lagrange_derivative(xq, D);
+  std::vector<double> Nd(P * P), tab(3 * TP_MAT, 0.0);
   for (int d = 0; d < 3; ++d) {
     const double h2 = 0.5 * c->h[d];
     for (int q = 0; q < P; ++q)
-      for (int i = 0; i < P; ++i) {
-        Nd[q * P + i] = sqrt(wq[q] * h2) * N1[q * P + i];
-        double acc = 0.0;
-        for (int g = 0; g < P; ++g) acc += wq[g] * D[g * P + q] * D[g * P + i];
-        S[q * P + i] = 0.5 * acc / (sqrt(wq[q] * wq[i]) * h2 * h2);
-      }
+      for (int i = 0; i < P; ++i) Nd[q * P + i] = sqrt(wq[q] * h2) * N1[q * P + i];
     even_odd(P, Nd, &tab[d * TP_MAT], &tab[d * TP_MAT + 16]);
-    even_odd(P, S, &tab[(3 + d) * TP_MAT], &tab[(3 + d) * TP_MAT + 16]);
   }
-  if ((st = efe_alloc(c, (void **)&c->d_tpm, tab.size() * 8))) return st;
-  HIPCHK(c, hipMemcpyAsync(c->d_tpm, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+  all.insert(all.end(), tab.begin(), tab.end());
+  tab.assign(6 * TP_MAT, 0.0);
   // the cell operator's own copy, from extended precision, and sqrt(w) of the
   // cell's Gauss points
   std::vector<long double> Nl(P * P), Sl(P * P);
@@ -315,9 +252,57 @@ efe_status efe_tp_setup(efe_ctx *c, const std::vector<double> &xq, const std::ve
   const long double jac = 0.125L * c->h[0] * c->h[1] * c->h[2];
   for (int q = 0; q < P * P * P; ++q)
     tab.push_back((double)sqrtl(wql[q % P] * wql[q / P % P] * wql[q / (P * P)] * jac));
-  if ((st = efe_alloc(c, (void **)&c->d_tpc, tab.size() * 8))) return st;
-  HIPCHK(c, hipMemcpyAsync(c->d_tpc, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, c->stream));
+  all.insert(all.end(), tab.begin(), tab.end());
+}
+
+}  // namespace
+
+efe_status efe_tp_setup(efe_ctx *c, const std::vector<double> &wq, const std::vector<double> &N1,
+                        const std::vector<double> &D1, const std::vector<double> &wg,
+                        const std::vector<long double> &wql, const std::vector<long double> &N1l,
+                        const std::vector<long double> &Dl) {
+  c->tp = c->nq == c->P && c->P >= 2;
+  const int P = c->P;
+  // separable factors of the lumped mass: 1 (0 on the boundary), then 1/m
+  const int64_t n3 = c->n1[0] + c->n1[1] + c->n1[2];
+  std::vector<double> s1(2 * n3, 0.0);
+  int64_t o = 0;
+  for (int d = 0; d < 3; ++d)
+    for (int64_t i = 0; i < c->n1[d]; ++i, ++o) {
+      if (i == 0 || i == c->n1[d] - 1) continue;
+      const int l = (int)(i % c->p);
+      s1[o] = 1.0;
+      s1[n3 + o] = 1.0 / (0.5 * c->h[d] * (l == 0 ? wg[0] + wg[c->p] : wg[l]));
+    }
+  // 1-D mass and stiffness of the Gauss rule on the nodes (any nq): the cell
+  // stiffness is K x M x M + M x K x M + M x M x K
+  std::vector<double> mk(6 * TP_MAT, 0.0), M(P * P), K(P * P);
+  for (int d = 0; d < 3 && P >= 2; ++d) {
+    const double h2 = 0.5 * c->h[d];
+    for (int i = 0; i < P; ++i)
+      for (int j = 0; j < P; ++j) {
+        double m = 0.0, k = 0.0;
+        for (int q = 0; q < c->nq; ++q) {
+          m += wq[q] * N1[q * P + i] * N1[q * P + j];
+          k += wq[q] * D1[q * P + i] * D1[q * P + j];
+        }
+        M[i * P + j] = h2 * m;
+        K[i * P + j] = k / h2;
+      }
+    even_odd(P, M, &mk[d * TP_MAT], &mk[d * TP_MAT + 16]);
+    even_odd(P, K, &mk[(3 + d) * TP_MAT], &mk[(3 + d) * TP_MAT + 16]);
+  }
+  std::vector<double> all = s1;            // s1, mk, and with c->tp the matrices
+  all.insert(all.end(), mk.begin(), mk.end());
+  if (c->tp) tp_tables(c, wq, N1, wql, N1l, Dl, all);
+  efe_status st;
+  if ((st = efe_alloc(c, (void **)&c->d_tpt, all.size() * 8))) return st;
+  HIPCHK(c, hipMemcpyAsync(c->d_tpt, all.data(), all.size() * 8, hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  c->d_s1 = c->d_tpt;
+  c->d_mk = c->d_s1 + s1.size();
+  c->d_tpm = c->d_mk + mk.size();
+  c->d_tpc = c->d_tpm + 3 * TP_MAT;
   return EFE_OK;
 }
 

@@ -372,16 +372,27 @@ __global__ void k_coef_matrix(int natoms, int nf, int nx, const double *__restri
 }
 
 // ------------------------------------------------------------------ host
-template <class T>
-efe_status upload(efe_ctx *c, T **dst, const std::vector<T> &src) {
-  efe_status s = efe_alloc(c, (void **)dst, std::max<size_t>(src.size(), 1) * sizeof(T));
-  if (s) return s;
-  if (!src.empty())
-    HIPCHK(c, hipMemcpyAsync(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice,
-                             c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  return EFE_OK;
-}
+// Tables of the coupling, copied to the device in one piece (about thirty copies and
+// waits of their own were a fifth of the setup of a small system)
+struct Pack {
+  std::vector<char> host;
+  std::vector<std::pair<void **, size_t>> at;
+  template <class T>
+  void add(T **dst, const std::vector<T> &v) {
+    const size_t o = (host.size() + 255) & ~(size_t)255;
+    host.resize(o + std::max<size_t>(v.size(), 1) * sizeof(T));
+    std::copy((const char *)v.data(), (const char *)(v.data() + v.size()), host.data() + o);
+    at.push_back({(void **)dst, o});
+  }
+  efe_status upload(efe_ctx *c, char **base) {
+    efe_status s = efe_alloc(c, (void **)base, host.size());
+    if (s) return s;
+    HIPCHK(c, hipMemcpyAsync(*base, host.data(), host.size(), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    for (auto &a : at) *a.first = *base + a.second;
+    return EFE_OK;
+  }
+};
 
 // atoms touching every box of edge e (ascending), from each atom's cells
 void box_atoms(const efe_ctx *c, const std::vector<int32_t> &ptr, const std::vector<int32_t> &cells,
@@ -419,9 +430,8 @@ void box_atoms(const efe_ctx *c, const std::vector<int32_t> &ptr, const std::vec
     for (int32_t q = lptr[I]; q < lptr[I + 1]; ++q) batom[fill[list[q]]++] = I;
 }
 
-efe_status build_set(efe_ctx *c, const std::vector<int32_t> &ptr, const std::vector<int32_t> &cells,
-                     int nf, CoupleSet &S) {
-  efe_status s;
+void build_set(const efe_ctx *c, const std::vector<int32_t> &ptr, const std::vector<int32_t> &cells,
+               int nf, CoupleSet &S, Pack &pk) {
   S.nf = nf;
   // (atom, cell) -> pair over the bounding box of the atom's cells
   std::vector<int32_t> box(6 * (size_t)c->natoms, 0), map;
@@ -450,9 +460,9 @@ efe_status build_set(efe_ctx *c, const std::vector<int32_t> &ptr, const std::vec
           (int64_t)box[6 * I + 3] * ((ijk(cells[q], 1) - lo[1]) +
                                      (int64_t)box[6 * I + 4] * (ijk(cells[q], 2) - lo[2]))] = q;
   }
-  if ((s = upload(c, &S.d_box, box)) || (s = upload(c, &S.d_map, map)) ||
-      (s = upload(c, &S.d_off, off)))
-    return s;
+  pk.add(&S.d_box, box);
+  pk.add(&S.d_map, map);
+  pk.add(&S.d_off, off);
   // bricks
   std::vector<int32_t> bptr, batom;
   box_atoms(c, ptr, cells, BK, bptr, batom);
@@ -461,9 +471,9 @@ efe_status build_set(efe_ctx *c, const std::vector<int32_t> &ptr, const std::vec
     ksoff[b + 1] = ksoff[b] + cdiv((int64_t)(bptr[b + 1] - bptr[b]) * nf, 4);
   S.n_brick = (int64_t)bptr.size() - 1;
   S.brick_tile = 256 * ksoff.back();
-  if ((s = upload(c, &S.d_bk_ptr, bptr)) || (s = upload(c, &S.d_bk_atom, batom)) ||
-      (s = upload(c, &S.d_bk_off, ksoff)))
-    return s;
+  pk.add(&S.d_bk_ptr, bptr);
+  pk.add(&S.d_bk_atom, batom);
+  pk.add(&S.d_bk_off, ksoff);
   // boxes
   box_atoms(c, ptr, cells, BX, bptr, batom);
   std::vector<int32_t> rboff(bptr.size(), 0), rbbox;
@@ -476,18 +486,19 @@ efe_status build_set(efe_ctx *c, const std::vector<int32_t> &ptr, const std::vec
   S.n_boxpairs = (int64_t)batom.size();
   S.n_rb = rboff.back();
   S.h_rboff = rboff;
-  if ((s = efe_alloc(c, (void **)&S.d_live, std::max<int64_t>(S.n_rb, 1) * 4))) return s;
+  pk.add(&S.d_live, std::vector<uint32_t>(S.n_rb, 0));
   S.box_tile = S.n_rb * (BX * BX * BX / 4) * 64;
   std::vector<int32_t> aptr(c->natoms + 1, 0), apos(batom.size());
   for (int32_t a : batom) aptr[a + 1]++;
   for (int I = 0; I < c->natoms; ++I) aptr[I + 1] += aptr[I];
   std::vector<int32_t> fill(aptr.begin(), aptr.end() - 1);
   for (size_t q = 0; q < batom.size(); ++q) apos[fill[batom[q]]++] = (int32_t)q;
-  if ((s = upload(c, &S.d_bx_ptr, bptr)) || (s = upload(c, &S.d_bx_atom, batom)) ||
-      (s = upload(c, &S.d_rboff, rboff)) || (s = upload(c, &S.d_rbbox, rbbox)) ||
-      (s = upload(c, &S.d_at_ptr, aptr)) || (s = upload(c, &S.d_at_pos, apos)))
-    return s;
-  return EFE_OK;
+  pk.add(&S.d_bx_ptr, bptr);
+  pk.add(&S.d_bx_atom, batom);
+  pk.add(&S.d_rboff, rboff);
+  pk.add(&S.d_rbbox, rbbox);
+  pk.add(&S.d_at_ptr, aptr);
+  pk.add(&S.d_at_pos, apos);
 }
 
 Entries entries(const efe_ctx *c, const CoupleSet &S, const double *epair, const double *bam,
@@ -529,8 +540,9 @@ efe_status efe_couple_setup(efe_ctx *c, const std::vector<int32_t> &eptr,
   HIPCHK(c, hipFuncSetAttribute((const void *)k_hee_box, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)box_lds(1, 1)));
   const std::vector<int32_t> none(c->natoms + 1, 0);
-  if ((s = build_set(c, c->nf > 0 ? eptr : none, ecells, std::max(c->nf, 1), E))) return s;
-  if ((s = build_set(c, c->nproj ? c->kb_ptr : none, c->kb_cells, 1, K))) return s;
+  Pack pk;
+  build_set(c, c->nf > 0 ? eptr : none, ecells, std::max(c->nf, 1), E, pk);
+  build_set(c, c->nproj ? c->kb_ptr : none, c->kb_cells, 1, K, pk);
   std::vector<int32_t> items[3];
   for (int64_t b = 0; b < E.n_box; ++b) {
     const int ne = E.h_rboff[b + 1] - E.h_rboff[b], nk = K.h_rboff[b + 1] - K.h_rboff[b];
@@ -544,8 +556,9 @@ efe_status efe_couple_setup(efe_ctx *c, const std::vector<int32_t> &eptr,
   }
   for (int which = 0; which < 3; ++which) {
     c->n_items[which] = (int64_t)items[which].size() / 2;
-    if ((s = upload(c, &c->d_items[which], items[which]))) return s;
+    pk.add(&c->d_items[which], items[which]);
   }
+  if ((s = pk.upload(c, &c->d_cpl))) return s;
   if (c->nproj) {
     if ((s = efe_alloc(c, (void **)&K.d_T1, std::max<int64_t>(K.brick_tile, 1) * 8))) return s;
     if ((s = efe_alloc(c, (void **)&K.d_T2, std::max<int64_t>(K.box_tile, 1) * 8))) return s;
@@ -600,10 +613,8 @@ efe_status efe_couple_build(efe_ctx *c, bool want32) {
 
 void efe_couple_free(efe_ctx *c) {
   for (CoupleSet *S : {&c->cpl_e, &c->cpl_k}) {
-    void *ptrs[] = {S->d_box,   S->d_map,   S->d_off,    S->d_bk_ptr, S->d_bk_atom, S->d_bk_off,
-                    S->d_bx_ptr, S->d_bx_atom, S->d_rboff, S->d_rbbox, S->d_at_ptr, S->d_at_pos,
-                    S->d_T1,    S->d_T2,    S->d_T1f,    S->d_T2f,  S->d_live};
+    void *ptrs[] = {S->d_T1, S->d_T2, S->d_T1f, S->d_T2f};
     for (void *p : ptrs) efe_free(c, p);
   }
-  for (int32_t *p : c->d_items) efe_free(c, p);
+  efe_free(c, c->d_cpl);   // every table
 }

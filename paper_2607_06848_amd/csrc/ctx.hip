@@ -461,7 +461,7 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
     // non-zero on shared nodes although phi vanishes), with the local-to-
     // support map and the support pair of the cell (-1 for the outer layer)
     {
-      std::vector<int32_t> cptr(c->natoms + 1, 0), catom, ccell, cspair, clmap;
+      std::vector<int32_t> cptr(c->natoms + 1, 0), ccell, cspair, clmap;
       std::vector<int32_t> pos(c->n_nodes, -1), cmark(c->n_cells, -1);
       const int64_t n1x = c->n1[0], n1y = c->n1[1];
       for (int I = 0; I < c->natoms && c->nf > 0; ++I) {
@@ -490,7 +490,6 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
         }
         std::sort(cl.begin(), cl.end());
         for (int32_t cell : cl) {
-          catom.push_back(I);
           ccell.push_back(cell);
           auto it = std::lower_bound(E.cells.begin() + E.ptr[I], E.cells.begin() + E.ptr[I + 1],
                                      cell);
@@ -500,10 +499,10 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
           const int32_t *gl = &c->c2g[(size_t)cell * c->nloc];
           for (int l = 0; l < c->nloc; ++l) clmap.push_back(c->boundary[gl[l]] ? -1 : pos[gl[l]]);
         }
-        cptr[I + 1] = (int32_t)catom.size();
+        cptr[I + 1] = (int32_t)ccell.size();
         for (int32_t sI = E.snode_ptr[I]; sI < E.snode_ptr[I + 1]; ++sI) pos[E.snode[sI]] = -1;
       }
-      c->ncpairs = (int64_t)catom.size();
+      c->ncpairs = (int64_t)ccell.size();
       std::vector<int32_t> percell(c->n_cells, 0);
       for (int32_t cc : ccell) percell[cc]++;
       int maxr = 0;
@@ -525,10 +524,8 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
       }
       TRY(upload(c, &c->d_cell_eptr, eptr));
       TRY(upload(c, &c->d_cell_epair, epair));
-      TRY(upload(c, &c->d_cpair_atom, catom));
       TRY(upload(c, &c->d_cpair_spair, cspair));
       TRY(upload(c, &c->d_cpair_lmap, clmap));
-      TRY(upload(c, &c->d_cpair_cell, ccell));
       TRY(efe_couple_setup(c, cptr, ccell));
       HIPCHK(c, hipStreamSynchronize(c->stream));
     }
@@ -647,8 +644,8 @@ extern "C" void efe_destroy(efe_ctx *c) {
                   c->d_Htile16,   c->d_g_ptr,
                   c->d_g_atom,    c->d_nm_gslot,     c->d_Cg,
                   c->d_Bkin_pair, c->d_B_pair,       c->d_Hee,
-                  c->d_Ptil,      c->d_cpair_atom, c->d_cpair_spair, c->d_cell_eptr, c->d_cell_epair,
-                  c->d_cpair_lmap, c->d_s1,          c->d_tpm, c->d_tpc, c->d_mk, c->d_Epair, c->d_cpair_cell, c->d_S};
+                  c->d_Ptil,      c->d_cpair_spair, c->d_cell_eptr, c->d_cell_epair,
+                  c->d_cpair_lmap, c->d_tpt, c->d_Epair, c->d_S};
   efe_couple_free(c);
   for (void *p : ptrs) efe_free(c, p);
   for (auto &b : c->ws) efe_free(c, b.p);

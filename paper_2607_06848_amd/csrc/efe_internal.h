@@ -122,8 +122,7 @@ struct efe_ctx {
   // the layer outside the support) and the local-to-support map
   int64_t ncpairs = 0;
   int32_t *d_cell_eptr = nullptr, *d_cell_epair = nullptr;   // coupling pairs cell by cell
-  int32_t *d_cpair_cell = nullptr, *d_cpair_atom = nullptr, *d_cpair_spair = nullptr,
-          *d_cpair_lmap = nullptr;
+  int32_t *d_cpair_spair = nullptr, *d_cpair_lmap = nullptr;
   int max_rbe = 0;                                     // max padded rows / 16 over cells
   // per-pair cell blocks [pair][l][k]: kinetic part of B (setup), B and the
   // coupling E_c = B_c - C_c H_c of the orthogonalized basis (per potential)
@@ -131,6 +130,7 @@ struct efe_ctx {
   // coupling blocks over boxes of nodes: enrichment, projectors; work items of
   // the box products (E only, P^C only, both); matrix of the coefficients
   CoupleSet cpl_e, cpl_k;
+  char *d_cpl = nullptr;   // their tables, in one piece
   int32_t *d_items[3] = {nullptr, nullptr, nullptr};
   int64_t n_items[3] = {0, 0, 0};
   double *d_S = nullptr;
@@ -159,6 +159,7 @@ struct efe_ctx {
   // projections and the density, and the separable row factors [2][n1x + n1y +
   // n1z] (interior mask, 1/m)
   bool tp = false;
+  double *d_tpt = nullptr;   // these tables, in one piece
   double *d_tpc = nullptr, *d_tpm = nullptr, *d_s1 = nullptr;
   double *d_mk = nullptr;   // 1-D mass and stiffness per axis (Poisson)
 
@@ -280,10 +281,10 @@ size_t efe_syev_iwork(int64_t n);
 
 // tensor-product cell operator (cell_tp.hip): the products of every cell into
 // Yc [cell][local node][column], or (Yc = nullptr) added to Y times alpha
-efe_status efe_tp_setup(efe_ctx *ctx, const std::vector<double> &xq, const std::vector<double> &wq,
-                        const std::vector<double> &N1, const std::vector<double> &D1,
-                        const std::vector<double> &wg, const std::vector<long double> &wql,
-                        const std::vector<long double> &N1l, const std::vector<long double> &Dl);
+efe_status efe_tp_setup(efe_ctx *ctx, const std::vector<double> &wq, const std::vector<double> &N1,
+                        const std::vector<double> &D1, const std::vector<double> &wg,
+                        const std::vector<long double> &wql, const std::vector<long double> &N1l,
+                        const std::vector<long double> &Dl);
 efe_status efe_tp_apply(efe_ctx *ctx, const double *X, int64_t ldx, bool minv, int ncols,
                         double *Yc, int64_t ldc, double *Y, int64_t ldy, double alpha);
 // E_c = B_c - H_c C_c^T of every coupling pair into d_Epair

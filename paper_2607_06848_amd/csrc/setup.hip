@@ -1028,7 +1028,7 @@ efe_status efe_build_reference(efe_ctx *c) {
   gauss_rule(c->nq, xql, wql);
   lagrange(xgl, xql, N1l, D1l);
   lagrange(xql, xql, Il, Dl);
-  return efe_tp_setup(c, xq, wq, N1, D1, wg, wql, N1l, Dl);
+  return efe_tp_setup(c, wq, N1, D1, wg, wql, N1l, Dl);
 }
 
 efe_status efe_build_enrichment(efe_ctx *c) {
