@@ -602,7 +602,8 @@ efe_status efe_couple_build(efe_ctx *c, bool want32) {
   if (c->nf > 0 && E.n_boxpairs > 0) {
     const Entries e = entries(c, E, c->d_Epair, nullptr, c->d_cpair_lmap);
     launch_tiles(c, E, e, want32);
-    k_hee_box<<<dim3(E.n_rb, E.n_rb < HEE_FEW ? 8 : 1), 256, box_lds(c->p, c->nf), c->stream>>>(
+    if (c->max_rbe > 2)   // else k_build_E forms E C^T
+      k_hee_box<<<dim3(E.n_rb, E.n_rb < HEE_FEW ? 8 : 1), 256, box_lds(c->p, c->nf), c->stream>>>(
         e, E.d_bx_ptr, E.d_bx_atom, E.d_rboff, E.d_rbbox, E.d_T2, E.d_live, c->d_C_am, ne, c->d_Hee);
   }
   k_coef_matrix<<<cdiv(n * n, 256), 256, 0, c->stream>>>(c->natoms, c->nf, nx, c->d_Hee, c->d_Ptil,

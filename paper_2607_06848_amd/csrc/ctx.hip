@@ -461,7 +461,7 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
     // non-zero on shared nodes although phi vanishes), with the local-to-
     // support map and the support pair of the cell (-1 for the outer layer)
     {
-      std::vector<int32_t> cptr(c->natoms + 1, 0), ccell, cspair, clmap;
+      std::vector<int32_t> cptr(c->natoms + 1, 0), catom, ccell, cspair, clmap;
       std::vector<int32_t> pos(c->n_nodes, -1), cmark(c->n_cells, -1);
       const int64_t n1x = c->n1[0], n1y = c->n1[1];
       for (int I = 0; I < c->natoms && c->nf > 0; ++I) {
@@ -490,6 +490,7 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
         }
         std::sort(cl.begin(), cl.end());
         for (int32_t cell : cl) {
+          catom.push_back(I);
           ccell.push_back(cell);
           auto it = std::lower_bound(E.cells.begin() + E.ptr[I], E.cells.begin() + E.ptr[I + 1],
                                      cell);
@@ -524,6 +525,7 @@ extern "C" efe_status efe_setup_mesh(const efe_mesh_desc *mesh, const efe_system
       }
       TRY(upload(c, &c->d_cell_eptr, eptr));
       TRY(upload(c, &c->d_cell_epair, epair));
+      TRY(upload(c, &c->d_cpair_atom, catom));
       TRY(upload(c, &c->d_cpair_spair, cspair));
       TRY(upload(c, &c->d_cpair_lmap, clmap));
       TRY(efe_couple_setup(c, cptr, ccell));
@@ -644,7 +646,7 @@ extern "C" void efe_destroy(efe_ctx *c) {
                   c->d_Htile16,   c->d_g_ptr,
                   c->d_g_atom,    c->d_nm_gslot,     c->d_Cg,
                   c->d_Bkin_pair, c->d_B_pair,       c->d_Hee,
-                  c->d_Ptil,      c->d_cpair_spair, c->d_cell_eptr, c->d_cell_epair,
+                  c->d_Ptil,      c->d_cpair_atom, c->d_cpair_spair, c->d_cell_eptr, c->d_cell_epair,
                   c->d_cpair_lmap, c->d_tpt, c->d_Epair, c->d_S};
   efe_couple_free(c);
   for (void *p : ptrs) efe_free(c, p);

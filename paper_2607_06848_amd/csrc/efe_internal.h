@@ -122,7 +122,7 @@ struct efe_ctx {
   // the layer outside the support) and the local-to-support map
   int64_t ncpairs = 0;
   int32_t *d_cell_eptr = nullptr, *d_cell_epair = nullptr;   // coupling pairs cell by cell
-  int32_t *d_cpair_spair = nullptr, *d_cpair_lmap = nullptr;
+  int32_t *d_cpair_atom = nullptr, *d_cpair_spair = nullptr, *d_cpair_lmap = nullptr;
   int max_rbe = 0;                                     // max padded rows / 16 over cells
   // per-pair cell blocks [pair][l][k]: kinetic part of B (setup), B and the
   // coupling E_c = B_c - C_c H_c of the orthogonalized basis (per potential)

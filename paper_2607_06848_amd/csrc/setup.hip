@@ -594,12 +594,20 @@ __global__ __launch_bounds__(256) void k_mee_rows(int nf, int64_t n_enr, const i
 // cell run on one XCD, whose L2 they share (64 atoms: 3.0 ms, 7.8 with the loads
 // before their products and a cell spread over the XCDs; 27 atoms of 4 functions at
 // p = 6: 0.55 ms, 1.23, and 0.93 as 16 functions a work-group).
+//
+// EC (no cell couples to more than 32 functions): the work-group holds E_c and C_c
+// of the whole cell, and H^E_ee -= E_c C_c^T is formed on the way, four products more
+// per 16 nodes whose operand is the accumulator as it stands (two atoms on 5^3
+// cells: the 12.5 us of k_hee_box less).
+template <bool EC>
 __global__ __launch_bounds__(512) void k_build_E(
     int64_t ncells, int nloc, int RB, int KS, int nf, int max_cb, const double *__restrict__ Ht,
     const int32_t *__restrict__ eptr, const int32_t *__restrict__ epair,
     const int32_t *__restrict__ lmap, const int32_t *__restrict__ spair,
-    const double *__restrict__ C_am, const double *__restrict__ B_pair, double *__restrict__ E) {
+    const double *__restrict__ C_am, const double *__restrict__ B_pair, double *__restrict__ E,
+    const int32_t *__restrict__ atom, int64_t n_enr, double *__restrict__ Hee) {
   __shared__ double Cs[2][EFE_MAXLOC + 16][16];
+  __shared__ double Hs[EC ? 32 : 1][33];
   const int slot = blockIdx.x / 8, cb = slot % max_cb;
   const int64_t cell = (int64_t)(slot / max_cb) * 8 + blockIdx.x % 8;
   if (cell >= ncells) return;
@@ -607,7 +615,9 @@ __global__ __launch_bounds__(512) void k_build_E(
   const int ne = (eptr[cell + 1] - p0) * nf;
   if (32 * cb >= ne) return;
   const bool two = ne - 32 * cb > 16;
-  for (int i = threadIdx.x; i < 4 * KS * 32; i += 512) {
+  if constexpr (EC)
+    for (int i = threadIdx.x; i < 32 * 33; i += 512) Hs[i / 33][i % 33] = 0.0;
+  for (int i = threadIdx.x; i < (EC ? 16 * RB : 4 * KS) * 32; i += 512) {
     const int l = i / 32, j = i % 32, e = 32 * cb + j;
     double v = 0.0;
     if (l < nloc && e < ne) {
@@ -618,6 +628,10 @@ __global__ __launch_bounds__(512) void k_build_E(
   }
   __syncthreads();
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, lk = lane / 16;
+  v4d_p hc[2][2];
+  if constexpr (EC)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) hc[b / 2][b % 2] = (v4d_p){0.0, 0.0, 0.0, 0.0};
   for (int rb = wave; rb < RB; rb += 8) {
     const double *hp = Ht + (cell * RB + rb) * KS * 64 + lane;
     v4d_p acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
@@ -648,7 +662,7 @@ __global__ __launch_bounds__(512) void k_build_E(
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const int e = 32 * cb + 16 * b + li;
-      if (e >= ne) continue;
+      if (e >= ne) continue;   // acc is zero there: so is C
       const int64_t pr = epair[p0 + e / nf];
       const int32_t sp = spair[pr];
 #pragma unroll
@@ -657,8 +671,33 @@ __global__ __launch_bounds__(512) void k_build_E(
         if (l >= nloc) continue;
         // B_c vanishes on the layer of cells outside the support
         const double bv = sp >= 0 ? B_pair[((int64_t)sp * nloc + l) * nf + e % nf] : 0.0;
-        E[(pr * nloc + l) * nf + e % nf] = bv - acc[b][v];
+        acc[b][v] = bv - acc[b][v];
+        E[(pr * nloc + l) * nf + e % nf] = acc[b][v];
       }
+    }
+    if constexpr (EC)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)   // nodes 16 rb + 4 v ..: function l%16 of E, node l/16
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if (two || b == 0)
+            hc[b / 2][b % 2] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                acc[b / 2][v], Cs[b % 2][16 * rb + 4 * v + lk][li], hc[b / 2][b % 2], 0, 0, 0);
+  }
+  if constexpr (EC) {
+    if (wave < RB)
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (two || b == 0)
+            atomicAdd(&Hs[16 * (b / 2) + 4 * v + lk][16 * (b % 2) + li], hc[b / 2][b % 2][v]);
+    __syncthreads();
+    for (int i = threadIdx.x; i < ne * ne; i += 512) {
+      const int f = i / ne, h = i % ne;
+      atomicAdd(&Hee[((int64_t)atom[epair[p0 + f / nf]] * nf + f % nf) * n_enr +
+                     (int64_t)atom[epair[p0 + h / nf]] * nf + h % nf],
+                -Hs[f][h]);
     }
   }
 }
@@ -1216,18 +1255,24 @@ efe_status efe_build_operators(efe_ctx *c, const double *vq, int precisions) {
     if (c->n_ppv > 0)
       k_enr_ppv<<<c->n_ppv, 256, 0, c->stream>>>(g, e, c->d_xq1, c->d_W3, c->d_xyz, c->d_nu,
                                                 c->d_ppv, c->d_trip, c->d_vq, ne, c->d_Hpp);
+    k_hee_rows<<<ne, 256, ne * 8, c->stream>>>(nf, ne, c->d_snode_ptr, c->d_snode, c->d_nm_ptr,
+                                               c->d_nm_atom, c->d_nm_src, c->d_C_am, c->d_B_am,
+                                               c->d_Hpp, c->d_Hee);
     // coupling of the orthogonalized basis, E_c per (atom, cell) pair
-    k_build_E<<<cdiv(c->n_cells, 8) * 8 * cdiv(c->max_rbe, 2), 512, 0, c->stream>>>(
-        c->n_cells, c->nloc, c->RB, c->KS, nf, (int)cdiv(c->max_rbe, 2), c->d_Htile64, c->d_cell_eptr,
-        c->d_cell_epair, c->d_cpair_lmap, c->d_cpair_spair, c->d_C_am, c->d_B_pair, c->d_Epair);
-  }
-  if (ne) {
-    if (coupled)
-      k_hee_rows<<<ne, 256, ne * 8, c->stream>>>(nf, ne, c->d_snode_ptr, c->d_snode, c->d_nm_ptr,
-                                                 c->d_nm_atom, c->d_nm_src, c->d_C_am, c->d_B_am,
-                                                 c->d_Hpp, c->d_Hee);
+    const int mcb = (int)cdiv(c->max_rbe, 2);
+    const int64_t nwg = cdiv(c->n_cells, 8) * 8 * mcb;
+#define GO(EC)                                                                                    \
+  k_build_E<EC><<<nwg, 512, 0, c->stream>>>(                                                      \
+      c->n_cells, c->nloc, c->RB, c->KS, nf, mcb, c->d_Htile64, c->d_cell_eptr, c->d_cell_epair,  \
+      c->d_cpair_lmap, c->d_cpair_spair, c->d_C_am, c->d_B_pair, c->d_Epair, c->d_cpair_atom, ne, \
+      c->d_Hee)
+    if (c->max_rbe <= 2)
+      GO(true);
     else
-      k_copy<<<cdiv(ne * ne, 256), 256, 0, c->stream>>>(ne * ne, c->d_Hpp_kin, c->d_Hee);
+      GO(false);
+#undef GO
+  } else if (ne) {
+    k_copy<<<cdiv(ne * ne, 256), 256, 0, c->stream>>>(ne * ne, c->d_Hpp_kin, c->d_Hee);
   }
   if ((s = efe_couple_build(c, want32))) return s;
   HIPCHK(c, hipGetLastError());
