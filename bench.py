@@ -36,8 +36,7 @@ PREC = {"fp64": 0, "fp32": 1, "bf16": 2}
 STEP_TIMERS = ("t_filter_ms", "t_rr_ms", "t_poisson_ms", "t_density_ms", "t_operators_ms",
                "t_bound_ms", "t_energy_ms", "t_other_ms")
 COL_CHUNK = 160   # column chunk of the filter and of one apply
-NODE_KERNEL = {"fp64": "k_node_update<double, 4, false>", "fp32": "k_node_update<float, 4, false>",
-               "bf16": "k_node_update<double, 4, false>"}
+NODE_KERNEL = "k_node_update"             # every launch of one apply (column parts)
 
 
 def log(*a):
@@ -45,7 +44,7 @@ def log(*a):
 
 
 def measured_traffic(kernel, workload):
-    """HBM bytes per launch of `kernel` on `workload` from the committed
+    """HBM bytes of `kernel` in one apply of `workload`, from the committed
     counter summary (rocprofv3 FETCH_SIZE and WRITE_SIZE runs, each scaled by
     the same counter's reading for a 1 GiB device copy), or None when the
     summary is missing or was taken from a different source of the kernel."""
@@ -63,6 +62,34 @@ def measured_traffic(kernel, workload):
     if k is None or rec.get("apply_hip_sha256") != sha:
         return None
     return k["read_bytes"] + k["write_bytes"]
+
+
+def roofline(prec, n, nloc, n_cells, n_nodes, timers):
+    """Roofline of the dominant kernel of the timed steps, from the launches and
+    milliseconds of the timer classes (cell, pre, recur), for n columns.
+
+    Where an apply's cells go into a workspace (one launch each), it is the
+    node update: it reads the cells' products (nloc rows a cell) and, in a
+    recurrence step, Z_{k-1}, Z_{k-2} and G, and writes Y^C.  The coupling
+    blocks, which the column parts of a brick share, and the coefficient rows
+    come on top and are not counted.  Where dense cells are added to Y^C colour
+    by colour (eight launches each), it is one colour pass."""
+    ncell, cell_ms = timers["cell"]
+    nupd, upd_ms = timers["pre"]
+    if ncell > nupd:
+        work = 2.0 * nloc ** 2 * n_cells * n / 8.0
+        seconds, peak, unit, key = cell_ms * 1e-3 / ncell, PEAK[prec], "TFLOP/s", "flops_per_launch"
+        bound, kernel, ms = "mfma", "dense cell products (one colour pass)", cell_ms
+    else:
+        rows = nloc * n_cells + n_nodes * (1.0 + 3.0 * timers["recur"][0] / max(nupd, 1))
+        work = 8.0 * n * rows
+        seconds, peak, unit, key = upd_ms * 1e-3 / max(nupd, 1), PEAK["hbm"], "TB/s", \
+            "bytes_per_launch"
+        bound, kernel, ms = "hbm", NODE_KERNEL, upd_ms
+    achieved = work / seconds
+    return {"bound": bound, "kernel": kernel, "achieved": achieved / 1e12, "peak": peak / 1e12,
+            "unit": unit, "frac": achieved / peak, "launch_ms": seconds * 1e3, key: work,
+            "total_ms": ms}
 
 
 def cpu_baseline(w):
@@ -387,17 +414,9 @@ def filter_bench(args, w):
                for k, (c, ms) in timers.items()}
     log(f"step {ms_step:.1f} ms; " + ", ".join(f"{k} {v['ms_avg']:.3f} ms x {v['launches']}"
                                               for k, v in kernels.items()))
-    # roofline of the node update: it reads the cells' products (nloc rows a
-    # cell) and, in a recurrence step, Z_{k-1}, Z_{k-2} and G, and writes Y^C.
-    # The coupling blocks, which the column parts of a brick share, and the
-    # coefficient rows come on top and are not counted.
-    nupd, upd_ms = timers["pre"]
-    nrec = timers["recur"][0]
-    rows_moved = ctx.nloc * ctx.n_cells + ctx.n_nodes * (1.0 + 3.0 * nrec / max(nupd, 1))
-    bytes_per_launch = 8.0 * n * rows_moved
-    avg_upd_s = upd_ms * 1e-3 / max(nupd, 1)
-    achieved = bytes_per_launch / avg_upd_s
-    peak = PEAK["hbm"]
+    roof = roofline(args.prec, n, ctx.nloc, ctx.n_cells, ctx.n_nodes, timers)
+    roof["traffic"] = measured_traffic(roof["kernel"], w["name"])
+    roof["share_of_step"] = roof.pop("total_ms") / ((t1 - t0) * 1e3)
     full_pass_s = (t1 - t0) / args.steps * w["nvec"] / n
     return {
         "metric": "Cheb-filter DoF*vec*deg/s",
@@ -423,12 +442,7 @@ def filter_bench(args, w):
                    "full_block_pass_s": full_pass_s,
                    "full_block_pass_rule": f"{w['nvec']} / {n} chunk passes back to back",
                    "kernels": kernels},
-        "roofline": {"bound": "hbm", "kernel": NODE_KERNEL[args.prec],
-                     "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TB/s",
-                     "frac": achieved / peak,
-                     "traffic": measured_traffic(NODE_KERNEL[args.prec], w["name"]),
-                     "launch_ms": avg_upd_s * 1e3, "bytes_per_launch": bytes_per_launch,
-                     "share_of_step": upd_ms / ((t1 - t0) * 1e3)},
+        "roofline": roof,
         **({} if args.no_cpu else {"cpu_baseline": _cpu(w)}),
     }
 
