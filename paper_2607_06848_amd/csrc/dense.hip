@@ -467,8 +467,8 @@ __device__ __forceinline__ int slot_bottom(int step, int t) {
   return 1 + (x >= J2 - 1 ? x - (J2 - 1) : x);
 }
 
-__global__ __launch_bounds__(1024) void k_jacobi_sub(int64_t np, const double *__restrict__ A,
-                                                     int64_t lda, const int *__restrict__ pairs,
+__global__ __launch_bounds__(1024) void k_jacobi_sub(const double *__restrict__ A, int64_t lda,
+                                                     const int *__restrict__ pairs,
                                                      double *__restrict__ U, int max_sweeps,
                                                      double thr) {
   static_assert(J2 == 64, "slots and lanes are laid out for 64 indices");
@@ -759,7 +759,7 @@ efe_status efe_syev_jacobi(efe_ctx *c, int64_t n, const double *H, int64_t ldh, 
     prev = h2[0];
     for (int r = 0; r < nb - 1; ++r) {
       const int *pr = iwork + (int64_t)r * 2 * npair;
-      k_jacobi_sub<<<npair, 1024, 0, c->stream>>>(np, A, np, pr, U, 8, 1e-30 * hn2);
+      k_jacobi_sub<<<npair, 1024, 0, c->stream>>>(A, np, pr, U, 8, 1e-30 * hn2);
       // B = U^T A on the paired rows (every row belongs to one pair), then
       // A = B U and V = V U on the paired columns (np is a multiple of 64)
       k_jacobi_rows<<<dim3((unsigned)(np / 64), npair), 256, 0, c->stream>>>(A, np, pr, U, B);
