@@ -205,9 +205,10 @@ efe_status efe_set_potential(efe_ctx *ctx, const double *vq, int32_t precisions)
  * contractions (dense cell matrices where nq != p + 1), and E and P^C as dense
  * blocks over boxes of nodes.  The cells' products take n_cells x nloc x
  * min(ncols, 160) doubles of workspace; without room for them they are added
- * colour by colour.  EFE_EINVAL if n_nodes x 160 reaches 2^31 (32-bit offsets
- * of the dense cell products); efe_setup_mesh refuses systems with more than 768 enrichment functions
- * coupled to one cell. */
+ * colour by colour, to the same result (sums in another order).  EFE_EINVAL if
+ * n_nodes x 160 reaches 2^31 (32-bit offsets of the dense cell products);
+ * efe_setup_mesh refuses systems with more than 768 enrichment functions coupled
+ * to one cell. */
 efe_status efe_apply_H(efe_ctx *ctx, const double *X, double *Y, int32_t ncols, int64_t ld);
 /* Y = H^E X in the given precision (EFE_FP64, or EFE_FP32 / EFE_BF16 with
  * FP32 accumulation; the reduced-precision blocks must have been built by
@@ -233,8 +234,8 @@ typedef struct {
   double a, b, a_min; /* unwanted interval (a, b); a_min <= lowest eigenvalue < a */
   int32_t mode;       /* EFE_FILTER_RESIDUAL or EFE_FILTER_STANDARD */
   int32_t prec;       /* EFE_FP64, EFE_FP32, EFE_BF16: operands of the coupling and
-                       * dense cell products of the recurrence; projectors, enrichment rows, G and
-                       * V_out stay FP64 */
+                       * dense cell products of the recurrence; projectors,
+                       * enrichment rows, G and V_out stay FP64 */
 } efe_cheb_params;
 
 /* Round-off amplification of (M~^E)^-1, set when the context is built:

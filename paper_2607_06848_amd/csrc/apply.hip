@@ -14,10 +14,12 @@
 //            W   = D (P^C s X^C + P~^phi X^E)    (MFMA)
 //   nodes    Y^C = alpha (sum_c P_c^T Yc + E^T X^E + P^C^T W) + beta Z1 + gamma Z2
 //                  + alpha G Cl                  (MFMA, one pass over the rows)
-// in five launches, with s = 1, or X = M~^-1 Z: s = 1/m and X^E = (M~^ee)^-1
-// Z^E formed by the sum step.  Gauss rules with nq != p + 1 points, and BF16,
-// add dense cell products H_c s X^C_c to Y^C in eight colour passes instead of
-// the cells step (no two cells of a pass share a node).
+// in five launches (six where the columns leave a rest of 64-column parts, one more
+// in FP32, whose gather takes E and P^C apart; one less without enrichment), with
+// s = 1, or X = M~^-1 Z: s = 1/m and X^E = (M~^ee)^-1 Z^E formed by the sum step.
+// Gauss rules with nq != p + 1 points, and BF16, add dense cell products H_c s
+// X^C_c to Y^C in eight colour passes instead of the cells step (no two cells of a
+// pass share a node); so do the tensor products without room for Yc.
 #include <algorithm>
 
 #include "efe_device.h"
@@ -28,7 +30,8 @@ typedef double v2d __attribute__((ext_vector_type(2)));
 // Streams that a launch reads or writes once and that are far larger than the
 // caches (the cells' products, the recurrence blocks, the coupling blocks, the
 // partial rows) go with the non-temporal hint, so that they do not evict what
-// is re-read through L2 (the rows of a box, the coefficient rows).  The hint changes cache policy only, not the values.
+// is re-read through L2 (the rows of a box, the coefficient rows).  The hint changes
+// cache policy only, not the values.
 template <typename T>
 __device__ inline T ld_nt(const T *p) {
   return __builtin_nontemporal_load(p);
@@ -510,9 +513,10 @@ struct BoxSet {
 // then P^C), one a wave, and all columns; the box's 512 nodes stream through
 // LDS in 16-row chunks, double buffered, while the next chunk's rows and matrix
 // fragments are on their way in registers.  Bound by the FP64 matrix cores at
-// 160 vectors (64 atoms: 22 GF of non-zero products in 0.86 ms; two waves a
-// SIMD without spills beat three with 21 spilled registers and every chunk
-// multiplied, 1.23 ms) and by reading the blocks at one.
+// 160 vectors, which counters find busy 49% of the time (64 atoms: 0.85 ms, 3.9 GB
+// through HBM, 4.6 TB/s; 500 atoms 57%); two waves a SIMD without spills beat three
+// with 21 spilled registers and every chunk multiplied, 1.23 ms.  Bound by reading
+// the blocks at one vector.
 template <typename T>
 struct GatherArgs {
   const int32_t *items;
@@ -847,8 +851,10 @@ __global__ __launch_bounds__(256) void k_coef_dense(int64_t n, int nf, int nx, i
 // (one z layer) by all columns, the coefficient rows of the brick's atoms
 // streaming through LDS; the other terms are read and Y^C is written once, in
 // 16-byte pieces.  HBM-bound: the products of one brick run while others
-// wait for their rows (64 atoms, 160 vectors: 6.5 GB in 1.61 ms, 4.0 TB/s;
-// the separate start-value pass and colour passes it replaces took 5.3 ms).
+// wait for their rows (counters, 64 atoms, 160 vectors: 7.2 GB read and 1.2 GB
+// written in 1.62 ms, 5.2 TB/s, matrix cores busy 22% of the time; 500 atoms 56 and
+// 7.6 GB in 14.9 ms, 4.3 TB/s, 28%; the separate start-value pass and colour passes
+// it replaces took 5.3 ms for 64 atoms).
 template <typename T>
 struct NodeArgs {
   BoxSet<T> E;

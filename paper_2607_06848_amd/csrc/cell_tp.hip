@@ -10,11 +10,11 @@
 // derivative matrix of the Lagrange basis on the Gauss points.  That is nine
 // 1-D contractions, 18 P^4 flops instead of 2 P^6 (43 k instead of 235 k at
 // P = 7), and it reads the potential (P^3 numbers a cell) in place of a
-// P^3 x P^3 matrix, so the bound moves from the matrix cores to HBM: 0.88 ms
-// for 4,096 cells x 160 vectors at P = 7 (1.17 GB of X read and 1.80 GB of
-// products written, 3.4 TB/s), 52 us for one vector; the dense products of the
-// same cells took 3.0 ms and 0.67 ms.  Both 1-D matrices are symmetric under reflection of the
-// element, so every length-P contraction runs on the even and odd parts of its
+// P^3 x P^3 matrix, so the bound moves from the matrix cores to HBM: 0.86 ms
+// for 4,096 cells x 160 vectors at P = 7 (counters: 1.47 GB read, 1.87 GB
+// written, 3.9 TB/s), 51 us for one vector; the dense products of the same cells
+// took 3.0 ms and 0.67 ms.  Both 1-D matrices are symmetric under reflection of
+// the element, so every length-P contraction runs on the even and odd parts of its
 // input: 25 multiply-adds and 12 additions at P = 7 in place of 49.
 #include <cmath>
 #include <vector>

@@ -134,13 +134,15 @@ struct efe_ctx {
   int32_t *d_items[3] = {nullptr, nullptr, nullptr};
   int64_t n_items[3] = {0, 0, 0};
   double *d_S = nullptr;
-  double *d_Hee = nullptr;                             // H^E_ee without projectors
+  double *d_Hee = nullptr;                             // H^E_ee + P~^T D P~
   double *d_Ptil = nullptr;                            // P^phi - P^C C^T, [nproj][n_enr]
   // (cell, I, J) triples of atoms sharing a support cell
   int64_t ntrip = 0;
   int32_t *d_trip = nullptr;
   int64_t n_ppv = 0;
   int32_t *d_ppv = nullptr;        // work items over the triples of a cell
+  // (d_Hpp_kin: kinetic part of H^phiphi plus the projectors' P~^T D P~, which the
+  // potential does not change; d_Hpp: with the potential part)
   double *d_Mpp = nullptr, *d_Mee = nullptr, *d_Hpp_kin = nullptr, *d_Hpp = nullptr;
   double *d_Mee_inv = nullptr;                         // [natoms][nf][nf]
   double amplification = 1.0;                          // efe_enrichment_amplification
@@ -197,7 +199,6 @@ struct efe_ctx {
 
   // SCF state (scf.hip)
   void *scf = nullptr;
-  // rocBLAS handle of the dense eigensolver (created on first use)
   int rr_sweeps = 0;          // block Jacobi sweeps of the last Rayleigh-Ritz
 
   // event timing (efe_timing)
@@ -227,7 +228,6 @@ void efe_free(efe_ctx *ctx, void *p);
 // per-device address of the static scratch region of efe_cheb_filter_noalloc
 // (noalloc.hip), taken once per device at context setup
 efe_status efe_scratch_attach(efe_ctx *ctx);
-// rocBLAS handle bound to the context's stream (rr.hip)
 // message returned by efe_last_error(NULL) (calls that take no context)
 void efe_set_global_error(const std::string &msg);
 // workspace slot `slot` of at least `bytes` bytes (kept across calls)
@@ -287,7 +287,6 @@ efe_status efe_tp_setup(efe_ctx *ctx, const std::vector<double> &wq, const std::
                         const std::vector<long double> &Dl);
 efe_status efe_tp_apply(efe_ctx *ctx, const double *X, int64_t ldx, bool minv, int ncols,
                         double *Yc, int64_t ldc, double *Y, int64_t ldy, double alpha);
-// E_c = B_c - H_c C_c^T of every coupling pair into d_Epair
 // coupling blocks (couple.hip): lists from the coupling pairs (per atom its
 // cells), blocks of the projectors (once), blocks of E, H^E_ee and the matrix
 // of the coefficients (per potential; d_Epair, d_B_am and, in d_Hee, H^phiphi)

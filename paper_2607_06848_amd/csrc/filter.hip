@@ -150,9 +150,8 @@ static efe_status filter_chunk(efe_ctx *c, double *V, const double *lambda, int3
   k_residual_init<<<nb, T, 0, c->stream>>>(rows, ncols, W, Zb, lambda, sig[1] / e, G, Zc, Zp);
   for (int k = 2; k <= m; ++k) {
     // the recurrence's H applies run in the requested precision (G stays
-    // FP64); its three affine terms enter the assembly itself: Z_k is
-    // written in place of Z_{k-2}, starting from the terms and accumulating
-    // alpha H M~^-1 Z_{k-1} over the colour passes
+    // FP64); its three affine terms are added where alpha H M~^-1 Z_{k-1} is
+    // assembled, and Z_k is written in place of Z_{k-2}
     ApplyEpilogue ep;
     ep.alpha = 2.0 * sig[k] / e;
     ep.beta = -cc * ep.alpha;

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(256) void k_load_vector(int nloc, int nqp, const in
 // order (the result does not depend on timing), and all of them see the same
 // stopping test, so iterations queued after the last one do nothing and the
 // loop ends after the same iteration as one that tests r.r each time.  An
-// iteration takes 45 us for 4,096 cells and 22 us for 64 (107 and 42 us with
+// iteration takes 40 us for 4,096 cells and 18 us for 64 (107 and 42 us with
 // matrix products, five kernels and a separate p).
 //   sc[0] done flag, sc[1] iterations, sc[2] squared stopping threshold, sc[3] b.b
 //   part[0], part[1]: [r.r, r.z][CG_NP] of even and odd iterations; part[2]: p.Ap

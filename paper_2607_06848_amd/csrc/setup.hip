@@ -702,14 +702,15 @@ __global__ __launch_bounds__(512) void k_build_E(
   }
 }
 
-// Rows of the enrichment block of the orthogonalized Hamiltonian without the
-// projectors, H^E_ee = H^phiphi - C B^T - E C^T (the expansion of T^T Hhat T
-// with E = B - C H^cc), first part: Hee = H^phiphi (symmetrized) - C B^T, row f = (I, k)
-// summed over the support nodes of atom I and, at each node, the atoms whose
-// support holds it (B vanishes off the support).  C B^T cancels nearly all of
-// H^phiphi and what is left is magnified by (M~^ee)^-1, so a filter's output
-// follows the rounding of this sum: over boxes of nodes (couple.hip) it takes 3.3
-// ms instead of 14.1 for 64 atoms, but moves the output of degree 40 by 1.5e-9.
+// Rows of the enrichment block of the orthogonalized Hamiltonian, H^E_ee =
+// H^phiphi - C B^T - E C^T (the expansion of T^T Hhat T with E = B - C H^cc; the
+// projectors' P~^T D P~ is in Hpp already), first part: Hee = H^phiphi
+// (symmetrized) - C B^T, row f = (I, k) summed over the support nodes of atom I
+// and, at each node, the atoms whose support holds it (B vanishes off the
+// support).  C B^T cancels nearly all of H^phiphi and what is left is magnified by
+// (M~^ee)^-1, so a filter's output follows the rounding of this sum: over boxes of
+// nodes (couple.hip) it takes 3.3 ms instead of 14.1 for 64 atoms, but moves the
+// output of degree 40 by 1.5e-9.
 __global__ __launch_bounds__(256) void k_hee_rows(int nf, int64_t n_enr,
                                                   const int32_t *__restrict__ snode_ptr,
                                                   const int32_t *__restrict__ snode,
