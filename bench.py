@@ -43,11 +43,12 @@ def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
 
-def measured_traffic(kernel, workload):
-    """HBM bytes of `kernel` in one apply of `workload`, from the committed
-    counter summary (rocprofv3 FETCH_SIZE and WRITE_SIZE runs, each scaled by
-    the same counter's reading for a 1 GiB device copy), or None when the
-    summary is missing or was taken from a different source of the kernel."""
+def measured_traffic(kernel, workload, prec):
+    """HBM bytes of `kernel` in one apply of `workload` in precision `prec`,
+    from the committed counter summary (rocprofv3 FETCH_SIZE and WRITE_SIZE
+    runs, each scaled by the same counter's reading for a 1 GiB device copy),
+    or None when the summary is missing, of another precision, or taken from a
+    different source of the kernel."""
     import hashlib
     path = os.path.join(ROOT, "profiles", f"node_update_{workload}_traffic.json")
     src = os.path.join(ROOT, "paper_2607_06848_amd", "csrc", "apply.hip")
@@ -59,7 +60,7 @@ def measured_traffic(kernel, workload):
     except OSError:
         return None
     k = rec.get("kernels", {}).get(kernel)
-    if k is None or rec.get("apply_hip_sha256") != sha:
+    if k is None or rec.get("prec") != prec or rec.get("apply_hip_sha256") != sha:
         return None
     return k["read_bytes"] + k["write_bytes"]
 
@@ -415,7 +416,7 @@ def filter_bench(args, w):
     log(f"step {ms_step:.1f} ms; " + ", ".join(f"{k} {v['ms_avg']:.3f} ms x {v['launches']}"
                                               for k, v in kernels.items()))
     roof = roofline(args.prec, n, ctx.nloc, ctx.n_cells, ctx.n_nodes, timers)
-    roof["traffic"] = measured_traffic(roof["kernel"], w["name"])
+    roof["traffic"] = measured_traffic(roof["kernel"], w["name"], args.prec)
     roof["share_of_step"] = roof.pop("total_ms") / ((t1 - t0) * 1e3)
     full_pass_s = (t1 - t0) / args.steps * w["nvec"] / n
     return {

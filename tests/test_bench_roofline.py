@@ -31,3 +31,22 @@ def test_dense_cells_are_a_colour_pass():
     assert r["bound"] == "mfma" and "colour" in r["kernel"] and "bytes_per_launch" not in r
     assert abs(r["flops_per_launch"] - want) < 1e-6 * want
     assert abs(r["frac"] - want / 0.5e-3 / 2.5e15) < 1e-9
+
+
+def test_traffic_is_of_this_source_and_precision(tmp_path, monkeypatch):
+    import hashlib
+    import json
+    m = bench()
+    monkeypatch.setattr(m, "ROOT", str(tmp_path))
+    src = tmp_path / "paper_2607_06848_amd" / "csrc" / "apply.hip"
+    src.parent.mkdir(parents=True)
+    src.write_text("a")
+    assert m.measured_traffic("k_node_update", "c64", "fp64") is None
+    rec = {"apply_hip_sha256": hashlib.sha256(b"a").hexdigest(), "prec": "fp64",
+           "kernels": {"k_node_update": {"read_bytes": 5.0, "write_bytes": 2.0}}}
+    (tmp_path / "profiles").mkdir()
+    (tmp_path / "profiles" / "node_update_c64_traffic.json").write_text(json.dumps(rec))
+    assert m.measured_traffic("k_node_update", "c64", "fp64") == 7.0
+    assert m.measured_traffic("k_node_update", "c64", "fp32") is None
+    src.write_text("b")
+    assert m.measured_traffic("k_node_update", "c64", "fp64") is None
